@@ -1,26 +1,31 @@
 // Memory-bound helpers of the phantom layer: local error, bias gradient,
-// in-memory reduce-scatter, MSE output error, SGD update.
+// in-memory reduce-scatter, the loss's final sum.
 #pragma once
 #include "common.h"
 
 namespace phantom {
 
-// delta = dY * sigma'(S)   (Eq. (deltaL); the sigma' factor of Eq. (backprop)).
+// delta = dY * sigma'(S)   (Eq. (deltaL); the sigma' factor of Eq. (backprop)), 16 bytes per thread and pass.
 // S is the pre-activation (any activation) or, for ReLU, the layer output.
 template <typename T>
 __global__ __launch_bounds__(256) void delta_kernel(const T *__restrict__ dY, const T *__restrict__ S,
                                                    T *__restrict__ delta, int64_t count, int act)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < count; i += stride) {
-        float d = to_f32(dY[i]);
-        if (act != ACT_IDENTITY) d *= act_deriv(act, to_f32(S[i]));
-        delta[i] = from_f32<T>(d);
+    constexpr int VEC = 16 / (int)sizeof(T);
+    typedef T TV __attribute__((ext_vector_type(VEC)));
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x, first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < count / VEC; i += stride) {
+        TV d = ((const TV *)dY)[i];
+        const TV s = ((const TV *)S)[i];
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) d[u] = from_f32<T>(to_f32((T)d[u]) * act_deriv(act, to_f32((T)s[u])));
+        ((TV *)delta)[i] = d;
     }
+    for (int64_t i = count / VEC * VEC + first; i < count; i += stride)
+        delta[i] = from_f32<T>(to_f32(dY[i]) * act_deriv(act, to_f32(S[i])));
 }
 
-// The loss of a step is left as partial sums (one per workgroup of the output-error kernel, or one per tile of
+// The loss of a step is left as partial sums (one per tile of
 // the last layer's product); a launch of its own for adding up to 1024 of them costs 4 us, so the first
 // memory-bound kernel that follows in the stream carries the sum as a rider: one of its workgroups (all
 // 256 threads) calls finish_loss, which adds the partial sums in a fixed order into loss = scale * sum.
@@ -161,145 +166,6 @@ __global__ __launch_bounds__(256) void reduce_scatter_kernel(const T *__restrict
     }
     __shared__ float lred[256];
     if (tail.partial && blockIdx.x == 0 && blockIdx.y == 0) finish_loss(tail, lred);      // uniform; rider, see LossTail
-}
-
-// MSE output error (Section IV-B, "Local error at the output", Eq. (deltaL)):
-// delta_L = ((Y - T) / B) * sigma'(S) with one rounding (Eq. (deltaL) for the MSE loss), and one partial
-// sum of (Y - T)^2 per workgroup (added up by the rider of colsum_kernel).  S: pre-activation, or the
-// output for ReLU (s_kind 0: storage type, 1: float), or sigma'(pre-activation) itself in float
-// (s_kind 2).  VEC elements per thread and iteration (VEC > 1: count is a multiple of VEC and
-// every pointer is VEC-element aligned).
-// Rider: the kernel also clears `zero_count` floats at `zero` (the step's bias-gradient buffers, which later
-// launches add into), a launch of its own otherwise.
-template <typename T, int VEC>
-__global__ __launch_bounds__(256) void mse_delta_kernel(const T *__restrict__ Y, const T *__restrict__ Tg,
-                                                       const void *__restrict__ S, int s_kind, T *__restrict__ delta,
-                                                       int64_t count, float inv_b, int act,
-                                                       float *__restrict__ partial, float *__restrict__ zero,
-                                                       int64_t zero_count)
-{
-    for (int64_t z = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; z < zero_count; z += (int64_t)gridDim.x * blockDim.x)
-        zero[z] = 0.f;
-    typedef T TV __attribute__((ext_vector_type(VEC)));
-    typedef float FV __attribute__((ext_vector_type(VEC)));
-    __shared__ float red[256];
-    int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * VEC;
-    float acc = 0.f;
-    for (; i < count; i += stride) {
-        TV y, t, o;
-        FV sv;
-        if constexpr (VEC > 1) {
-            y = *(const TV *)(Y + i);
-            t = *(const TV *)(Tg + i);
-            if (act != ACT_IDENTITY) {
-                if (s_kind == 1 || s_kind == 2) {
-                    sv = *(const FV *)((const float *)S + i);
-                } else {
-                    const TV sraw = *(const TV *)((const T *)S + i);
-#pragma unroll
-                    for (int u = 0; u < VEC; ++u) sv[u] = to_f32((T)sraw[u]);
-                }
-            }
-        } else {
-            y[0] = Y[i]; t[0] = Tg[i];
-            if (act != ACT_IDENTITY)
-                sv[0] = s_kind != 0 ? ((const float *)S)[i] : to_f32(((const T *)S)[i]);
-        }
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-            const float d = to_f32((T)y[u]) - to_f32((T)t[u]);
-            acc += d * d;
-            float e = d * inv_b;
-            if (act != ACT_IDENTITY) e *= s_kind == 2 ? sv[u] : act_deriv(act, sv[u]);
-            o[u] = from_f32<T>(e);
-        }
-        if constexpr (VEC > 1) *(TV *)(delta + i) = o;
-        else delta[i] = o[0];
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-// SGD on the (up to four) parameter tensors of one layer in one launch; blockIdx.y picks the tensor.
-// fp32 storage: w -= lr * g.  bf16 storage: master -= lr * g, w = bf16(master).
-// Four elements per thread and iteration where the count allows (every pointer is 16-byte aligned).
-struct SgdTensor {
-    void *w;             // storage-type weights
-    float *master;       // bf16 storage: fp32 master copy
-    const float *grad;
-    int64_t count;
-};
-struct SgdBatch {
-    SgdTensor t[4];
-    LossTail tail;       // rider for workgroup (0,0), see LossTail
-};
-
-// one tensor's update by workgroup `job` of `jobs` (all of the workgroup's `threads` threads)
-template <typename T>
-__device__ __forceinline__ void sgd_tensor(const SgdTensor &t, float lr, int job, int jobs, int threads)
-{
-    typedef float F4 __attribute__((ext_vector_type(4)));
-    typedef T T4 __attribute__((ext_vector_type(4)));
-    int64_t i = (int64_t)job * threads + threadIdx.x;
-    const int64_t stride = (int64_t)jobs * threads;
-    if ((t.count & 3) == 0) {                          // uniform
-        for (const int64_t quads = t.count >> 2; i < quads; i += stride) {
-            const F4 gr = ((const F4 *)t.grad)[i];
-            if constexpr (sizeof(T) == 4) {
-                F4 *w = (F4 *)t.w;
-                w[i] = w[i] - lr * gr;
-            } else {
-                const F4 m = ((const F4 *)t.master)[i] - lr * gr;
-                ((F4 *)t.master)[i] = m;
-                T4 o;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) o[u] = from_f32<T>(m[u]);
-                ((T4 *)t.w)[i] = o;
-            }
-        }
-        return;
-    }
-    for (; i < t.count; i += stride) {
-        const float gr = t.grad[i];
-        if constexpr (sizeof(T) == 4) {
-            float *w = (float *)t.w;
-            w[i] = w[i] - lr * gr;
-        } else {
-            const float m = t.master[i] - lr * gr;
-            t.master[i] = m;
-            ((T *)t.w)[i] = from_f32<T>(m);
-        }
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void sgd_kernel(SgdBatch batch, float lr)
-{
-    // fixed-index copies selected by value: indexing the argument block with blockIdx.y would make
-    // every access a dependent load
-    SgdTensor t = batch.t[0];
-    if (blockIdx.y == 1) t = batch.t[1];
-    if (blockIdx.y == 2) t = batch.t[2];
-    if (blockIdx.y == 3) t = batch.t[3];
-    __shared__ float lred[256];
-    if (batch.tail.partial && blockIdx.x == 0 && blockIdx.y == 0) finish_loss(batch.tail, lred);      // uniform
-    sgd_tensor<T>(t, lr, blockIdx.x, gridDim.x, 256);
-}
-
-// The same update as a few workgroups of another launch (workgroup `job` of `jobs`): every tensor in turn.
-template <typename T>
-__device__ __forceinline__ void sgd_rider(const SgdBatch &batch, float lr, int job, int jobs, int threads, float *lred)
-{
-    if (batch.tail.partial && job == 0) finish_loss(batch.tail, lred);      // uniform
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (batch.t[i].count > 0) sgd_tensor<T>(batch.t[i], lr, job, jobs, threads);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float *__restrict__ dst, int64_t count)

@@ -1,0 +1,757 @@
+// Products of any shape and either storage type on the matrix cores:
+//   C(m, n) = sum_c A(m, c) * B(n, c)
+// for the problems that the 128 x 128 kernels of gemm_mfma.h do not fit: fp32 storage, widths and phantom widths that
+// are no multiples of their vectors, and launches with too few 128 x 128 tiles to fill the chip.
+//
+// Vectors.  Both operands are read 16 bytes at a time whatever their alignment (the memory pipe takes any address), and
+// an index that is cut into a head and peer segments (views.h) is renumbered so that every piece starts on a vector:
+// the head is padded to a multiple of V = 8 (bf16) or 4 (float), and so is every segment.  A vector then never straddles
+// two pieces; one at the end of a piece holds fewer than V elements and its tail is masked to zero on the way to LDS
+// (reduction index) or never stored (free index).  Such a vector is read beyond its piece, but never beyond the
+// piece's last row: there the read starts earlier and the register is shifted.  Both operands of a product share the
+// numbering.
+//
+// Tile and wavefronts.  A team of wavefronts owns a TM x TN tile (2 x 2 wavefronts, or one for a 32 x 32 tile) and
+// TEAMS teams of a workgroup share the tile, taking alternate reduction steps; their sums are added in the order of
+// the teams through LDS.  Every reduction step goes global -> registers (two steps ahead) -> LDS (two stages; one
+// for a team of one wavefront, whose LDS accesses are in order anyway).
+//
+// fp32 runs on v_mfma_f32_32x32x2_f32: true fp32 products and sums, 256 FLOP per clock and compute unit, twice what
+// single (unpacked) vector FMAs reach, and a lane's operand is one float, so LDS has an eighth of the bf16 kernel's
+// traffic per cycle and the matrix pipe alone bounds the loop.  Sums in three levels (16 terms, 16 of those, the
+// rest), terms in order: one running fp32 sum over a batch of some thousand rows drifts past 1e-5 of a weight gradient.
+#pragma once
+#include "common.h"
+#include "elementwise.h"
+#include "epilogue.h"
+
+namespace phantom {
+
+template <typename T> struct FlexType;
+template <> struct FlexType<bf16_t> { static constexpr int V = 8; };     // elements per vector
+template <> struct FlexType<float> { static constexpr int V = 4; };
+// reduction step of a team of `team` threads
+template <typename T> constexpr int flex_step(int team) { return sizeof(T) == 2 ? 64 : team == 64 ? 16 : 32; }
+
+enum { FLEX_KC = 0, FLEX_KM = 1 };   // reduction index contiguous / free index contiguous in memory
+
+struct FlexAxis {        // one index of a product, as the kernel numbers it
+    int head, head_pad;  // length of the head block, and padded
+    int seg, seg_pad;    // length of a peer segment, and padded; 0: there are none
+    int total;           // padded length of the whole index
+    uint32_t magic;      // ceil(2^32 / seg_pad)
+};
+
+struct FlexOperand {
+    const void *p0, *p1; // head block, peer segments
+    int64_t g0, g1;      // elements from one group to the next
+    int64_t ld0, ld1;    // elements from one position of the strided index to the next, in each region
+    int64_t seg_stride;
+    int skip0, skip_g;   // slot skip0 + group * skip_g of the segments' buffer is passed over
+    int tiny;            // one of the buffers may have fewer than V elements altogether
+};
+
+struct FlexParams {
+    FlexOperand a, b;
+    void *o0, *o1;       // output regions (the column index decides)
+    int64_t o_g0, o_g1, o_ld0, o_ld1, o_seg_stride;
+    Epilogue ep;
+    SgdInPlace sgd;
+    FlexAxis k, n;       // reduction index, column index
+    int M;
+    int tiles_m, tiles_n, total_wg;
+    int kind;            // 0: A along the reduction index (forward and input-gradient layouts); 1: weight-gradient layout
+    float *rowsum;       // weight-gradient layout, optional: [M] per group <- sums of A over the reduction index (Eq. (bpb))
+};
+
+constexpr int FLEX_MAX_PRODUCTS = 4;
+struct FlexBatch {
+    FlexParams p[FLEX_MAX_PRODUCTS];
+    int count;
+    int first_wg[FLEX_MAX_PRODUCTS];   // multiples of 8
+    LossTail tail;       // the first workgroup also finishes the loss (partial == NULL: nothing to do)
+};
+
+static_assert(sizeof(FlexBatch) <= 3840, "a batch travels as kernel arguments (4 KB with the hidden ones)");
+
+struct FlexLoc {         // where a position of an index lies
+    int region;
+    int64_t off;         // of the position inside its region, contiguous direction
+    int in_piece;        // position inside the head or segment
+    int len;             // length of that piece
+};
+
+// second ? b : a, on values: between members of a structure the compiler would choose an address instead and force the
+// structure into memory
+template <typename I> __device__ __forceinline__ I flex_pick(bool second, I a, I b) { return a ^ ((a ^ b) & -(I)second); }
+
+__device__ __forceinline__ FlexLoc flex_locate(const FlexAxis &ax, int idx, int64_t seg_stride, int skip)
+{
+    FlexLoc l;
+    const bool tail = idx >= ax.head_pad;
+    const unsigned t = tail ? (unsigned)(idx - ax.head_pad) : 0u;
+    unsigned i = flex_pick<unsigned>(ax.seg_pad <= 1, __umulhi(t, ax.magic), t);
+    i -= i * (unsigned)ax.seg_pad > t ? 1u : 0u;       // the rounded-up reciprocal is at most one too high
+    const int w = (int)(t - i * (unsigned)ax.seg_pad), slot = (int)i + ((int)i >= skip ? 1 : 0);
+    l.region = tail ? 1 : 0;
+    l.in_piece = flex_pick(tail, idx, w);
+    l.len = flex_pick(tail, ax.head, ax.seg);
+    l.off = flex_pick<int64_t>(tail, idx, (int64_t)slot * seg_stride + w);
+    return l;
+}
+
+// 16 bytes at any element boundary
+template <typename T> struct FlexVec;
+template <> struct FlexVec<bf16_t> {
+    typedef uint32_t Any __attribute__((ext_vector_type(4), aligned(2)));
+    static __device__ __forceinline__ u32x4 keep(u32x4 v, int valid)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] &= valid >= 2 * i + 2 ? 0xffffffffu : valid == 2 * i + 1 ? 0xffffu : 0u;
+        return v;
+    }
+    static __device__ __forceinline__ u32x4 shift(u32x4 v, int n)        // element u <- element u + n (0 behind the last)
+    {
+        v = n & 4 ? u32x4{v[2], v[3], 0u, 0u} : v;
+        v = n & 2 ? u32x4{v[1], v[2], v[3], 0u} : v;
+        const int bits = (n & 1) * 16;
+        return u32x4{__builtin_amdgcn_alignbit(v[1], v[0], bits), __builtin_amdgcn_alignbit(v[2], v[1], bits),
+                     __builtin_amdgcn_alignbit(v[3], v[2], bits), __builtin_amdgcn_alignbit(0u, v[3], bits)};
+    }
+};
+template <> struct FlexVec<float> {
+    typedef uint32_t Any __attribute__((ext_vector_type(4), aligned(4)));
+    static __device__ __forceinline__ u32x4 keep(u32x4 v, int valid)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = i < valid ? v[i] : 0u;
+        return v;
+    }
+    static __device__ __forceinline__ u32x4 shift(u32x4 v, int n)
+    {
+        v = n & 2 ? u32x4{v[2], v[3], 0u, 0u} : v;
+        v = n & 1 ? u32x4{v[1], v[2], v[3], 0u} : v;
+        return v;
+    }
+};
+template <typename T> __device__ __forceinline__ u32x4 flex_load(const T *p)
+{
+    typedef typename FlexVec<T>::Any Any;
+    return gload<Any>(p);
+}
+
+// How TT threads stage an operand tile of TF free positions x KT reduction positions.
+// KC: LDS rows = free positions, 16 bytes of padding per row: 16 lanes of an operand read fall on all banks.  float: eight
+//     reduction positions of a row are kept in the order 0 2 4 6 1 3 5 7, see flex_operand.
+// KM: LDS rows = reduction positions.  bf16: four rows that a transposing read touches start 16 banks apart.
+//     float: neighbouring rows (the two halves of a wavefront) start 32 banks apart.
+template <typename T, int KIND, int TF, int TT>
+struct FlexStage {
+    static constexpr int V = FlexType<T>::V, KT = flex_step<T>(TT);
+    static constexpr int PER_ROW = (KIND == FLEX_KC ? KT : TF) / V, ROWS = KIND == FLEX_KC ? TF : KT;
+    static constexpr int NV = ROWS * PER_ROW / TT, ROW_STEP = TT / PER_ROW;
+    static_assert(NV >= 1 && NV * TT == ROWS * PER_ROW, "the team's threads tile the stage");
+    static constexpr int PITCH = KIND == FLEX_KC ? KT + V
+                                 : TF == 32 ? 32 : TF + 32;
+    static constexpr int ELEMS = ROWS * PITCH;
+};
+
+template <typename T, int KIND, int TF, int TT>
+struct FlexLoader {
+    typedef FlexStage<T, KIND, TF, TT> S;
+    static constexpr int V = S::V, KT = S::KT;
+    // KC: p0, p1 = the tile's first row in the two regions (uniform).  KM: this thread's free position in them.
+    int64_t p0, p1, start0, start1;            // (addresses as numbers, see flex_pick); start: of the regions' buffers
+    uint32_t off[S::NV];                       // plain tiles: byte offset of vector j from p0
+    int64_t ld0, ld1, seg_stride;
+    int row0[S::NV];                           // KC: element offset of row j in the head block, from p0;
+    int row1[S::NV];                           //     in a segment, from p1
+    int after[S::NV];                          //     rows behind row j
+    int col, row, skip;
+    int left;                                  // KM: elements from the vector's start to the end of its piece
+    bool tiny;
+
+    // f0: first free position; ax: the reduction index, fax: the free index
+    __device__ __forceinline__ void init(const FlexOperand &op, const FlexAxis &ax, const FlexAxis &fax, int f0, int g, int tid)
+    {
+        constexpr int64_t E = sizeof(T);
+        start0 = (int64_t)(uintptr_t)op.p0; start1 = (int64_t)(uintptr_t)op.p1;
+        p0 = start0 + g * op.g0 * E; p1 = start1 + g * op.g1 * E;
+        ld0 = op.ld0; ld1 = op.ld1; seg_stride = op.seg_stride; skip = op.skip0 + g * op.skip_g; tiny = op.tiny;
+        col = (tid % S::PER_ROW) * V;
+        row = tid / S::PER_ROW;
+        if (KIND == FLEX_KC) {
+            p0 += f0 * ld0 * E;
+            p1 += f0 * ld1 * E;
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                const int r = min(row + j * S::ROW_STEP, fax.head - 1 - f0);
+                row0[j] = r * (int)ld0;
+                row1[j] = r * (int)ld1;
+                after[j] = fax.head - 1 - f0 - r;
+                off[j] = (uint32_t)(row0[j] + col) * (uint32_t)E;
+            }
+        } else {
+            const FlexLoc l = flex_locate(fax, min(f0 + col, fax.total - V), seg_stride, skip);
+            left = l.len - l.in_piece;
+            const bool folds = fax.seg_pad > 0 && l.region;      // the free index decides: this thread stays in region 1
+            p0 = flex_pick(folds, p0, p1) + l.off * E;
+            start0 = flex_pick(folds, start0, start1);
+            ld0 = flex_pick(folds, ld0, ld1);
+            p1 += l.off * E;
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) off[j] = (uint32_t)((row + j * S::ROW_STEP) * (int)ld0) * (uint32_t)E;
+        }
+    }
+
+    // Is the tile that starts at c0 one whose vectors are all whole and inside (uniform)?  KC: it lies in the head block.
+    // KM: so do V rows behind it.
+    __device__ __forceinline__ bool plain(const FlexAxis &ax, int c0) const { return c0 + KT + (KIND == FLEX_KC ? 0 : V) <= ax.head; }
+
+    struct Col {             // KC: what the vectors of a tile that is not plain share, this thread's reduction position
+        int region, n, valid;            // n: elements from there to the end of the piece
+        int64_t off;
+    };
+    struct At {              // vector j of such a tile
+        int64_t p;
+        int back;            // how many elements ahead of its place it is read, so that the read ends with the piece's last row
+        int valid;           // elements that count
+    };
+    __device__ __forceinline__ Col column(const FlexAxis &ax, int c0) const
+    {
+        Col k{};
+        if (KIND == FLEX_KC) {
+            int c = c0 + col;
+            asm volatile("" : "+v"(c));                // (opaque: hoisted out of the reduction loop it would hold registers there)
+            const bool any = c < ax.total;
+            const FlexLoc l = flex_locate(ax, any ? c : 0, seg_stride, skip);
+            k.region = l.region; k.off = l.off; k.n = l.len - l.in_piece;
+            k.valid = any ? min(V, k.n) : 0;
+        }
+        return k;
+    }
+    __device__ __forceinline__ At at(const FlexAxis &ax, const Col &k, int c0, int j) const
+    {
+        At a;
+        int rest;            // elements from the vector's start to the end of the piece's last row (V and more are alike)
+        bool tail;
+        if (KIND == FLEX_KC) {
+            tail = k.region;
+            a.valid = k.valid;
+            a.p = flex_pick(tail, p0, p1) + (k.off + flex_pick(tail, row0[j], row1[j])) * (int)sizeof(T);
+            rest = min(after[j], V) * flex_pick(tail, min((int)ld0, V), min((int)ld1, V)) + k.n;
+        } else {
+            const int c = c0 + row + j * S::ROW_STEP;
+            tail = ax.seg > 0 && c >= ax.head_pad;
+            const int last = flex_pick(tail, ax.head, ax.seg) - 1, t = c - (tail ? ax.head_pad : 0), r = min(t, last);
+            const int64_t ld = flex_pick(tail, ld0, ld1);
+            a.valid = t <= last ? min(V, left) : 0;
+            a.p = flex_pick(tail, p0, p1) + r * ld * (int)sizeof(T);
+            rest = min(last - r, V) * min((int)ld, V) + left;
+        }
+        a.back = max(0, V - rest);
+        if (tiny) {          // uniform
+            // A buffer with fewer than V elements altogether is read from its start, which is 16-byte aligned: such a read
+            // stays within the 16 bytes that the buffer begins.
+            const int64_t before = (a.p - flex_pick(tail, start0, start1)) / (int)sizeof(T);
+            a.back = before < a.back ? (int)before : a.back;
+        }
+        return a;
+    }
+
+    // Are the tile's vectors all whole, wherever they lie (uniform)?  Then nothing has to be shifted or masked.
+    __device__ __forceinline__ bool whole(const FlexAxis &ax, int c0) const
+    {
+        return plain(ax, c0) || (KIND == FLEX_KC && ax.seg == ax.seg_pad && (ax.head == ax.head_pad || c0 >= ax.head_pad) && c0 + KT <= ax.total);
+    }
+
+    // The addresses are worked out in branches, the loads stand behind them: loads inside the branches would make the
+    // compiler wait for all of them where it could count.
+    __device__ __forceinline__ void fetch(const FlexAxis &ax, u32x4 (&regs)[S::NV], int c0) const
+    {
+        int64_t q[S::NV];
+        if (plain(ax, c0)) {
+            const int64_t p = p0 + (KIND == FLEX_KC ? c0 : c0 * ld0) * (int)sizeof(T);
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) q[j] = p + off[j];
+        } else if (whole(ax, c0)) {                    // (a KC operand)
+            const FlexLoc l = flex_locate(ax, c0 + col, seg_stride, skip);
+            const int64_t p = flex_pick(l.region, p0, p1) + l.off * (int)sizeof(T);
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) q[j] = p + (int64_t)flex_pick(l.region, row0[j], row1[j]) * (int)sizeof(T);
+        } else {
+            const Col k = column(ax, c0);
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                const At a = at(ax, k, c0, j);
+                q[j] = a.p - a.back * (int)sizeof(T);
+                __builtin_amdgcn_sched_barrier(0);     // one vector's arithmetic at a time: it takes many registers
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < S::NV; ++j) asm volatile("" : "+v"(q[j]));
+#pragma unroll
+        for (int j = 0; j < S::NV; ++j) regs[j] = flex_load((const T *)(uintptr_t)q[j]);
+    }
+
+    __device__ __forceinline__ void store(const FlexAxis &ax, u32x4 (&regs)[S::NV], T *tile, int c0) const
+    {
+        if (!whole(ax, c0)) {                          // uniform
+            const Col k = column(ax, c0);
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                const At a = at(ax, k, c0, j);
+                regs[j] = FlexVec<T>::keep(FlexVec<T>::shift(regs[j], a.back), a.valid);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (KIND == FLEX_KC && sizeof(T) == 4) {
+            T *dst = tile + row * S::PITCH + (col & ~7) + ((col >> 1) & 2);
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                *(u32x2 *)(dst + j * S::ROW_STEP * S::PITCH) = u32x2{regs[j][0], regs[j][2]};
+                *(u32x2 *)(dst + j * S::ROW_STEP * S::PITCH + 4) = u32x2{regs[j][1], regs[j][3]};
+            }
+        } else {
+            T *dst = tile + row * S::PITCH + col;
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) *(u32x4 *)(dst + j * S::ROW_STEP * S::PITCH) = regs[j];
+        }
+    }
+};
+
+// one reduction step of a wavefront's MI x NI blocks of 32 x 32 (B operand first: a lane then holds row (lane & 31) of a
+// block and the columns 8 * (e / 4) + 4 * (lane >> 5) + e % 4)
+template <int KIND, int PITCH>
+__device__ __forceinline__ bf16x8 flex_operand(const bf16_t *tile, int rbase, int kk, int lane)
+{
+    if (KIND == FLEX_KC) return *(const bf16x8 *)(tile + (rbase + (lane & 31)) * PITCH + kk * 16 + (lane >> 5) * 8);
+    const int krow = kk * 16 + (lane >> 5) * 8 + ((lane & 15) >> 2);
+    const int rcol = rbase + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+    const bf16_t *p = tile + krow * PITCH + rcol;
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+    u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
+    u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * PITCH));
+    return u.v;
+}
+// float: the four reduction positions 8 kk + 2 t + (lane >> 5), t = 0..3, one per MFMA.  v_mfma_f32_32x32x2_f32 adds its
+// two products one after the other, each with one rounding, so the terms are added in the order of the reduction index.
+template <int KIND, int PITCH>
+__device__ __forceinline__ f32x4 flex_operand(const float *tile, int rbase, int kk, int lane)
+{
+    if (KIND == FLEX_KC) return *(const f32x4 *)(tile + (rbase + (lane & 31)) * PITCH + kk * 8 + (lane >> 5) * 4);
+    f32x4 v;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = tile[(kk * 8 + 2 * t + (lane >> 5)) * PITCH + rbase + (lane & 31)];
+    return v;
+}
+
+// bf16: adds a reduction step to acc.
+template <int KA, int KB, int PA, int PB, int MI, int NI>
+__device__ __forceinline__ void flex_multiply(f32x16 (&acc)[MI][NI], const bf16_t *ta, const bf16_t *tb, int wm, int wn, int lane)
+{
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        bf16x8 av[MI], bv[NI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) av[i] = flex_operand<KA, PA>(ta, wm + 32 * i, kk, lane);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) bv[j] = flex_operand<KB, PB>(tb, wn + 32 * j, kk, lane);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bv[j], av[i], acc[i][j], 0, 0, 0);
+    }
+}
+// fp32: adds every 16 terms of a reduction step (of KT) to mid.
+template <int KA, int KB, int PA, int PB, int KT, int MI, int NI>
+__device__ __forceinline__ void flex_multiply(f32x16 (&mid)[MI][NI], const float *ta, const float *tb, int wm, int wn, int lane)
+{
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int part = 0; part < KT / 16; ++part) {
+        f32x16 acc[MI][NI];
+#pragma unroll
+        for (int kk = 2 * part; kk < 2 * part + 2; ++kk) {
+            f32x4 av[MI], bv[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) av[i] = flex_operand<KA, PA>(ta, wm + 32 * i, kk, lane);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) bv[j] = flex_operand<KB, PB>(tb, wn + 32 * j, kk, lane);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[j][t], av[i][t], kk == 2 * part && t == 0 ? zero : acc[i][j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mid[i][j][e] += acc[i][j][e];
+    }
+}
+
+// V consecutive elements to or from memory at any element boundary, the first `valid` of them
+template <int V> struct FlexRow { float x[V]; };
+template <typename E, int V> __device__ __forceinline__ FlexRow<V> flex_read(const E *p, int valid)
+{
+    typedef E Vec __attribute__((ext_vector_type(V), aligned(sizeof(E))));
+    FlexRow<V> r;
+    if (valid == V) {
+        const Vec v = gload<Vec>(p);
+#pragma unroll
+        for (int u = 0; u < V; ++u) r.x[u] = (float)v[u];
+    } else {
+#pragma unroll
+        for (int u = 0; u < V; ++u) r.x[u] = u < valid ? (float)gload<E>(p + u) : 0.f;
+    }
+    return r;
+}
+template <typename E, int V, bool NT = true> __device__ __forceinline__ void flex_write(E *p, const FlexRow<V> &r, int valid)
+{
+    typedef E Vec __attribute__((ext_vector_type(V), aligned(sizeof(E))));
+    if (valid == V) {
+        Vec v;
+#pragma unroll
+        for (int u = 0; u < V; ++u) v[u] = (E)r.x[u];
+        if (NT) gstore_nt<Vec>(p, v);
+        else gstore<Vec>(p, v);
+    } else {
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+            if (u < valid) gstore<E>(p + u, (E)r.x[u]);
+    }
+}
+
+template <typename T, int TM, int TN, int TEAMS>
+struct FlexShape {
+    static constexpr int WM = TM >= 64 ? 2 : 1, WN = TN >= 64 ? 2 : 1;     // wavefronts of a team along each side
+    static constexpr int MI = TM / 32 / WM, NI = TN / 32 / WN;             // 32 x 32 blocks per wavefront
+    static constexpr int TT = 64 * WM * WN, THREADS = TT * TEAMS;
+    static constexpr int STAGES = TT == 64 ? 1 : 2;
+    // fp32: a step's MFMAs take longer than a load, so one step ahead is enough
+    static constexpr int SETS = 2;
+    static constexpr int MIN_WAVES = TT == 64 || MI * NI > 1   ? 2 : sizeof(T) == 4 ? 3 : 4;      // wavefronts per SIMD that the registers have to allow
+
+    static constexpr int CPITCH = TN + 4;
+    static constexpr int C_BYTES = TM * CPITCH * 4;
+};
+constexpr int flex_max(int a, int b) { return a > b ? a : b; }
+template <typename T, int TM, int TN, int TEAMS, int KA, int KB>
+constexpr int flex_lds_bytes()
+{
+    typedef FlexShape<T, TM, TN, TEAMS> F;
+    return flex_max(TEAMS * F::STAGES * (FlexStage<T, KA, TM, F::TT>::ELEMS + FlexStage<T, KB, TN, F::TT>::ELEMS) * (int)sizeof(T),
+                    TEAMS * F::C_BYTES + F::THREADS * 4 + 64);
+}
+
+// orders a wavefront's own LDS accesses for the compiler (the hardware keeps them in order)
+__device__ __forceinline__ void flex_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One workgroup's work on the product P: workgroup number wg of P.total_wg.
+template <typename T, int TM, int TN, int TEAMS, int KA, int KB, typename TOut, int EPI>
+__device__ __forceinline__ void flex_workgroup(const FlexParams &P, int wg, unsigned char *lds)
+{
+    typedef FlexShape<T, TM, TN, TEAMS> F;
+    typedef FlexLoader<T, KA, TM, F::TT> LA;
+    typedef FlexLoader<T, KB, TN, F::TT> LB;
+    constexpr int KT = flex_step<T>(F::TT), V = FlexType<T>::V, MI = F::MI, NI = F::NI;
+    constexpr bool ROWSUM = KA == FLEX_KM && KB == FLEX_KM;
+
+    const int tiles = P.tiles_m * P.tiles_n;
+    const int g = wg / tiles;
+    const int rem = wg - g * tiles;
+    constexpr int RASTER = 8;                          // bands of tile rows, down the band first: see gemm_mfma.h
+    const int band = rem / (RASTER * P.tiles_n);
+    const int in_band = rem - band * (RASTER * P.tiles_n);
+    const int band_rows = min(P.tiles_m - band * RASTER, RASTER);
+    const int tn = in_band / band_rows, tm = band * RASTER + (in_band - tn * band_rows);
+    const int m0 = tm * TM, n0 = tn * TN;
+
+    const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / F::TT) : 0;
+    const int tid = (int)threadIdx.x - team * F::TT, lane = tid & 63, wave = tid >> 6;
+    const int wm = (wave / F::WN) * MI * 32, wn = (wave % F::WN) * NI * 32;
+
+    const FlexAxis &ka = P.k;
+    FlexAxis ma{};                                     // the row index: never cut
+    ma.head = P.M; ma.head_pad = (P.M + V - 1) / V * V; ma.total = ma.head_pad;
+    LA la;
+    LB lb;
+    la.init(P.a, ka, ma, m0, g, tid);
+    lb.init(P.b, ka, P.n, n0, g, tid);
+
+    f32x16 acc[MI][NI], mid[MI][NI];                   // fp32 storage: the second and third level of partial sums are mid and acc
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { acc[i][j][e] = 0.f; mid[i][j][e] = 0.f; }
+    const bool rows = ROWSUM && P.rowsum && n0 == 0;   // uniform
+    float row_acc = 0.f, row_mid = 0.f;
+    int in_mid = 0;
+
+    T *stage0 = (T *)lds + team * F::STAGES * (LA::S::ELEMS + LB::S::ELEMS);
+    const int steps = (ka.total + KT - 1) / KT, loops = (steps + TEAMS - 1) / TEAMS;
+    auto c_of = [=](int i) { return (i * TEAMS + team) * KT; };
+    constexpr int SETS = F::SETS;                      // steps that the loads run ahead
+    u32x4 ra[SETS][LA::S::NV], rb[SETS][LB::S::NV];
+#pragma unroll
+    for (int d = 0; d < SETS; ++d) { la.fetch(ka, ra[d], c_of(d)); lb.fetch(ka, rb[d], c_of(d)); }
+    // step i: LDS stage d = i % 2, register set d % SETS
+    auto step = [&](int d, int i, bool last) {
+        T *ta = stage0 + (F::STAGES == 2 ? d : 0) * (LA::S::ELEMS + LB::S::ELEMS), *tb = ta + LA::S::ELEMS;
+        const int c0 = c_of(i);
+        u32x4 (&ma_)[LA::S::NV] = ra[d % SETS];
+        u32x4 (&mb_)[LB::S::NV] = rb[d % SETS];
+        la.store(ka, ma_, ta, c0);
+        lb.store(ka, mb_, tb, c0);
+        if (!last) {
+            la.fetch(ka, ma_, c_of(i + SETS));
+            lb.fetch(ka, mb_, c_of(i + SETS));
+        }
+        if constexpr (F::TT > 64) __syncthreads();
+        else flex_wave_sync();
+        if constexpr (sizeof(T) == 2) flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH>(acc, ta, tb, wm, wn, lane);
+        else flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH, KT>(mid, ta, tb, wm, wn, lane);
+        if constexpr (ROWSUM) {
+            if (rows) {
+                constexpr int PARTS = F::TT / TM;
+                const int part = tid / TM;
+                float t = 0.f;
+#pragma unroll 8
+                for (int r = 0; r < KT / PARTS; ++r) t += (float)ta[(part + r * PARTS) * LA::S::PITCH + tid % TM];
+                row_mid += t;
+            }
+        }
+        if constexpr (sizeof(T) == 4) {
+            in_mid += KT / 16;
+            if (in_mid == 16) {                        // uniform
+#pragma unroll
+                for (int a = 0; a < MI; ++a)
+#pragma unroll
+                    for (int b = 0; b < NI; ++b)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) { acc[a][b][e] += mid[a][b][e]; mid[a][b][e] = 0.f; }
+                in_mid = 0;
+                row_acc += row_mid; row_mid = 0.f;
+            }
+        }
+        if constexpr (F::TT == 64) flex_wave_sync();
+    };
+    // (two whole steps per pass, no way out in between: the compiler counts the loads in flight)
+    int i = 0;
+    for (; i + 1 < loops; i += 2) {
+        step(0, i, false);
+        step(1, i + 1, false);
+    }
+    if (i < loops) step(0, i, true);
+    row_acc += row_mid;
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int a = 0; a < MI; ++a)
+#pragma unroll
+            for (int b = 0; b < NI; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[a][b][e] += mid[a][b][e];
+    }
+    __syncthreads();
+
+    // the finished tile goes through LDS, so that every global access of the epilogue is a run of whole rows
+    float *ctile = (float *)lds;
+    float *extra = (float *)(lds + TEAMS * F::C_BYTES);   // THREADS floats
+    {
+        float *mine = ctile + team * (F::C_BYTES / 4);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                    *(f32x4 *)(mine + (wm + 32 * i + (lane & 31)) * F::CPITCH + wn + 32 * j + 8 * q + 4 * (lane >> 5)) = v;
+                }
+    }
+    if (rows) extra[threadIdx.x] = row_acc;
+    __syncthreads();
+
+    const Epilogue &ep = P.ep;
+    const SgdInPlace &sgd = P.sgd;
+    if constexpr (ROWSUM) {
+        if (rows && (int)threadIdx.x < TM && m0 + (int)threadIdx.x < P.M) {
+            float t = 0.f;
+#pragma unroll 4
+            for (int r = threadIdx.x; r < F::THREADS; r += TM) t += extra[r];        // parts of a team, then the next team
+            const int64_t at = (int64_t)g * P.M + m0 + threadIdx.x;
+            gstore<float>(P.rowsum + at, t);
+            if (sgd.bias_w) {
+                if constexpr (sizeof(T) == 2) {
+                    const float nb = gload<float>(sgd.bias_master + at) - sgd.lr * t;
+                    gstore<float>(sgd.bias_master + at, nb);
+                    gstore<bf16_t>((bf16_t *)sgd.bias_w + at, (bf16_t)nb);
+                } else {
+                    float *w = (float *)sgd.bias_w + at;
+                    gstore<float>(w, gload<float>(w) - sgd.lr * t);
+                }
+            }
+        }
+    }
+    constexpr int PER_ROW = TN / V;
+    float sq_sum = 0.f;
+    for (int v = (int)threadIdx.x; v < TM * PER_ROW; v += F::THREADS) {
+        const int row = v / PER_ROW, col = (v % PER_ROW) * V, m = m0 + row, n = n0 + col;
+        if (m >= P.M || n >= P.n.total) continue;
+        const FlexLoc l = flex_locate(P.n, n, P.o_seg_stride, NO_SKIP);
+        const int valid = min(V, l.len - l.in_piece);
+        FlexRow<V> x;
+#pragma unroll
+        for (int h = 0; h < V / 4; ++h) {
+            f32x4 t = *(const f32x4 *)(ctile + row * F::CPITCH + col + 4 * h);
+#pragma unroll
+            for (int q = 1; q < TEAMS; ++q) t += *(const f32x4 *)(ctile + q * (F::C_BYTES / 4) + row * F::CPITCH + col + 4 * h);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x.x[4 * h + u] = t[u];
+        }
+        const int64_t aux_at = g * ep.aux_g + (int64_t)m * ep.aux_ld + n;      // (such outputs are plain: n is the column)
+        FlexRow<V> deriv;
+        if (EPI == EPI_BIAS_ACT && ep.mode == EPI_BIAS_ACT) {
+            const FlexRow<V> bias = flex_read<T, V>((const T *)ep.bias + g * ep.bias_g + n, valid);
+            FlexRow<V> pre;
+#pragma unroll
+            for (int u = 0; u < V; ++u) {
+                pre.x[u] = x.x[u] + bias.x[u];
+                if (sizeof(T) == 2 && ep.act == ACT_GELU) {
+                    gelu_both(pre.x[u], x.x[u], deriv.x[u]);
+                } else {
+                    x.x[u] = act_apply(ep.act, pre.x[u]);
+                    deriv.x[u] = 1.f;
+                }
+            }
+            if (!(sizeof(T) == 2 && ep.act == ACT_GELU) && (ep.aux_deriv || ep.mse_target)) {      // uniform
+#pragma unroll
+                for (int u = 0; u < V; ++u) deriv.x[u] = act_deriv(ep.act, pre.x[u]);
+            }
+            if (ep.aux) {                              // uniform
+                if (ep.aux_deriv) flex_write<float, V>((float *)ep.aux + aux_at, deriv, valid);
+                else if (ep.aux_f32) flex_write<float, V>((float *)ep.aux + aux_at, pre, valid);
+                else flex_write<T, V>((T *)ep.aux + aux_at, pre, valid);
+            }
+        } else if (EPI == EPI_DACT && ep.mode == EPI_DACT && ep.aux) {
+            if (ep.aux_deriv) {
+                const FlexRow<V> a = flex_read<float, V>((const float *)ep.aux + aux_at, valid);
+#pragma unroll
+                for (int u = 0; u < V; ++u) x.x[u] *= a.x[u];
+            } else {
+                const FlexRow<V> a = ep.aux_f32 ? flex_read<float, V>((const float *)ep.aux + aux_at, valid)
+                                                : flex_read<T, V>((const T *)ep.aux + aux_at, valid);
+#pragma unroll
+                for (int u = 0; u < V; ++u) x.x[u] *= act_deriv(ep.act, a.x[u]);
+            }
+        }
+        const int64_t o_at = l.region ? g * P.o_g1 + (int64_t)m * P.o_ld1 + l.off : g * P.o_g0 + (int64_t)m * P.o_ld0 + l.off;
+        if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
+            if (sgd.w0) {                              // uniform
+                void *const w0 = sgd.w0, *const w1 = sgd.w1;
+                void *const w = l.region ? w1 : w0;
+                if constexpr (sizeof(T) == 2) {
+                    float *const m0 = sgd.master0, *const m1 = sgd.master1;
+                    float *const master = (l.region ? m1 : m0) + o_at;
+                    FlexRow<V> mv = flex_read<float, V>(master, valid);
+#pragma unroll
+                    for (int u = 0; u < V; ++u) mv.x[u] -= sgd.lr * x.x[u];
+                    flex_write<float, V>(master, mv, valid);
+                    flex_write<bf16_t, V, false>((bf16_t *)w + o_at, mv, valid);
+                } else {
+                    FlexRow<V> wv = flex_read<float, V>((const float *)w + o_at, valid);
+#pragma unroll
+                    for (int u = 0; u < V; ++u) wv.x[u] -= sgd.lr * x.x[u];
+                    flex_write<float, V, false>((float *)w + o_at, wv, valid);
+                }
+                if (!sgd.keep_grad) continue;
+            }
+        }
+        void *const o0 = P.o0, *const o1 = P.o1;
+        flex_write<TOut, V>((TOut *)(l.region ? o1 : o0) + o_at, x, valid);
+        if (EPI == EPI_BIAS_ACT && ep.mode == EPI_BIAS_ACT && ep.mse_target) {         // uniform
+            // the MSE output error of Eq. (deltaL) from the output as stored, rounded once
+            const FlexRow<V> t = flex_read<T, V>((const T *)ep.mse_target + aux_at, valid);
+            FlexRow<V> dl;
+#pragma unroll
+            for (int u = 0; u < V; ++u) {
+                const float diff = (float)(T)x.x[u] - t.x[u];
+                if (u < valid) sq_sum += diff * diff;
+                dl.x[u] = diff * ep.mse_inv_b;
+                if (ep.act != ACT_IDENTITY) dl.x[u] *= deriv.x[u];
+            }
+            flex_write<T, V, false>((T *)ep.mse_delta + aux_at, dl, valid);
+        }
+    }
+    if (EPI == EPI_BIAS_ACT && ep.mode == EPI_BIAS_ACT && ep.mse_target) {             // uniform
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sq_sum += __shfl_down(sq_sum, off);
+        if ((threadIdx.x & 63) == 0) extra[threadIdx.x >> 6] = sq_sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float total = 0.f;
+#pragma unroll
+            for (int w = 0; w < F::THREADS / 64; ++w) total += extra[w];
+            ep.mse_partial[(g * P.tiles_m + tm) * P.tiles_n + tn] = total;
+        }
+    }
+}
+
+__device__ __forceinline__ int flex_xcd_order(int i, int count)     // see xcd_order in gemm_mfma.h
+{
+    const int per = count >> 3;
+    return i < per * 8 ? (i & 7) * per + (i >> 3) : i;
+}
+
+// Product number j of the batch, read from the kernel-argument segment where it is needed (see params_at in gemm_mfma.h)
+__device__ __forceinline__ FlexParams flex_params_at(int j)
+{
+    constexpr int WORDS = sizeof(FlexParams) / 4;
+    union Words { FlexParams p; uint32_t w[WORDS]; __device__ Words() {} };
+    Words out;
+#if defined(__HIP_DEVICE_COMPILE__)
+    size_t offset = offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams);
+    asm volatile("" : "+s"(offset) :: "memory");
+    typedef const uint32_t __attribute__((address_space(4))) *ArgWords;
+    const ArgWords in = (ArgWords)((const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) out.w[i] = in[i];
+#endif
+    return out.p;
+}
+
+// FORWARD: products in the forward layout (bias + activation, or plain store).  Otherwise: products in the input-gradient
+// layout (sigma' or plain store, kind 0) and in the weight-gradient layout (kind 1, float out), in any mix.
+template <typename T, int TM, int TN, int TEAMS, bool FORWARD>
+__global__ __launch_bounds__((FlexShape<T, TM, TN, TEAMS>::THREADS), (FlexShape<T, TM, TN, TEAMS>::MIN_WAVES)) void gemm_flex_kernel(FlexBatch batch)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    if (batch.tail.partial && blockIdx.x == 0) {       // uniform
+        finish_loss(batch.tail, (float *)smem_raw);
+        __syncthreads();
+    }
+    int j = 0;
+    while (j + 1 < batch.count && (int)blockIdx.x >= batch.first_wg[j + 1]) ++j;       // uniform
+    const int local = (int)blockIdx.x - batch.first_wg[j];
+    const FlexParams P = flex_params_at(j);
+    if (local >= P.total_wg) return;
+    const int wg = flex_xcd_order(local, P.total_wg);
+    if constexpr (FORWARD) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KC, T, EPI_BIAS_ACT>(P, wg, smem_raw);
+    else if (P.kind == 0) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KM, T, EPI_DACT>(P, wg, smem_raw);
+    else flex_workgroup<T, TM, TN, TEAMS, FLEX_KM, FLEX_KM, float, EPI_STORE>(P, wg, smem_raw);
+}
+
+}  // namespace phantom

@@ -35,12 +35,12 @@
 //   gemm_mfma_kernel       one product, or two of the same operand layout and output type
 //   gemm_mfma_table_kernel one rank: the weight + compressor gradients of all layers, parameter blocks in device memory
 //   gemm_mfma_tail_kernel  weight + compressor gradients with riders of other layouts (the error compression of
-//                          the layer below, the SGD update of the layer above)
+//                          the layer below, the loss)
 //   gemm_mfma_fwd_kernel   a rank's layer update with the thin compression shared out over its workgroups
 #pragma once
 #include "common.h"
-#include "elementwise.h"    // SgdBatch, sgd_rider
-#include "gemm_generic.h"   // Epilogue, EPI_*
+#include "elementwise.h"    // LossTail
+#include "epilogue.h"
 #include "thin_product.h"   // thin_workgroup
 #include "views.h"
 
@@ -62,12 +62,6 @@ constexpr int TILE_ELEMS = (MT * KC_PITCH > KT * KM_PITCH) ? MT * KC_PITCH : KT 
 constexpr int MFMA_THREADS = 512;       // two teams of four wavefronts
 constexpr int MFMA_LDS_BYTES = 2 /*teams*/ * 2 /*stages*/ * 2 /*operands*/ * TILE_ELEMS * 2;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <int VEC> struct VecOf;
 template <> struct VecOf<8> { typedef u32x4 type; };
 template <> struct VecOf<4> { typedef u32x2 type; };
@@ -78,20 +72,6 @@ template <typename V>
 __device__ __forceinline__ V load_global(const __bf16 *p)
 {
     return *(const __attribute__((address_space(1))) V *)(uintptr_t)p;
-}
-
-// The epilogues' loads and stores, likewise: their pointers come out of parameter blocks, so the compiler would
-// take them for generic ones and use flat instructions (which also count as LDS operations: every wait for an LDS
-// read then waits for all of them).  _nt: streaming (read or written once).
-template <typename V> __device__ __forceinline__ V gload(const void *p) { return *(const __attribute__((address_space(1))) V *)(uintptr_t)p; }
-template <typename V> __device__ __forceinline__ V gload_nt(const void *p)
-{
-    return __builtin_nontemporal_load((const __attribute__((address_space(1))) V *)(uintptr_t)p);
-}
-template <typename V> __device__ __forceinline__ void gstore(void *p, const V &v) { *(__attribute__((address_space(1))) V *)(uintptr_t)p = v; }
-template <typename V> __device__ __forceinline__ void gstore_nt(void *p, const V &v)
-{
-    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) V *)(uintptr_t)p);
 }
 
 // ---- staging one operand tile ---------------------------------------------------------
@@ -341,27 +321,14 @@ struct SumOnRead {
     int p, k;
 };
 
-// SGD inside the epilogue that finishes a weight gradient (float output with 8-element vectors, whole or cut into
-// pieces): the parameters that the gradient belongs to, laid out like the output View's two regions.
-// master0 == nullptr: none.
-struct SgdInPlace {
-    float *master0, *master1;    // fp32 master copies: master -= lr * gradient
-    __bf16 *w0, *w1;             // bf16 compute copies: w = bf16(master)
-    float lr;
-    int keep_grad;               // also store the gradient (the caller wants to see it)
-    float *bias_master;          // weight gradients only: the layer's bias [M], its bf16 copy and its finished gradient
-    __bf16 *bias_w;              //   (Eq. (bpb): column sums of delta, left by earlier launches); the tiles of the
-    const float *bias_grad;      //   first tile column update the rows they cover.  NULL: none
-};
-
 struct MfmaParams {
     View a, b, o;        // o: the row index must not decide the region (true for every output here)
     Epilogue ep;
     SumOnRead rs;
     int M, N, K;
     int tiles_m, tiles_n;
-    int ksplit;          // > 1: the reduction range is cut into ksplit pieces; their results are added atomically
-                         //   (ATOMIC kernels) or by the piece that finishes last (parts)
+    int ksplit;          // > 1: the reduction range is cut into ksplit pieces; their results are added
+                         //   by the piece that finishes last (parts)
     int k_per_split;     // multiple of KT
     int total_wg;
     float *parts;        // ksplit > 1 without atomics (float output, 8-element vectors, one group): room for ksplit
@@ -637,7 +604,6 @@ static_assert((2 * CT_ELEMS + MFMA_THREADS / 64) * 4 <= MFMA_LDS_BYTES, "both te
 // in the untransposed layout the same data would take four 4-byte writes).
 __device__ __forceinline__ void acc_to_lds(float *ctile, const f32x16 (&acc)[2][2], int wm, int wn, int lane)
 {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -812,11 +778,11 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
         OutV o;
 #pragma unroll
         for (int u = 0; u < VEC; ++u) o[u] = from_f32<TOut>(x[u]);
-        if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4 && VEC == 8) {
-            if (P.sgd.master0) {                       // uniform: Section VI's plain SGD on the finished gradient
+        if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
+            if (P.sgd.w0) {                       // uniform: Section VI's plain SGD on the finished gradient
                 const int64_t at = dst - (region ? o1 : o0);
                 float *master = (region ? P.sgd.master1 : P.sgd.master0) + g * (region ? P.o.g1 : P.o.g0) + at;
-                __bf16 *w = (region ? P.sgd.w1 : P.sgd.w0) + g * (region ? P.o.g1 : P.o.g0) + at;
+                __bf16 *w = (__bf16 *)(region ? P.sgd.w1 : P.sgd.w0) + g * (region ? P.o.g1 : P.o.g0) + at;
                 const FlV before = gload<FlV>(master);     // (requested ahead of the loop like sigma', the launch got 4 % slower)
                 FlV after;
                 BfV rounded;
@@ -862,12 +828,12 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
             for (int u = 0; u < VEC; ++u) csum[u] += (float)o[u];
         }
     }
-    if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4 && VEC == 8) {
+    if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
         if (P.sgd.bias_master && n0 == 0 && thread < MT && m0 + thread < P.M) {
             const int64_t at = g * (int64_t)P.M + m0 + thread;
             const float nb = gload<float>(P.sgd.bias_master + at) - P.sgd.lr * gload<float>(P.sgd.bias_grad + at);
             gstore<float>(P.sgd.bias_master + at, nb);
-            gstore<__bf16>(P.sgd.bias_w + at, (__bf16)nb);
+            gstore<__bf16>((__bf16 *)P.sgd.bias_w + at, (__bf16)nb);
         }
     }
     if (EPI == EPI_BIAS_ACT && sizeof(TOut) == 2 && ep.mode == EPI_BIAS_ACT && ep.mse_target) {          // uniform
@@ -906,48 +872,6 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
     }
 }
 
-// Split reductions: the sum of the two teams' fp32 tiles is ADDED to a float output, element by element
-// (plain store semantics only: no bias, activation or column sums).  Device-wide float atomics that
-// fall into one 64-byte line are served together, so the 16 lanes that share a tile row take 16
-// consecutive columns per instruction (thread: row t / 16 of each group of 32 rows, columns
-// t % 16 + 16 u), four full lines per wavefront instruction; eight consecutive columns per lane touch 32
-// half-used lines per instruction (measured on a 1024 x 1984 x 4096 product cut into 390 partial tiles:
-// 186 us against 47 us for the whole launch).  What remains is about one add per clock and memory
-// channel, 15-20 us for those 6.4 M adds, which is why a split reduction is a last resort.
-__device__ __forceinline__ void epilogue_atomic_from_lds(const MfmaParams &P, int g, const float *ctile, int m0, int n0, int thread)
-{
-    constexpr int LANES = 16;                          // lanes per tile row
-    constexpr int COLS = MT / LANES;                   // columns per thread
-    constexpr int ROWS_PER_PASS = MFMA_THREADS / LANES;
-    float *o0 = (float *)P.o.p0 + g * P.o.g0, *o1 = (float *)P.o.p1 + g * P.o.g1;
-    const int skip_o = P.o.skip0 + g * P.o.skip_g;
-    const int cl = thread % LANES, r0 = thread / LANES;
-    // a thread keeps its columns from pass to pass: their places in the output, once
-    int64_t col_off[COLS];
-    bool col_tail[COLS];
-#pragma unroll
-    for (int u = 0; u < COLS; ++u) {
-        const int n = min(n0 + cl + LANES * u, P.N - 1);
-        const Loc ln = locate(P.o.c, n, skip_o);
-        col_tail[u] = ln.region > 0;
-        col_off[u] = col_tail[u] ? ln.off1 : ln.off0;
-    }
-#pragma unroll 2
-    for (int i = 0; i < MT / ROWS_PER_PASS; ++i) {
-        const int row = r0 + i * ROWS_PER_PASS;
-        const int m = m0 + row;
-        if (m >= P.M) continue;
-#pragma unroll
-        for (int u = 0; u < COLS; ++u) {
-            const int col = cl + LANES * u;
-            if (n0 + col >= P.N) continue;
-            const float x = ctile[row * CT_PITCH + col] + ctile[CT_ELEMS + row * CT_PITCH + col];
-            float *dst = (col_tail[u] ? o1 + (int64_t)m * P.o.r.mult1 : o0 + (int64_t)m * P.o.r.mult0) + col_off[u];
-            unsafeAtomicAdd(dst, x);
-        }
-    }
-}
-
 // The epilogue of one piece of a reduction that is cut into ksplit pieces without atomics (float output, plain store
 // semantics, 8 columns per thread, all 512 threads).  Every piece writes its 128 x 128 result to its own slot of
 // P.parts and then counts itself in P.arrived[tile]; the piece that finds all others counted adds the slots up in the
@@ -962,7 +886,6 @@ __device__ __forceinline__ void epilogue_pieces_from_lds(const MfmaParams &P, in
                                                          int m0, int n0, int thread)
 {
     typedef unsigned long long u64;
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int VEC = 8, PER_ROW = MT / VEC, PASSES = MT * PER_ROW / MFMA_THREADS, WORDS = VEC / 2;
     constexpr int ROWS_PER_PASS = MFMA_THREADS / PER_ROW;
     constexpr int64_t SLOT = MT * MT / 2;              // 8-byte words per slot
@@ -1045,9 +968,9 @@ __device__ __forceinline__ void epilogue_pieces_from_lds(const MfmaParams &P, in
         const int region = ln.region > 0 ? 1 : 0;
         const int64_t at = (region ? ln.off1 : ln.off0) + (int64_t)m * (region ? P.o.r.mult1 : P.o.r.mult0);
         float *dst = (region ? o1 : o0) + at;
-        if (P.sgd.master0) {                           // uniform: Section VI's plain SGD on the finished gradient
+        if (P.sgd.w0) {                           // uniform: Section VI's plain SGD on the finished gradient
             float *master = (region ? P.sgd.master1 : P.sgd.master0) + at;
-            __bf16 *w = (region ? P.sgd.w1 : P.sgd.w0) + at;
+            __bf16 *w = (__bf16 *)(region ? P.sgd.w1 : P.sgd.w0) + at;
             const f32x4 m_lo = gload<f32x4>(master), m_hi = gload<f32x4>(master + 4);
             float nm[VEC];
             bf16x8 nw;
@@ -1129,13 +1052,11 @@ __device__ __forceinline__ int xcd_order(int id, int first, int count)
 // One workgroup's work: workgroup number wg (of P.total_wg, in tile order) of the product P.
 // FOLD (the forward layout with 8-element vectors, regular shapes only): the workgroup also computes its block of
 // the compression F (FoldParams).
-template <int KA, int KB, int VA, int VB, typename TOut, bool ATOMIC, bool DUAL, int EPI, bool FOLD = false>
+template <int KA, int KB, int VA, int VB, typename TOut, bool DUAL, int EPI, bool FOLD = false>
 __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, const FoldParams *Fp = nullptr)
 {
-    static_assert(!FOLD || (KA == LD_KC && KB == LD_KC && VA == 8 && !ATOMIC), "the compression rides with the forward product only");
+    static_assert(!FOLD || (KA == LD_KC && KB == LD_KC && VA == 8), "the compression rides with the forward product only");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    static_assert(!(DUAL && ATOMIC), "a split reduction keeps the two-teams-per-tile form");
-    static_assert(!ATOMIC || EPI == EPI_STORE, "partial sums are added as they are");
     constexpr int BP = DUAL ? 2 : 1;                   // share of the B tile one team stages
     PH_PHASE(0);
     const int tiles = P.tiles_m * P.tiles_n;           // DUAL: tiles_m counts pairs of tile rows
@@ -1333,12 +1254,11 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, cons
     // each team writes its fp32 tile over the staging space (free after the barrier above).  Two teams
     // on one tile hold partial sums of it: the epilogue adds the two while reading.
     float *ctile = (float *)smem_raw;
-    constexpr bool PIECES = !ATOMIC && !DUAL && !FOLD && EPI == EPI_STORE && sizeof(TOut) == 4 && VA == 8;
+    constexpr bool PIECES = !DUAL && !FOLD && EPI == EPI_STORE && sizeof(TOut) == 4 && VA == 8;
     acc_to_lds(ctile + team * CT_ELEMS, acc, wm, wn, lane);
     __syncthreads();
     PH_PHASE(4);
-    if constexpr (ATOMIC) epilogue_atomic_from_lds(P, g, ctile, m0, n0, (int)threadIdx.x);
-    else if constexpr (DUAL) epilogue_from_lds<VA, TOut, true, EPI>(P, g, ctile + team * CT_ELEMS, m0, n0, tid, ctile + 2 * CT_ELEMS);
+    if constexpr (DUAL) epilogue_from_lds<VA, TOut, true, EPI>(P, g, ctile + team * CT_ELEMS, m0, n0, tid, ctile + 2 * CT_ELEMS);
     else if constexpr (PIECES) {
         if (P.parts && P.ksplit > 1)                                 // uniform (one group: the host sees to that)
             epilogue_pieces_from_lds(P, rem, ks, ctile, (unsigned *)(ctile + 2 * CT_ELEMS), m0, n0, (int)threadIdx.x);
@@ -1383,14 +1303,14 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, cons
     }
 }
 
-template <int KA, int KB, int VA, int VB, typename TOut, bool ATOMIC, bool PAIR, bool DUAL, int EPI>
+template <int KA, int KB, int VA, int VB, typename TOut, bool PAIR, bool DUAL, int EPI>
 __global__ __launch_bounds__(512, 1) void gemm_mfma_kernel(MfmaBatch batch)
 {
     int wg = xcd_order(blockIdx.x, 0, batch.total_wg);
     const bool second = PAIR && wg >= batch.first_wg;
     if (second) wg -= batch.first_wg;
     const MfmaParams P = params_at(second ? offsetof(MfmaBatch, p[1]) : offsetof(MfmaBatch, p[0]));
-    mfma_workgroup<KA, KB, VA, VB, TOut, ATOMIC, DUAL, EPI>(P, wg);
+    mfma_workgroup<KA, KB, VA, VB, TOut, DUAL, EPI>(P, wg);
 }
 
 // The last launch of a layer's backward pass, the weight + compressor gradients (tail[0], tail[1]: weight-gradient
@@ -1401,20 +1321,17 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_kernel(MfmaBatch batch)
 //    One rank, first layer (no input gradient to share a launch with): the layer's own error compression.  Nothing
 //    waits for it, so with more workgroups than compute units it goes out last (rotate) and fills in behind the
 //    longer weight-gradient workgroups.
-//  - the SGD update of the layer above (sgd_wg workgroups from sgd_first on) on compute units that the
-//    products leave idle; its gradients sit in other buffers than the ones tail[] writes.
-// tail_first and sgd_first are multiples of 8; workgroups in the gaps do nothing.
+//  - the loss's final sum, one more workgroup.
+// tail_first is a multiple of 8; workgroups in the gap do nothing.
 struct MfmaTailBatch {
     MfmaParams head;
     MfmaParams tail[2];
-    SgdBatch sgd;
-    float lr;
+    LossTail loss;
     int head_wg;         // = head.total_wg (0: no head)
     int tail_first;
     int tail_wg;         // = tail[0].total_wg + tail[1].total_wg
     int tail0_wg;        // = tail[0].total_wg
-    int sgd_first;
-    int sgd_wg;          // 0: no update
+    int loss_first;      // the workgroup behind the tail's finishes the loss (loss.partial != NULL)
     int rotate;          // workgroup b does the work of number (b + rotate) mod the grid size: rotate = tail_first
                          //   sends the head's workgroups out last instead of first
     int dual;            // every product of the launch in two-tile workgroups (DUAL of mfma_workgroup): for a launch
@@ -1429,10 +1346,9 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_tail_kernel(MfmaTailBatch tb
     if (id < tb.tail_first) {                          // uniform, like every branch here
         if (id >= tb.head_wg) return;
         const MfmaParams P = params_at(offsetof(MfmaTailBatch, head));
-        if (tb.dual) mfma_workgroup<LD_KC, LD_KM, VEC, VEC, __bf16, false, true, EPI_STORE>(P, xcd_order(id, 0, tb.head_wg));
-        else mfma_workgroup<LD_KC, LD_KM, VEC, VEC, __bf16, false, false, EPI_STORE>(P, xcd_order(id, 0, tb.head_wg));
-    } else if (id < tb.sgd_first) {
-        if (id >= tb.tail_first + tb.tail_wg) return;
+        if (tb.dual) mfma_workgroup<LD_KC, LD_KM, VEC, VEC, __bf16, true, EPI_STORE>(P, xcd_order(id, 0, tb.head_wg));
+        else mfma_workgroup<LD_KC, LD_KM, VEC, VEC, __bf16, false, EPI_STORE>(P, xcd_order(id, 0, tb.head_wg));
+    } else if (id < tb.loss_first) {
         // The XCD-aware order within each product, and within each slab of pieces of a product whose reduction is cut
         // (all first pieces, then all second ones, ...: a piece waits for the one before it, which must not sit
         // behind it in the dispatch order)
@@ -1441,11 +1357,11 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_tail_kernel(MfmaTailBatch tb
         if (second) wg -= tb.tail0_wg;
         wg = xcd_order(wg, 0, second ? tb.tail_wg - tb.tail0_wg : tb.tail0_wg);
         const MfmaParams P = params_at(second ? offsetof(MfmaTailBatch, tail[1]) : offsetof(MfmaTailBatch, tail[0]));
-        if (tb.dual) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, true, EPI_STORE>(P, wg);
-        else mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, false, EPI_STORE>(P, wg);
+        if (tb.dual) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, true, EPI_STORE>(P, wg);
+        else mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, EPI_STORE>(P, wg);
     } else {
         extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-        sgd_rider<__bf16>(tb.sgd, tb.lr, id - tb.sgd_first, tb.sgd_wg, MFMA_THREADS, (float *)smem_raw);
+        finish_loss(tb.loss, (float *)smem_raw);
     }
 }
 
@@ -1527,8 +1443,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_table_kernel(const ProductTa
     const ArgWords in = (ArgWords)&t->p[j];
 #pragma unroll
     for (int i = 0; i < WORDS; ++i) blk.w[i] = in[i];
-    if (t->dual[j]) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, true, EPI_STORE>(blk.p, xcd_order(local, 0, wgs));
-    else mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, false, EPI_STORE>(blk.p, xcd_order(local, 0, wgs));
+    if (t->dual[j]) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, true, EPI_STORE>(blk.p, xcd_order(local, 0, wgs));
+    else mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, EPI_STORE>(blk.p, xcd_order(local, 0, wgs));
 #endif
 }
 
@@ -1563,9 +1479,9 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_fwd_kernel(MfmaFwdBatch fb)
     const MfmaParams update = params_at(offsetof(MfmaFwdBatch, update));
     if constexpr (FOLD) {
         // the compression rides inside the update's reduction loop (FoldParams)
-        mfma_workgroup<LD_KC, LD_KC, VEC, VEC, __bf16, false, DUAL, EPI_BIAS_ACT, true>(update, wg, &fb.fold);
+        mfma_workgroup<LD_KC, LD_KC, VEC, VEC, __bf16, DUAL, EPI_BIAS_ACT, true>(update, wg, &fb.fold);
     } else {
-        mfma_workgroup<LD_KC, LD_KC, VEC, VEC, __bf16, false, DUAL, EPI_BIAS_ACT>(update, wg);
+        mfma_workgroup<LD_KC, LD_KC, VEC, VEC, __bf16, DUAL, EPI_BIAS_ACT>(update, wg);
         const int grp = wg / fb.wg_per_group;
         const int first = (wg - grp * fb.wg_per_group) * fb.thin_rows;
         const int last = min(first + fb.thin_rows, fb.M);

@@ -17,7 +17,7 @@
 
 #include "common.h"
 #include "elementwise.h"
-#include "gemm_generic.h"
+#include "gemm_flex.h"
 #include "gemm_mfma.h"
 #include "thin_product.h"
 #include "views.h"
@@ -62,7 +62,7 @@ struct Geo {
     bool all;         // all-ranks mode
     int act, dtype, rank, layers;
     size_t esz;       // bytes per element of the storage type
-    int vec;          // bf16: widest vector (8, 4, 2 elements) dividing si, so and k; 0: shape-agnostic kernels only
+    int vec;          // bf16: widest vector (8 or 4 elements) dividing si, so and k; 0: the kernels of gemm_flex.h only
 };
 
 // Checks the problem and fills in the shapes of layer `layer` (0-based).
@@ -100,12 +100,12 @@ ph_status make_geo(const ph_problem *pr, Geo &g, int layer = 0)
     g.esz = pr->dtype == PH_BF16 ? 2 : 4;
     g.vec = 0;
     if (pr->dtype == PH_BF16) {
-        for (int v = 8; v >= 2 && !g.vec; v >>= 1)
+        for (int v = 8; v >= 4 && !g.vec; v >>= 1)
             if (si % v == 0 && so % v == 0 && (g.q == 0 || g.k % v == 0)) g.vec = v;
     }
     // The matrix-core kernels address an operand with 32-bit element offsets inside one rank's share of a tensor:
-    // a problem with a larger tensor goes through the shape-agnostic kernels (64-bit offsets) like one whose widths
-    // allow no vector loads.
+    // a problem with a larger tensor goes through the kernels with 64-bit offsets like one whose widths
+    // allow no vector loads (gemm_flex.h).
     {
         const int64_t wide = std::max(si, so), slots = g.all ? g.p : g.q;
         const int64_t largest = std::max({g.B * wide, slots * g.B * g.k, so * si, slots * so * g.k, g.k * si});
@@ -223,7 +223,6 @@ struct Arena {
     }
 };
 
-constexpr int MSE_BLOCKS = 1024;
 constexpr int PIECE_WORDS = 512;      // output tiles of the products of one launch whose reduction may be cut into pieces (MfmaParams::arrived)
 
 struct BwdWs {
@@ -335,7 +334,9 @@ StepWs carve_step(Arena &a, const std::vector<Geo> &geos)
         w.parts = nullptr;
         w.table = nullptr;
     }
-    w.mse_partial = (float *)a.take(MSE_BLOCKS * sizeof(float));
+    // one partial sum of the loss per output tile of the last layer, at the smallest tile (32 x 32)
+    const Geo &gL = geos.back();
+    w.mse_partial = (float *)a.take((size_t)((gL.B + 31) / 32) * (size_t)((gL.so + 31) / 32 * g0.groups) * sizeof(float));
     w.bwd.delta = a.take(groups * B * act_max * g0.esz);
     return w;
 }
@@ -349,26 +350,54 @@ inline unsigned blocks_for(int64_t count, int per_block = 256, int cap = 8192)
     return (unsigned)b;
 }
 
-// How a product is to be run: loader kinds of the two operands for the MFMA kernel, the vector
-// width the problem allows (0: use the shape-agnostic kernel), and whether the reduction may be
-// split over workgroups (float outputs only; the output is cleared first and added to atomically).
+// Does this bf16 problem run on the kernels of gemm_flex.h rather than the 128 x 128 ones?  Widths or phantom widths that
+// no 8- or 4-element vector divides always do.  Otherwise where a layer's output has so few 128 x 128 tiles that they leave
+// compute units idle: 64 x 64 tiles then spread over four times as many workgroups, and the backward pass has fewer launches.
+// Measured (us, 128 x 128 kernels against these): 3 layers of 1024 with batch 1000 trained, 64 tiles, 158 : 130; 4 layers
+// forward, 32 / 64 / 128 tiles, 76 : 59, 78 : 62, 80 : 77; 3 layers of 1024 trained at batch 2000, 128 tiles, 169 : 179; 256
+// tiles and more lose everywhere (8 layers of 1024 at batch 4096: 719 : 907).  At 128 tiles the weight gradients
+// decide: with a batch longer than the layer is wide they have few tiles and a long reduction (512 wide, batch 4000:
+// 151 : 195), otherwise many (2048 wide, batch 1000: 254 : 234).
+// A layer's backward call saves two launches more: up to 192 tiles (1000 wide, batch 3000: 91 : 81).
+// All ranks on the device: the 128 x 128 kernels' launches carry the next layer's error compression and sum the
+// reduce-scatter on read.
+bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call = false)
+{
+    int64_t tiles = 0;
+    bool wide = true;
+    for (const Geo &g : geos) {
+        if (g.vec == 0) return true;
+        tiles = std::max(tiles, tiles_of(g.B, g.so) * g.groups);
+        wide = wide && g.B <= g.so;
+    }
+    static const char *force = tuning_env("PHANTOM_FLEX");
+    if (force) return force[0] == '1';
+    if (geos[0].all) return false;
+    if (single_call) return tiles <= 192;
+    return tiles <= (!backward || wide ? 128 : 96);
+}
+
+// How a product is to be run on the 128 x 128 kernels: loader kinds of the two operands and the vector width the
+// problem allows.
 struct GemmPlan {
     int ka, kb;
     int vec;
-    bool may_split;
 };
 
 struct Product {
     View a, b, o;
     Epilogue ep;
     int64_t M, N, K;
-    SumOnRead rs;        // matrix-core path only: the tail block of a is summed on read (src != nullptr)
+    SumOnRead rs;        // gemm_mfma kernels only: the tail block of a is summed on read (src != nullptr)
+    SgdInPlace sgd;      // weight gradients: the update applied by the epilogue that finishes them (w0 == nullptr: none)
+    float *rowsum;       // gemm_flex kernels, weight gradients: receives the bias gradient (MfmaParams has no such thing)
+    bool km;             // gemm_flex kernels: weight-gradient layout (both operands along their free index), float out
 };
 
-template <int KA, int KB, int VEC, typename TOut, bool ATOMIC, bool PAIR, bool DUAL, int EPI>
+template <int KA, int KB, int VEC, typename TOut, bool PAIR, bool DUAL, int EPI>
 ph_status launch_mfma_kernel(const MfmaBatch &batch, hipStream_t st, const char *what)
 {
-    auto kern = gemm_mfma_kernel<KA, KB, VEC, VEC, TOut, ATOMIC, PAIR, DUAL, EPI>;
+    auto kern = gemm_mfma_kernel<KA, KB, VEC, VEC, TOut, PAIR, DUAL, EPI>;
     static thread_local bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
@@ -380,34 +409,29 @@ ph_status launch_mfma_kernel(const MfmaBatch &batch, hipStream_t st, const char 
     return check_launch(what);
 }
 
-template <int KA, int KB, int VEC, typename TOut, bool ATOMIC, int EPI>
+template <int KA, int KB, int VEC, typename TOut, int EPI>
 ph_status launch_mfma_inst(const MfmaBatch &batch, bool dual, hipStream_t st, const char *what)
 {
-    if constexpr (!ATOMIC) {
-        if (dual) {
-            if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, false, true, true, EPI>(batch, st, what);
-            return launch_mfma_kernel<KA, KB, VEC, TOut, false, false, true, EPI>(batch, st, what);
-        }
+    if (dual) {
+        if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, true, true, EPI>(batch, st, what);
+        return launch_mfma_kernel<KA, KB, VEC, TOut, false, true, EPI>(batch, st, what);
     }
-    if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, ATOMIC, true, false, EPI>(batch, st, what);
-    return launch_mfma_kernel<KA, KB, VEC, TOut, ATOMIC, false, false, EPI>(batch, st, what);
+    if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, true, false, EPI>(batch, st, what);
+    return launch_mfma_kernel<KA, KB, VEC, TOut, false, false, EPI>(batch, st, what);
 }
 
 // EPI: the epilogue mode the kernel is built for besides the plain store (see epilogue_from_lds)
-template <int KA, int KB, typename TOut, bool ATOMIC, int EPI>
+template <int KA, int KB, typename TOut, int EPI>
 ph_status launch_mfma_vec(const MfmaBatch &batch, int vec, bool dual, hipStream_t st, const char *what)
 {
-    switch (vec) {
-    case 8: return launch_mfma_inst<KA, KB, 8, TOut, ATOMIC, EPI>(batch, dual, st, what);
-    case 4: return launch_mfma_inst<KA, KB, 4, TOut, ATOMIC, EPI>(batch, dual, st, what);
-    default: return launch_mfma_inst<KA, KB, 2, TOut, ATOMIC, EPI>(batch, dual, st, what);
-    }
+    if (vec == 8) return launch_mfma_inst<KA, KB, 8, TOut, EPI>(batch, dual, st, what);
+    return launch_mfma_inst<KA, KB, 4, TOut, EPI>(batch, dual, st, what);
 }
 
 MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
 {
     MfmaParams P{};
-    P.a = pr.a; P.b = pr.b; P.o = pr.o; P.ep = pr.ep; P.rs = pr.rs;
+    P.a = pr.a; P.b = pr.b; P.o = pr.o; P.ep = pr.ep; P.rs = pr.rs; P.sgd = pr.sgd;
     P.M = (int)pr.M; P.N = (int)pr.N; P.K = (int)pr.K;
     const int mt = dual ? 2 * MT : MT;               // rows of C per workgroup
     P.tiles_m = (int)((pr.M + mt - 1) / mt);
@@ -424,34 +448,18 @@ MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
 template <typename TOut>
 ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int groups, hipStream_t st, const char *what)
 {
-    int ksplit = 1;
     const Product &first = prods[0];
-    const int64_t tiles = ((first.M + MT - 1) / MT) * ((first.N + MT - 1) / MT) * groups;
+    const int64_t tiles = tiles_of(first.M, first.N) * groups;
     if (tiles * 8 > 0x7fffffff) return fail(PH_ERR_LAUNCH, "%s: internal error, too many tiles (make_geo admits none such)", what);
-    if (count == 1 && plan.may_split && std::is_same<TOut, float>::value && first.ep.mode == EPI_STORE) {
-        // Splitting pays only when the tiles cover a small part of the 256 compute units: the atomic
-        // adds of a split cost about as much as the product itself (measured: 512 x 736 x 1024 x 8
-        // takes 34 us unsplit, 64 us in 3 pieces).  Then aim at one workgroup per compute unit and
-        // keep at least 8 reduction steps per piece.
-        const int ksteps = (int)((first.K + KT - 1) / KT);
-        // A short reduction is not worth a split either (32 x 512 x 1024 x 16: 13 us whole, 27 us + a clear in pieces).
-        if (tiles < 96 && ksteps >= 32)
-            ksplit = (int)std::max<int64_t>(1, std::min<int64_t>((256 + tiles - 1) / tiles, ksteps / 8));
-    }
     // More tiles than compute units: the launch would run in rounds.  Then two tiles, one above the other,
     // go to one workgroup (its teams share the B tile): fewer bytes staged per FLOP and half the rounds.
     // PHANTOM_DUAL=0 / 1 forces the choice (for measurements).
-    bool dual = false;
-    if (ksplit == 1) {
-        int64_t all_tiles = tiles;
-        if (count == 2) all_tiles += ((prods[1].M + MT - 1) / MT) * ((prods[1].N + MT - 1) / MT) * groups;
-        dual = all_tiles > 256;
-        static const char *force = tuning_env("PHANTOM_DUAL");
-        if (force) dual = force[0] == '1';
-    }
+    bool dual = tiles + (count == 2 ? tiles_of(prods[1].M, prods[1].N) * groups : 0) > 256;
+    static const char *force = tuning_env("PHANTOM_DUAL");
+    if (force) dual = force[0] == '1';
     MfmaBatch batch{};
     batch.count = count;
-    batch.p[0] = mfma_params(first, groups, ksplit, dual);
+    batch.p[0] = mfma_params(first, groups, 1, dual);
     batch.total_wg = batch.p[0].total_wg;
     batch.first_wg = batch.p[0].total_wg;
     if (count == 2) {
@@ -459,23 +467,6 @@ ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int
         batch.total_wg += batch.p[1].total_wg;
     }
     const Product &second = prods[count - 1];
-    if (batch.p[0].ksplit > 1) {
-        if constexpr (std::is_same<TOut, float>::value) {
-            // clear what the split pieces add into (both regions of the output view)
-            for (int region = 0; region < 2; ++region) {
-                float *base = (float *)(region ? first.o.p1 : first.o.p0);
-                const int64_t per_group = region ? first.o.g1 : first.o.g0;
-                if (!base || per_group <= 0) continue;
-                const int64_t n = per_group * groups;
-                ProfScope prof("clear split-K output", 0, n, 0, 1, st);
-                hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks_for(n, 1024)), dim3(256), 0, st, base, n);
-                PH_TRY(check_launch("clear split-K output"));
-            }
-            ProfScope prof(what, first.M, first.N, first.K, groups, st);
-            if (plan.ka == LD_KM && plan.kb == LD_KM) return launch_mfma_vec<LD_KM, LD_KM, float, true, EPI_STORE>(batch, plan.vec, false, st, what);
-        }
-        return fail(PH_ERR_LAUNCH, "%s: internal error, split reduction asked for an operand layout that has none", what);
-    }
     ProfScope prof(what, first.M, first.N, first.K, groups, st, count == 2 ? second.M : 0, count == 2 ? second.N : 0,
                    count == 2 ? second.K : 0);
     // The kernels that exist: the forward layout (both operands read along the reduction index) with the
@@ -486,23 +477,23 @@ ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int
     if (count == 2 && second.ep.mode != EPI_STORE) return fail(PH_ERR_LAUNCH, "%s: internal error, the second product of a pair must store plainly", what);
     if constexpr (std::is_same<TOut, float>::value) {
         if (plan.ka == LD_KM && plan.kb == LD_KM && mode == EPI_STORE)
-            return launch_mfma_vec<LD_KM, LD_KM, float, false, EPI_STORE>(batch, plan.vec, dual, st, what);
+            return launch_mfma_vec<LD_KM, LD_KM, float, EPI_STORE>(batch, plan.vec, dual, st, what);
     } else {
         if (plan.ka == LD_KC && plan.kb == LD_KC) {
-            if (mode == EPI_BIAS_ACT) return launch_mfma_vec<LD_KC, LD_KC, TOut, false, EPI_BIAS_ACT>(batch, plan.vec, dual, st, what);
-            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KC, TOut, false, EPI_STORE>(batch, plan.vec, dual, st, what);
+            if (mode == EPI_BIAS_ACT) return launch_mfma_vec<LD_KC, LD_KC, TOut, EPI_BIAS_ACT>(batch, plan.vec, dual, st, what);
+            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KC, TOut, EPI_STORE>(batch, plan.vec, dual, st, what);
         }
         if (plan.ka == LD_KC && plan.kb == LD_KM) {
-            if (mode == EPI_DACT) return launch_mfma_vec<LD_KC, LD_KM, TOut, false, EPI_DACT>(batch, plan.vec, dual, st, what);
-            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KM, TOut, false, EPI_STORE>(batch, plan.vec, dual, st, what);
+            if (mode == EPI_DACT) return launch_mfma_vec<LD_KC, LD_KM, TOut, EPI_DACT>(batch, plan.vec, dual, st, what);
+            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KM, TOut, EPI_STORE>(batch, plan.vec, dual, st, what);
         }
     }
     return fail(PH_ERR_LAUNCH, "%s: internal error, no kernel for this operand layout, output type and epilogue", what);
 }
 
 // The weight + compressor gradients (tail0, tail1; tail1 may be empty) with their riders in one launch: the
-// error compression of the layer below (head, may be NULL) and the SGD update of the layer above (sgd, may be
-// NULL, on sgd_wg workgroups): see MfmaTailBatch.
+// error compression of the layer below (head, may be NULL) and the loss's final sum (loss.partial may be NULL): see
+// MfmaTailBatch.
 template <int VEC>
 ph_status launch_tail_kernel(const MfmaTailBatch &tb, unsigned total_wg, hipStream_t st, const char *what)
 {
@@ -518,8 +509,7 @@ ph_status launch_tail_kernel(const MfmaTailBatch &tb, unsigned total_wg, hipStre
     return check_launch(what);
 }
 
-ph_status launch_tail(const Product *head, const Product &tail0, const Product &tail1, const SgdBatch *sgd, float lr,
-                      int sgd_wg, int groups, int vec, hipStream_t st, const char *what, bool head_last = false)
+ph_status launch_tail(const Product *head, const Product &tail0, const Product &tail1, const LossTail &loss, int groups, int vec, hipStream_t st, const char *what, bool head_last = false)
 {
     MfmaTailBatch tb{};
     const bool two = tail1.M > 0 && tail1.N > 0;
@@ -544,27 +534,22 @@ ph_status launch_tail(const Product *head, const Product &tail0, const Product &
         tb.tail[1] = mfma_params(tail1, groups, 1, dual);
         tb.tail_wg += tb.tail[1].total_wg;
     }
-    tb.sgd_first = (tb.tail_first + tb.tail_wg + 7) & ~7;
-    tb.sgd_wg = sgd ? sgd_wg : 0;
-    if (sgd) { tb.sgd = *sgd; tb.lr = lr; }
+    tb.loss_first = tb.tail_first + tb.tail_wg;
+    tb.loss = loss;
     ProfScope prof(what, tail0.M, tail0.N, tail0.K, groups, st, two ? tail1.M : 0, two ? tail1.N : 0, two ? tail1.K : 0,
                    head ? head->M : 0, head ? head->N : 0, head ? head->K : 0);
-    const unsigned total = (unsigned)(tb.sgd_first + tb.sgd_wg);
+    const unsigned total = (unsigned)(tb.loss_first + (loss.partial ? 1 : 0));
     tb.rotate = (head && head_last) ? tb.tail_first : 0;
-    switch (vec) {
-    case 8: return launch_tail_kernel<8>(tb, total, st, what);
-    case 4: return launch_tail_kernel<4>(tb, total, st, what);
-    default: return launch_tail_kernel<2>(tb, total, st, what);
-    }
+    return vec == 8 ? launch_tail_kernel<8>(tb, total, st, what) : launch_tail_kernel<4>(tb, total, st, what);
 }
 
 // The weight-gradient-layout products `prods` (float out, 8-element vectors, one group each; at most TABLE_PRODUCTS)
 // in one launch through a parameter table in device memory: see gemm_mfma_table_kernel.  upload_product_table
 // fills the table (small launches, any time before); launch_product_table runs the products.
 // splits[j] > 1 cuts product j's reduction into pieces (parts, arrived: room for all of them, see MfmaParams);
-// sgd[j].master0 != NULL puts the SGD update into product j's epilogue.  tail: the launch's first workgroup finishes
+// A product's sgd.w0 != NULL puts the SGD update into its epilogue.  tail: the launch's first workgroup finishes
 // the loss.  clear_at, clear_count: floats that the first upload launch clears on its way.  *grid: the launch's size.
-ph_status upload_product_table(const std::vector<Product> &prods, const std::vector<int> &splits, const std::vector<SgdInPlace> &sgd,
+ph_status upload_product_table(const std::vector<Product> &prods, const std::vector<int> &splits,
                                ProductTable *table, float *parts, unsigned *arrived, const LossTail &tail, float *clear_at,
                                int64_t clear_count, hipStream_t st, int *grid)
 {
@@ -589,7 +574,6 @@ ph_status upload_product_table(const std::vector<Product> &prods, const std::vec
             P.parts = parts + slot * MT * MT; P.arrived = arrived + word;
             slot += (size_t)tiles * splits[j]; word += (size_t)tiles;
         }
-        P.sgd = sgd[j];
         first.push_back(next);
         next += (P.total_wg + 7) & ~7;
         blocks.push_back(P);
@@ -672,15 +656,12 @@ ph_status launch_fwd_pair(const Product &update, const Product &compress, int gr
         fb.fold.N = (int)k; fb.fold.K = (int)si; fb.fold.ncb = ncb; fb.fold.nblocks = 4 * ncb;
         return launch_fwd_kernel<8, false, true>(fb, total, st, what);
     }
-    switch (vec) {
-    case 8: return dual ? launch_fwd_kernel<8, true>(fb, total, st, what) : launch_fwd_kernel<8, false>(fb, total, st, what);
-    case 4: return dual ? launch_fwd_kernel<4, true>(fb, total, st, what) : launch_fwd_kernel<4, false>(fb, total, st, what);
-    default: return dual ? launch_fwd_kernel<2, true>(fb, total, st, what) : launch_fwd_kernel<2, false>(fb, total, st, what);
-    }
+    if (vec == 8) return dual ? launch_fwd_kernel<8, true>(fb, total, st, what) : launch_fwd_kernel<8, false>(fb, total, st, what);
+    return dual ? launch_fwd_kernel<4, true>(fb, total, st, what) : launch_fwd_kernel<4, false>(fb, total, st, what);
 }
 
-// Runs one product, or two independent ones of the same kind (names: `what` for the pair on the
-// matrix cores, `what` / `what2` when they run as separate launches of the shape-agnostic kernel).
+// Runs one product, or two independent ones of the same kind (names: `what` for the pair, `what_first` / `what_second`
+// when they run as launches of their own).
 template <typename TIn, typename TOut>
 ph_status launch_products(const GemmPlan &plan, const Product *prods_in, int count_in, int groups, hipStream_t st,
                           const char *what, const char *what_first = nullptr, const char *what_second = nullptr)
@@ -694,51 +675,158 @@ ph_status launch_products(const GemmPlan &plan, const Product *prods_in, int cou
             prods[count++] = prods_in[i];
         }
     if (count == 0 || groups <= 0) return PH_OK;
-    if constexpr (std::is_same<TIn, bf16_t>::value) {
-        if (plan.vec > 0) {
-            // Two products share a launch when the launch-time model below says the pair is faster.  A
-            // workgroup occupies a whole compute unit, so up to 256 tiles run at once (fixed cost ~8.6 us +
-            // 0.5 us per 64 of the reduction length); above that, workgroups take two tiles each (~9.5 us +
-            // 0.76 us per 64) and run in rounds of 256.  Separate launches pay ~2.5 us for the extra launch.
-            // PHANTOM_PAIR=0 / 1 forces the choice (for measurements).
-            bool pair = count == 2;
-            if (pair) {
-                auto tiles_of = [&](const Product &pr) { return ((pr.M + MT - 1) / MT) * ((pr.N + MT - 1) / MT) * groups; };
-                auto launch_us = [](int64_t tiles, int64_t K) {
-                    const double steps = (double)((K + KT - 1) / KT);
-                    if (tiles <= 256) return 8.6 + 0.5 * steps;
-                    return (double)(((tiles + 1) / 2 + 255) / 256) * (9.5 + 0.76 * steps);
-                };
-                const int64_t t0 = tiles_of(prods[0]), t1 = tiles_of(prods[1]);
-                const double together = launch_us(t0 + t1, std::max(prods[0].K, prods[1].K));
-                const double apart = launch_us(t0, prods[0].K) + launch_us(t1, prods[1].K) + 2.5;
-                pair = together < apart;
-                static const char *force = tuning_env("PHANTOM_PAIR");
-                if (force) pair = force[0] == '1';
-            }
-            if (pair || count == 1) return launch_mfma<TOut>(plan, prods, count, groups, st, count == 2 ? what : names[0]);
-            GemmPlan single = plan;
-            PH_TRY(launch_mfma<TOut>(single, &prods[0], 1, groups, st, names[0]));
-            return launch_mfma<TOut>(single, &prods[1], 1, groups, st, names[1]);
-        }
+    // Two products share a launch when the launch-time model below says the pair is faster.  A
+    // workgroup occupies a whole compute unit, so up to 256 tiles run at once (fixed cost ~8.6 us +
+    // 0.5 us per 64 of the reduction length); above that, workgroups take two tiles each (~9.5 us +
+    // 0.76 us per 64) and run in rounds of 256.  Separate launches pay ~2.5 us for the extra launch.
+    // PHANTOM_PAIR=0 / 1 forces the choice (for measurements).
+    bool pair = count == 2;
+    if (pair) {
+        auto tiles_of = [&](const Product &pr) { return ((pr.M + MT - 1) / MT) * ((pr.N + MT - 1) / MT) * groups; };
+        auto launch_us = [](int64_t tiles, int64_t K) {
+            const double steps = (double)((K + KT - 1) / KT);
+            if (tiles <= 256) return 8.6 + 0.5 * steps;
+            return (double)(((tiles + 1) / 2 + 255) / 256) * (9.5 + 0.76 * steps);
+        };
+        const int64_t t0 = tiles_of(prods[0]), t1 = tiles_of(prods[1]);
+        const double together = launch_us(t0 + t1, std::max(prods[0].K, prods[1].K));
+        const double apart = launch_us(t0, prods[0].K) + launch_us(t1, prods[1].K) + 2.5;
+        pair = together < apart;
+        static const char *force = tuning_env("PHANTOM_PAIR");
+        if (force) pair = force[0] == '1';
     }
-    for (int i = 0; i < count; ++i) {
-        const Product &pr = prods[i];
-        ProfScope prof(names[i], pr.M, pr.N, pr.K, groups, st);
-        dim3 grid((unsigned)((pr.N + GT - 1) / GT), (unsigned)((pr.M + GT - 1) / GT), (unsigned)groups);
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, TOut>), grid, dim3(256), 0, st, pr.a, pr.b, pr.o, pr.ep, (int)pr.M,
-                           (int)pr.N, (int)pr.K);
-        PH_TRY(check_launch(names[i]));
-    }
-    return PH_OK;
+    if (pair || count == 1) return launch_mfma<TOut>(plan, prods, count, groups, st, count == 2 ? what : names[0]);
+    GemmPlan single = plan;
+    PH_TRY(launch_mfma<TOut>(single, &prods[0], 1, groups, st, names[0]));
+    return launch_mfma<TOut>(single, &prods[1], 1, groups, st, names[1]);
 }
 
-template <typename TIn, typename TOut>
-ph_status launch_gemm(const GemmPlan &plan, const View &a, const View &b, const View &o, const Epilogue &ep,
-                      int64_t M, int64_t N, int64_t K, int groups, hipStream_t st, const char *what)
+// ---- products of any shape and storage type (gemm_flex.h) ------------------------------------
+FlexAxis flex_axis(const Axis &ax, int64_t length, int V)
 {
-    Product pr{a, b, o, ep, M, N, K};
-    return launch_products<TIn, TOut>(plan, &pr, 1, groups, st, what);
+    auto pad = [V](int64_t x) { return (int)((x + V - 1) / V * V); };
+    FlexAxis f{};
+    f.head = ax.decides ? ax.split : (int)length;
+    f.head_pad = pad(f.head);
+    f.total = f.head_pad;
+    if (ax.decides && length > ax.split) {
+        f.seg = ax.seg; f.seg_pad = pad(ax.seg);
+        f.magic = (uint32_t)((0x100000000ull + (uint32_t)f.seg_pad - 1) / (uint32_t)f.seg_pad);
+        f.total += (int)((length - ax.split) / ax.seg) * f.seg_pad;
+    }
+    return f;
+}
+
+// k, free: the operand's reduction index and free index
+FlexOperand flex_operand_of(const View &v, bool km, const FlexAxis &k, const FlexAxis &free, int V)
+{
+    FlexOperand o{};
+    const Axis &strided = km ? v.c : v.r, &contiguous = km ? v.r : v.c;
+    o.p0 = v.p0; o.p1 = v.p1; o.g0 = v.g0; o.g1 = v.g1;
+    o.ld0 = strided.mult0; o.ld1 = strided.mult1;
+    o.seg_stride = contiguous.seg_stride;
+    o.skip0 = v.skip0; o.skip_g = v.skip_g;
+    // rows times length of the head block and of one segment
+    const FlexAxis &c = km ? free : k, &r = km ? k : free;
+    auto small = [V](int64_t rows, int64_t len) { return rows * len > 0 && rows * len < V; };
+    o.tiny = small(r.head, c.head) || ((c.seg > 0 || r.seg > 0) && small(r.seg > 0 ? r.seg : r.head, c.seg > 0 ? c.seg : c.head));
+    return o;
+}
+
+// Tile of a launch, by how many tiles of 64 x 64 it has.  More than one per compute unit: 64 x 64 with one team of four
+// wavefronts, several workgroups per unit.  Fewer: two teams that share the reduction (a lone workgroup otherwise spends
+// half of a step waiting: 3 layers of 512 trained at batch 1000, 112 -> 92 us).  Very few: 32 x 32 and
+// eight teams of one wavefront (6 layers of 1024 at batch 48, 17 tiles: 80 -> 62 us).
+// fp32 adds its terms in the order of the reduction index (gemm_flex.h) and so has one team, except where eight teams
+// take one group of 16 terms each, the first level of its sums.
+enum FlexTile { FLEX_64, FLEX_64_2, FLEX_32_8 };
+
+template <typename T>
+FlexTile flex_tile_for(const Product *prods, int count, int groups)
+{
+    int64_t tiles = 0, longest = 0;
+    for (int i = 0; i < count; ++i) {
+        tiles += ((prods[i].M + 63) / 64) * ((prods[i].N + 63) / 64) * groups;
+        const int64_t pad = prods[i].km ? 0 : ((prods[i].K - prods[i].a.c.split) / std::max(prods[i].a.c.seg, 1) + 1) * (FlexType<T>::V - 1);
+        longest = std::max(longest, prods[i].K + (prods[i].a.c.decides ? pad : 0));      // (at most; the numbering pads pieces to vectors)
+    }
+    static const char *force = tuning_env("PHANTOM_FLEX_TILE");
+    if (force) return (FlexTile)atoi(force);
+    if (sizeof(T) == 4) return tiles <= 128 && longest <= 8 * 16 ? FLEX_32_8 : FLEX_64;
+    return tiles > 256 ? FLEX_64 : tiles > 24 ? FLEX_64_2 : FLEX_32_8;
+}
+
+template <typename T, int TM, int TN, int TEAMS, bool FORWARD>
+ph_status launch_flex_kernel(const FlexBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
+{
+    auto kern = gemm_flex_kernel<T, TM, TN, TEAMS, FORWARD>;
+    constexpr int LDS = FORWARD ? flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KC, FLEX_KC>()
+                                : flex_max(flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KC, FLEX_KM>(), flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KM, FLEX_KM>());
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
+        configured = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(total_wg), dim3(FlexShape<T, TM, TN, TEAMS>::THREADS), LDS, st, batch);
+    return check_launch(what);
+}
+
+// Up to FLEX_MAX_PRODUCTS independent products in one launch.  forward: all in the forward layout; else any mix of the
+// input-gradient and the weight-gradient (Product::km) layout.  Empty products are left out.  tail: finished by the
+// launch's first workgroup.
+// mse_tiles: receives the number of tiles of the first product (one partial sum of the loss each).
+template <typename T>
+ph_status launch_flex(const Product *prods_in, int count_in, bool forward, int groups, const LossTail &tail, hipStream_t st,
+                      const char *what, int *mse_tiles = nullptr)
+{
+    Product prods[FLEX_MAX_PRODUCTS];
+    int count = 0;
+    for (int i = 0; i < count_in; ++i)
+        if (prods_in[i].M > 0 && prods_in[i].N > 0) prods[count++] = prods_in[i];
+    if (count == 0 || groups <= 0) return PH_OK;
+    const FlexTile tile = flex_tile_for<T>(prods, count, groups);
+    const int t = tile == FLEX_32_8 ? 32 : 64;
+    constexpr int V = FlexType<T>::V;
+    FlexBatch batch{};
+    batch.count = count;
+    batch.tail = tail;
+    int next = 0;
+    for (int i = 0; i < count; ++i) {
+        const Product &pr = prods[i];
+        FlexParams &P = batch.p[i];
+        P.kind = pr.km ? 1 : 0;
+        P.o0 = pr.o.p0; P.o1 = pr.o.p1; P.o_g0 = pr.o.g0; P.o_g1 = pr.o.g1;
+        P.o_ld0 = pr.o.r.mult0; P.o_ld1 = pr.o.r.mult1; P.o_seg_stride = pr.o.c.seg_stride;
+        P.ep = pr.ep; P.sgd = pr.sgd; P.rowsum = pr.rowsum;
+        P.k = flex_axis(pr.km ? Axis{} : pr.a.c, pr.K, V);
+        P.n = flex_axis(pr.o.c, pr.N, V);
+        P.M = (int)pr.M;
+        FlexAxis rows{};
+        rows.head = P.M;
+        P.a = flex_operand_of(pr.a, pr.km, P.k, rows, V);
+        P.b = flex_operand_of(pr.b, !forward, P.k, P.n, V);
+        P.tiles_m = (int)((pr.M + t - 1) / t);
+        P.tiles_n = (P.n.total + t - 1) / t;
+        P.total_wg = P.tiles_m * P.tiles_n * groups;
+        if (i == 0 && mse_tiles) *mse_tiles = P.total_wg;
+        batch.first_wg[i] = next;
+        next += (P.total_wg + 7) & ~7;
+    }
+    auto dim = [&](int i, int64_t Product::*d) { return i < count ? prods[i].*d : (int64_t)0; };
+    ProfScope prof(what, prods[0].M, prods[0].N, prods[0].K, groups, st, dim(1, &Product::M), dim(1, &Product::N), dim(1, &Product::K),
+                   dim(2, &Product::M), dim(2, &Product::N), dim(2, &Product::K), dim(3, &Product::M), dim(3, &Product::N), dim(3, &Product::K));
+    const unsigned total = (unsigned)next;
+    if (forward) {
+        if (tile == FLEX_64) return launch_flex_kernel<T, 64, 64, 1, true>(batch, total, st, what);
+        if constexpr (sizeof(T) == 2)
+            if (tile == FLEX_64_2) return launch_flex_kernel<T, 64, 64, 2, true>(batch, total, st, what);
+        return launch_flex_kernel<T, 32, 32, 8, true>(batch, total, st, what);
+    }
+    if (tile == FLEX_64) return launch_flex_kernel<T, 64, 64, 1, false>(batch, total, st, what);
+    if constexpr (sizeof(T) == 2)
+        if (tile == FLEX_64_2) return launch_flex_kernel<T, 64, 64, 2, false>(batch, total, st, what);
+    return launch_flex_kernel<T, 32, 32, 8, false>(batch, total, st, what);
 }
 
 Epilogue epi_store()
@@ -778,18 +866,22 @@ bool thin_launch_before_update(const Geo &g)
     return g.all && g.dtype == PH_BF16 && g.q > 0 && g.k <= THIN_MAX_N && g.si % 16 == 0 && g.vec > 0;
 }
 
-template <typename T>
-ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
+// The products of a layer's forward pass (Eq. (ylq)).
+struct FwdProducts {
+    Product update, compress;
+};
+
+FwdProducts make_fwd_products(const Geo &g, const FwdArgs &f)
 {
     const int64_t B = g.B, si = g.si, so = g.so, k = g.k, q = g.q;
-    const GemmPlan plan{LD_KC, LD_KC, g.vec, false};
+    FwdProducts pr{};
     // compression g = C y: [B, si] x [k, si]^T -> [B, k]
-    Product compress{view_plain(f.X, si, B * si), view_plain(f.Cw, si, k * si), view_plain(f.g_own, k, B * k), epi_store(),
-                     q > 0 ? B : 0, k, si};
+    pr.compress = Product{view_plain(f.X, si, B * si), view_plain(f.Cw, si, k * si), view_plain(f.g_own, k, B * k), epi_store(),
+                          q > 0 ? B : 0, k, si};
     // local update + decompression + remote update + bias + activation: one product over the
     // concatenated reduction index [y | g_1 .. g_{p-1}] . [L | D_1 .. D_{p-1}]^T
     const void *gathered = g.all ? f.g_own : f.G;
-    Product update{};
+    Product &update = pr.update;
     update.a = q > 0 ? view_rowseg(f.X, si, (int)si, B * si, gathered, (int)k, B * k, 0, g.all ? 0 : NO_SKIP, g.all ? 1 : 0)
                      : view_plain(f.X, si, B * si);
     update.b = q > 0 ? view_rowseg(f.Lw, si, (int)si, so * si, f.Dw, (int)k, so * k, q * so * k) : view_plain(f.Lw, si, so * si);
@@ -797,30 +889,49 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
     update.ep.mode = EPI_BIAS_ACT; update.ep.act = g.act; update.ep.bias = f.bias; update.ep.bias_g = so;
     update.ep.aux = f.A_save; update.ep.aux_ld = so; update.ep.aux_g = B * so; update.ep.aux_f32 = f.a_f32; update.ep.aux_deriv = f.a_deriv; update.ep.aux_bits = f.a_bits;
     update.M = B; update.N = so; update.K = g.Kc;
-    float *clear_at = nullptr;
-    int64_t clear_count = 0;
     if (f.mse) {
         update.ep.mse_target = f.mse->target; update.ep.mse_delta = f.mse->delta; update.ep.mse_partial = f.mse->partial;
         update.ep.mse_inv_b = f.mse->inv_b;
         update.ep.colsum = f.mse->dbias; update.ep.colsum_g = so;
-        clear_at = f.mse->clear_at; clear_count = f.mse->clear_count;
     }
+    return pr;
+}
+
+// Forward through gemm_flex.h.  mse_tiles: with f.mse, the number of partial sums of the loss it leaves.
+template <typename T>
+ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tiles = nullptr)
+{
+    const FwdProducts pr = make_fwd_products(g, f);
+    if (g.all) {
+        // every rank reads the other ranks' g: the compression of all ranks has to finish first
+        PH_TRY((launch_flex<T>(&pr.compress, 1, true, g.groups, LossTail{}, st, "compression")));
+        return launch_flex<T>(&pr.update, 1, true, g.groups, LossTail{}, st, "layer update", mse_tiles);
+    }
+    const Product both[2] = {pr.update, pr.compress};
+    return launch_flex<T>(both, 2, true, g.groups, LossTail{}, st, g.q > 0 ? "layer update + compression" : "layer update", mse_tiles);
+}
+
+ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
+{
+    typedef bf16_t T;
+    const int64_t B = g.B, si = g.si, so = g.so, k = g.k, q = g.q;
+    const GemmPlan plan{LD_KC, LD_KC, g.vec};
+    FwdProducts prods = make_fwd_products(g, f);
+    const Product &update = prods.update, &compress = prods.compress;
+    float *clear_at = f.mse ? f.mse->clear_at : nullptr;
+    const int64_t clear_count = f.mse ? f.mse->clear_count : 0;
     // A compression with few phantom neurons has a kernel of its own (32 rows per workgroup instead of 128)
-    bool thin = false;
-    if constexpr (std::is_same<T, bf16_t>::value) thin = q > 0 && k <= THIN_MAX_N && si % 16 == 0 && g.vec > 0;
+    const bool thin = q > 0 && k <= THIN_MAX_N && si % 16 == 0 && g.vec > 0;
     auto launch_thin = [&]() -> ph_status {
-        if constexpr (std::is_same<T, bf16_t>::value) {
-            ProfScope prof("compression", B, k, si, g.groups, st);
-            dim3 grid((unsigned)((B + THIN_ROWS - 1) / THIN_ROWS), (unsigned)g.groups);
-            if (k <= 32)
-                hipLaunchKernelGGL((thin_product_kernel<1>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
-                                   (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, clear_at, clear_count);
-            else
-                hipLaunchKernelGGL((thin_product_kernel<2>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
-                                   (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, clear_at, clear_count);
-            return check_launch("compression");
-        }
-        return PH_OK;
+        ProfScope prof("compression", B, k, si, g.groups, st);
+        dim3 grid((unsigned)((B + THIN_ROWS - 1) / THIN_ROWS), (unsigned)g.groups);
+        if (k <= 32)
+            hipLaunchKernelGGL((thin_product_kernel<1>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
+                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, clear_at, clear_count);
+        else
+            hipLaunchKernelGGL((thin_product_kernel<2>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
+                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, clear_at, clear_count);
+        return check_launch("compression");
     };
     if (g.all) {
         // every rank reads the other ranks' g: the compression of all ranks has to finish first
@@ -832,11 +943,9 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
     // fit the device together
     const int64_t tiles_both = (tiles_of(B, so) + tiles_of(B, k)) * g.groups;
     if (thin && tiles_both > 256) {
-        if constexpr (std::is_same<T, bf16_t>::value) {
-            static const char *force = tuning_env("PHANTOM_FWD_PAIR");     // =0: two launches (for measurements)
-            if (!(force && force[0] == '0'))
-                return launch_fwd_pair(update, compress, g.groups, g.vec, st, "layer update + thin compression");
-        }
+        static const char *force = tuning_env("PHANTOM_FWD_PAIR");         // =0: two launches (for measurements)
+        if (!(force && force[0] == '0'))
+            return launch_fwd_pair(update, compress, g.groups, g.vec, st, "layer update + thin compression");
         PH_TRY(launch_thin());
         return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update");
     }
@@ -865,9 +974,7 @@ struct BwdArgs {
     const void *below_Dw;      // step only, all ranks: D of the layer below; its error compression (dX -> dG_send)
     const Geo *below_g;        //   (that layer's shapes)
     bool *below_done;          //   may then ride with this layer's weight gradients; *below_done says whether it did
-    const SgdBatch *ride_sgd;  // step only: the update of the layer above, not launched yet; it may ride with this
-    float ride_lr;             //   layer's weight gradients on compute units they leave idle; *ride_sgd_done says
-    bool *ride_sgd_done;       //   whether it did
+    SgdInPlace sgd_w, sgd_c;   // step only: the update of L, D, the bias / of C in the epilogues that finish their gradients
     LossTail *loss_tail;       // step only, last layer: the first memory-bound kernel of this backward finishes
                                //   the loss as a rider and clears loss_tail->partial; left alone if there is none
     void *tap_dG_send;         // step only, optional: copies of this layer's dG_send / (all ranks) dg_own, taken right
@@ -941,24 +1048,69 @@ BwdProducts make_bwd_products(const Geo &g, const BwdArgs &b, const void *delta)
     dw.M = so; dw.N = g.Kc; dw.K = B;
     pr.dc = Product{view_plain_t(b.dg_own, k, B * k), view_plain_t(b.X, si, B * si), view_plain(b.dCw, si, k * si), epi_store(),
                     q > 0 ? k : 0, si, B};
+    dw.sgd = b.sgd_w;
+    pr.dc.sgd = b.sgd_c;
     return pr;
 }
 
+// In-memory reduce-scatter: dg_own of every rank from what all ranks sent; tail: finished by its first workgroup.
 template <typename T>
+ph_status launch_reduce_scatter(const Geo &g, const void *dG_send, void *dg_own, const LossTail &tail, hipStream_t st)
+{
+    const int64_t per_slot = g.B * g.k;
+    constexpr int RS_VEC = 16 / (int)sizeof(T);
+    const bool wide = per_slot % RS_VEC == 0 && (((uintptr_t)dG_send | (uintptr_t)dg_own) & 15) == 0;
+    const int64_t per_wg = 32 * (wide ? RS_VEC : 1);
+    dim3 grid((unsigned)((per_slot + per_wg - 1) / per_wg), (unsigned)g.p);
+    ProfScope prof("reduce-scatter", 0, per_slot * g.p * (g.p - 1), 0, 1, st);
+    if (wide)
+        hipLaunchKernelGGL((reduce_scatter_kernel<T, RS_VEC>), grid, dim3(256), 0, st, (const T *)dG_send, (T *)dg_own, (int)g.p, per_slot, tail);
+    else
+        hipLaunchKernelGGL((reduce_scatter_kernel<T, 1>), grid, dim3(256), 0, st, (const T *)dG_send, (T *)dg_own, (int)g.p, per_slot, tail);
+    return check_launch("reduce-scatter");
+}
+
+// delta = dY * sigma'(S); with the identity, dY itself and no launch
+template <typename T>
+ph_status local_error(const Geo &g, const BwdArgs &b, void *buffer, const void **delta, hipStream_t st)
+{
+    if (g.act == PH_ACT_IDENTITY) { *delta = b.dY; return PH_OK; }
+    const int64_t count = (int64_t)g.groups * g.B * g.so;
+    ProfScope prof("local error", 0, count, 0, 1, st);
+    hipLaunchKernelGGL((delta_kernel<T>), dim3(blocks_for(count, 256 * 16 / (int)sizeof(T))), dim3(256), 0, st,
+                       (const T *)b.dY, (const T *)b.S, (T *)buffer, count, g.act);
+    *delta = buffer;
+    return check_launch("local error");
+}
+
+// A layer's backward call through gemm_flex.h: everything that needs the local error alone goes out together.
+template <typename T>
+ph_status flex_layer_bwd(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t st)
+{
+    const void *delta = nullptr;
+    PH_TRY(local_error<T>(g, b, w.delta, &delta, st));
+    BwdProducts pr = make_bwd_products(g, b, delta);
+    pr.dw.km = pr.dc.km = true;
+    pr.dw.rowsum = b.dbias;
+    if (g.all && g.q > 0) {
+        PH_TRY((launch_flex<T>(&pr.send, 1, false, g.groups, LossTail{}, st, "error compression")));
+        PH_TRY(launch_reduce_scatter<T>(g, b.dG_send, b.dg_own, LossTail{}, st));
+        const Product rest[3] = {pr.dw, pr.dc, pr.dx};
+        return launch_flex<T>(rest, 3, false, g.groups, LossTail{}, st, "weight + compressor + input gradients");
+    }
+    const Product every[4] = {pr.dw, pr.dc, pr.dx, pr.send};
+    return launch_flex<T>(every, 4, false, g.groups, LossTail{}, st, "gradients | error compression");
+}
+
 ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t st)
 {
+    typedef bf16_t T;
     const int64_t B = g.B, so = g.so, k = g.k, q = g.q;
     const int64_t act_count = (int64_t)g.groups * B * so;
 
     // local error delta = dY * sigma'
     const void *delta = b.delta_ready;
-    if (!delta) {
-        ProfScope prof("local error", 0, act_count, 0, 1, st);
-        hipLaunchKernelGGL((delta_kernel<T>), dim3(blocks_for(act_count)), dim3(256), 0, st,
-                           (const T *)b.dY, (const T *)b.S, (T *)w.delta, act_count, g.act);
-        PH_TRY(check_launch("local error"));
-        delta = w.delta;
-    }
+    if (!delta) PH_TRY(local_error<T>(g, b, w.delta, &delta, st));
 
     // the loss rider goes to the first launch that can carry it
     auto take_tail = [&]() {
@@ -972,7 +1124,6 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
         const int strips = (int)((so + CSUM_COLS - 1) / CSUM_COLS);
         // enough workgroups to pull the whole tensor at memory speed: split the rows when the strips are few
         int chunks = (int)std::max<int64_t>(1, std::min<int64_t>(256 / ((int64_t)strips * g.groups), B / 128));
-        if (g.dtype == PH_F32) chunks = 1;      // the fp32 path keeps a fixed summation order
         const int rows_per_chunk = (int)((B + chunks - 1) / chunks);
         chunks = (int)((B + rows_per_chunk - 1) / rows_per_chunk);
         if (chunks > 1 && !b.dbias_zeroed && !b.dbias_ready) {
@@ -1000,12 +1151,13 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
     // tile per compute unit.  PHANTOM_TAIL=0 switches them off (for measurements).
     const int64_t tail_tiles = (tiles_of(dw.M, dw.N) + tiles_of(dc.M, dc.N)) * g.groups;
     static const char *tail_force = tuning_env("PHANTOM_TAIL");
-    const bool riders = std::is_same<T, bf16_t>::value && g.vec > 0 && tail_tiles <= 256 && !(tail_force && tail_force[0] == '0');
+    const bool riders = tail_tiles <= 256 && !(tail_force && tail_force[0] == '0');
     // One rank, no input gradient wanted (the first layer): this layer's error compression has no launch to share
     // with the input gradient and nothing waits for it, so it rides with the weight gradients.
-    const bool send_rides = riders && !g.all && !b.dX && q > 0 && !b.defer;
+    // (not with an update in the epilogues: it would write the D that the error compression reads)
+    const bool send_rides = riders && !g.all && !b.dX && q > 0 && !b.defer && !b.sgd_w.w0;
 
-    const GemmPlan plan_x{LD_KC, LD_KM, g.vec, false};
+    const GemmPlan plan_x{LD_KC, LD_KM, g.vec};
     const int64_t send_count = (int64_t)g.groups * q * B * k;
     if (g.all) {
         // the input gradient needs dg_own, which is the sum of what all ranks send: three launches
@@ -1017,25 +1169,13 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
         // k a divisor of 64), 16-byte vectors, and at most 8 ranks: a thread has the loads of seven senders
         // in flight at a time, and with 16 ranks the step got 0.4 % slower instead of 1.8 % faster.  PHANTOM_RS_ON_READ=0 keeps the kernel of its own (for measurements).
         static const char *rs_force = tuning_env("PHANTOM_RS_ON_READ");
-        const bool sum_on_read = std::is_same<T, bf16_t>::value && g.vec == 8 && q > 0 && b.dX && g.p <= 8 && k <= KT &&
+        const bool sum_on_read = g.vec == 8 && q > 0 && b.dX && g.p <= 8 && k <= KT &&
                                  KT % k == 0 && so % KT == 0 && !(rs_force && rs_force[0] == '0');
         if (sum_on_read) {
             dx.rs.src = (const __bf16 *)b.dG_send; dx.rs.out = (__bf16 *)b.dg_own;
             dx.rs.per_slot = B * k; dx.rs.p = (int)g.p; dx.rs.k = (int)k;
         } else if (q > 0) {
-            const int64_t per_slot = B * k;
-            constexpr int RS_VEC = 16 / (int)sizeof(T);
-            const bool wide = per_slot % RS_VEC == 0 && (((uintptr_t)b.dG_send | (uintptr_t)b.dg_own) & 15) == 0;
-            const int64_t per_wg = 32 * (wide ? RS_VEC : 1);
-            dim3 grid((unsigned)((per_slot + per_wg - 1) / per_wg), (unsigned)g.p);
-            ProfScope prof("reduce-scatter", 0, per_slot * g.p * (g.p - 1), 0, 1, st);
-            if (wide)
-                hipLaunchKernelGGL((reduce_scatter_kernel<T, RS_VEC>), grid, dim3(256), 0, st, (const T *)b.dG_send,
-                                   (T *)b.dg_own, (int)g.p, per_slot, take_tail());
-            else
-                hipLaunchKernelGGL((reduce_scatter_kernel<T, 1>), grid, dim3(256), 0, st, (const T *)b.dG_send,
-                                   (T *)b.dg_own, (int)g.p, per_slot, take_tail());
-            PH_TRY(check_launch("reduce-scatter"));
+            PH_TRY(launch_reduce_scatter<T>(g, b.dG_send, b.dg_own, take_tail(), st));
         }
         PH_TRY((launch_products<T, T>(plan_x, &dx, 1, g.groups, st, "input gradient")));
         PH_TRY(tap_copy<T>(b.tap_dg_own, b.dg_own, (int64_t)g.groups * B * k, st));
@@ -1046,60 +1186,42 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
         PH_TRY(tap_copy<T>(b.tap_dG_send, b.dG_send, send_count, st));
     }
 
-    Product grads[2] = {dw, dc};
     if (b.below_done) *b.below_done = false;
-    if (b.ride_sgd_done) *b.ride_sgd_done = false;
     if (b.defer) return PH_OK;
-    if constexpr (std::is_same<T, bf16_t>::value) {
-        if (riders) {
-            // The layer below starts its backward with an error compression that fills half of the device or less
-            // for a short while: it comes along when it leaves at least half of the compute units to the weight
-            // gradients from the start (they take over the rest as it finishes).  The update of the layer above
-            // comes along when at least a quarter of the compute units would otherwise be idle.
-            Product below{};
-            bool with_head = false;
-            int64_t used = tail_tiles;
-            int vec = g.vec;
-            if (send_rides) {
-                below = send;
-                with_head = true;
-                used += (tiles_of(below.M, below.N) * g.groups + 7) & ~(int64_t)7;
-            } else if (b.below_Dw && b.below_g && b.below_g->vec > 0 && b.dX && g.all && q > 0) {
-                below = error_compression(b.dX, b.below_Dw, b.below_g->so, b.below_g->k);
-                vec = std::min(vec, b.below_g->vec);
-                const int64_t head_tiles = tiles_of(below.M, below.N) * g.groups;
-                with_head = head_tiles <= 128;
-                if (with_head) used += (head_tiles + 7) & ~(int64_t)7;
-            }
-            const int64_t idle = 256 - ((used + 7) & ~(int64_t)7);      // negative: the launch runs in rounds
-            // (a launch that runs in rounds anyway takes the update along on a quarter of the compute units: its
-            // workgroups go out before the error compression, which fills in as compute units come free)
-            const bool rounds = send_rides && used > 256;
-            const bool with_sgd = b.ride_sgd && (idle >= 64 || rounds);
-            // a loss that no kernel has finished yet (and no update to carry it): one more workgroup does it
-            const bool with_loss = !with_sgd && !b.ride_sgd && b.loss_tail && b.loss_tail->partial;
-            if (with_head || with_sgd || with_loss) {
-                SgdBatch loss_only{};
-                if (with_loss) loss_only.tail = take_tail();
-                PH_TRY(launch_tail(with_head ? &below : nullptr, dw, dc, with_sgd ? b.ride_sgd : with_loss ? &loss_only : nullptr,
-                                   b.ride_lr, with_sgd ? (int)std::max<int64_t>(idle, 64) : 1, g.groups, vec, st,
-                                   send_rides ? (with_sgd ? "weight + compressor gradients | error compression | SGD above"
-                                                          : "weight + compressor gradients | error compression")
-                                   : with_head ? (with_sgd ? "weight + compressor gradients | error compr. below | SGD above"
-                                                           : "weight + compressor gradients | error compression below")
-                                               : with_sgd ? "weight + compressor gradients | SGD above"
-                                                          : "weight + compressor gradients | loss",
-                                   rounds));
-                if (b.below_done) *b.below_done = with_head && !send_rides;
-                if (b.ride_sgd_done) *b.ride_sgd_done = with_sgd;
-                if (send_rides) PH_TRY(tap_copy<T>(b.tap_dG_send, b.dG_send, send_count, st));
-                return PH_OK;
-            }
+    if (riders) {
+        // The layer below starts its backward with an error compression that fills half of the device or less
+        // for a short while: it comes along when it leaves at least half of the compute units to the weight
+        // gradients from the start (they take over the rest as it finishes).
+        Product below{};
+        bool with_head = false;
+        int64_t used = tail_tiles;
+        int vec = g.vec;
+        if (send_rides) {
+            below = send;
+            with_head = true;
+            used += (tiles_of(below.M, below.N) * g.groups + 7) & ~(int64_t)7;
+        } else if (b.below_Dw && b.below_g && b.below_g->vec > 0 && b.dX && g.all && q > 0) {
+            below = error_compression(b.dX, b.below_Dw, b.below_g->so, b.below_g->k);
+            vec = std::min(vec, b.below_g->vec);
+            with_head = tiles_of(below.M, below.N) * g.groups <= 128;
+        }
+        // a loss that no kernel has finished yet: one more workgroup does it
+        const bool with_loss = b.loss_tail && b.loss_tail->partial;
+        if (with_head || with_loss) {
+            const LossTail tail = with_loss ? take_tail() : LossTail{};
+            PH_TRY(launch_tail(with_head ? &below : nullptr, dw, dc, tail, g.groups, vec, st,
+                               send_rides  ? "weight + compressor gradients | error compression"
+                               : with_head ? "weight + compressor gradients | error compression below"
+                                           : "weight + compressor gradients | loss",
+                               send_rides && used > 256));
+            if (b.below_done) *b.below_done = with_head && !send_rides;
+            if (send_rides) PH_TRY(tap_copy<T>(b.tap_dG_send, b.dG_send, send_count, st));
+            return PH_OK;
         }
     }
-    // a lone weight-gradient product with few tiles may split its reduction; a pair never does
+    Product grads[2] = {dw, dc};
     // (send_rides never gets here: its launch above carries the error compression)
-    return launch_products<T, float>(GemmPlan{LD_KM, LD_KM, g.vec, true}, grads, q > 0 ? 2 : 1, g.groups, st,
+    return launch_products<T, float>(GemmPlan{LD_KM, LD_KM, g.vec}, grads, q > 0 ? 2 : 1, g.groups, st,
                                      "weight + compressor gradients", "weight gradients", "compressor gradient");
 }
 
@@ -1136,29 +1258,143 @@ ph_status check_ws(void *ws, size_t have, size_t want)
     return PH_OK;
 }
 
+// The update of layer l in the epilogues that finish its gradients (Section VI: plain SGD), `weights` (L, D and the bias) or
+// C; keep: the gradients are stored too.
+SgdInPlace sgd_of(const ph_step_args &a, int l, int64_t q, bool weights, const float *bias_grad)
+{
+    auto at = [l](auto *const *arr) { return arr ? arr[l] : nullptr; };
+    SgdInPlace s{};
+    s.lr = a.lr;
+    if (weights) {
+        s.master0 = at(a.Lw_master); s.w0 = a.Lw[l];
+        s.master1 = q ? at(a.Dw_master) : nullptr; s.w1 = q ? a.Dw[l] : nullptr;
+        s.keep_grad = a.dLw || a.dDw;
+        s.bias_master = at(a.bias_master); s.bias_w = a.bias[l]; s.bias_grad = bias_grad;
+    } else if (q) {
+        s.master0 = at(a.Cw_master); s.w0 = a.Cw[l];
+        s.keep_grad = a.dCw != nullptr;
+    }
+    return s;
+}
+
+// Copies of a layer's forward results for the taps of the step.
 template <typename T>
+ph_status forward_taps(const Geo &g, const ph_step_args &a, const StepWs &w, int l, hipStream_t st)
+{
+    if (!a.taps) return PH_OK;
+    if (a.taps->Y) PH_TRY(tap_copy<T>(a.taps->Y[l], w.Y[(size_t)l], (int64_t)g.groups * g.B * g.so, st));
+    if (a.taps->g_own && g.q) PH_TRY(tap_copy<T>(a.taps->g_own[l], w.G[(size_t)l], (int64_t)g.groups * g.B * g.k, st));
+    return PH_OK;
+}
+
+// One step through gemm_flex.h.  The weight + compressor gradients of a layer (with the update in their epilogues: by then
+// nothing reads that layer's weights any more) go out with the first launch of the layer below, so that a layer's
+// backward pass is one launch with one rank and three with all ranks on the device.
+template <typename T>
+ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const StepWs &w, hipStream_t st)
+{
+    const Geo &g = geos.back();       // what does not depend on the layer is read from the last one
+    const int L = g.layers;
+    const int64_t B = g.B, q = g.q;
+    const bool train = a.mode != PH_STEP_FORWARD, update = a.mode == PH_STEP_TRAIN;
+    const bool gelu = g.act == PH_ACT_GELU, save_deriv = gelu && std::is_same<T, bf16_t>::value;
+    // delta_l is read until the launch after the next one is out: three buffers in turn
+    void *const deltas[3] = {w.dYa, w.dYb, w.bwd.delta};
+    auto delta_of = [&](int l) { return deltas[l % 3]; };
+    auto dbias_of = [&](int l) { return a.dbias ? a.dbias[l] : w.dbias + w.dbias_at[(size_t)l]; };
+
+    OutputError oe{a.T, delta_of(L - 1), w.mse_partial, 1.0f / (float)B, nullptr, nullptr, 0};
+    int mse_tiles = 0;
+    for (int l = 0; l < L; ++l) {
+        FwdArgs f{};
+        f.X = l > 0 ? w.Y[(size_t)l - 1] : a.X0;
+        f.Lw = a.Lw[l]; f.Cw = q ? a.Cw[l] : nullptr; f.Dw = q ? a.Dw[l] : nullptr; f.bias = a.bias[l];
+        f.G = (q && !g.all) ? a.G[l] : nullptr;
+        f.Y = w.Y[(size_t)l]; f.g_own = w.G[(size_t)l]; f.A_save = train ? w.A[(size_t)l] : nullptr;
+        f.a_f32 = !save_deriv; f.a_deriv = save_deriv;
+        f.mse = train && l == L - 1 ? &oe : nullptr;
+        PH_TRY(flex_fwd<T>(geos[(size_t)l], f, st, f.mse ? &mse_tiles : nullptr));
+        PH_TRY(forward_taps<T>(geos[(size_t)l], a, w, l, st));
+    }
+    if (!train) return PH_OK;
+    if (a.taps && a.taps->delta) PH_TRY(tap_copy<T>(a.taps->delta[L - 1], delta_of(L - 1), (int64_t)g.groups * B * g.so, st));
+
+    LossTail tail{w.mse_partial, mse_tiles, 0.5f / (float)B, a.loss};
+    std::vector<Product> next;        // the next launch's products
+    auto go = [&](const char *what) -> ph_status {
+        bool any = false;
+        for (const Product &pr : next) any = any || (pr.M > 0 && pr.N > 0);
+        if (!any) { next.clear(); return PH_OK; }
+        PH_TRY((launch_flex<T>(next.data(), (int)next.size(), false, g.groups, tail, st, what)));
+        tail.partial = nullptr;
+        next.clear();
+        return PH_OK;
+    };
+    for (int l = L - 1; l >= 0; --l) {
+        const Geo &gl = geos[(size_t)l];
+        BwdArgs b{};
+        b.X = l > 0 ? w.Y[(size_t)l - 1] : a.X0;
+        b.Lw = a.Lw[l]; b.Cw = q ? a.Cw[l] : nullptr; b.Dw = q ? a.Dw[l] : nullptr;
+        b.G = q ? (g.all ? w.G[(size_t)l] : a.G[l]) : nullptr;
+        b.dg_own = q ? (g.all ? w.dg_own : const_cast<void *>(a.dg_own[l])) : nullptr;
+        b.dX = l > 0 ? delta_of(l - 1) : nullptr;
+        b.dx_S = l > 0 ? (gelu ? w.A[(size_t)l - 1] : w.Y[(size_t)l - 1]) : nullptr;
+        b.dx_S_f32 = gelu && !save_deriv; b.dx_S_deriv = save_deriv;
+        b.dLw = a.dLw ? a.dLw[l] : w.dLw[l & 1];
+        b.dCw = q ? (a.dCw ? a.dCw[l] : w.dCw[l & 1]) : nullptr;
+        b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[l & 1]) : nullptr;
+        b.dbias = dbias_of(l);
+        b.dG_send = w.dG_send;
+        if (update) {
+            b.sgd_w = sgd_of(a, l, q, true, b.dbias);
+            b.sgd_c = sgd_of(a, l, q, false, nullptr);
+        }
+        BwdProducts pr = make_bwd_products(gl, b, delta_of(l));
+        pr.dw.km = pr.dc.km = true;
+        pr.dw.rowsum = b.dbias;
+        const int64_t send_count = (int64_t)g.groups * q * B * gl.k;
+        void *tap_send = (a.taps && a.taps->dG_send && q) ? a.taps->dG_send[l] : nullptr;
+        if (g.all && q > 0) {
+            next.push_back(pr.send);
+            PH_TRY(go("error compression | gradients above"));
+            PH_TRY(tap_copy<T>(tap_send, b.dG_send, send_count, st));
+            PH_TRY(launch_reduce_scatter<T>(gl, b.dG_send, b.dg_own, LossTail{}, st));
+            PH_TRY(tap_copy<T>(a.taps && a.taps->dg_own ? a.taps->dg_own[l] : nullptr, b.dg_own, (int64_t)g.groups * B * gl.k, st));
+            next.push_back(pr.dx);
+            PH_TRY(go("input gradient"));
+        } else {
+            next.push_back(pr.dx);
+            next.push_back(pr.send);
+            PH_TRY(go("input gradient + error compression | gradients above"));
+            PH_TRY(tap_copy<T>(tap_send, b.dG_send, send_count, st));
+        }
+        if (a.taps && a.taps->delta && l > 0) PH_TRY(tap_copy<T>(a.taps->delta[l - 1], b.dX, (int64_t)g.groups * B * gl.si, st));
+        next.push_back(pr.dw);
+        next.push_back(pr.dc);
+    }
+    return go("weight + compressor gradients");
+}
+
+// One bf16 step on the 128 x 128 kernels of gemm_mfma.h.
 ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const StepWs &w, hipStream_t st)
 {
+    typedef bf16_t T;
     const Geo &g = geos.back();       // the last layer; what does not depend on the layer is read from it
     const int L = g.layers;
     const int64_t B = g.B, q = g.q;
     const int64_t act_count = (int64_t)g.groups * B * g.so;      // elements of the network output
 
     // What the backward pass needs of a layer's pre-activation A is sigma'(A) alone.  ReLU reads it off the
-    // layer's output.  GELU in bf16 storage has the forward epilogue, which evaluates erf and exp for
+    // layer's output.  GELU has the forward epilogue, which evaluates erf and exp for
     // sigma(A) anyway, store sigma'(A) in float: the bytes of an fp32 A and no second evaluation in the
     // input-gradient epilogue.  (Any coarser grid for that factor moves delta across bf16 rounding
-    // boundaries often enough to show after a few layers.)  fp32 storage keeps A itself.
-    const bool gelu = g.act == PH_ACT_GELU;
-    const bool save_deriv = gelu && std::is_same<T, bf16_t>::value;
+    // boundaries often enough to show after a few layers.)
+    const bool save_deriv = g.act == PH_ACT_GELU;
 
-    // Bias gradients (Eq. (bpb)) are column sums of delta.  On the MFMA path the product that writes a
-    // layer's delta (the input gradient of the layer above; for the last layer its own update, see below)
-    // adds them up on its way out, so every layer's bias gradient has a buffer of its own that is zeroed once
-    // for the whole step: the caller's buffers by launches of their own, the workspace's (one block) by a
-    // kernel that runs anyway.
-    const bool train = a.mode != PH_STEP_FORWARD;
-    auto on_mfma = [&](int l) { return std::is_same<T, bf16_t>::value && geos[(size_t)l].vec > 0; };
+    // Bias gradients (Eq. (bpb)) are column sums of delta: the product that writes a layer's delta (the input gradient
+    // of the layer above; for the last layer its own update, see below) adds them up on its way out, so every
+    // layer's bias gradient has a buffer of its own that is zeroed once for the whole step.
+    const bool train = a.mode != PH_STEP_FORWARD, update = a.mode == PH_STEP_TRAIN;
     auto dbias_of = [&](int l) { return a.dbias ? a.dbias[l] : w.dbias + w.dbias_at[(size_t)l]; };
     if (train && a.dbias) {
         for (int l = 0; l < L; ++l) {
@@ -1171,18 +1407,16 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     float *clear_at = a.dbias ? (float *)w.arrived : w.dbias;
     const int64_t clear_count = a.dbias ? PIECE_WORDS : w.dbias_at[(size_t)L] + PIECE_WORDS;
 
-    // The output error of the MSE loss (Eq. (deltaL)) is elementwise in the last layer's output, so on the MFMA
-    // path that layer's update forms it in its epilogue, together with the last bias gradient and one partial
+    // The output error of the MSE loss (Eq. (deltaL)) is elementwise in the last layer's output, so
+    // that layer's update forms it in its epilogue, together with the last bias gradient and one partial
     // sum of the loss per tile: two launches less than a kernel for the error and one for the column sums.
     // The buffers it adds into have to be clear by then: the thin compression launch right before it does that
     // on its way where there is one, else a launch of its own at the start of the step.
     const int64_t out_tiles = tiles_of(B, g.so) * g.groups;
-    const bool mse_in_update = train && on_mfma(L - 1) && out_tiles <= MSE_BLOCKS;
-    const bool clear_in_compression = mse_in_update && thin_launch_before_update(g);
+    const bool clear_in_compression = train && thin_launch_before_update(g);
     // (one rank with deferred weight gradients keeps every layer's delta: the last layer's goes to its own buffer)
-    bool deferred = false;
-    if constexpr (std::is_same<T, bf16_t>::value) deferred = mse_in_update && w.table && deferred_weight_gradients(geos);
-    if (mse_in_update && !clear_in_compression && !deferred && clear_count > 0) {
+    const bool deferred = train && w.table && deferred_weight_gradients(geos);
+    if (train && !clear_in_compression && !deferred && clear_count > 0) {
         ProfScope prof("clear bias gradients", 0, clear_count, 0, 1, st);
         hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks_for(clear_count)), dim3(256), 0, st, clear_at, clear_count);
         PH_TRY(check_launch("clear bias gradients"));
@@ -1199,10 +1433,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     int table_grid = 0;
     Product table_dw{}, table_dc{};
     if (deferred) {
-        const bool update = a.mode != PH_STEP_NO_UPDATE;
         std::vector<Product> later;
         std::vector<int> splits;
-        std::vector<SgdInPlace> inside;
         for (int pass = 0; pass < 2; ++pass)
             for (int l = L - 1; l >= 0; --l) {
                 const Geo &gl = geos[(size_t)l];
@@ -1215,98 +1447,52 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
                 b.dLw = a.dLw ? a.dLw[l] : w.dLw[0];
                 b.dCw = q ? (a.dCw ? a.dCw[l] : w.dCw[0]) : nullptr;
                 b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[0]) : nullptr;
+                if (update) {
+                    b.sgd_w = sgd_of(a, l, q, true, dbias_of(l));
+                    b.sgd_c = sgd_of(a, l, q, false, nullptr);
+                }
                 const BwdProducts all = make_bwd_products(gl, b, w.delta_of[(size_t)l]);
                 const Product &pr = pass ? all.dw : all.dc;
                 if (l == L - 1) (pass ? table_dw : table_dc) = pr;
                 if (pr.M <= 0 || pr.N <= 0) continue;
-                SgdInPlace in{};
-                if (update && pass)
-                    in = SgdInPlace{a.Lw_master[l], q ? a.Dw_master[l] : nullptr, (__bf16 *)a.Lw[l], q ? (__bf16 *)a.Dw[l] : nullptr, a.lr,
-                                    (a.dLw || a.dDw) ? 1 : 0, a.bias_master[l], (__bf16 *)a.bias[l], dbias_of(l)};
-                if (update && !pass)
-                    in = SgdInPlace{a.Cw_master[l], nullptr, (__bf16 *)a.Cw[l], nullptr, a.lr, a.dCw ? 1 : 0, nullptr, nullptr, nullptr};
                 later.push_back(pr);
                 splits.push_back(pass ? 1 : compressor_gradient_pieces(gl));
-                inside.push_back(in);
             }
         const LossTail tail{w.mse_partial, (int)out_tiles, 0.5f / (float)B, a.loss};
-        PH_TRY(upload_product_table(later, splits, inside, w.table, w.parts, w.arrived, tail, clear_at, clear_count, st, &table_grid));
+        PH_TRY(upload_product_table(later, splits, w.table, w.parts, w.arrived, tail, clear_at, clear_count, st, &table_grid));
     }
 
     // forward through every layer; y_l stays in the storage type between layers
-    const void *in = a.X0;
-    std::vector<const void *> inputs(L);
     for (int l = 0; l < L; ++l) {
-        inputs[l] = in;
         const bool bits = train && w.relu_bits[(size_t)l] != nullptr;
-        FwdArgs f{in, a.Lw[l], q ? a.Cw[l] : nullptr, q ? a.Dw[l] : nullptr, a.bias[l],
-                  (q && !g.all) ? a.G[l] : nullptr, w.Y[l], w.G[l], bits ? w.relu_bits[(size_t)l] : w.A[l],
-                  !save_deriv && !bits, save_deriv, bits, (mse_in_update && l == L - 1) ? &oe : nullptr};
-        PH_TRY(fwd_impl<T>(geos[(size_t)l], f, st));
-        in = w.Y[l];
-        if (a.taps) {
-            const Geo &gl = geos[(size_t)l];
-            if (a.taps->Y) PH_TRY(tap_copy<T>(a.taps->Y[l], w.Y[l], (int64_t)gl.groups * B * gl.so, st));
-            if (a.taps->g_own && q) PH_TRY(tap_copy<T>(a.taps->g_own[l], w.G[l], (int64_t)gl.groups * B * gl.k, st));
-        }
-    }
-    if (a.Y_out) {
-        hipLaunchKernelGGL((copy_kernel<T>), dim3(blocks_for(act_count)), dim3(256), 0, st, (const T *)w.Y[L - 1],
-                           (T *)a.Y_out, act_count);
-        PH_TRY(check_launch("output copy"));
+        FwdArgs f{l > 0 ? w.Y[(size_t)l - 1] : a.X0, a.Lw[l], q ? a.Cw[l] : nullptr, q ? a.Dw[l] : nullptr, a.bias[l],
+                  (q && !g.all) ? a.G[l] : nullptr, w.Y[l], w.G[l], bits ? w.relu_bits[(size_t)l] : train ? w.A[l] : nullptr,
+                  !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr};
+        PH_TRY(fwd_impl(geos[(size_t)l], f, st));
+        PH_TRY(forward_taps<T>(geos[(size_t)l], a, w, l, st));
     }
     if (!train) return PH_OK;
 
     // The loss is the sum of partial sums that the output-error computation leaves; the first memory-bound
     // kernel after it adds them up as a rider (LossTail), a kernel of its own if there is none.
     LossTail loss_tail{w.mse_partial, (int)out_tiles, 0.5f / (float)B, a.loss};
-    if (!mse_in_update) {
-        // output error as a kernel of its own; it also clears the workspace's bias-gradient block
-        const void *S = gelu ? w.A[L - 1] : w.Y[L - 1];
-        const int s_kind = save_deriv ? 2 : (gelu ? 1 : 0);
-        const bool wide = act_count % 8 == 0 && (((uintptr_t)a.T | (uintptr_t)w.Y[L - 1] | (uintptr_t)S | (uintptr_t)w.dYa) & 31) == 0;
-        const unsigned mse_blocks = blocks_for(wide ? act_count / 8 : act_count, 256, MSE_BLOCKS);
-        loss_tail.n = (int)mse_blocks;
-        ProfScope prof("output error", 0, act_count, 0, 1, st);
-        if (wide)
-            hipLaunchKernelGGL((mse_delta_kernel<T, 8>), dim3(mse_blocks), dim3(256), 0, st, (const T *)w.Y[L - 1],
-                               (const T *)a.T, S, s_kind, (T *)w.dYa, act_count, 1.0f / (float)B, g.act,
-                               w.mse_partial, clear_at, clear_count);
-        else
-            hipLaunchKernelGGL((mse_delta_kernel<T, 1>), dim3(mse_blocks), dim3(256), 0, st, (const T *)w.Y[L - 1],
-                               (const T *)a.T, S, s_kind, (T *)w.dYa, act_count, 1.0f / (float)B, g.act,
-                               w.mse_partial, clear_at, clear_count);
-        PH_TRY(check_launch("output error"));
-    }
-
     if (a.taps && a.taps->delta) PH_TRY(tap_copy<T>(a.taps->delta[L - 1], delta_top, act_count, st));   // delta_L, Eq. (deltaL)
 
     void *dY = w.dYa, *dX = w.dYb;    // delta of the current layer / of the layer below
     bool send_done = false;           // the current layer's error compression went out with the layer above
-    SgdBatch pending{};               // the update of the layer above, if it has not been launched yet
-    int64_t pending_elems = 0, pending_largest = 0;
-    bool have_pending = false;
-    auto launch_sgd = [&](const SgdBatch &batch, int tensors, int64_t largest, int64_t total) -> ph_status {
-        ProfScope prof("SGD update", 0, total, 0, 1, st);
-        hipLaunchKernelGGL((sgd_kernel<T>), dim3(blocks_for(largest, 256, 2048), (unsigned)tensors), dim3(256), 0, st, batch, a.lr);
-        return check_launch("SGD update");
-    };
     for (int l = L - 1; l >= 0; --l) {
         BwdArgs b{};
         b.send_done = send_done;
         b.below_Dw = (g.all && q > 0 && l > 0) ? a.Dw[l - 1] : nullptr;
         b.below_g = l > 0 ? &geos[(size_t)l - 1] : nullptr;
         b.below_done = &send_done;
-        b.dbias_zeroed = true;
+        b.dbias_ready = true;         // the product that wrote this layer's delta took the column sums
         b.loss_tail = &loss_tail;
-        // the layer's bias gradient is there already if the product that wrote its delta took the column sums
-        b.dbias_ready = l < L - 1 ? on_mfma(l + 1) : mse_in_update;
-        b.dx_colsum = (on_mfma(l) && l > 0) ? dbias_of(l - 1) : nullptr;
+        b.dx_colsum = l > 0 ? dbias_of(l - 1) : nullptr;
         if (deferred) { dY = w.delta_of[(size_t)l]; dX = l > 0 ? w.delta_of[(size_t)l - 1] : nullptr; b.defer = true; b.loss_tail = nullptr; }
-        b.delta_ready = dY; b.X = inputs[l];
+        b.delta_ready = dY; b.X = l > 0 ? w.Y[(size_t)l - 1] : a.X0;
         b.dx_S_bits = l > 0 && w.relu_bits[(size_t)l - 1] != nullptr;
-        b.dx_S = l > 0 ? (b.dx_S_bits ? w.relu_bits[(size_t)l - 1] : g.act == PH_ACT_GELU ? w.A[l - 1] : w.Y[l - 1]) : nullptr;
-        b.dx_S_f32 = gelu && !save_deriv;
+        b.dx_S = l > 0 ? (b.dx_S_bits ? w.relu_bits[(size_t)l - 1] : save_deriv ? w.A[l - 1] : w.Y[l - 1]) : nullptr;
         b.dx_S_deriv = save_deriv;
         b.Lw = a.Lw[l]; b.Cw = q ? a.Cw[l] : nullptr; b.Dw = q ? a.Dw[l] : nullptr;
         b.G = q ? (g.all ? w.G[l] : a.G[l]) : nullptr;
@@ -1317,70 +1503,32 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
         b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[l & 1]) : nullptr;
         b.dbias = dbias_of(l);
         b.dG_send = w.dG_send;
-        bool sgd_rode = false;
-        b.ride_sgd = have_pending ? &pending : nullptr;
-        b.ride_lr = a.lr;
-        b.ride_sgd_done = &sgd_rode;
+        // SGD on this layer in the epilogues of its gradients: every launch that reads its weights is out by then
+        if (update && !deferred) {
+            b.sgd_w = sgd_of(a, l, q, true, b.dbias);
+            b.sgd_c = sgd_of(a, l, q, false, nullptr);
+        }
         const Geo &gl = geos[(size_t)l];
-        const int64_t si = gl.si, so = gl.so, k = gl.k;
         if (a.taps) {
             b.tap_dG_send = (a.taps->dG_send && q) ? a.taps->dG_send[l] : nullptr;
             b.tap_dg_own = (a.taps->dg_own && q && g.all) ? a.taps->dg_own[l] : nullptr;
         }
-        PH_TRY(bwd_impl<T>(gl, b, w.bwd, st));
+        PH_TRY(bwd_impl(gl, b, w.bwd, st));
         // what the input gradient's epilogue left in dX is delta_{l-1} (Eq. (backprop), sigma' applied)
-        if (a.taps && a.taps->delta && l > 0) PH_TRY(tap_copy<T>(a.taps->delta[l - 1], dX, (int64_t)g.groups * B * si, st));
-        if (have_pending && !sgd_rode) PH_TRY(launch_sgd(pending, 4, pending_largest, pending_elems));
-        have_pending = false;
+        if (a.taps && a.taps->delta && l > 0) PH_TRY(tap_copy<T>(a.taps->delta[l - 1], dX, (int64_t)g.groups * B * gl.si, st));
         if (deferred) continue;
-
-        if (a.mode == PH_STEP_NO_UPDATE) {
-            if (loss_tail.partial) {                   // no kernel of this layer's backward could carry the rider
-                ProfScope prof("loss", 0, loss_tail.n, 0, 1, st);
-                hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, st, loss_tail);
-                PH_TRY(check_launch("loss"));
-                loss_tail.partial = nullptr;
-            }
-            void *t = dY; dY = dX; dX = t;
-            continue;
-        }
-        // SGD on this layer: nothing later in the backward pass reads its weights
-        struct Upd { void *w; float *master; const float *grad; int64_t count; };
-        Upd upd[4] = {
-            {a.Lw[l], a.Lw_master ? a.Lw_master[l] : nullptr, b.dLw, (int64_t)g.groups * so * si},
-            {a.bias[l], a.bias_master ? a.bias_master[l] : nullptr, b.dbias, (int64_t)g.groups * so},
-            {q ? a.Cw[l] : nullptr, (q && a.Cw_master) ? a.Cw_master[l] : nullptr, b.dCw, (int64_t)g.groups * k * si},
-            {q ? a.Dw[l] : nullptr, (q && a.Dw_master) ? a.Dw_master[l] : nullptr, b.dDw, (int64_t)g.groups * q * so * k},
-        };
-        SgdBatch batch{};
-        int tensors = 0;
-        int64_t largest = 0, total = 0;
-        for (const Upd &u : upd) {
-            if (!u.w || u.count == 0) continue;
-            batch.t[tensors++] = SgdTensor{u.w, u.master, u.grad, u.count};
-            largest = std::max(largest, u.count);
-            total += u.count;
-        }
-        if (tensors > 0) {
-            batch.tail = loss_tail;                    // still set: no kernel of this layer's backward carried the rider
+        std::swap(dY, dX);
+        if (loss_tail.partial) {                       // no kernel of this layer's backward could carry the rider
+            ProfScope prof("loss", 0, loss_tail.n, 0, 1, st);
+            hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, st, loss_tail);
+            PH_TRY(check_launch("loss"));
             loss_tail.partial = nullptr;
-            // The update may wait for the weight-gradient launch of the layer below and use the compute units
-            // that launch leaves idle (bwd_impl decides); the first layer's has nothing to wait for.
-            if (l > 0 && on_mfma(l - 1)) {
-                pending = batch;
-                pending_elems = total;
-                pending_largest = largest;
-                have_pending = true;
-            } else {
-                PH_TRY(launch_sgd(batch, tensors, largest, total));
-            }
         }
-        void *t = dY; dY = dX; dX = t;
     }
     if (deferred)
         PH_TRY(launch_product_table(w.table, table_grid, st,
-                                    a.mode != PH_STEP_NO_UPDATE ? "weight + compressor gradients of all layers + SGD | loss"
-                                                                : "weight + compressor gradients of all layers | loss",
+                                    update ? "weight + compressor gradients of all layers + SGD | loss"
+                                           : "weight + compressor gradients of all layers | loss",
                                     table_dw, table_dc, L));
     return PH_OK;
 }
@@ -1480,7 +1628,8 @@ ph_status phantom_layer_fwd(const ph_problem *prob, const void *X, const void *L
     f.X = X; f.Lw = Lw; f.Cw = Cw; f.Dw = Dw; f.bias = bias; f.G = G; f.Y = Y; f.g_own = g_own; f.A_save = A_save;
     PH_TRY(check_fwd_args(g, f));
     hipStream_t st = (hipStream_t)hip_stream;
-    return g.dtype == PH_F32 ? fwd_impl<float>(g, f, st) : fwd_impl<bf16_t>(g, f, st);
+    if (g.dtype == PH_F32) return flex_fwd<float>(g, f, st);
+    return use_flex({g}, false, true) ? flex_fwd<bf16_t>(g, f, st) : fwd_impl(g, f, st);
 }
 
 ph_status phantom_layer_bwd(const ph_problem *prob, const void *dY, const void *X, const void *A_or_Y,
@@ -1500,7 +1649,8 @@ ph_status phantom_layer_bwd(const ph_problem *prob, const void *dY, const void *
     Arena a{(char *)workspace, 0};
     BwdWs w = carve_bwd(a, g);
     hipStream_t st = (hipStream_t)hip_stream;
-    return g.dtype == PH_F32 ? bwd_impl<float>(g, b, w, st) : bwd_impl<bf16_t>(g, b, w, st);
+    if (g.dtype == PH_F32) return flex_layer_bwd<float>(g, b, w, st);
+    return use_flex({g}, true, true) ? flex_layer_bwd<bf16_t>(g, b, w, st) : bwd_impl(g, b, w, st);
 }
 
 }  // extern "C"
@@ -1567,7 +1717,9 @@ ph_status run_step(const std::vector<Geo> &geos, const ph_step_args *args, void 
     Arena a{(char *)workspace, 0};
     StepWs w = carve_step(a, geos);
     hipStream_t st = (hipStream_t)hip_stream;
-    return geos[0].dtype == PH_F32 ? step_impl<float>(geos, *args, w, st) : step_impl<bf16_t>(geos, *args, w, st);
+    if (args->Y_out) w.Y.back() = args->Y_out;         // the last layer writes the network output where the caller wants it
+    if (geos[0].dtype == PH_F32) return flex_step<float>(geos, *args, w, st);
+    return use_flex(geos, args->mode != PH_STEP_FORWARD) ? flex_step<bf16_t>(geos, *args, w, st) : step_impl(geos, *args, w, st);
 }
 
 // ---- the step for callers that cannot allocate -------------------------------------------------

@@ -34,11 +34,11 @@ FAMILIES = [
     (("gemm_mfma_kernel<1, 1", "gemm_mfma_kernelILi1ELi1E"), "km_km", ("weight + compressor gradients", "weight gradients", "compressor gradient")),
     (("thin_product_kernel",), "thin", ("compression",)),
     (("reduce_scatter_kernel",), "rs", ("reduce-scatter",)),
-    (("sgd_kernel",), "sgd", ("SGD update",)),
-    (("mse_delta_kernel",), "mse", ("output error",)),
     (("colsum_kernel",), "colsum", ("bias gradient",)),
     (("loss_kernel",), "loss", ("loss",)),
-    (("gemm_generic_kernel",), "generic", ()),
+    (("gemm_flex_kernel",), "flex", ("layer update", "compression", "input gradient", "error compression", "weight + compressor gradients",
+                                     "gradients")),
+    (("delta_kernel",), "delta", ("local error",)),
     (("fill_zero_kernel",), "fill", ("clear",)),
     (("copy_kernel",), "copy", ()),
 ]
