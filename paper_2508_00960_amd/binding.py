@@ -73,6 +73,7 @@ class PhProfileEntry(ctypes.Structure):
 
 
 _lib = None
+_fast = None                      # the native module, once load() has run
 
 
 def library_path() -> str:
@@ -81,13 +82,17 @@ def library_path() -> str:
 
 def load():
     """Load libphantom.so.  It is never replaced by a fallback: a missing library is an error."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     import torch  # noqa: F401  (brings the HIP runtime the library links against into the process first)
     if not os.path.exists(_LIB_PATH):
         from .build import build_library
         build_library(verbose=False)
+    if not os.path.exists(os.path.join(_HERE, "_marshal.so")):
+        from .build import build_marshal
+        build_marshal(verbose=False)
+    from . import _marshal
     lib = ctypes.CDLL(_LIB_PATH)
     vp, sz = ctypes.c_void_p, ctypes.c_size_t
     prob = ctypes.POINTER(PhProblem)
@@ -108,8 +113,15 @@ def load():
     lib.phantom_profile_begin.argtypes = [ctypes.c_int32]
     lib.phantom_profile_end.restype = ctypes.c_int
     lib.phantom_profile_end.argtypes = [ctypes.POINTER(PhProfileEntry), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
-    _lib = lib
+    _marshal.bind(*(ctypes.cast(f, vp).value for f in (lib.phantom_layer_fwd, lib.phantom_layer_bwd, lib.phantom_ffn_step,
+                                                       lib.phantom_ffn_step_static)))
+    _lib, _fast = lib, _marshal
     return lib
+
+
+def _loaded():
+    load()
+    return _fast
 
 
 def profile_begin(max_launches: int = 4096) -> None:
@@ -236,6 +248,9 @@ def workspace_bytes(prob: PhProblem) -> int:
 
 
 def layer_fwd(prob, X, Lw, Cw, Dw, bias, G, Y, g_own, A_save, workspace=None, stream=None):
+    status = (_fast or _loaded()).layer_fwd(prob, X, Lw, Cw, Dw, bias, G, Y, g_own, A_save, workspace, stream)
+    if status is not None:
+        return _check(status)
     wp, wb = _ws(workspace)
     _check_layer_tensors(prob, 0, {"X": (X, "in"), "Lw": (Lw, "L"), "Cw": (Cw, "C"), "Dw": (Dw, "D"), "bias": (bias, "b"),
                                    "G": (G if prob.rank >= 0 else None, "gathered"), "Y": (Y, "out"),
@@ -246,6 +261,10 @@ def layer_fwd(prob, X, Lw, Cw, Dw, bias, G, Y, g_own, A_save, workspace=None, st
 
 def layer_bwd(prob, dY, X, A_or_Y, Lw, Cw, Dw, G, dg_own, dX, dLw, dCw, dDw, dbias, dG_send, workspace=None,
               stream=None):
+    status = (_fast or _loaded()).layer_bwd(prob, dY, X, A_or_Y, Lw, Cw, Dw, G, dg_own, dX, dLw, dCw, dDw, dbias, dG_send,
+                                            workspace, stream)
+    if status is not None:
+        return _check(status)
     wp, wb = _ws(workspace)
     _check_layer_tensors(prob, 0, {"dY": (dY, "out"), "X": (X, "in"), "A_or_Y": (A_or_Y, "out"), "Lw": (Lw, "L"),
                                    "Cw": (Cw, "C"), "Dw": (Dw, "D"), "G": (G, "gathered"), "dg_own": (dg_own, "g"),
@@ -270,6 +289,12 @@ def ffn_step(prob, X0, T, Lw, Cw, Dw, bias, *, Lw_master=None, Cw_master=None, D
              mode="train", workspace=None, stream=None, taps=None, static=False):
     """phantom_ffn_step; per-layer arguments are sequences of prob.layers tensors (or None).
     taps: dict with any of "Y", "g_own", "delta", "dG_send", "dg_own" -> sequence of prob.layers tensors (ph_step_taps)."""
+    if taps is None:
+        status = (_fast or _loaded()).ffn_step(prob, X0, T, Y_out, loss, lr, STEP_MODES[mode], static, workspace, stream,
+                                               Lw, Cw, Dw, bias, Lw_master, Cw_master, Dw_master, bias_master, G, dg_own,
+                                               dLw, dCw, dDw, dbias)
+        if status is not None:
+            return _check(status)
     L = prob.layers
     keep = []
     kinds = {"Lw": "L", "Cw": "C", "Dw": "D", "bias": "b", "Lw_master": "L32", "Cw_master": "C32", "Dw_master": "D32",

@@ -1,4 +1,4 @@
-"""Build libphantom.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Build libphantom.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's native module, in-tree."""
 from __future__ import annotations
 
 import os
@@ -8,6 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libphantom.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -40,5 +41,26 @@ def build_library(verbose: bool = True) -> str:
     return LIB
 
 
+def build_marshal(verbose: bool = True) -> str:
+    """Compile csrc/marshal.cpp, a CPython module that reads torch tensors (host code only)."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    inc, lib = os.path.join(base, "include"), os.path.join(base, "lib")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL,
+           f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError(f"g++ failed ({proc.returncode}):\n{proc.stderr}")
+    return MARSHAL
+
+
 if __name__ == "__main__":
     print(build_library())
+    print(build_marshal())
