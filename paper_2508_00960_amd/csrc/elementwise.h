@@ -168,6 +168,24 @@ __global__ __launch_bounds__(256) void reduce_scatter_kernel(const T *__restrict
     if (tail.partial && blockIdx.x == 0 && blockIdx.y == 0) finish_loss(tail, lred);      // uniform; rider, see LossTail
 }
 
+// Buffers that a step adds into (bias gradients, counters), cleared by a launch that runs anyway before the first of them
+// is added to, or by one launch of their own.
+constexpr int CLEAR_MAX = 8;
+struct ClearList {
+    int count;               // 0: nothing to do
+    int n[CLEAR_MAX];        // floats
+    float *p[CLEAR_MAX];
+};
+// workgroup `job` of `jobs`, of `threads` threads
+__device__ __forceinline__ void clear_rider(const ClearList &c, int job, int jobs, int threads)
+{
+    if (c.count == 0) return;                          // uniform
+#pragma unroll 1
+    for (int i = 0; i < c.count; ++i)
+        for (int z = job * threads + (int)threadIdx.x; z < c.n[i]; z += jobs * threads) c.p[i][z] = 0.f;
+}
+__global__ __launch_bounds__(256) void clear_kernel(ClearList c) { clear_rider(c, (int)blockIdx.x, (int)gridDim.x, 256); }
+
 __global__ __launch_bounds__(256) void fill_zero_kernel(float *__restrict__ dst, int64_t count)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

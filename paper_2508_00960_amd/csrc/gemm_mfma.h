@@ -33,7 +33,10 @@
 //
 // Kernels in this file, all built on mfma_workgroup (one workgroup's work on one product):
 //   gemm_mfma_kernel       one product, or two of the same operand layout and output type
-//   gemm_mfma_table_kernel one rank: the weight + compressor gradients of all layers, parameter blocks in device memory
+//   gemm_mfma_uniform_kernel, gemm_mfma_table_kernel
+//                          one rank: the weight + compressor gradients of all layers, with parameter blocks in the kernel
+//                          arguments (layers of the same shapes) or in device memory
+//   gemm_mfma_many_kernel  one rank: the compressions of all layers
 //   gemm_mfma_tail_kernel  weight + compressor gradients with riders of other layouts (the error compression of
 //                          the layer below, the loss)
 //   gemm_mfma_fwd_kernel   a rank's layer update with the thin compression shared out over its workgroups
@@ -1313,6 +1316,29 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_kernel(MfmaBatch batch)
     mfma_workgroup<KA, KB, VA, VB, TOut, DUAL, EPI>(P, wg);
 }
 
+// Several independent products of one shape class in one launch: the compressions of all layers of one rank with more
+// phantom neurons than thin_product.h takes.  One rank's g goes to the peers and nothing on the rank waits for it, so they
+// go out together behind the forward pass: alone, a layer's fills half of the compute units (configuration 5, k = 256: 128
+// tiles, 16.4 us a layer, 6 layers).
+constexpr int MANY_PRODUCTS = 6;
+struct MfmaMany {
+    MfmaParams p[MANY_PRODUCTS];
+    int count;
+    int first_wg[MANY_PRODUCTS + 1];       // multiples of 8
+};
+static_assert(sizeof(MfmaMany) <= 3840, "travels as kernel arguments (4 KB with the hidden ones)");
+
+template <int VEC, bool DUAL>
+__global__ __launch_bounds__(512, 1) void gemm_mfma_many_kernel(MfmaMany many)
+{
+    int j = 0;
+    while (j + 1 < many.count && (int)blockIdx.x >= many.first_wg[j + 1]) ++j;          // uniform
+    const MfmaParams P = params_at(offsetof(MfmaMany, p) + (size_t)j * sizeof(MfmaParams));
+    const int local = (int)blockIdx.x - many.first_wg[j];
+    if (local >= P.total_wg) return;
+    mfma_workgroup<LD_KC, LD_KC, VEC, VEC, __bf16, DUAL, EPI_STORE>(P, xcd_order(local, 0, P.total_wg));
+}
+
 // The last launch of a layer's backward pass, the weight + compressor gradients (tail[0], tail[1]: weight-gradient
 // layout, float out; tail[1] may be empty: total_wg = 0), with up to two riders that need nothing it produces:
 //  - head, all ranks on the device: the error compression of the layer below (input-gradient layout, storage
@@ -1393,8 +1419,6 @@ struct TableChunk {
     int wgs[CHUNK_PRODUCTS];
     int dual[CHUNK_PRODUCTS];
     LossTail tail;
-    float *clear_at;                       // the upload also clears clear_count floats there (the step's buffers that
-    int clear_count;                       //   are added into: one launch less)
     MfmaParams p[CHUNK_PRODUCTS];
 };
 static_assert(sizeof(TableChunk) + sizeof(void *) <= 3840, "a chunk travels as kernel arguments (4 KB with the hidden ones)");
@@ -1412,7 +1436,57 @@ __global__ __launch_bounds__(256) void table_upload_kernel(TableChunk c, Product
     if ((int)threadIdx.x <= c.n) table->first_wg[c.at + threadIdx.x] = c.first_wg[threadIdx.x];
     if ((int)threadIdx.x < c.n) { table->wgs[c.at + threadIdx.x] = c.wgs[threadIdx.x]; table->dual[c.at + threadIdx.x] = c.dual[threadIdx.x]; }
     if (threadIdx.x == 0) { table->count = c.count; table->tail = c.tail; }
-    for (int i = (int)threadIdx.x; i < c.clear_count; i += 256) c.clear_at[i] = 0.f;
+}
+
+// Layers of the same shapes (the uniform network) need no table: their parameter blocks differ in pointers alone, and two
+// blocks and every layer's pointers fit the kernel arguments.  (Two small launches less per step: 9 us.)
+constexpr int UNIFORM_LAYERS = 12;
+struct UniformGradients {
+    MfmaParams dw, dc;                     // any layer's blocks (dc.total_wg = 0: no compressor)
+    int layers, dc_wg, dw_wg;              // workgroups per layer, multiples of 8
+    int dw_dual;
+    int64_t parts_layer, arrived_layer;    // floats / words from one layer's pieces to the next's
+    LossTail tail;
+    struct { const void *dw_a, *dw_b0, *dw_b1, *dc_a; void *dw_o0, *dw_o1, *dc_o0;
+             float *l_master, *d_master, *c_master, *bias_master; void *l_w, *d_w, *c_w, *bias_w; const float *bias_grad; } at[UNIFORM_LAYERS];
+};
+static_assert(sizeof(UniformGradients) <= 3840, "travels as kernel arguments (4 KB with the hidden ones)");
+
+template <int VEC>
+__global__ __launch_bounds__(512, 1) void gemm_mfma_uniform_kernel(UniformGradients u)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const int id = (int)blockIdx.x;
+    if (id == 0 && u.tail.partial) {                            // uniform
+        finish_loss(u.tail, (float *)smem_raw);
+        __syncthreads();
+    }
+    const bool weights = id >= u.layers * u.dc_wg;
+    const int i = weights ? id - u.layers * u.dc_wg : id, per = weights ? u.dw_wg : u.dc_wg;
+    const int l = i / per, local = i - l * per;
+    MfmaParams P = params_at(weights ? offsetof(UniformGradients, dw) : offsetof(UniformGradients, dc));
+    if (local >= P.total_wg) return;
+#if defined(__HIP_DEVICE_COMPILE__)
+    // this layer's pointers, read where they are needed (see params_at)
+    size_t offset = offsetof(UniformGradients, at) + (size_t)l * sizeof(u.at[0]);
+    asm volatile("" : "+s"(offset) :: "memory");
+    typedef void *const __attribute__((address_space(4))) *ArgPtrs;
+    const ArgPtrs q = (ArgPtrs)((const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+    P.b.p0 = q[1];
+    if (weights) {
+        P.a.p0 = q[0]; P.b.p1 = q[2];
+        P.o.p0 = q[4]; P.o.p1 = q[5];
+        P.sgd.master0 = (float *)q[7]; P.sgd.master1 = (float *)q[8]; P.sgd.w0 = q[11]; P.sgd.w1 = q[12];
+        P.sgd.bias_master = (float *)q[10]; P.sgd.bias_w = q[14]; P.sgd.bias_grad = (const float *)q[15];
+    } else {
+        P.a.p0 = q[3];
+        P.o.p0 = q[6];
+        P.sgd.master0 = (float *)q[9]; P.sgd.w0 = q[13];
+        P.parts += l * u.parts_layer; P.arrived += l * u.arrived_layer;
+    }
+#endif
+    if (weights && u.dw_dual) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, true, EPI_STORE>(P, xcd_order(local, 0, P.total_wg));
+    else mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, EPI_STORE>(P, xcd_order(local, 0, P.total_wg));
 }
 
 template <int VEC>
@@ -1468,6 +1542,7 @@ struct MfmaFwdBatch {
     int update_wg;           // = update.total_wg
     int wg_per_group;        // workgroups of the update per group
     int thin_rows;           // rows of the compression per workgroup: wg_per_group * thin_rows >= M
+    ClearList clear;
     FoldParams fold;         // FOLD kernels: the compression inside the update's loop instead (the fields above unused)
 };
 
@@ -1476,6 +1551,7 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_fwd_kernel(MfmaFwdBatch fb)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int wg = xcd_order((int)blockIdx.x, 0, fb.update_wg);
+    clear_rider(fb.clear, (int)blockIdx.x, (int)gridDim.x, MFMA_THREADS);
     const MfmaParams update = params_at(offsetof(MfmaFwdBatch, update));
     if constexpr (FOLD) {
         // the compression rides inside the update's reduction loop (FoldParams)

@@ -548,10 +548,9 @@ ph_status launch_tail(const Product *head, const Product &tail0, const Product &
 // fills the table (small launches, any time before); launch_product_table runs the products.
 // splits[j] > 1 cuts product j's reduction into pieces (parts, arrived: room for all of them, see MfmaParams);
 // A product's sgd.w0 != NULL puts the SGD update into its epilogue.  tail: the launch's first workgroup finishes
-// the loss.  clear_at, clear_count: floats that the first upload launch clears on its way.  *grid: the launch's size.
+// the loss.  *grid: the launch's size.
 ph_status upload_product_table(const std::vector<Product> &prods, const std::vector<int> &splits,
-                               ProductTable *table, float *parts, unsigned *arrived, const LossTail &tail, float *clear_at,
-                               int64_t clear_count, hipStream_t st, int *grid)
+                               ProductTable *table, float *parts, unsigned *arrived, const LossTail &tail, hipStream_t st, int *grid)
 {
     const char *what = "parameter table";
     if (prods.size() > (size_t)TABLE_PRODUCTS) return fail(PH_ERR_LAUNCH, "%s: internal error, more products than the table holds", what);
@@ -584,10 +583,9 @@ ph_status upload_product_table(const std::vector<Product> &prods, const std::vec
     for (int at = 0; at < count; at += CHUNK_PRODUCTS) {
         TableChunk c{};
         c.at = at; c.n = std::min(CHUNK_PRODUCTS, count - at); c.count = count; c.tail = tail;
-        if (at == 0) { c.clear_at = clear_at; c.clear_count = (int)clear_count; }
         for (int i = 0; i < c.n; ++i) { c.p[i] = blocks[(size_t)(at + i)]; c.wgs[i] = blocks[(size_t)(at + i)].total_wg; c.dual[i] = duals[(size_t)(at + i)]; }
         for (int i = 0; i <= c.n; ++i) c.first_wg[i] = first[(size_t)(at + i)];
-        ProfScope prof(what, 0, (int64_t)c.n * (int64_t)(sizeof(MfmaParams) / 4) + c.clear_count, 0, 1, st);
+        ProfScope prof(what, 0, (int64_t)c.n * (int64_t)(sizeof(MfmaParams) / 4), 0, 1, st);
         hipLaunchKernelGGL(table_upload_kernel, dim3(1), dim3(256), 0, st, c, table);
         PH_TRY(check_launch(what));
     }
@@ -613,6 +611,81 @@ ph_status launch_product_table(const ProductTable *table, int grid, hipStream_t 
     return check_launch(what);
 }
 
+// The same launch for layers of one shape, without a table (dw, dc: by layer; dc empty without compressors).
+ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::vector<Product> &dc, int pieces, float *parts,
+                                   unsigned *arrived, const LossTail &tail, hipStream_t st, const char *what)
+{
+    const int L = (int)dw.size();
+    const bool two = dc[0].M > 0;
+    UniformGradients u{};
+    int64_t tiles = tiles_of(dw[0].M, dw[0].N) * L;
+    if (two) tiles += tiles_of(dc[0].M, dc[0].N) * L;
+    u.dw_dual = tiles > 256;
+    u.dw = mfma_params(dw[0], 1, 1, u.dw_dual);
+    u.dw_wg = (u.dw.total_wg + 7) & ~7;
+    if (two) {
+        u.dc = mfma_params(dc[0], 1, pieces, false);
+        u.dc_wg = (u.dc.total_wg + 7) & ~7;
+        const int64_t t = tiles_of(dc[0].M, dc[0].N);
+        if (u.dc.ksplit > 1) {
+            if (t * L > PIECE_WORDS) return fail(PH_ERR_LAUNCH, "%s: internal error, more cut tiles than words to count them", what);
+            u.dc.parts = parts; u.dc.arrived = arrived;
+            u.parts_layer = t * pieces * MT * MT; u.arrived_layer = t;
+        }
+    }
+    u.layers = L;
+    u.tail = tail;
+    for (int l = 0; l < L; ++l) {
+        const Product &w = dw[(size_t)l], &c = dc[(size_t)l];
+        u.at[l] = {w.a.p0, w.b.p0, w.b.p1, c.a.p0, w.o.p0, w.o.p1, c.o.p0, w.sgd.master0, w.sgd.master1, c.sgd.master0, w.sgd.bias_master,
+                   w.sgd.w0, w.sgd.w1, c.sgd.w0, w.sgd.bias_w, w.sgd.bias_grad};
+    }
+    auto kern = gemm_mfma_uniform_kernel<8>;
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES, hipGetErrorString(e));
+        configured = true;
+    }
+    ProfScope prof(what, dw[0].M, dw[0].N, dw[0].K, L, st, dc[0].M, dc[0].N, dc[0].K);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(L * (u.dc_wg + u.dw_wg))), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, u);
+    return check_launch(what);
+}
+
+// Up to MANY_PRODUCTS products of the forward layout with a plain store, in one launch.
+template <int VEC, bool DUAL>
+ph_status launch_many_kernel(const MfmaMany &many, hipStream_t st, const char *what)
+{
+    auto kern = gemm_mfma_many_kernel<VEC, DUAL>;
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES, hipGetErrorString(e));
+        configured = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)many.first_wg[many.count]), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, many);
+    return check_launch(what);
+}
+
+ph_status launch_many(const std::vector<Product> &prods, int vec, hipStream_t st, const char *what)
+{
+    for (size_t at = 0; at < prods.size(); at += MANY_PRODUCTS) {
+        MfmaMany many{};
+        many.count = (int)std::min<size_t>(MANY_PRODUCTS, prods.size() - at);
+        int64_t tiles = 0;
+        for (int i = 0; i < many.count; ++i) tiles += tiles_of(prods[at + i].M, prods[at + i].N);
+        const bool dual = tiles > 256;                 // as for any launch
+        for (int i = 0; i < many.count; ++i) {
+            many.p[i] = mfma_params(prods[at + i], 1, 1, dual);
+            many.first_wg[i + 1] = many.first_wg[i] + ((many.p[i].total_wg + 7) & ~7);
+        }
+        ProfScope prof(what, prods[at].M, prods[at].N, prods[at].K, many.count, st);
+        if (vec == 8) PH_TRY(dual ? (launch_many_kernel<8, true>(many, st, what)) : (launch_many_kernel<8, false>(many, st, what)));
+        else PH_TRY(dual ? (launch_many_kernel<4, true>(many, st, what)) : (launch_many_kernel<4, false>(many, st, what)));
+    }
+    return PH_OK;
+}
+
 // One rank's thin compression and layer update in one launch: see MfmaFwdBatch.
 template <int VEC, bool DUAL, bool FOLD = false>
 ph_status launch_fwd_kernel(const MfmaFwdBatch &fb, unsigned total_wg, hipStream_t st, const char *what)
@@ -629,12 +702,14 @@ ph_status launch_fwd_kernel(const MfmaFwdBatch &fb, unsigned total_wg, hipStream
     return check_launch(what);
 }
 
-ph_status launch_fwd_pair(const Product &update, const Product &compress, int groups, int vec, hipStream_t st, const char *what)
+ph_status launch_fwd_pair(const Product &update, const Product &compress, int groups, int vec, const ClearList &clear, hipStream_t st,
+                          const char *what)
 {
     const int64_t tiles = tiles_of(update.M, update.N) * groups;
     if (tiles * 8 > 0x7fffffff) return fail(PH_ERR_LAUNCH, "%s: internal error, too many tiles (make_geo admits none such)", what);
     const bool dual = tiles > 256;                     // as for a launch of the update alone
     MfmaFwdBatch fb{};
+    fb.clear = clear;
     fb.update = mfma_params(update, groups, 1, dual);
     fb.X = (const __bf16 *)compress.a.p0; fb.C = (const __bf16 *)compress.b.p0; fb.G = (__bf16 *)compress.o.p0;
     fb.M = (int)compress.M; fb.N = (int)compress.N; fb.K = (int)compress.K;
@@ -844,26 +919,29 @@ struct FwdArgs {
     bool a_deriv; // step only: A_save receives sigma'(A), in float, instead of A
     bool a_bits;  // step only, ReLU: A_save receives one bit per element (stored output > 0)
     const struct OutputError *mse;   // step only, last layer: form the MSE output error in the update's epilogue
+    ClearList *clear;                // step only: buffers to clear; a launch that can do it on its way empties the list
+    std::vector<Product> *later;     // step only, one rank: takes a compression that would leave compute units idle (launch_many)
 };
 
-// What the last layer's update needs to leave the output error of the MSE loss behind (Epilogue::mse_*), and
-// the buffers a thin compression launch before it clears on its way (they are added into from then on;
-// clear_count = 0: the caller has cleared them).
+// What the last layer's update needs to leave the output error of the MSE loss behind (Epilogue::mse_*).
 struct OutputError {
     const void *target;      // [groups, B, s] storage type
     void *delta;             // [groups, B, s] storage type
     float *partial;          // one partial sum of squares per tile of the update
     float inv_b;
     float *dbias;            // [groups, s], receives the column sums of delta (zero on entry)
-    float *clear_at;         // cleared by the compression launch: clear_count floats
-    int64_t clear_count;
 };
 
-// Does the forward of this geometry run its compression as the thin kernel in a launch of its own before the
-// update?  (All ranks on the device, and the conditions of the thin kernel as in fwd_impl.)
-bool thin_launch_before_update(const Geo &g)
+// A list of buffers to clear, in a launch of its own.
+ph_status launch_clear(ClearList &list, hipStream_t st)
 {
-    return g.all && g.dtype == PH_BF16 && g.q > 0 && g.k <= THIN_MAX_N && g.si % 16 == 0 && g.vec > 0;
+    if (list.count == 0) return PH_OK;
+    int64_t n = 0;
+    for (int i = 0; i < list.count; ++i) n += list.n[i];
+    ProfScope prof("clear bias gradients", 0, n, 0, 1, st);
+    hipLaunchKernelGGL(clear_kernel, dim3(blocks_for(n)), dim3(256), 0, st, list);
+    list = ClearList{};
+    return check_launch("clear bias gradients");
 }
 
 // The products of a layer's forward pass (Eq. (ylq)).
@@ -918,8 +996,11 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
     const GemmPlan plan{LD_KC, LD_KC, g.vec};
     FwdProducts prods = make_fwd_products(g, f);
     const Product &update = prods.update, &compress = prods.compress;
-    float *clear_at = f.mse ? f.mse->clear_at : nullptr;
-    const int64_t clear_count = f.mse ? f.mse->clear_count : 0;
+    auto take_clear = [&]() {
+        ClearList c{};
+        if (f.clear) std::swap(c, *f.clear);
+        return c;
+    };
     // A compression with few phantom neurons has a kernel of its own (32 rows per workgroup instead of 128)
     const bool thin = q > 0 && k <= THIN_MAX_N && si % 16 == 0 && g.vec > 0;
     auto launch_thin = [&]() -> ph_status {
@@ -927,12 +1008,14 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
         dim3 grid((unsigned)((B + THIN_ROWS - 1) / THIN_ROWS), (unsigned)g.groups);
         if (k <= 32)
             hipLaunchKernelGGL((thin_product_kernel<1>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
-                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, clear_at, clear_count);
+                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, take_clear());
         else
             hipLaunchKernelGGL((thin_product_kernel<2>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
-                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, clear_at, clear_count);
+                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, take_clear());
         return check_launch("compression");
     };
+    // (this layer's update adds into the buffers itself if it is the last one)
+    if (f.clear && f.mse && !(g.all && thin)) PH_TRY(launch_clear(*f.clear, st));
     if (g.all) {
         // every rank reads the other ranks' g: the compression of all ranks has to finish first
         if (thin) PH_TRY(launch_thin());
@@ -945,8 +1028,12 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
     if (thin && tiles_both > 256) {
         static const char *force = tuning_env("PHANTOM_FWD_PAIR");         // =0: two launches (for measurements)
         if (!(force && force[0] == '0'))
-            return launch_fwd_pair(update, compress, g.groups, g.vec, st, "layer update + thin compression");
+            return launch_fwd_pair(update, compress, g.groups, g.vec, take_clear(), st, "layer update + thin compression");
         PH_TRY(launch_thin());
+        return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update");
+    }
+    if (f.later && q > 0 && k > THIN_MAX_N) {
+        f.later->push_back(compress);
         return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update");
     }
     Product both[2] = {update, compress};
@@ -1303,7 +1390,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
     auto delta_of = [&](int l) { return deltas[l % 3]; };
     auto dbias_of = [&](int l) { return a.dbias ? a.dbias[l] : w.dbias + w.dbias_at[(size_t)l]; };
 
-    OutputError oe{a.T, delta_of(L - 1), w.mse_partial, 1.0f / (float)B, nullptr, nullptr, 0};
+    OutputError oe{a.T, delta_of(L - 1), w.mse_partial, 1.0f / (float)B, nullptr};
     int mse_tiles = 0;
     for (int l = 0; l < L; ++l) {
         FwdArgs f{};
@@ -1396,80 +1483,85 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     // layer's bias gradient has a buffer of its own that is zeroed once for the whole step.
     const bool train = a.mode != PH_STEP_FORWARD, update = a.mode == PH_STEP_TRAIN;
     auto dbias_of = [&](int l) { return a.dbias ? a.dbias[l] : w.dbias + w.dbias_at[(size_t)l]; };
-    if (train && a.dbias) {
-        for (int l = 0; l < L; ++l) {
-            const int64_t bias_count = (int64_t)g.groups * geos[(size_t)l].so;
-            hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks_for(bias_count)), dim3(256), 0, st, a.dbias[l], bias_count);
-            PH_TRY(check_launch("clear bias gradients"));
+    // What the step adds into is cleared by its first forward launch that can do it on the way, else by one of its own (the
+    // words for cut reductions lie right behind the workspace's block and are cleared with it).
+    ClearList clear{};
+    if (train) {
+        auto add = [&](void *p, int64_t n) { clear.p[clear.count] = (float *)p; clear.n[clear.count++] = (int)n; };
+        if (a.dbias) {
+            for (int l = 0; l < L; ++l) {
+                if (clear.count == CLEAR_MAX - 1) PH_TRY(launch_clear(clear, st));
+                add(a.dbias[l], (int64_t)g.groups * geos[(size_t)l].so);
+            }
+            add(w.arrived, PIECE_WORDS);
+        } else {
+            add(w.dbias, w.dbias_at[(size_t)L] + PIECE_WORDS);
         }
     }
-    // (the words for cut reductions lie right behind the workspace's block and are cleared with it)
-    float *clear_at = a.dbias ? (float *)w.arrived : w.dbias;
-    const int64_t clear_count = a.dbias ? PIECE_WORDS : w.dbias_at[(size_t)L] + PIECE_WORDS;
 
     // The output error of the MSE loss (Eq. (deltaL)) is elementwise in the last layer's output, so
     // that layer's update forms it in its epilogue, together with the last bias gradient and one partial
     // sum of the loss per tile: two launches less than a kernel for the error and one for the column sums.
-    // The buffers it adds into have to be clear by then: the thin compression launch right before it does that
-    // on its way where there is one, else a launch of its own at the start of the step.
     const int64_t out_tiles = tiles_of(B, g.so) * g.groups;
-    const bool clear_in_compression = train && thin_launch_before_update(g);
     // (one rank with deferred weight gradients keeps every layer's delta: the last layer's goes to its own buffer)
     const bool deferred = train && w.table && deferred_weight_gradients(geos);
-    if (train && !clear_in_compression && !deferred && clear_count > 0) {
-        ProfScope prof("clear bias gradients", 0, clear_count, 0, 1, st);
-        hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks_for(clear_count)), dim3(256), 0, st, clear_at, clear_count);
-        PH_TRY(check_launch("clear bias gradients"));
-    }
     void *delta_top = deferred ? w.delta_of[(size_t)L - 1] : w.dYa;
-    OutputError oe{a.T, delta_top, w.mse_partial, 1.0f / (float)B, dbias_of(L - 1), clear_in_compression ? clear_at : nullptr,
-                   clear_in_compression ? clear_count : 0};
+    OutputError oe{a.T, delta_top, w.mse_partial, 1.0f / (float)B, dbias_of(L - 1)};
 
-    // Deferred weight gradients: the products of all layers are known from the buffers alone.  Their parameter table
-    // goes up now, ahead of the forward pass (the first of those small launches also clears what the step adds
-    // into), and the launch itself comes at the end of the backward pass: the compressor gradients first (few
+    // Deferred weight gradients: the products of all layers are known from the buffers alone.  Their launch comes at the
+    // end of the backward pass (layers of different shapes: its parameter table goes up now, ahead of the
+    // forward pass): the compressor gradients first (few
     // tiles with half of their rows empty, cut into pieces), then the weight gradients' tiles, which fill the compute
     // units as those come free; the SGD update of L, C, D and the bias in the epilogues, the loss by the first workgroup.
     int table_grid = 0;
-    Product table_dw{}, table_dc{};
+    std::vector<Product> all_dw, all_dc;               // by layer
+    const bool uniform = L <= UNIFORM_LAYERS && std::all_of(geos.begin(), geos.end(), [&](const Geo &x) {
+        return x.si == g.si && x.so == g.so && x.k == g.k;
+    });
+    const LossTail table_tail{w.mse_partial, (int)out_tiles, 0.5f / (float)B, a.loss};
     if (deferred) {
-        std::vector<Product> later;
-        std::vector<int> splits;
-        for (int pass = 0; pass < 2; ++pass)
-            for (int l = L - 1; l >= 0; --l) {
-                const Geo &gl = geos[(size_t)l];
-                BwdArgs b{};
-                b.X = l > 0 ? w.Y[l - 1] : a.X0;
-                b.G = q ? a.G[l] : nullptr;
-                b.dg_own = q ? const_cast<void *>(a.dg_own[l]) : nullptr;
-                // (gradients that the caller does not want: a training step has the update in the epilogues and stores
-                // none; a step without update stores every layer's in the same place, where nobody reads them)
-                b.dLw = a.dLw ? a.dLw[l] : w.dLw[0];
-                b.dCw = q ? (a.dCw ? a.dCw[l] : w.dCw[0]) : nullptr;
-                b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[0]) : nullptr;
-                if (update) {
-                    b.sgd_w = sgd_of(a, l, q, true, dbias_of(l));
-                    b.sgd_c = sgd_of(a, l, q, false, nullptr);
-                }
-                const BwdProducts all = make_bwd_products(gl, b, w.delta_of[(size_t)l]);
-                const Product &pr = pass ? all.dw : all.dc;
-                if (l == L - 1) (pass ? table_dw : table_dc) = pr;
-                if (pr.M <= 0 || pr.N <= 0) continue;
-                later.push_back(pr);
-                splits.push_back(pass ? 1 : compressor_gradient_pieces(gl));
+        for (int l = 0; l < L; ++l) {
+            BwdArgs b{};
+            b.X = l > 0 ? w.Y[l - 1] : a.X0;
+            b.G = q ? a.G[l] : nullptr;
+            b.dg_own = q ? const_cast<void *>(a.dg_own[l]) : nullptr;
+            // (gradients that the caller does not want: a training step has the update in the epilogues and stores
+            // none; a step without update stores every layer's in the same place, where nobody reads them)
+            b.dLw = a.dLw ? a.dLw[l] : w.dLw[0];
+            b.dCw = q ? (a.dCw ? a.dCw[l] : w.dCw[0]) : nullptr;
+            b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[0]) : nullptr;
+            if (update) {
+                b.sgd_w = sgd_of(a, l, q, true, dbias_of(l));
+                b.sgd_c = sgd_of(a, l, q, false, nullptr);
             }
-        const LossTail tail{w.mse_partial, (int)out_tiles, 0.5f / (float)B, a.loss};
-        PH_TRY(upload_product_table(later, splits, w.table, w.parts, w.arrived, tail, clear_at, clear_count, st, &table_grid));
+            const BwdProducts all = make_bwd_products(geos[(size_t)l], b, w.delta_of[(size_t)l]);
+            all_dw.push_back(all.dw);
+            all_dc.push_back(all.dc);
+        }
+        if (!uniform) {
+            std::vector<Product> later;
+            std::vector<int> splits;
+            for (int l = L - 1; l >= 0; --l)
+                if (all_dc[(size_t)l].M > 0) { later.push_back(all_dc[(size_t)l]); splits.push_back(compressor_gradient_pieces(geos[(size_t)l])); }
+            for (int l = L - 1; l >= 0; --l) { later.push_back(all_dw[(size_t)l]); splits.push_back(1); }
+            PH_TRY(upload_product_table(later, splits, w.table, w.parts, w.arrived, table_tail, st, &table_grid));
+        }
     }
 
     // forward through every layer; y_l stays in the storage type between layers
+    std::vector<Product> later;
     for (int l = 0; l < L; ++l) {
         const bool bits = train && w.relu_bits[(size_t)l] != nullptr;
         FwdArgs f{l > 0 ? w.Y[(size_t)l - 1] : a.X0, a.Lw[l], q ? a.Cw[l] : nullptr, q ? a.Dw[l] : nullptr, a.bias[l],
                   (q && !g.all) ? a.G[l] : nullptr, w.Y[l], w.G[l], bits ? w.relu_bits[(size_t)l] : train ? w.A[l] : nullptr,
-                  !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr};
+                  !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr, &clear, g.all || a.taps || L == 1 ? nullptr : &later};
         PH_TRY(fwd_impl(geos[(size_t)l], f, st));
         PH_TRY(forward_taps<T>(geos[(size_t)l], a, w, l, st));
+    }
+    if (!later.empty()) {
+        int vec = 8;
+        for (const Geo &x : geos) vec = std::min(vec, x.vec);
+        PH_TRY(launch_many(later, vec, st, "compressions of all layers"));
     }
     if (!train) return PH_OK;
 
@@ -1525,11 +1617,11 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
             loss_tail.partial = nullptr;
         }
     }
-    if (deferred)
-        PH_TRY(launch_product_table(w.table, table_grid, st,
-                                    update ? "weight + compressor gradients of all layers + SGD | loss"
-                                           : "weight + compressor gradients of all layers | loss",
-                                    table_dw, table_dc, L));
+    if (deferred) {
+        const char *what = update ? "weight + compressor gradients of all layers + SGD | loss" : "weight + compressor gradients of all layers | loss";
+        if (uniform) PH_TRY(launch_uniform_gradients(all_dw, all_dc, compressor_gradient_pieces(g), w.parts, w.arrived, table_tail, st, what));
+        else PH_TRY(launch_product_table(w.table, table_grid, st, what, all_dw.back(), all_dc.back(), L));
+    }
     return PH_OK;
 }
 

@@ -9,6 +9,7 @@
 // then add their partial sums through LDS.  C (k x s, at most 128 KB) is read by every workgroup, from L2.
 #pragma once
 #include "common.h"
+#include "elementwise.h"    // ClearList
 
 namespace phantom {
 
@@ -92,18 +93,14 @@ __device__ __forceinline__ void thin_workgroup(const __bf16 *__restrict__ X, con
 }
 
 // The kernel: workgroup (x, y) = rows [32 x, 32 x + 32) of group y, THIN_WAVES wavefronts.
-// Rider: the kernel also clears zero_count floats at `zero` (buffers that later launches of a training step
-// add into; the compression is the launch before the first of them).
+// Rider: the kernel also clears buffers that later launches of a training step add into.
 template <int NF>
 __global__ __launch_bounds__(THIN_WAVES * 64) void thin_product_kernel(const __bf16 *__restrict__ X, const __bf16 *__restrict__ C,
                                                           __bf16 *__restrict__ G, int M, int N, int K,
                                                           int64_t x_g, int64_t c_g, int64_t o_g,
-                                                          float *__restrict__ zero, int64_t zero_count)
+                                                          ClearList clear)
 {
-    constexpr int THREADS = THIN_WAVES * 64;
-    for (int64_t z = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * THREADS + threadIdx.x; z < zero_count;
-         z += (int64_t)gridDim.x * gridDim.y * THREADS)
-        zero[z] = 0.f;
+    clear_rider(clear, (int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y), THIN_WAVES * 64);
     __shared__ float part[THIN_WAVES * NF * 16 * 64];  // [wavefront][column block][accumulator][lane]
     thin_workgroup<NF, THIN_WAVES>(X, C, G, M, N, K, x_g, c_g, o_g, blockIdx.x * THIN_ROWS, blockIdx.y, part);
 }
