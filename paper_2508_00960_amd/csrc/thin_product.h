@@ -11,6 +11,8 @@
 #include "common.h"
 #include "elementwise.h"    // ClearList
 
+#include <type_traits>
+
 namespace phantom {
 
 constexpr int THIN_ROWS = 32;       // rows of X per workgroup
@@ -51,20 +53,25 @@ __device__ __forceinline__ void thin_workgroup(const __bf16 *__restrict__ X, con
     for (int f = 0; f < NF; ++f)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[f][e] = 0.f;
+    // eight chunks' loads in flight together, then four, then one at a time (a 1024-wide shard gives a wavefront exactly eight)
     int ch = c_lo;
-    for (; ch + 4 <= c_hi; ch += 4) {                  // four chunks' loads in flight together
-        thin_bf16x8 a[4], b[NF][4];
+    auto batch = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        thin_bf16x8 a[N], b[NF][N];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < N; ++u) {
             a[u] = *(const thin_bf16x8 *)(xrow + (ch + u) * 16);
 #pragma unroll
             for (int f = 0; f < NF; ++f) b[f][u] = *(const thin_bf16x8 *)(crow[f] + (ch + u) * 16);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < N; ++u)
 #pragma unroll
             for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[f][u], acc[f], 0, 0, 0);
-    }
+        ch += N;
+    };
+    while (ch + 8 <= c_hi) batch(std::integral_constant<int, 8>{});
+    if (ch + 4 <= c_hi) batch(std::integral_constant<int, 4>{});
     for (; ch < c_hi; ++ch) {
         const thin_bf16x8 a = *(const thin_bf16x8 *)(xrow + ch * 16);
 #pragma unroll
