@@ -51,17 +51,26 @@ struct FlexOperand {
     int tiny;            // one of the buffers may have fewer than V elements altogether
 };
 
-struct FlexParams {
+// A product's parameter block: what its reduction needs ...
+struct FlexIn {
     FlexOperand a, b;
-    void *o0, *o1;       // output regions (the column index decides)
-    int64_t o_g0, o_g1, o_ld0, o_ld1, o_seg_stride;
-    Epilogue ep;
-    SgdInPlace sgd;
     FlexAxis k, n;       // reduction index, column index
     int M;
     int tiles_m, tiles_n, total_wg;
     int kind;            // 0: A along the reduction index (forward and input-gradient layouts); 1: weight-gradient layout
+    int rowsum;          // FlexOut::rowsum is wanted
+};
+// ... and what its epilogue needs
+struct FlexOut {
+    void *o0, *o1;       // output regions (the column index decides)
+    int64_t o_g0, o_g1, o_ld0, o_ld1, o_seg_stride;
+    Epilogue ep;
+    SgdInPlace sgd;
     float *rowsum;       // weight-gradient layout, optional: [M] per group <- sums of A over the reduction index (Eq. (bpb))
+};
+struct FlexParams {
+    FlexIn in;
+    FlexOut out;
 };
 
 constexpr int FLEX_MAX_PRODUCTS = 4;
@@ -450,6 +459,25 @@ constexpr int flex_lds_bytes()
                     TEAMS * F::C_BYTES + F::THREADS * 4 + 64);
 }
 
+// A piece of the kernel's one argument (a FlexBatch), read where it is needed at an offset that the compiler cannot see
+// through (see params_at in gemm_mfma.h).  The epilogue's part is read behind the reduction loop: with both parts read at
+// the top the scalar registers do not hold them, and spilled ones come back through vector instructions in the loop.
+template <typename Part>
+__device__ __forceinline__ Part flex_args_at(size_t offset)
+{
+    constexpr int WORDS = sizeof(Part) / 4;
+    union Words { Part p; uint32_t w[WORDS]; __device__ Words() {} };
+    Words out;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(offset) :: "memory");
+    typedef const uint32_t __attribute__((address_space(4))) *ArgWords;
+    const ArgWords in = (ArgWords)((const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) out.w[i] = in[i];
+#endif
+    return out.p;
+}
+
 // orders a wavefront's own LDS accesses for the compiler (the hardware keeps them in order)
 __device__ __forceinline__ void flex_wave_sync()
 {
@@ -460,7 +488,7 @@ __device__ __forceinline__ void flex_wave_sync()
 
 // One workgroup's work on the product P: workgroup number wg of P.total_wg.
 template <typename T, int TM, int TN, int TEAMS, int KA, int KB, typename TOut, int EPI>
-__device__ __forceinline__ void flex_workgroup(const FlexParams &P, int wg, unsigned char *lds)
+__device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int wg, unsigned char *lds)
 {
     typedef FlexShape<T, TM, TN, TEAMS> F;
     typedef FlexLoader<T, KA, TM, F::TT> LA;
@@ -585,15 +613,16 @@ __device__ __forceinline__ void flex_workgroup(const FlexParams &P, int wg, unsi
     if (rows) extra[threadIdx.x] = row_acc;
     __syncthreads();
 
-    const Epilogue &ep = P.ep;
-    const SgdInPlace &sgd = P.sgd;
+    const FlexOut Q = flex_args_at<FlexOut>(offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out));
+    const Epilogue &ep = Q.ep;
+    const SgdInPlace &sgd = Q.sgd;
     if constexpr (ROWSUM) {
         if (rows && (int)threadIdx.x < TM && m0 + (int)threadIdx.x < P.M) {
             float t = 0.f;
 #pragma unroll 4
             for (int r = threadIdx.x; r < F::THREADS; r += TM) t += extra[r];        // parts of a team, then the next team
             const int64_t at = (int64_t)g * P.M + m0 + threadIdx.x;
-            gstore<float>(P.rowsum + at, t);
+            gstore<float>(Q.rowsum + at, t);
             if (sgd.bias_w) {
                 if constexpr (sizeof(T) == 2) {
                     const float nb = gload<float>(sgd.bias_master + at) - sgd.lr * t;
@@ -611,7 +640,7 @@ __device__ __forceinline__ void flex_workgroup(const FlexParams &P, int wg, unsi
     for (int v = (int)threadIdx.x; v < TM * PER_ROW; v += F::THREADS) {
         const int row = v / PER_ROW, col = (v % PER_ROW) * V, m = m0 + row, n = n0 + col;
         if (m >= P.M || n >= P.n.total) continue;
-        const FlexLoc l = flex_locate(P.n, n, P.o_seg_stride, NO_SKIP);
+        const FlexLoc l = flex_locate(P.n, n, Q.o_seg_stride, NO_SKIP);
         const int valid = min(V, l.len - l.in_piece);
         FlexRow<V> x;
 #pragma unroll
@@ -658,7 +687,7 @@ __device__ __forceinline__ void flex_workgroup(const FlexParams &P, int wg, unsi
                 for (int u = 0; u < V; ++u) x.x[u] *= act_deriv(ep.act, a.x[u]);
             }
         }
-        const int64_t o_at = l.region ? g * P.o_g1 + (int64_t)m * P.o_ld1 + l.off : g * P.o_g0 + (int64_t)m * P.o_ld0 + l.off;
+        const int64_t o_at = l.region ? g * Q.o_g1 + (int64_t)m * Q.o_ld1 + l.off : g * Q.o_g0 + (int64_t)m * Q.o_ld0 + l.off;
         if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
             if (sgd.w0) {                              // uniform
                 void *const w0 = sgd.w0, *const w1 = sgd.w1;
@@ -680,7 +709,7 @@ __device__ __forceinline__ void flex_workgroup(const FlexParams &P, int wg, unsi
                 if (!sgd.keep_grad) continue;
             }
         }
-        void *const o0 = P.o0, *const o1 = P.o1;
+        void *const o0 = Q.o0, *const o1 = Q.o1;
         flex_write<TOut, V>((TOut *)(l.region ? o1 : o0) + o_at, x, valid);
         if (EPI == EPI_BIAS_ACT && ep.mode == EPI_BIAS_ACT && ep.mse_target) {         // uniform
             // the MSE output error of Eq. (deltaL) from the output as stored, rounded once
@@ -716,23 +745,6 @@ __device__ __forceinline__ int flex_xcd_order(int i, int count)     // see xcd_o
     return i < per * 8 ? (i & 7) * per + (i >> 3) : i;
 }
 
-// Product number j of the batch, read from the kernel-argument segment where it is needed (see params_at in gemm_mfma.h)
-__device__ __forceinline__ FlexParams flex_params_at(int j)
-{
-    constexpr int WORDS = sizeof(FlexParams) / 4;
-    union Words { FlexParams p; uint32_t w[WORDS]; __device__ Words() {} };
-    Words out;
-#if defined(__HIP_DEVICE_COMPILE__)
-    size_t offset = offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams);
-    asm volatile("" : "+s"(offset) :: "memory");
-    typedef const uint32_t __attribute__((address_space(4))) *ArgWords;
-    const ArgWords in = (ArgWords)((const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() + offset);
-#pragma unroll
-    for (int i = 0; i < WORDS; ++i) out.w[i] = in[i];
-#endif
-    return out.p;
-}
-
 // FORWARD: products in the forward layout (bias + activation, or plain store).  Otherwise: products in the input-gradient
 // layout (sigma' or plain store, kind 0) and in the weight-gradient layout (kind 1, float out), in any mix.
 template <typename T, int TM, int TN, int TEAMS, bool FORWARD>
@@ -746,12 +758,12 @@ __global__ __launch_bounds__((FlexShape<T, TM, TN, TEAMS>::THREADS), (FlexShape<
     int j = 0;
     while (j + 1 < batch.count && (int)blockIdx.x >= batch.first_wg[j + 1]) ++j;       // uniform
     const int local = (int)blockIdx.x - batch.first_wg[j];
-    const FlexParams P = flex_params_at(j);
+    const FlexIn P = flex_args_at<FlexIn>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, in));
     if (local >= P.total_wg) return;
     const int wg = flex_xcd_order(local, P.total_wg);
-    if constexpr (FORWARD) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KC, T, EPI_BIAS_ACT>(P, wg, smem_raw);
-    else if (P.kind == 0) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KM, T, EPI_DACT>(P, wg, smem_raw);
-    else flex_workgroup<T, TM, TN, TEAMS, FLEX_KM, FLEX_KM, float, EPI_STORE>(P, wg, smem_raw);
+    if constexpr (FORWARD) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KC, T, EPI_BIAS_ACT>(P, j, wg, smem_raw);
+    else if (P.kind == 0) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KM, T, EPI_DACT>(P, j, wg, smem_raw);
+    else flex_workgroup<T, TM, TN, TEAMS, FLEX_KM, FLEX_KM, float, EPI_STORE>(P, j, wg, smem_raw);
 }
 
 }  // namespace phantom

@@ -869,11 +869,12 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, int g
     int next = 0;
     for (int i = 0; i < count; ++i) {
         const Product &pr = prods[i];
-        FlexParams &P = batch.p[i];
+        FlexIn &P = batch.p[i].in;
+        FlexOut &Q = batch.p[i].out;
         P.kind = pr.km ? 1 : 0;
-        P.o0 = pr.o.p0; P.o1 = pr.o.p1; P.o_g0 = pr.o.g0; P.o_g1 = pr.o.g1;
-        P.o_ld0 = pr.o.r.mult0; P.o_ld1 = pr.o.r.mult1; P.o_seg_stride = pr.o.c.seg_stride;
-        P.ep = pr.ep; P.sgd = pr.sgd; P.rowsum = pr.rowsum;
+        Q.o0 = pr.o.p0; Q.o1 = pr.o.p1; Q.o_g0 = pr.o.g0; Q.o_g1 = pr.o.g1;
+        Q.o_ld0 = pr.o.r.mult0; Q.o_ld1 = pr.o.r.mult1; Q.o_seg_stride = pr.o.c.seg_stride;
+        Q.ep = pr.ep; Q.sgd = pr.sgd; Q.rowsum = pr.rowsum; P.rowsum = pr.rowsum != nullptr;
         P.k = flex_axis(pr.km ? Axis{} : pr.a.c, pr.K, V);
         P.n = flex_axis(pr.o.c, pr.N, V);
         P.M = (int)pr.M;
