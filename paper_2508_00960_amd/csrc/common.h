@@ -32,6 +32,20 @@ __device__ __forceinline__ float act_deriv(int act, float a)
     return 1.f;
 }
 
+// The same for the activations whose derivative can be read off their output (all but GELU).  The bf16 epilogues use these
+// where GELU cannot occur: erff and expf inlined eight times per unrolled pass made them 70 KB of code that every
+// workgroup fetches cold.
+template <int N> __device__ __forceinline__ void piecewise_both(int act, float (&x)[N], float (&deriv)[N])      // in place
+{
+    if (act == ACT_RELU) {                             // uniform
+#pragma unroll
+        for (int u = 0; u < N; ++u) { deriv[u] = x[u] > 0.f ? 1.f : 0.f; x[u] = x[u] > 0.f ? x[u] : 0.f; }
+    } else {
+#pragma unroll
+        for (int u = 0; u < N; ++u) deriv[u] = 1.f;
+    }
+}
+
 // GELU and its derivative together, for bf16 outputs: erf by the five-term rational formula of Abramowitz &
 // Stegun 7.1.26 (absolute error of erf below 1.5e-7, far under a bf16 rounding step), whose exp(-z^2) with
 // z = a / sqrt(2) is the same exponential that phi(a) needs.  One v_exp, one v_rcp and a dozen FMAs instead of

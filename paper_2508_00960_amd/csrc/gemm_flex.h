@@ -657,16 +657,19 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
             const FlexRow<V> bias = flex_read<T, V>((const T *)ep.bias + g * ep.bias_g + n, valid);
             FlexRow<V> pre;
 #pragma unroll
-            for (int u = 0; u < V; ++u) {
-                pre.x[u] = x.x[u] + bias.x[u];
-                if (sizeof(T) == 2 && ep.act == ACT_GELU) {
-                    gelu_both(pre.x[u], x.x[u], deriv.x[u]);
+            for (int u = 0; u < V; ++u) { x.x[u] += bias.x[u]; pre.x[u] = x.x[u]; }
+            if constexpr (sizeof(T) == 2) {
+                if (ep.act == ACT_GELU) {              // uniform
+#pragma unroll
+                    for (int u = 0; u < V; ++u) gelu_both(pre.x[u], x.x[u], deriv.x[u]);
                 } else {
-                    x.x[u] = act_apply(ep.act, pre.x[u]);
-                    deriv.x[u] = 1.f;
+                    piecewise_both(ep.act, x.x, deriv.x);
                 }
+            } else {
+#pragma unroll
+                for (int u = 0; u < V; ++u) { x.x[u] = act_apply(ep.act, pre.x[u]); deriv.x[u] = 1.f; }
             }
-            if (!(sizeof(T) == 2 && ep.act == ACT_GELU) && (ep.aux_deriv || ep.mse_target)) {      // uniform
+            if (sizeof(T) == 4 && (ep.aux_deriv || ep.mse_target)) {       // uniform
 #pragma unroll
                 for (int u = 0; u < V; ++u) deriv.x[u] = act_deriv(ep.act, pre.x[u]);
             }
@@ -684,7 +687,7 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
                 const FlexRow<V> a = ep.aux_f32 ? flex_read<float, V>((const float *)ep.aux + aux_at, valid)
                                                 : flex_read<T, V>((const T *)ep.aux + aux_at, valid);
 #pragma unroll
-                for (int u = 0; u < V; ++u) x.x[u] *= act_deriv(ep.act, a.x[u]);
+                for (int u = 0; u < V; ++u) x.x[u] *= sizeof(T) == 2 ? (a.x[u] > 0.f ? 1.f : 0.f) : act_deriv(ep.act, a.x[u]);   // (bf16: ReLU output)
             }
         }
         const int64_t o_at = l.region ? g * Q.o_g1 + (int64_t)m * Q.o_ld1 + l.off : g * Q.o_g0 + (int64_t)m * Q.o_ld0 + l.off;

@@ -673,9 +673,6 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
         } else if (ep.aux_deriv) {
 #pragma unroll
             for (int i = 0; i < AUX_PASSES; ++i) aux_v[i].f = gload_nt<FlV>((const float *)ep.aux + at[i]);   // read once
-        } else if (ep.aux_f32) {
-#pragma unroll
-            for (int i = 0; i < AUX_PASSES; ++i) aux_v[i].f = gload<FlV>((const float *)ep.aux + at[i]);
         } else {
 #pragma unroll
             for (int i = 0; i < AUX_PASSES; ++i) aux_v[i].h = gload<BfV>((const __bf16 *)ep.aux + at[i]);
@@ -736,11 +733,6 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
 #pragma unroll
                         for (int u = 0; u < VEC; ++u) a[u] = deriv[u];
                         gstore_nt<FlV>((float *)ep.aux + aux_at, a);
-                    } else if (ep.aux_f32) {
-                        FlV a;
-#pragma unroll
-                        for (int u = 0; u < VEC; ++u) a[u] = pre[u];
-                        gstore<FlV>((float *)ep.aux + aux_at, a);
                     } else {
                         BfV a;
 #pragma unroll
@@ -750,28 +742,12 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
                 }
             } else {
                 if (ep.aux && !ep.aux_bits) {
-                    if (ep.aux_deriv) {
-                        FlV a;
+                    BfV a;
 #pragma unroll
-                        for (int u = 0; u < VEC; ++u) a[u] = act_deriv(ep.act, x[u]);
-                        gstore<FlV>((float *)ep.aux + aux_at, a);
-                    } else if (ep.aux_f32) {
-                        FlV a;
-#pragma unroll
-                        for (int u = 0; u < VEC; ++u) a[u] = x[u];
-                        gstore<FlV>((float *)ep.aux + aux_at, a);
-                    } else {
-                        BfV a;
-#pragma unroll
-                        for (int u = 0; u < VEC; ++u) a[u] = (__bf16)x[u];
-                        gstore<BfV>((__bf16 *)ep.aux + aux_at, a);
-                    }
+                    for (int u = 0; u < VEC; ++u) a[u] = (__bf16)x[u];
+                    gstore<BfV>((__bf16 *)ep.aux + aux_at, a);
                 }
-#pragma unroll
-                for (int u = 0; u < VEC; ++u) {
-                    deriv[u] = act_deriv(ep.act, x[u]);
-                    x[u] = act_apply(ep.act, x[u]);
-                }
+                piecewise_both(ep.act, x, deriv);
             }
         } else if (EPI == EPI_DACT && ep.mode == EPI_DACT && ep.aux) {      // no aux: sigma' = 1, column sums only
             const AuxU &av = aux_v[EPI == EPI_DACT ? i : 0];
@@ -783,12 +759,9 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
             } else if (ep.aux_deriv) {                 // sigma' itself, float
 #pragma unroll
                 for (int u = 0; u < VEC; ++u) x[u] *= av.f[u];
-            } else if (ep.aux_f32) {
+            } else {                                   // ReLU output in bf16
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) x[u] *= act_deriv(ep.act, av.f[u]);
-            } else {                                   // the pre-activation (or ReLU output) in bf16
-#pragma unroll
-                for (int u = 0; u < VEC; ++u) x[u] *= act_deriv(ep.act, (float)av.h[u]);
+                for (int u = 0; u < VEC; ++u) x[u] = (float)av.h[u] > 0.f ? x[u] : x[u] * 0.f;
             }
         }
         const Loc ln = locate(P.o.c, n, skip_o);
