@@ -1365,13 +1365,16 @@ SgdInPlace sgd_of(const ph_step_args &a, int l, int64_t q, bool weights, const f
     return s;
 }
 
-// Copies of a layer's forward results for the taps of the step.
+// Copies of the layers' forward results for the taps of the step.
 template <typename T>
-ph_status forward_taps(const Geo &g, const ph_step_args &a, const StepWs &w, int l, hipStream_t st)
+ph_status forward_taps(const std::vector<Geo> &geos, const ph_step_args &a, const StepWs &w, hipStream_t st)
 {
     if (!a.taps) return PH_OK;
-    if (a.taps->Y) PH_TRY(tap_copy<T>(a.taps->Y[l], w.Y[(size_t)l], (int64_t)g.groups * g.B * g.so, st));
-    if (a.taps->g_own && g.q) PH_TRY(tap_copy<T>(a.taps->g_own[l], w.G[(size_t)l], (int64_t)g.groups * g.B * g.k, st));
+    for (size_t l = 0; l < geos.size(); ++l) {
+        const Geo &g = geos[l];
+        if (a.taps->Y) PH_TRY(tap_copy<T>(a.taps->Y[l], w.Y[l], (int64_t)g.groups * g.B * g.so, st));
+        if (a.taps->g_own && g.q) PH_TRY(tap_copy<T>(a.taps->g_own[l], w.G[l], (int64_t)g.groups * g.B * g.k, st));
+    }
     return PH_OK;
 }
 
@@ -1402,8 +1405,8 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
         f.a_f32 = !save_deriv; f.a_deriv = save_deriv;
         f.mse = train && l == L - 1 ? &oe : nullptr;
         PH_TRY(flex_fwd<T>(geos[(size_t)l], f, st, f.mse ? &mse_tiles : nullptr));
-        PH_TRY(forward_taps<T>(geos[(size_t)l], a, w, l, st));
     }
+    PH_TRY(forward_taps<T>(geos, a, w, st));
     if (!train) return PH_OK;
     if (a.taps && a.taps->delta) PH_TRY(tap_copy<T>(a.taps->delta[L - 1], delta_of(L - 1), (int64_t)g.groups * B * g.so, st));
 
@@ -1555,15 +1558,15 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
         const bool bits = train && w.relu_bits[(size_t)l] != nullptr;
         FwdArgs f{l > 0 ? w.Y[(size_t)l - 1] : a.X0, a.Lw[l], q ? a.Cw[l] : nullptr, q ? a.Dw[l] : nullptr, a.bias[l],
                   (q && !g.all) ? a.G[l] : nullptr, w.Y[l], w.G[l], bits ? w.relu_bits[(size_t)l] : train ? w.A[l] : nullptr,
-                  !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr, &clear, g.all || a.taps || L == 1 ? nullptr : &later};
+                  !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr, &clear, g.all || L == 1 ? nullptr : &later};
         PH_TRY(fwd_impl(geos[(size_t)l], f, st));
-        PH_TRY(forward_taps<T>(geos[(size_t)l], a, w, l, st));
     }
     if (!later.empty()) {
         int vec = 8;
         for (const Geo &x : geos) vec = std::min(vec, x.vec);
         PH_TRY(launch_many(later, vec, st, "compressions of all layers"));
     }
+    PH_TRY(forward_taps<T>(geos, a, w, st));
     if (!train) return PH_OK;
 
     // The loss is the sum of partial sums that the output-error computation leaves; the first memory-bound

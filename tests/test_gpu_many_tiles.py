@@ -1,0 +1,27 @@
+"""One rank's steps with more 128 x 128 tiles than gemm_flex.h takes, at the smallest sizes that still reach each launch of
+the step: the compressions of all layers together, all layers' gradients in one launch (equal layers: blocks in the
+kernel arguments; different ones: a table), compressor gradients in one to four pieces, a launch per layer, and more layers
+than one list of clears holds.  Every stage against the oracle, batches ragged."""
+import pytest
+
+import phantom_inputs as pin
+
+from stage_check import check_stages
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,p,k,B,L,act,rank,mode,widths,ks", [
+    (8192, 8, 32, 1630, 3, "relu", 1, "train", None, None),            # 13 x 8 tiles, the compressor gradients whole
+    (8192, 8, 32, 2100, 2, "gelu", 0, "no_update", None, None),        # in two pieces, gradients handed out
+    (4096, 8, 16, 3150, 9, "relu", 0, "train", None, None),            # in three, nine layers
+    (4096, 8, 128, 4099, 3, "relu", 7, "train", None, None),           # in four; k > 64: compressions of all layers together
+    (8192, 8, 68, 1630, 2, "gelu", 0, "train", None, None),            # 4-element vectors: a launch per layer
+    (16384, 8, 16, 1100, 2, "relu", 0, "train", None, None),           # 272 weight-gradient tiles per layer: a launch per layer
+    (4096, 8, 16, 3150, 17, "relu", 0, "no_update", None, None),       # more layers than the table holds
+    (8192, 8, 32, 2100, 2, "relu", 0, "train", (8192, 4096, 12288), (32, 16)),       # layers that differ
+])
+def test_step_every_stage(n, p, k, B, L, act, rank, mode, widths, ks):
+    print(f"case many tiles n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode} widths={widths}", flush=True)
+    prob = pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=rank, widths=widths, ks=ks)
+    check_stages(prob, seed=6, lr=0.02, mode=mode)
