@@ -65,6 +65,13 @@ constexpr int TILE_ELEMS = (MT * KC_PITCH > KT * KM_PITCH) ? MT * KC_PITCH : KT 
 constexpr int MFMA_THREADS = 512;       // two teams of four wavefronts
 constexpr int MFMA_LDS_BYTES = 2 /*teams*/ * 2 /*stages*/ * 2 /*operands*/ * TILE_ELEMS * 2;
 
+// How a workgroup's teams take output tiles (mfma_workgroup).  TILE_SHARED: both teams one tile, alternate reduction
+// steps.  TILE_DUAL: two tiles, one above the other, with the B tile in common.  TILE_SOLO: one team only, one tile: half
+// the threads and half the LDS, so that a compute unit holds two such workgroups.
+enum { TILE_SHARED = 0, TILE_DUAL = 1, TILE_SOLO = 2 };
+constexpr int mfma_threads(int mode) { return mode == TILE_SOLO ? MFMA_THREADS / 2 : MFMA_THREADS; }
+constexpr int mfma_lds_bytes(int mode) { return mode == TILE_SOLO ? MFMA_LDS_BYTES / 2 : MFMA_LDS_BYTES; }
+
 template <int VEC> struct VecOf;
 template <> struct VecOf<8> { typedef u32x4 type; };
 template <> struct VecOf<4> { typedef u32x2 type; };
@@ -625,10 +632,11 @@ template <typename T, int VEC> struct PackOf { typedef T type __attribute__((ext
 // EPI: the only mode other than EPI_STORE that the kernel is built for (the first product's; the second
 // product of a pair always stores plainly).  Building every mode into every kernel made the epilogue, which
 // every workgroup runs exactly once and so fetches cold, long enough to cost each launch about 1 us.
-template <int VEC, typename TOut, bool SOLO, int EPI>
+template <int VEC, typename TOut, int MODE, int EPI>
 __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, const float *ctile, int m0, int n0, int thread,
                                                   float *wave_sums)
 {
+    constexpr bool SOLO = MODE != TILE_SHARED;         // one team per tile
     constexpr int THREADS = SOLO ? 256 : MFMA_THREADS;
     typedef typename PackOf<TOut, VEC>::type OutV;
     typedef typename PackOf<__bf16, VEC>::type BfV;
@@ -682,7 +690,7 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaParams &P, int g, co
     // of them (pass by pass, each waits a memory latency behind the stores of the one before): all 8 ranks of 256 trained,
     // 48 tiles, 190 -> 185 us.  Not with two tiles per workgroup: such launches fill the chip and are bound by the bytes of
     // the update (dense 4096 x 4096: 642 -> 657 us with it).
-    constexpr int AHEAD = EPI == EPI_STORE && sizeof(TOut) == 4 && !SOLO ? 4 : 1;
+    constexpr int AHEAD = EPI == EPI_STORE && sizeof(TOut) == 4 && MODE != TILE_DUAL ? 4 : 1;
     FlV ahead[AHEAD];
     constexpr int EPI_UNROLL = EPI == EPI_DACT ? PASSES : AHEAD > 1 ? AHEAD : 2;     // EPI_DACT: unrolled, the prefetched vectors stay in registers
 #pragma unroll EPI_UNROLL
@@ -1033,6 +1041,9 @@ __device__ __forceinline__ MfmaParams params_at(size_t offset)
 // rows), so per FLOP a quarter less goes through the vector-memory return path and into LDS, which is
 // what bounds the loop; the price is half as many workgroups, so this is for launches with more tiles
 // than compute units (the host decides).  Each team finishes its own tile: no sum in the epilogue.
+// SOLO: a workgroup is one team with one tile, two workgroups to a compute unit.  The terms of a sum come in DUAL's order
+// (the results are the same bits).  Nothing is shared, but one workgroup's epilogue runs beside the other's loop: for
+// short reductions with a heavy epilogue (solo_tiles on the host).
 // XCD-aware id: hardware deals workgroup ids round-robin over 8 XCDs; `first` (a multiple of 8) is the id of the
 // first of `count` consecutive workgroups that share a list of tiles.  Workgroups of one XCD get neighbouring tiles.
 __device__ __forceinline__ int xcd_order(int id, int first, int count)
@@ -1044,11 +1055,12 @@ __device__ __forceinline__ int xcd_order(int id, int first, int count)
 // One workgroup's work: workgroup number wg (of P.total_wg, in tile order) of the product P.
 // FOLD (the forward layout with 8-element vectors, regular shapes only): the workgroup also computes its block of
 // the compression F (FoldParams).
-template <int KA, int KB, int VA, int VB, typename TOut, bool DUAL, int EPI, bool FOLD = false>
+template <int KA, int KB, int VA, int VB, typename TOut, int MODE, int EPI, bool FOLD = false>
 __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, const FoldParams *Fp = nullptr)
 {
     static_assert(!FOLD || (KA == LD_KC && KB == LD_KC && VA == 8), "the compression rides with the forward product only");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    constexpr bool DUAL = MODE == TILE_DUAL, SOLO = MODE == TILE_SOLO;
     constexpr int BP = DUAL ? 2 : 1;                   // share of the B tile one team stages
     PH_PHASE(0);
     const int tiles = P.tiles_m * P.tiles_n;           // DUAL: tiles_m counts pairs of tile rows
@@ -1064,7 +1076,7 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, cons
     const int band_rows = min(P.tiles_m - band * RASTER_M, RASTER_M);
     const int tn = in_band / band_rows;
     const int tm = band * RASTER_M + (in_band - tn * band_rows);
-    const int team = threadIdx.x >> 8;
+    const int team = SOLO ? 0 : (int)threadIdx.x >> 8;
     const int team_u = __builtin_amdgcn_readfirstlane(team);
     const int m0 = DUAL ? (tm * 2 + team_u) * MT : tm * MT, n0 = tn * MT;
     const int k_begin = ks * P.k_per_split;
@@ -1143,10 +1155,10 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, cons
     // The reduction range is cut into tiles of KT.  Two teams on one tile: team q takes the tiles q, q+2, ...;
     // DUAL: every team takes every tile.  Both teams pass the same number of barriers (`steps`).
     const int all_steps = (k_end - k_begin + KT - 1) / KT;
-    const int steps = DUAL ? all_steps : (all_steps + 1) >> 1;
-    const int my_steps = DUAL ? all_steps : (all_steps - team_u + 1) >> 1;      // tiles this team really has
-    constexpr int KS = DUAL ? KT : 2 * KT;
-    const int kfirst = DUAL ? k_begin : k_begin + team_u * KT;     // start of this team's first tile
+    const int steps = DUAL || SOLO ? all_steps : (all_steps + 1) >> 1;
+    const int my_steps = DUAL || SOLO ? all_steps : (all_steps - team_u + 1) >> 1;      // tiles this team really has
+    constexpr int KS = DUAL || SOLO ? KT : 2 * KT;
+    const int kfirst = DUAL || SOLO ? k_begin : k_begin + team_u * KT;     // start of this team's first tile
     // Regular shapes walk their tiles from the LAST one down: the only tile that can be ragged (the end of the
     // reduction range) then comes first and is staged by the careful prologue; every later tile is a full
     // one and every step takes the fast path.  Other shapes walk upwards through the general loop.
@@ -1246,16 +1258,16 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, cons
     // each team writes its fp32 tile over the staging space (free after the barrier above).  Two teams
     // on one tile hold partial sums of it: the epilogue adds the two while reading.
     float *ctile = (float *)smem_raw;
-    constexpr bool PIECES = !DUAL && !FOLD && EPI == EPI_STORE && sizeof(TOut) == 4 && VA == 8;
+    constexpr bool PIECES = MODE == TILE_SHARED && !FOLD && EPI == EPI_STORE && sizeof(TOut) == 4 && VA == 8;
     acc_to_lds(ctile + team * CT_ELEMS, acc, wm, wn, lane);
     __syncthreads();
     PH_PHASE(4);
-    if constexpr (DUAL) epilogue_from_lds<VA, TOut, true, EPI>(P, g, ctile + team * CT_ELEMS, m0, n0, tid, ctile + 2 * CT_ELEMS);
+    if constexpr (DUAL || SOLO) epilogue_from_lds<VA, TOut, MODE, EPI>(P, g, ctile + team * CT_ELEMS, m0, n0, tid, ctile + (SOLO ? 1 : 2) * CT_ELEMS);
     else if constexpr (PIECES) {
         if (P.parts && P.ksplit > 1)                                 // uniform (one group: the host sees to that)
             epilogue_pieces_from_lds(P, rem, ks, ctile, (unsigned *)(ctile + 2 * CT_ELEMS), m0, n0, (int)threadIdx.x);
-        else epilogue_from_lds<VA, TOut, false, EPI>(P, g, ctile, m0, n0, (int)threadIdx.x, ctile + 2 * CT_ELEMS);
-    } else epilogue_from_lds<VA, TOut, false, EPI>(P, g, ctile, m0, n0, (int)threadIdx.x, ctile + 2 * CT_ELEMS);
+        else epilogue_from_lds<VA, TOut, MODE, EPI>(P, g, ctile, m0, n0, (int)threadIdx.x, ctile + 2 * CT_ELEMS);
+    } else epilogue_from_lds<VA, TOut, MODE, EPI>(P, g, ctile, m0, n0, (int)threadIdx.x, ctile + 2 * CT_ELEMS);
     PH_PHASE(5);
     if constexpr (FOLD) {
         if (fs.on) {                                                 // uniform
@@ -1295,14 +1307,14 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaParams &P, int wg, cons
     }
 }
 
-template <int KA, int KB, int VA, int VB, typename TOut, bool PAIR, bool DUAL, int EPI>
-__global__ __launch_bounds__(512, 1) void gemm_mfma_kernel(MfmaBatch batch)
+template <int KA, int KB, int VA, int VB, typename TOut, bool PAIR, int MODE, int EPI>
+__global__ __launch_bounds__(mfma_threads(MODE), MODE == TILE_SOLO ? 2 : 1) void gemm_mfma_kernel(MfmaBatch batch)
 {
     int wg = xcd_order(blockIdx.x, 0, batch.total_wg);
     const bool second = PAIR && wg >= batch.first_wg;
     if (second) wg -= batch.first_wg;
     const MfmaParams P = params_at(second ? offsetof(MfmaBatch, p[1]) : offsetof(MfmaBatch, p[0]));
-    mfma_workgroup<KA, KB, VA, VB, TOut, DUAL, EPI>(P, wg);
+    mfma_workgroup<KA, KB, VA, VB, TOut, MODE, EPI>(P, wg);
 }
 
 // Several independent products of one shape class in one launch: the compressions of all layers of one rank with more

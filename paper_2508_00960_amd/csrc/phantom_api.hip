@@ -394,38 +394,44 @@ struct Product {
     bool km;             // gemm_flex kernels: weight-gradient layout (both operands along their free index), float out
 };
 
-template <int KA, int KB, int VEC, typename TOut, bool PAIR, bool DUAL, int EPI>
+template <int KA, int KB, int VEC, typename TOut, bool PAIR, int MODE, int EPI>
 ph_status launch_mfma_kernel(const MfmaBatch &batch, hipStream_t st, const char *what)
 {
-    auto kern = gemm_mfma_kernel<KA, KB, VEC, VEC, TOut, PAIR, DUAL, EPI>;
+    auto kern = gemm_mfma_kernel<KA, KB, VEC, VEC, TOut, PAIR, MODE, EPI>;
+    constexpr int LDS = mfma_lds_bytes(MODE);
     static thread_local bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES,
-                                         hipGetErrorString(e));
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
         configured = true;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)batch.total_wg), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, batch);
+    hipLaunchKernelGGL(kern, dim3((unsigned)batch.total_wg), dim3(mfma_threads(MODE)), LDS, st, batch);
     return check_launch(what);
 }
 
 template <int KA, int KB, int VEC, typename TOut, int EPI>
-ph_status launch_mfma_inst(const MfmaBatch &batch, bool dual, hipStream_t st, const char *what)
+ph_status launch_mfma_inst(const MfmaBatch &batch, int mode, hipStream_t st, const char *what)
 {
-    if (dual) {
-        if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, true, true, EPI>(batch, st, what);
-        return launch_mfma_kernel<KA, KB, VEC, TOut, false, true, EPI>(batch, st, what);
+    if constexpr (KB == LD_KM) {
+        if (mode == TILE_SOLO) {
+            if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, true, TILE_SOLO, EPI>(batch, st, what);
+            return launch_mfma_kernel<KA, KB, VEC, TOut, false, TILE_SOLO, EPI>(batch, st, what);
+        }
     }
-    if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, true, false, EPI>(batch, st, what);
-    return launch_mfma_kernel<KA, KB, VEC, TOut, false, false, EPI>(batch, st, what);
+    if (mode == TILE_DUAL) {
+        if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, true, TILE_DUAL, EPI>(batch, st, what);
+        return launch_mfma_kernel<KA, KB, VEC, TOut, false, TILE_DUAL, EPI>(batch, st, what);
+    }
+    if (batch.count == 2) return launch_mfma_kernel<KA, KB, VEC, TOut, true, TILE_SHARED, EPI>(batch, st, what);
+    return launch_mfma_kernel<KA, KB, VEC, TOut, false, TILE_SHARED, EPI>(batch, st, what);
 }
 
 // EPI: the epilogue mode the kernel is built for besides the plain store (see epilogue_from_lds)
 template <int KA, int KB, typename TOut, int EPI>
-ph_status launch_mfma_vec(const MfmaBatch &batch, int vec, bool dual, hipStream_t st, const char *what)
+ph_status launch_mfma_vec(const MfmaBatch &batch, int vec, int mode, hipStream_t st, const char *what)
 {
-    if (vec == 8) return launch_mfma_inst<KA, KB, 8, TOut, EPI>(batch, dual, st, what);
-    return launch_mfma_inst<KA, KB, 4, TOut, EPI>(batch, dual, st, what);
+    if (vec == 8) return launch_mfma_inst<KA, KB, 8, TOut, EPI>(batch, mode, st, what);
+    return launch_mfma_inst<KA, KB, 4, TOut, EPI>(batch, mode, st, what);
 }
 
 MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
@@ -444,6 +450,25 @@ MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
     return P;
 }
 
+// More tiles than compute units: two workgroups of one tile each per compute unit (TILE_SOLO), or one of two tiles that
+// share their B operand (TILE_DUAL)?  All workgroups of a round are in the same phase, so the memory idles during DUAL's
+// loop and the matrix cores during its epilogue; SOLO's overlap, for a third more bytes staged.  It wins where the loop is
+// short against the epilogue.  Weight gradients with the update (10 to 14 bytes of weights per element; us per step,
+// DUAL : SOLO): batch 256 and 32 ranks of 1024 485 : 446, batch 1024 and 64 ranks of 128 631 : 561, dense 4096 656 : 610,
+// batch 1536 dense 365 : 350, but batch 2048 and 64 ranks of 256 1261 : 1282 and 4096 dense 781 : 803.  Input gradients (one
+// or four bytes of sigma' per element): 264 long 1282 : 1269, 528 long 632 : 631, 1036 long 419 : 429.  Plain stores:
+// 128 long 561 : 532, 256 long 474 : 470, 512 long 632 : 639.  The forward layout loses at 760 already (488 : 498).
+template <typename TOut>
+bool solo_tiles(const GemmPlan &plan, const Product *prods, int count)
+{
+    int64_t K = 0;
+    for (int i = 0; i < count; ++i) K = std::max(K, prods[i].K);
+    static const char *force = tuning_env("PHANTOM_SOLO");         // =0 / 1 (for measurements)
+    if (force) return force[0] == '1' && plan.kb == LD_KM;
+    if (std::is_same<TOut, float>::value) return K <= 1536;
+    return plan.kb == LD_KM && K <= (prods[0].ep.mode == EPI_DACT ? 768 : 256);
+}
+
 // bf16 operands on the matrix cores: one product, or two of the same layout side by side in one launch
 template <typename TOut>
 ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int groups, hipStream_t st, const char *what)
@@ -457,6 +482,8 @@ ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int
     bool dual = tiles + (count == 2 ? tiles_of(prods[1].M, prods[1].N) * groups : 0) > 256;
     static const char *force = tuning_env("PHANTOM_DUAL");
     if (force) dual = force[0] == '1';
+    const int tile_mode = !dual ? TILE_SHARED : solo_tiles<TOut>(plan, prods, count) ? TILE_SOLO : TILE_DUAL;
+    dual = tile_mode == TILE_DUAL;
     MfmaBatch batch{};
     batch.count = count;
     batch.p[0] = mfma_params(first, groups, 1, dual);
@@ -477,15 +504,15 @@ ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int
     if (count == 2 && second.ep.mode != EPI_STORE) return fail(PH_ERR_LAUNCH, "%s: internal error, the second product of a pair must store plainly", what);
     if constexpr (std::is_same<TOut, float>::value) {
         if (plan.ka == LD_KM && plan.kb == LD_KM && mode == EPI_STORE)
-            return launch_mfma_vec<LD_KM, LD_KM, float, EPI_STORE>(batch, plan.vec, dual, st, what);
+            return launch_mfma_vec<LD_KM, LD_KM, float, EPI_STORE>(batch, plan.vec, tile_mode, st, what);
     } else {
         if (plan.ka == LD_KC && plan.kb == LD_KC) {
-            if (mode == EPI_BIAS_ACT) return launch_mfma_vec<LD_KC, LD_KC, TOut, EPI_BIAS_ACT>(batch, plan.vec, dual, st, what);
-            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KC, TOut, EPI_STORE>(batch, plan.vec, dual, st, what);
+            if (mode == EPI_BIAS_ACT) return launch_mfma_vec<LD_KC, LD_KC, TOut, EPI_BIAS_ACT>(batch, plan.vec, tile_mode, st, what);
+            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KC, TOut, EPI_STORE>(batch, plan.vec, tile_mode, st, what);
         }
         if (plan.ka == LD_KC && plan.kb == LD_KM) {
-            if (mode == EPI_DACT) return launch_mfma_vec<LD_KC, LD_KM, TOut, EPI_DACT>(batch, plan.vec, dual, st, what);
-            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KM, TOut, EPI_STORE>(batch, plan.vec, dual, st, what);
+            if (mode == EPI_DACT) return launch_mfma_vec<LD_KC, LD_KM, TOut, EPI_DACT>(batch, plan.vec, tile_mode, st, what);
+            if (mode == EPI_STORE) return launch_mfma_vec<LD_KC, LD_KM, TOut, EPI_STORE>(batch, plan.vec, tile_mode, st, what);
         }
     }
     return fail(PH_ERR_LAUNCH, "%s: internal error, no kernel for this operand layout, output type and epilogue", what);

@@ -1,4 +1,4 @@
-"""One rank's steps with more 128 x 128 tiles than gemm_flex.h takes, at the smallest sizes that still reach each launch of
+"""Steps with more 128 x 128 tiles than compute units in one-team workgroups (all ranks), and one rank's steps with more 128 x 128 tiles than gemm_flex.h takes, at the smallest sizes that still reach each launch of
 the step: the compressions of all layers together, all layers' gradients in one launch (equal layers: blocks in the
 kernel arguments; different ones: a table), compressor gradients in one to four pieces, a launch per layer, and more layers
 than one list of clears holds.  Every stage against the oracle, batches ragged."""
@@ -25,3 +25,15 @@ def test_step_every_stage(n, p, k, B, L, act, rank, mode, widths, ks):
     print(f"case many tiles n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode} widths={widths}", flush=True)
     prob = pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=rank, widths=widths, ks=ks)
     check_stages(prob, seed=6, lr=0.02, mode=mode)
+
+
+@pytest.mark.parametrize("n,p,k,B,L,act,mode", [
+    (2048, 64, 16, 72, 2, "relu", "train"),        # weight gradients and error compression in one-team workgroups; shard 32
+    (8192, 64, 12, 100, 2, "gelu", "no_update"),   # 4-element vectors
+    (4096, 16, 16, 2100, 2, "relu", "train"),      # the input gradient; 34 tile rows, the last ragged
+    (4096, 1, 0, 200, 2, "gelu", "train"),         # dense
+])
+def test_one_team_workgroups(n, p, k, B, L, act, mode):
+    print(f"case one team n={n} p={p} k={k} B={B} L={L} {act} {mode}", flush=True)
+    prob = pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=-1 if p > 1 else 0)
+    check_stages(prob, seed=7, lr=0.02, mode=mode)
