@@ -27,7 +27,8 @@ FAMILIES = [
     # (substrings of the kernel's name, demangled or not, family, prefixes of the bench names it can carry)
     (("gemm_mfma_fwd_kernel",), "fwd", ("layer update + thin compression",)),
     (("gemm_mfma_tail_kernel",), "tail", ("weight + compressor gradients |",)),
-    (("gemm_mfma_table_kernel",), "table", ("weight + compressor gradients of all layers",)),
+    (("gemm_mfma_table_kernel", "gemm_mfma_uniform_kernel"), "table", ("weight + compressor gradients of all layers",)),
+    (("gemm_mfma_many_kernel",), "many", ("compression",)),
     (("table_upload_kernel",), "upload", ("parameter table",)),
     (("gemm_mfma_kernel<0, 0", "gemm_mfma_kernelILi0ELi0E"), "kc_kc", ("layer update", "compression")),
     (("gemm_mfma_kernel<0, 1", "gemm_mfma_kernelILi0ELi1E"), "kc_km", ("input gradient", "error compression")),
@@ -66,6 +67,7 @@ def short(kernel_name):
             args = m.group(2).replace("DF16b", "@,").replace("Lb0E", "0,").replace("Lb1E", "1,")
             args = re.sub(r"Li(\d+)E", r"\1,", args).replace("f", "float,").replace("@", "bf16").rstrip(",")
             name = f"{m.group(1)}<{args}>"
+    name = name.replace("bool _Accum, bool, E", "bf16, 1")     # ... and one that it reads wrongly: bfloat16, true
     return name[:70]
 
 
@@ -95,7 +97,7 @@ def carries_pair(kernel_name):
     if not m:
         return None
     args = [a.strip() for a in m.group(1).split(",")]
-    return len(args) >= 7 and args[6] in ("1", "true")
+    return len(args) >= 6 and args[5] in ("1", "true")
 
 
 def match_rows(groups, rows):
