@@ -31,6 +31,9 @@
  * pointer, 16-byte aligned, unless stated otherwise ("host").  Inputs are not
  * modified.
  *
+ * Overlap: an output must not share memory with an input or with another output of the same call, except
+ * where an argument's description says that it may (then the call reads the input as it was before).
+ *
  * Errors: every entry point returns a ph_status; phantom_last_error() gives
  * the message of the calling thread's last failure.  PH_ERR_INVALID_ARG,
  * PH_ERR_UNSUPPORTED and PH_ERR_WORKSPACE are decided from the arguments alone,
@@ -189,7 +192,8 @@ typedef struct {
     float *const *dCw;
     float *const *dDw;
     float *const *dbias;
-    void *Y_out;               /* optional: network output [B, s], storage type */
+    void *Y_out;               /* optional: network output [B, s], storage type; may overlap X0, T, G and dg_own (with
+                                *   PH_STEP_FORWARD also the weights): it is then written when nothing reads them any more */
     float *loss;               /* device scalar: 1/(2B) sum (y_L - t)^2 over batch, features and ranks held */
     float lr;                  /* SGD: w <- w - lr * dLoss/dw, all gradients taken before the update */
     int32_t mode;              /* ph_step_mode */

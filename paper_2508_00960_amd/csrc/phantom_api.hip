@@ -151,6 +151,12 @@ ph_status optional(const void *p, const char *name)
     return PH_OK;
 }
 
+// Do the `na` bytes at a and the `nb` bytes at b share any?
+bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 ph_status check_launch(const char *what)
 {
     hipError_t e = hipGetLastError();
@@ -1098,13 +1104,13 @@ struct BwdArgs {
                                //   layers' in one launch at the end of the backward pass)
 };
 
-// copy of a tensor for a tap of the step (count elements of the storage type)
+// copy of a tensor (count elements of the storage type), for a tap of the step or an output that lies over an input
 template <typename T>
 ph_status tap_copy(void *dst, const void *src, int64_t count, hipStream_t st)
 {
     if (!dst || !src || count <= 0) return PH_OK;
     hipLaunchKernelGGL((copy_kernel<T>), dim3(blocks_for(count)), dim3(256), 0, st, (const T *)src, (T *)dst, count);
-    return check_launch("tap copy");
+    return check_launch("copy");
 }
 
 // error compression: dG_send[i] = delta . D_i   ([B, so] x [so, k] for every peer, one product over N = q*k);
@@ -1835,14 +1841,40 @@ ph_status check_step_args(const ph_problem *prob, const ph_step_args *args, std:
     return PH_OK;
 }
 
+// Does Y_out share memory with anything that the step reads: its input, the target, the peers' buffers, the weights?
+bool output_overlaps_input(const std::vector<Geo> &geos, const ph_step_args &a)
+{
+    const Geo &last = geos.back();
+    const size_t out_bytes = (size_t)last.groups * last.B * last.so * last.esz;
+    auto hits = [&](const void *p, size_t elems) { return overlap(a.Y_out, out_bytes, p, elems * last.esz); };
+    const bool train = a.mode != PH_STEP_FORWARD;
+    bool any = hits(a.X0, (size_t)geos[0].groups * geos[0].B * geos[0].si) || (train && hits(a.T, out_bytes / last.esz));
+    for (size_t l = 0; l < geos.size(); ++l) {
+        const Geo &g = geos[l];
+        const size_t held = (size_t)g.groups;
+        any = any || hits(a.Lw[l], held * g.so * g.si) || hits(a.bias[l], held * g.so);
+        if (g.q == 0) continue;
+        any = any || hits(a.Cw[l], held * g.k * g.si) || hits(a.Dw[l], held * g.q * g.so * g.k);
+        if (!g.all) any = any || hits(a.G[l], (size_t)g.q * g.B * g.k) || (train && hits(a.dg_own[l], (size_t)g.B * g.k));
+    }
+    return any;
+}
+
 ph_status run_step(const std::vector<Geo> &geos, const ph_step_args *args, void *workspace, void *hip_stream)
 {
     Arena a{(char *)workspace, 0};
     StepWs w = carve_step(a, geos);
     hipStream_t st = (hipStream_t)hip_stream;
-    if (args->Y_out) w.Y.back() = args->Y_out;         // the last layer writes the network output where the caller wants it
-    if (geos[0].dtype == PH_F32) return flex_step<float>(geos, *args, w, st);
-    return use_flex(geos, args->mode != PH_STEP_FORWARD) ? flex_step<bf16_t>(geos, *args, w, st) : step_impl(geos, *args, w, st);
+    // The last layer writes the network output where the caller wants it, unless other workgroups or later launches still
+    // read what lies there: then it writes the workspace, and the output is copied when the step is over.
+    const bool copy = args->Y_out && output_overlaps_input(geos, *args);
+    if (args->Y_out && !copy) w.Y.back() = args->Y_out;
+    if (geos[0].dtype == PH_F32) PH_TRY(flex_step<float>(geos, *args, w, st));
+    else PH_TRY(use_flex(geos, args->mode != PH_STEP_FORWARD) ? flex_step<bf16_t>(geos, *args, w, st) : step_impl(geos, *args, w, st));
+    if (!copy) return PH_OK;
+    const Geo &last = geos.back();
+    const int64_t count = (int64_t)last.groups * last.B * last.so;
+    return last.dtype == PH_F32 ? tap_copy<float>(args->Y_out, w.Y.back(), count, st) : tap_copy<bf16_t>(args->Y_out, w.Y.back(), count, st);
 }
 
 // ---- the step for callers that cannot allocate -------------------------------------------------
