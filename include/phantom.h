@@ -124,7 +124,7 @@ ph_status phantom_layer_fwd(const ph_problem *prob,
  *   dX      = L^T delta + C^T dg_own                   braces of Eq. (backprop)
  *   dbias, dLw, dCw, dDw                               Eq. (bpb), (bpL), (bpC), (bpD); dDw in D's own [s, k] shape
  *
- *   dY      in   [B, s]   dLoss/dy_l^(j)
+ *   dY      in   [B, s]   dLoss/dy_l^(j).  Outputs may overlap dY and A_or_Y (dX == dY, for instance).
  *   X       in   [B, s]   the layer's input
  *   A_or_Y  in   [B, s]   GELU: the saved pre-activation.  ReLU: pre-activation or output (only the
  *                         sign is used; ReLU'(0) = 0).  Identity: ignored, may be NULL.

@@ -1191,12 +1191,28 @@ ph_status launch_reduce_scatter(const Geo &g, const void *dG_send, void *dg_own,
     return check_launch("reduce-scatter");
 }
 
-// delta = dY * sigma'(S); with the identity, dY itself and no launch
+// Does an output of a layer's backward call lie over dY?
+bool gradient_overlaps_dY(const Geo &g, const BwdArgs &b)
+{
+    const size_t held = (size_t)g.groups;
+    auto hits = [&](const void *p, size_t bytes) { return overlap(b.dY, held * g.B * g.so * g.esz, p, bytes); };
+    bool any = hits(b.dX, held * g.B * g.si * g.esz) || hits(b.dLw, held * g.so * g.si * 4) || hits(b.dbias, held * g.so * 4);
+    if (g.q > 0)
+        any = any || hits(b.dCw, held * g.k * g.si * 4) || hits(b.dDw, held * g.q * g.so * g.k * 4) ||
+              hits(b.dG_send, held * g.q * g.B * g.k * g.esz) || (g.all && hits(b.dg_own, held * g.B * g.k * g.esz));
+    return any;
+}
+
+// delta = dY * sigma'(S); with the identity, dY itself and no launch, or a copy of it if an output lies over it
 template <typename T>
 ph_status local_error(const Geo &g, const BwdArgs &b, void *buffer, const void **delta, hipStream_t st)
 {
-    if (g.act == PH_ACT_IDENTITY) { *delta = b.dY; return PH_OK; }
     const int64_t count = (int64_t)g.groups * g.B * g.so;
+    if (g.act == PH_ACT_IDENTITY) {
+        const bool copy = gradient_overlaps_dY(g, b);
+        *delta = copy ? buffer : b.dY;
+        return copy ? tap_copy<T>(buffer, b.dY, count, st) : PH_OK;
+    }
     ProfScope prof("local error", 0, count, 0, 1, st);
     hipLaunchKernelGGL((delta_kernel<T>), dim3(blocks_for(count, 256 * 16 / (int)sizeof(T))), dim3(256), 0, st,
                        (const T *)b.dY, (const T *)b.S, (T *)buffer, count, g.act);

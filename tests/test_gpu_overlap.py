@@ -64,3 +64,47 @@ def test_step_output_over_an_input(over, mode, n, p, k, B, L, act, dtype, rank):
     for name, t in want.items():
         assert bool(torch.isfinite(t.float()).all()), name
         assert torch.equal(t, got[name]), name
+
+
+def run_layer_bwd(prob, over):
+    """A layer's backward call; over: "dX" lies over dY, "A" dX lies over the pre-activation, None: nothing overlaps."""
+    dt, q, p = prob.dtype, prob.peers, prob.p
+    one = prob.rank >= 0
+    lead = () if one else (p,)
+    P = (pin.one_rank_step_inputs(prob, 4) if one else pin.all_rank_step_inputs(prob, 4))["layers"][0]
+    B, s, k = prob.batch, prob.s_in(0), prob.k_of(0)
+    pc = ph.make_problem(prob.n, p, prob.k, B, 1, prob.act, dt, prob.rank)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+
+    def normal(*shape):
+        return torch.randn(shape, device="cuda", generator=gen).to(torch.float32 if dt == "f32" else torch.bfloat16)
+
+    dY, X, A = normal(*lead, B, s), normal(*lead, B, s), normal(*lead, B, s)
+    dg_own = normal(*lead, B, k) if q else None
+    G = (normal(q, B, k) if one else normal(p, B, k)) if q else None
+    dX = {"dX": dY, "A": A, None: empty(lead + (B, s), dt)}[over]
+    grads = {nm: empty_f32(P[nm].shape) for nm in P if nm in ("Lw", "Cw", "Dw", "bias")}
+    W = {nm: to_gpu(P[nm], dt) for nm in grads}
+    dG_send = empty(lead + (q, B, k), dt) if q else None
+    ph.layer_bwd(pc, dY, X, A, W["Lw"], W.get("Cw"), W.get("Dw"), G, dg_own, dX, grads["Lw"], grads.get("Cw"), grads.get("Dw"),
+                 grads["bias"], dG_send, workspace(ph.workspace_bytes(pc)))
+    torch.cuda.synchronize()
+    return {"dX": dX, "dG_send": dG_send, "dg_own": dg_own, **{"d" + nm: t for nm, t in grads.items() if nm != "bias"}}
+
+
+@pytest.mark.parametrize("over,n,p,k,B,act,dtype,rank", [
+    ("dX", 128, 2, 8, 96, "identity", "f32", 0),
+    ("dX", 390, 3, 7, 130, "identity", "bf16", 2),
+    ("dX", 4096, 2, 64, 2100, "identity", "bf16", 0),          # 128 x 128 tiles
+    ("dX", 4096, 4, 16, 1100, "identity", "bf16", -1),
+    ("dX", 128, 1, 0, 96, "identity", "f32", 0),
+    ("dX", 390, 3, 7, 130, "gelu", "bf16", 2),
+    ("A", 4096, 4, 16, 1100, "relu", "bf16", -1),
+    ("A", 128, 2, 8, 96, "gelu", "f32", 0),
+])
+def test_layer_gradient_over_an_input(over, n, p, k, B, act, dtype, rank):
+    print(f"case overlap layer {over} n={n} p={p} k={k} B={B} {act} {dtype} rank={rank}", flush=True)
+    prob = pin.Problem(n=n, p=p, k=k, batch=B, layers=1, act=act, dtype=dtype, rank=rank)
+    want, got = run_layer_bwd(prob, None), run_layer_bwd(prob, over)
+    for name, t in want.items():
+        assert t is None or torch.equal(t, got[name]), name
