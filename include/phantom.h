@@ -105,7 +105,7 @@ ph_status phantom_workspace_bytes(const ph_problem *prob, size_t *bytes);
  *   G     in   one-rank: [p-1, B, k], the gathered g^(i) of the peers in increasing i.
  *              all-ranks: ignored (may be NULL); the gathered buffer is g_own.
  *   Y     out  [B, s]        y_l^(j)
- *   g_own out  [B, k]        g_l^(j) = C y_{l-1}^(j): the rank's All-Gather contribution.
+ *   g_own out  [B, k]        g_l^(j) = C y_{l-1}^(j): the rank's All-Gather contribution.  May overlap G.
  *              all-ranks: [p, B, k]; written first, then read as every rank's gathered buffer
  *              (rank j skips slot j).  Ignored when p == 1.
  *   A_save out [B, s] or NULL  pre-activation b + z, needed by phantom_layer_bwd for GELU

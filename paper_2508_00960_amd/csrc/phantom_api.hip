@@ -949,6 +949,7 @@ Epilogue epi_store()
 struct FwdArgs {
     const void *X, *Lw, *Cw, *Dw, *bias, *G;
     void *Y, *g_own, *A_save;
+    bool apart;   // one rank, layer call: g_own lies over G, so the compression waits for the update, which reads G
     bool a_f32;   // step only: A_save is float
     bool a_deriv; // step only: A_save receives sigma'(A), in float, instead of A
     bool a_bits;  // step only, ReLU: A_save receives one bit per element (stored output > 0)
@@ -1020,6 +1021,10 @@ ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tile
         return launch_flex<T>(&pr.update, 1, true, g.groups, LossTail{}, st, "layer update", mse_tiles);
     }
     const Product both[2] = {pr.update, pr.compress};
+    if (f.apart) {
+        PH_TRY((launch_flex<T>(&pr.update, 1, true, g.groups, LossTail{}, st, "layer update")));
+        return launch_flex<T>(&pr.compress, 1, true, g.groups, LossTail{}, st, "compression");
+    }
     return launch_flex<T>(both, 2, true, g.groups, LossTail{}, st, g.q > 0 ? "layer update + compression" : "layer update", mse_tiles);
 }
 
@@ -1055,6 +1060,10 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
         if (thin) PH_TRY(launch_thin());
         else PH_TRY((launch_products<T, T>(plan, &compress, 1, g.groups, st, "compression")));
         return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update");
+    }
+    if (f.apart) {
+        PH_TRY((launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update")));
+        return thin ? launch_thin() : launch_products<T, T>(plan, &compress, 1, g.groups, st, "compression");
     }
     // one rank: the peers' g are inputs, so the rank's own compression runs beside the update when the two
     // fit the device together
@@ -1607,7 +1616,7 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
         const bool bits = train && w.relu_bits[(size_t)l] != nullptr;
         FwdArgs f{l > 0 ? w.Y[(size_t)l - 1] : a.X0, a.Lw[l], q ? a.Cw[l] : nullptr, q ? a.Dw[l] : nullptr, a.bias[l],
                   (q && !g.all) ? a.G[l] : nullptr, w.Y[l], w.G[l], bits ? w.relu_bits[(size_t)l] : train ? w.A[l] : nullptr,
-                  !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr, &clear, g.all || L == 1 ? nullptr : &later};
+                  false, !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr, &clear, g.all || L == 1 ? nullptr : &later};
         PH_TRY(fwd_impl(geos[(size_t)l], f, st));
     }
     if (!later.empty()) {
@@ -1772,6 +1781,7 @@ ph_status phantom_layer_fwd(const ph_problem *prob, const void *X, const void *L
     FwdArgs f{};
     f.X = X; f.Lw = Lw; f.Cw = Cw; f.Dw = Dw; f.bias = bias; f.G = G; f.Y = Y; f.g_own = g_own; f.A_save = A_save;
     PH_TRY(check_fwd_args(g, f));
+    f.apart = !g.all && g.q > 0 && overlap(g_own, (size_t)(g.B * g.k) * g.esz, G, (size_t)(g.q * g.B * g.k) * g.esz);
     hipStream_t st = (hipStream_t)hip_stream;
     if (g.dtype == PH_F32) return flex_fwd<float>(g, f, st);
     return use_flex({g}, false, true) ? flex_fwd<bf16_t>(g, f, st) : fwd_impl(g, f, st);

@@ -108,3 +108,27 @@ def test_layer_gradient_over_an_input(over, n, p, k, B, act, dtype, rank):
     want, got = run_layer_bwd(prob, None), run_layer_bwd(prob, over)
     for name, t in want.items():
         assert t is None or torch.equal(t, got[name]), name
+
+
+@pytest.mark.parametrize("n,p,k,B,act,dtype", [
+    (128, 2, 8, 96, "relu", "f32"),
+    (390, 3, 7, 136, "gelu", "bf16"),
+    (4096, 2, 32, 4200, "relu", "bf16"),           # 128 x 128 tiles, thin compression
+    (4096, 2, 96, 4200, "relu", "bf16"),           # ... and a product of its own
+])
+def test_own_phantom_layer_over_the_peers(n, p, k, B, act, dtype):
+    print(f"case overlap g_own n={n} p={p} k={k} B={B} {act} {dtype}", flush=True)
+    prob = pin.Problem(n=n, p=p, k=k, batch=B, layers=1, act=act, dtype=dtype, rank=0)
+    d = {nm: to_gpu(v, dtype) for nm, v in pin.one_rank_layer_inputs(prob, 0, 6).items()}
+    pc = ph.make_problem(n, p, k, B, 1, act, dtype, 0)
+    out = []
+    for over in (False, True):
+        G = d["G"].clone()
+        Y, g_own = empty((B, n // p), dtype), G[p - 2] if over else empty((B, k), dtype)
+        ph.layer_fwd(pc, d["X"], d["Lw"], d["Cw"], d["Dw"], d["bias"], G, Y, g_own, None, workspace(ph.workspace_bytes(pc)))
+        torch.cuda.synchronize()
+        out.append((Y, g_own))
+    assert torch.equal(out[0][0], out[1][0])
+    # the two schedules may split the compression's sum differently: fp32 sums that differ by their own rounding errors (some
+    # 1e-7 of values around 1), which moves a bf16 result by one unit of its last place at most (2^-7 of the value)
+    assert torch.allclose(out[0][1].float(), out[1][1].float(), rtol=1e-5 if dtype == "f32" else 2 ** -7, atol=1e-6)
