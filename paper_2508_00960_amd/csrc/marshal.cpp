@@ -97,10 +97,28 @@ struct Released {             // the problem's buffer, given back on every way o
     ~Released() { if (held) PyBuffer_Release(&view); }
 };
 
+struct WithoutGil {           // taken back on every way out
+    PyThreadState *state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
 PyObject *none() { Py_RETURN_NONE; }
 
+// Tensor and stream queries throw (a sparse tensor has no address, a host without a GPU no stream) and CPython is C: an
+// exception must not leave here.  None sends the call down binding.py's path, where torch raises its own error.
+template <PyObject *(*Body)(PyObject *const *, Py_ssize_t)>
+PyObject *guarded(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    try {
+        return Body(a, n);
+    } catch (...) {
+        PyErr_Clear();
+        return none();
+    }
+}
+
 // (prob, X, Lw, Cw, Dw, bias, G, Y, g_own, A_save, workspace, stream)
-PyObject *layer_fwd(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *layer_fwd(PyObject *const *a, Py_ssize_t n)
 {
     Released r;
     const ph_problem *pr;
@@ -113,14 +131,15 @@ PyObject *layer_fwd(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!address(a[1 + i], elems[i], c.esz, &p[i])) return none();
     if (!workspace_of(a[10], &ws, &bytes) || !stream_of(a[11], &stream)) return none();
     int st;
-    Py_BEGIN_ALLOW_THREADS
-    st = g_fwd(pr, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], ws, bytes, stream);
-    Py_END_ALLOW_THREADS
+    {
+        WithoutGil released;
+        st = g_fwd(pr, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], ws, bytes, stream);
+    }
     return PyLong_FromLong(st);
 }
 
 // (prob, dY, X, A_or_Y, Lw, Cw, Dw, G, dg_own, dX, dLw, dCw, dDw, dbias, dG_send, workspace, stream)
-PyObject *layer_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *layer_bwd(PyObject *const *a, Py_ssize_t n)
 {
     Released r;
     const ph_problem *pr;
@@ -133,16 +152,17 @@ PyObject *layer_bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!address(a[1 + i], elems[i], i >= 9 && i <= 12 ? 4 : c.esz, &p[i])) return none();
     if (!workspace_of(a[15], &ws, &bytes) || !stream_of(a[16], &stream)) return none();
     int st;
-    Py_BEGIN_ALLOW_THREADS
-    st = g_bwd(pr, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], (float *)p[9], (float *)p[10], (float *)p[11], (float *)p[12],
-               p[13], ws, bytes, stream);
-    Py_END_ALLOW_THREADS
+    {
+        WithoutGil released;
+        st = g_bwd(pr, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], (float *)p[9], (float *)p[10], (float *)p[11], (float *)p[12],
+                   p[13], ws, bytes, stream);
+    }
     return PyLong_FromLong(st);
 }
 
 // (prob, X0, T, Y_out, loss, lr, mode, static, workspace, stream, and the 14 per-layer sequences
 //  Lw Cw Dw bias, their masters, G dg_own, dLw dCw dDw dbias)
-PyObject *ffn_step(PyObject *, PyObject *const *a, Py_ssize_t n)
+PyObject *ffn_step(PyObject *const *a, Py_ssize_t n)
 {
     Released r;
     const ph_problem *pr;
@@ -187,9 +207,10 @@ PyObject *ffn_step(PyObject *, PyObject *const *a, Py_ssize_t n)
     args.dLw = (float *const *)arrays[10]; args.dCw = (float *const *)arrays[11];
     args.dDw = (float *const *)arrays[12]; args.dbias = (float *const *)arrays[13];
     int st;
-    Py_BEGIN_ALLOW_THREADS
-    st = own ? g_static(pr, &args, stream) : g_step(pr, &args, ws, bytes, stream);
-    Py_END_ALLOW_THREADS
+    {
+        WithoutGil released;
+        st = own ? g_static(pr, &args, stream) : g_step(pr, &args, ws, bytes, stream);
+    }
     return PyLong_FromLong(st);
 }
 
@@ -204,9 +225,9 @@ PyObject *bind(PyObject *, PyObject *args)
 
 PyMethodDef methods[] = {
     {"bind", bind, METH_VARARGS, nullptr},
-    {"layer_fwd", (PyCFunction)(void (*)(void))layer_fwd, METH_FASTCALL, nullptr},
-    {"layer_bwd", (PyCFunction)(void (*)(void))layer_bwd, METH_FASTCALL, nullptr},
-    {"ffn_step", (PyCFunction)(void (*)(void))ffn_step, METH_FASTCALL, nullptr},
+    {"layer_fwd", (PyCFunction)(void (*)(void))guarded<layer_fwd>, METH_FASTCALL, nullptr},
+    {"layer_bwd", (PyCFunction)(void (*)(void))guarded<layer_bwd>, METH_FASTCALL, nullptr},
+    {"ffn_step", (PyCFunction)(void (*)(void))guarded<ffn_step>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
