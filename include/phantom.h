@@ -57,7 +57,8 @@ typedef enum {
     PH_ERR_INVALID_ARG = -1,   /* bad shape, enum, null or misaligned pointer */
     PH_ERR_UNSUPPORTED = -2,   /* valid request this build cannot run */
     PH_ERR_WORKSPACE = -3,     /* workspace missing or too small */
-    PH_ERR_LAUNCH = -4         /* the HIP runtime refused a launch in mid-call, or an internal inconsistency */
+    PH_ERR_LAUNCH = -4         /* the HIP runtime refused a launch in mid-call, no host memory for the call's own lists, or an
+                                  internal inconsistency */
 } ph_status;
 
 typedef enum { PH_ACT_IDENTITY = 0, PH_ACT_RELU = 1, PH_ACT_GELU = 2 /* x*Phi(x), erf form */ } ph_act;

@@ -11,7 +11,7 @@
 #include <cstring>
 #include <algorithm>
 #include <mutex>
-#include <string>
+#include <new>
 #include <type_traits>
 #include <vector>
 
@@ -26,17 +26,29 @@ using namespace phantom;
 
 namespace {
 
-thread_local std::string g_err;
+thread_local char g_err[512];
 
 ph_status fail(ph_status st, const char *fmt, ...)
 {
-    char buf[512];
     va_list ap;
     va_start(ap, fmt);
-    vsnprintf(buf, sizeof buf, fmt, ap);
+    vsnprintf(g_err, sizeof g_err, fmt, ap);
     va_end(ap);
-    g_err = buf;
     return st;
+}
+
+// The body of a C entry point: the lists that a call keeps of its layers may not fit the host's memory, and an exception must
+// not leave a C function.
+template <typename F>
+ph_status without_exceptions(F &&body)
+{
+    try {
+        return body();
+    } catch (const std::bad_alloc &) {
+        return fail(PH_ERR_LAUNCH, "out of host memory");
+    } catch (const std::exception &e) {
+        return fail(PH_ERR_LAUNCH, "internal error: %s", e.what());
+    }
 }
 
 #define PH_TRY(expr) do { ph_status st__ = (expr); if (st__ != PH_OK) return st__; } while (0)
@@ -1706,20 +1718,22 @@ int32_t phantom_abi_version(void) { return 4; }
 
 ph_status phantom_profile_begin(int32_t max_launches)
 {
-    if (max_launches < 1) return fail(PH_ERR_INVALID_ARG, "max_launches = %d must be >= 1", max_launches);
-    if (g_prof.on) return fail(PH_ERR_INVALID_ARG, "profiling is already on");
-    max_launches += PROF_CALIBRATION_LAUNCHES;
-    while (g_prof.ev.size() < (size_t)max_launches * 2) {
-        hipEvent_t e;
-        hipError_t err = hipEventCreate(&e);
-        if (err != hipSuccess) return fail(PH_ERR_LAUNCH, "hipEventCreate: %s", hipGetErrorString(err));
-        g_prof.ev.push_back(e);
-    }
-    g_prof.recs.clear();
-    g_prof.cap = (size_t)max_launches;
-    g_prof.calibrated = false;
-    g_prof.on = true;
-    return PH_OK;
+    return without_exceptions([&]() -> ph_status {
+        if (max_launches < 1) return fail(PH_ERR_INVALID_ARG, "max_launches = %d must be >= 1", max_launches);
+        if (g_prof.on) return fail(PH_ERR_INVALID_ARG, "profiling is already on");
+        max_launches += PROF_CALIBRATION_LAUNCHES;
+        while (g_prof.ev.size() < (size_t)max_launches * 2) {
+            hipEvent_t e;
+            hipError_t err = hipEventCreate(&e);
+            if (err != hipSuccess) return fail(PH_ERR_LAUNCH, "hipEventCreate: %s", hipGetErrorString(err));
+            g_prof.ev.push_back(e);
+        }
+        g_prof.recs.clear();
+        g_prof.cap = (size_t)max_launches;
+        g_prof.calibrated = false;
+        g_prof.on = true;
+        return PH_OK;
+    });
 }
 
 ph_status phantom_profile_end(ph_profile_entry *entries, int32_t capacity, int32_t *count)
@@ -1758,33 +1772,37 @@ ph_status phantom_profile_end(ph_profile_entry *entries, int32_t capacity, int32
     return PH_OK;
 }
 
-const char *phantom_last_error(void) { return g_err.c_str(); }
+const char *phantom_last_error(void) { return g_err; }
 
 ph_status phantom_workspace_bytes(const ph_problem *prob, size_t *bytes)
 {
-    std::vector<Geo> geos;
-    PH_TRY(make_geos(prob, geos));
-    if (!bytes) return fail(PH_ERR_INVALID_ARG, "bytes is NULL");
-    Arena a{nullptr, 0};
-    carve_step(a, geos);       // the step's layout contains the backward's; the forward needs none
-    *bytes = a.used + 256;
-    return PH_OK;
+    return without_exceptions([&]() -> ph_status {
+        std::vector<Geo> geos;
+        PH_TRY(make_geos(prob, geos));
+        if (!bytes) return fail(PH_ERR_INVALID_ARG, "bytes is NULL");
+        Arena a{nullptr, 0};
+        carve_step(a, geos);       // the step's layout contains the backward's; the forward needs none
+        *bytes = a.used + 256;
+        return PH_OK;
+    });
 }
 
 ph_status phantom_layer_fwd(const ph_problem *prob, const void *X, const void *Lw, const void *Cw, const void *Dw,
                             const void *bias, const void *G, void *Y, void *g_own, void *A_save,
                             void *workspace, size_t workspace_bytes, void *hip_stream)
 {
-    (void)workspace; (void)workspace_bytes;
-    Geo g;
-    PH_TRY(make_geo(prob, g));
-    FwdArgs f{};
-    f.X = X; f.Lw = Lw; f.Cw = Cw; f.Dw = Dw; f.bias = bias; f.G = G; f.Y = Y; f.g_own = g_own; f.A_save = A_save;
-    PH_TRY(check_fwd_args(g, f));
-    f.apart = !g.all && g.q > 0 && overlap(g_own, (size_t)(g.B * g.k) * g.esz, G, (size_t)(g.q * g.B * g.k) * g.esz);
-    hipStream_t st = (hipStream_t)hip_stream;
-    if (g.dtype == PH_F32) return flex_fwd<float>(g, f, st);
-    return use_flex({g}, false, true) ? flex_fwd<bf16_t>(g, f, st) : fwd_impl(g, f, st);
+    return without_exceptions([&]() -> ph_status {
+        (void)workspace; (void)workspace_bytes;
+        Geo g;
+        PH_TRY(make_geo(prob, g));
+        FwdArgs f{};
+        f.X = X; f.Lw = Lw; f.Cw = Cw; f.Dw = Dw; f.bias = bias; f.G = G; f.Y = Y; f.g_own = g_own; f.A_save = A_save;
+        PH_TRY(check_fwd_args(g, f));
+        f.apart = !g.all && g.q > 0 && overlap(g_own, (size_t)(g.B * g.k) * g.esz, G, (size_t)(g.q * g.B * g.k) * g.esz);
+        hipStream_t st = (hipStream_t)hip_stream;
+        if (g.dtype == PH_F32) return flex_fwd<float>(g, f, st);
+        return use_flex({g}, false, true) ? flex_fwd<bf16_t>(g, f, st) : fwd_impl(g, f, st);
+    });
 }
 
 ph_status phantom_layer_bwd(const ph_problem *prob, const void *dY, const void *X, const void *A_or_Y,
@@ -1792,20 +1810,22 @@ ph_status phantom_layer_bwd(const ph_problem *prob, const void *dY, const void *
                             void *dX, float *dLw, float *dCw, float *dDw, float *dbias, void *dG_send,
                             void *workspace, size_t workspace_bytes, void *hip_stream)
 {
-    Geo g;
-    PH_TRY(make_geo(prob, g));
-    BwdArgs b{};
-    b.dY = dY; b.X = X; b.S = A_or_Y; b.Lw = Lw; b.Cw = Cw; b.Dw = Dw; b.G = G; b.dg_own = dg_own; b.dX = dX;
-    b.dLw = dLw; b.dCw = dCw; b.dDw = dDw; b.dbias = dbias; b.dG_send = dG_send;
-    PH_TRY(check_bwd_args(g, b));
-    Arena sizing{nullptr, 0};
-    carve_bwd(sizing, g);
-    PH_TRY(check_ws(workspace, workspace_bytes, sizing.used));
-    Arena a{(char *)workspace, 0};
-    BwdWs w = carve_bwd(a, g);
-    hipStream_t st = (hipStream_t)hip_stream;
-    if (g.dtype == PH_F32) return flex_layer_bwd<float>(g, b, w, st);
-    return use_flex({g}, true, true) ? flex_layer_bwd<bf16_t>(g, b, w, st) : bwd_impl(g, b, w, st);
+    return without_exceptions([&]() -> ph_status {
+        Geo g;
+        PH_TRY(make_geo(prob, g));
+        BwdArgs b{};
+        b.dY = dY; b.X = X; b.S = A_or_Y; b.Lw = Lw; b.Cw = Cw; b.Dw = Dw; b.G = G; b.dg_own = dg_own; b.dX = dX;
+        b.dLw = dLw; b.dCw = dCw; b.dDw = dDw; b.dbias = dbias; b.dG_send = dG_send;
+        PH_TRY(check_bwd_args(g, b));
+        Arena sizing{nullptr, 0};
+        carve_bwd(sizing, g);
+        PH_TRY(check_ws(workspace, workspace_bytes, sizing.used));
+        Arena a{(char *)workspace, 0};
+        BwdWs w = carve_bwd(a, g);
+        hipStream_t st = (hipStream_t)hip_stream;
+        if (g.dtype == PH_F32) return flex_layer_bwd<float>(g, b, w, st);
+        return use_flex({g}, true, true) ? flex_layer_bwd<bf16_t>(g, b, w, st) : bwd_impl(g, b, w, st);
+    });
 }
 
 }  // extern "C"
@@ -1938,26 +1958,30 @@ extern "C" {
 ph_status phantom_ffn_step(const ph_problem *prob, const ph_step_args *args, void *workspace, size_t workspace_bytes,
                            void *hip_stream)
 {
-    std::vector<Geo> geos;
-    size_t ws_need = 0;
-    PH_TRY(check_step_args(prob, args, geos, ws_need));
-    PH_TRY(check_ws(workspace, workspace_bytes, ws_need));
-    return run_step(geos, args, workspace, hip_stream);
+    return without_exceptions([&]() -> ph_status {
+        std::vector<Geo> geos;
+        size_t ws_need = 0;
+        PH_TRY(check_step_args(prob, args, geos, ws_need));
+        PH_TRY(check_ws(workspace, workspace_bytes, ws_need));
+        return run_step(geos, args, workspace, hip_stream);
+    });
 }
 
 size_t phantom_static_workspace_bytes(void) { return STATIC_WS_BYTES; }
 
 ph_status phantom_ffn_step_static(const ph_problem *prob, const ph_step_args *args, void *hip_stream)
 {
-    std::vector<Geo> geos;
-    size_t ws_need = 0;
-    PH_TRY(check_step_args(prob, args, geos, ws_need));
-    if (ws_need > STATIC_WS_BYTES)
-        return fail(PH_ERR_WORKSPACE, "the step needs %zu bytes of workspace, the library's own scratch array holds %zu: "
-                                      "use phantom_ffn_step with a workspace of the caller's", ws_need, STATIC_WS_BYTES);
-    void *ws = nullptr;
-    PH_TRY(scratch_of_current_device(&ws));
-    return run_step(geos, args, ws, hip_stream);
+    return without_exceptions([&]() -> ph_status {
+        std::vector<Geo> geos;
+        size_t ws_need = 0;
+        PH_TRY(check_step_args(prob, args, geos, ws_need));
+        if (ws_need > STATIC_WS_BYTES)
+            return fail(PH_ERR_WORKSPACE, "the step needs %zu bytes of workspace, the library's own scratch array holds %zu: "
+                                          "use phantom_ffn_step with a workspace of the caller's", ws_need, STATIC_WS_BYTES);
+        void *ws = nullptr;
+        PH_TRY(scratch_of_current_device(&ws));
+        return run_step(geos, args, ws, hip_stream);
+    });
 }
 
 }  // extern "C"

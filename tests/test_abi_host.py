@@ -156,3 +156,23 @@ def test_binding_refuses_host_tensors():
     ok = 0x1000
     with pytest.raises(ValueError, match="X: tensor is on cpu"):
         ph.layer_fwd(prob, torch.zeros(32, 64), ok, ok, ok, ok, ok, ok, ok, None)
+
+
+def test_no_host_memory_is_an_error_not_an_abort():
+    """A count of layers whose lists do not fit the process's memory: an error, and no exception through the C entry point."""
+    import subprocess
+    import sys
+    code = """
+import resource
+import paper_2508_00960_amd as ph
+prob = ph.make_problem(256, 4, 8, 32, layers=50_000_000)
+ph.abi_version()
+pages = int(open("/proc/self/statm").read().split()[0])
+resource.setrlimit(resource.RLIMIT_AS, (pages * resource.getpagesize() + (1 << 28),) * 2)
+try:
+    ph.workspace_bytes(prob)
+except ph.PhantomError as e:
+    print(e.status, e)
+"""
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300, env={**os.environ, "PYTHONPATH": ROOT})
+    assert out.returncode == 0 and out.stdout.startswith("-4") and "host memory" in out.stdout, (out.returncode, out.stdout, out.stderr[-500:])
