@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -73,11 +74,32 @@ class PhProfileEntry(ctypes.Structure):
 
 
 _lib = None
-_fast = None                      # the native module, once load() has run
+_fast = None                      # the native module or its stand-in, once load() has run
 
 
 def library_path() -> str:
     return _LIB_PATH
+
+
+class _PythonOnly:
+    """In the place of the native marshalling: every call is left to the Python path."""
+    layer_fwd = layer_bwd = ffn_step = staticmethod(lambda *args: None)
+
+
+def _marshalling(lib):
+    """The native module, built if it is missing or stale.  It saves host time and nothing else, and it is tied to one
+    Python and one torch: where it cannot be built or loaded, the Python path does the work."""
+    try:
+        from .build import build_marshal, marshal_is_current
+        if not marshal_is_current():
+            build_marshal(verbose=False)
+        from . import _marshal
+    except (ImportError, OSError, RuntimeError) as e:
+        warnings.warn(f"calls are marshalled in Python, which takes longer: {e}")
+        return _PythonOnly
+    _marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.phantom_layer_fwd, lib.phantom_layer_bwd, lib.phantom_ffn_step,
+                                                                    lib.phantom_ffn_step_static)))
+    return _marshal
 
 
 def load():
@@ -89,10 +111,6 @@ def load():
     if not os.path.exists(_LIB_PATH):
         from .build import build_library
         build_library(verbose=False)
-    if not os.path.exists(os.path.join(_HERE, "_marshal.so")):
-        from .build import build_marshal
-        build_marshal(verbose=False)
-    from . import _marshal
     lib = ctypes.CDLL(_LIB_PATH)
     vp, sz = ctypes.c_void_p, ctypes.c_size_t
     prob = ctypes.POINTER(PhProblem)
@@ -113,9 +131,7 @@ def load():
     lib.phantom_profile_begin.argtypes = [ctypes.c_int32]
     lib.phantom_profile_end.restype = ctypes.c_int
     lib.phantom_profile_end.argtypes = [ctypes.POINTER(PhProfileEntry), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
-    _marshal.bind(*(ctypes.cast(f, vp).value for f in (lib.phantom_layer_fwd, lib.phantom_layer_bwd, lib.phantom_ffn_step,
-                                                       lib.phantom_ffn_step_static)))
-    _lib, _fast = lib, _marshal
+    _lib, _fast = lib, _marshalling(lib)
     return lib
 
 

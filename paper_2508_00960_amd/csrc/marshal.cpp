@@ -4,7 +4,8 @@
 // look-ups per tensor, a dictionary per layer, ctypes arrays) took 25-80 us of host time per call.  Every
 // function here handles the ordinary call only: GPU tensors that are contiguous, of the right element size and long
 // enough, passed as the entry point wants them.  Anything else (a raw address, a short tensor, a tuple as workspace,
-// taps) makes it return None, and binding.py then takes its own path, which raises what there is to raise.
+// taps) makes it return None, and binding.py then takes its own path, which raises what there is to raise.  That path also
+// does the work alone where this module is missing.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
@@ -230,7 +231,8 @@ PyMethodDef methods[] = {
     {"ffn_step", (PyCFunction)(void (*)(void))guarded<ffn_step>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+// (build.py looks for the stamp in the file: it names the sources, the Python and the torch that this module was built for)
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", PHANTOM_MARSHAL_STAMP, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 

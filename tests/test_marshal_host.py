@@ -36,3 +36,37 @@ def run(code):
 def test_exceptions_reach_python(call, raises):
     out = run(call)
     assert out.returncode == 1 and raises in out.stderr, (out.returncode, out.stderr[-2000:])
+
+
+def copy_of_package(tmp_path):
+    import shutil
+    shutil.copytree(os.path.join(ROOT, "paper_2508_00960_amd"), tmp_path / "paper_2508_00960_amd")
+    shutil.copytree(os.path.join(ROOT, "include"), tmp_path / "include")
+    return tmp_path / "paper_2508_00960_amd" / "_marshal.so"
+
+
+def run_copy(tmp_path, code, path):
+    env = {**os.environ, "HIP_VISIBLE_DEVICES": "", "PYTHONPATH": str(tmp_path), "PATH": path}
+    return subprocess.run([sys.executable, "-c", HEAD + code], capture_output=True, text=True, env=env, cwd=tmp_path, timeout=300)
+
+
+NULL_X = "ph.layer_fwd(prob, None, None, None, None, None, None, None, None, None)"
+
+
+def test_package_works_without_the_native_module(tmp_path):
+    """No module and no compiler to build it with."""
+    copy_of_package(tmp_path).unlink()
+    out = run_copy(tmp_path, "assert ph.workspace_bytes(prob) > 0\n" + NULL_X, path=str(tmp_path))
+    assert out.returncode == 1 and "X is NULL" in out.stderr and "marshalled in Python" in out.stderr, out.stderr[-2000:]
+
+
+@pytest.mark.parametrize("compiler", [True, False])
+def test_stale_native_module_is_not_used(tmp_path, compiler):
+    """Built from another header, for instance: rebuilt where that can be done, else left alone."""
+    so = copy_of_package(tmp_path)
+    with open(tmp_path / "include" / "phantom.h", "a") as f:
+        f.write("/* changed */\n")
+    code = "ph.load()\nfrom paper_2508_00960_amd import binding, build\nprint(binding._fast.__name__, build.marshal_is_current())\n" + NULL_X
+    out = run_copy(tmp_path, code, path=os.environ["PATH"] if compiler else str(tmp_path))
+    want = "paper_2508_00960_amd._marshal True" if compiler else "_PythonOnly False"
+    assert out.returncode == 1 and "X is NULL" in out.stderr and out.stdout.strip() == want, (out.stdout, out.stderr[-2000:])
