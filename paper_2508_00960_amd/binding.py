@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 import warnings
 from typing import Optional, Sequence
 
@@ -75,6 +76,7 @@ class PhProfileEntry(ctypes.Structure):
 
 _lib = None
 _fast = None                      # the native module or its stand-in, once load() has run
+_load_lock = threading.Lock()
 
 
 def library_path() -> str:
@@ -104,8 +106,15 @@ def _marshalling(lib):
 
 def load():
     """Load libphantom.so.  It is never replaced by a fallback: a missing library is an error."""
-    global _lib, _fast
     if _lib is not None:
+        return _lib
+    with _load_lock:
+        return _load()
+
+
+def _load():
+    global _lib, _fast
+    if _lib is not None:              # another thread was first
         return _lib
     import torch  # noqa: F401  (brings the HIP runtime the library links against into the process first)
     if not os.path.exists(_LIB_PATH):
@@ -131,7 +140,9 @@ def load():
     lib.phantom_profile_begin.argtypes = [ctypes.c_int32]
     lib.phantom_profile_end.restype = ctypes.c_int
     lib.phantom_profile_end.argtypes = [ctypes.POINTER(PhProfileEntry), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
-    _lib, _fast = lib, _marshalling(lib)
+    # (a call that finds _lib set takes _fast for granted)
+    _fast = _marshalling(lib)
+    _lib = lib
     return lib
 
 

@@ -70,3 +70,45 @@ def test_stale_native_module_is_not_used(tmp_path, compiler):
     out = run_copy(tmp_path, code, path=os.environ["PATH"] if compiler else str(tmp_path))
     want = "paper_2508_00960_amd._marshal True" if compiler else "_PythonOnly False"
     assert out.returncode == 1 and "X is NULL" in out.stderr and out.stdout.strip() == want, (out.stdout, out.stderr[-2000:])
+
+
+def test_load_is_never_half_done():
+    """At no bytecode of load() may another thread see the library and not the marshalling that calls go through."""
+    out = run("""
+import sys
+from paper_2508_00960_amd import binding
+seen = 0
+def trace(frame, event, arg):
+    global seen
+    if frame.f_code.co_filename != binding.__file__:
+        return None
+    frame.f_trace_opcodes = True
+    seen += event == "opcode"
+    assert binding._lib is None or binding._fast is not None
+    return trace
+sys.settrace(trace)
+binding.load()
+sys.settrace(None)
+assert seen > 100 and binding._lib is not None
+print("whole")
+""")
+    assert out.returncode == 0 and out.stdout.strip() == "whole", out.stderr[-2000:]
+
+
+def test_threads_load_together():
+    out = run("""
+import threading
+gate, errors = threading.Barrier(8), []
+def call():
+    gate.wait()
+    try:
+        """ + NULL_X + """
+    except ph.PhantomError:
+        return
+    errors.append("no error")
+threads = [threading.Thread(target=call) for _ in range(8)]
+for t in threads: t.start()
+for t in threads: t.join()
+print(errors)
+""")
+    assert out.returncode == 0 and out.stdout.strip() == "[]" and "Traceback" not in out.stderr, out.stderr[-2000:]
