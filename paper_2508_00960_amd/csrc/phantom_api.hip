@@ -241,8 +241,6 @@ struct Arena {
     }
 };
 
-constexpr int PIECE_WORDS = 512;      // output tiles of the products of one launch whose reduction may be cut into pieces (MfmaParams::arrived)
-
 struct BwdWs {
     void *delta;        // [groups, B, so] storage type
 };
@@ -262,8 +260,9 @@ struct StepWs {
                                                     //   its gradients while the layer below writes its own
     float *dbias, *mse_partial;                     // dbias: one block, layer l's [groups, so_l] at dbias_at[l]
     std::vector<int64_t> dbias_at;                  // float offsets into dbias; dbias_at[layers] = the block's length
-    unsigned *arrived;                              // PIECE_WORDS words right behind the dbias block: cleared with it at the
-                                                    //   start of a step, left zero by every launch that uses them
+    unsigned *arrived;                              // one word per cut tile (cut_tiles) right behind the dbias block: cleared with
+                                                    //   it at the start of a step, left zero by every launch that uses them
+    int64_t arrived_words;
     float *parts;                                   // deferred weight gradients (one rank): the pieces' results of the cut
     ProductTable *table;                            //   compressor gradients, the launch's parameter table, and every
     std::vector<void *> delta_of;                   //   layer's delta [B, so_l]
@@ -304,6 +303,15 @@ int compressor_gradient_pieces(const Geo &g)
     return (int)std::max<int64_t>(1, std::min<int64_t>(ksteps / 16, 4));
 }
 
+// Output tiles of that launch whose reduction is cut (MfmaParams::arrived has a word for each).
+int64_t cut_tiles(const std::vector<Geo> &geos)
+{
+    int64_t tiles = 0;
+    for (const Geo &g : geos)
+        if (g.q > 0 && compressor_gradient_pieces(g) > 1) tiles += tiles_of(g.k, g.si);
+    return tiles;
+}
+
 // geos: every layer's shapes.  Buffers that are reused from layer to layer take the largest layer's size.
 StepWs carve_step(Arena &a, const std::vector<Geo> &geos)
 {
@@ -338,7 +346,8 @@ StepWs carve_step(Arena &a, const std::vector<Geo> &geos)
         w.dCw[set] = (float *)a.take(groups * cw_max * 4 + 16);
         w.dDw[set] = (float *)a.take(groups * dw_max * 4 + 16);
     }
-    w.dbias = (float *)a.take((size_t)(dbias_total + PIECE_WORDS) * 4);
+    w.arrived_words = deferred_weight_gradients(geos) ? cut_tiles(geos) : 0;
+    w.dbias = (float *)a.take((size_t)(dbias_total + w.arrived_words) * 4);
     w.arrived = w.dbias ? (unsigned *)(w.dbias + dbias_total) : nullptr;
     if (deferred_weight_gradients(geos)) {
         size_t slots = 0;
@@ -623,7 +632,6 @@ ph_status upload_product_table(const std::vector<Product> &prods, const std::vec
         blocks.push_back(P);
     }
     first.push_back(next);
-    if (word > (size_t)PIECE_WORDS) return fail(PH_ERR_LAUNCH, "%s: internal error, more cut tiles than words to count them", what);
     const int count = (int)blocks.size();
     for (int at = 0; at < count; at += CHUNK_PRODUCTS) {
         TableChunk c{};
@@ -673,7 +681,6 @@ ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::ve
         u.dc_wg = (u.dc.total_wg + 7) & ~7;
         const int64_t t = tiles_of(dc[0].M, dc[0].N);
         if (u.dc.ksplit > 1) {
-            if (t * L > PIECE_WORDS) return fail(PH_ERR_LAUNCH, "%s: internal error, more cut tiles than words to count them", what);
             u.dc.parts = parts; u.dc.arrived = arrived;
             u.parts_layer = t * pieces * MT * MT; u.arrived_layer = t;
         }
@@ -1567,9 +1574,9 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
                 if (clear.count == CLEAR_MAX - 1) PH_TRY(launch_clear(clear, st));
                 add(a.dbias[l], (int64_t)g.groups * geos[(size_t)l].so);
             }
-            add(w.arrived, PIECE_WORDS);
+            if (w.arrived_words > 0) add(w.arrived, w.arrived_words);
         } else {
-            add(w.dbias, w.dbias_at[(size_t)L] + PIECE_WORDS);
+            add(w.dbias, w.dbias_at[(size_t)L] + w.arrived_words);
         }
     }
 

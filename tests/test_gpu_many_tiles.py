@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (16384, 8, 16, 1100, 2, "relu", 0, "train", None, None),           # 272 weight-gradient tiles per layer: a launch per layer
     (4096, 8, 16, 3150, 17, "relu", 0, "no_update", None, None),       # more layers than the table holds
     (8192, 8, 32, 2100, 2, "relu", 0, "train", (8192, 4096, 12288), (32, 16)),       # layers that differ
+    (2816, 2, 1408, 1990, 5, "relu", 0, "train", None, None),          # k = n/p: 605 tiles of compressor gradients in pieces
+    (2816, 2, 1408, 1990, 5, "relu", 1, "no_update", (2816, 2816, 2816, 2816, 2816, 2560), (1408,) * 4 + (1400,)),   # ... by a table
 ])
 def test_step_every_stage(n, p, k, B, L, act, rank, mode, widths, ks):
     print(f"case many tiles n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode} widths={widths}", flush=True)
