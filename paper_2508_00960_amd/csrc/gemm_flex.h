@@ -20,6 +20,13 @@
 // single (unpacked) vector FMAs reach, and a lane's operand is one float, so LDS has an eighth of the bf16 kernel's
 // traffic per cycle and the matrix pipe alone bounds the loop.  Sums in three levels (16 terms, 16 of those, the
 // rest), terms in order: one running fp32 sum over a batch of some thousand rows drifts past 1e-5 of a weight gradient.
+//
+// FINE, bf16: sums in three levels there too (64 terms, 4 of those, the rest).  For problems with an odd width or phantom
+// width, or a tensor beyond 2^31 elements; the others' sums are one running sum per team, as on the 128 x 128 kernels.
+// Error of the weight gradients against 64 bits, one running sum : levels (2-norm, shard 201, k 13): batch 1030
+// 1.3e-7 : 7.2e-8, 4096 4.0e-7 : 9.7e-8, 65536 1.7e-6 : 2.9e-7.  Time (us): 5 layers of 1153, k 9, trained at batch 4096
+// 663 : 673, 3 layers of 751, k 11, at batch 1000 101 : 107.  The second accumulator takes the registers of one wavefront
+// per SIMD; within those of four it spills (one rank's layer call of 64, shard 512, k 16: 44 -> 71 us).
 #pragma once
 #include "common.h"
 #include "elementwise.h"
@@ -356,10 +363,21 @@ __device__ __forceinline__ f32x4 flex_operand(const float *tile, int rbase, int 
     return v;
 }
 
-// bf16: adds a reduction step to acc.
-template <int KA, int KB, int PA, int PB, int MI, int NI>
+template <int MI, int NI> __device__ __forceinline__ void flex_add(f32x16 (&to)[MI][NI], const f32x16 (&part)[MI][NI])
+{
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) to[i][j][e] += part[i][j][e];
+}
+
+// bf16: a reduction step added to acc, or (FIRST) on its own.
+template <int KA, int KB, int PA, int PB, bool FIRST, int MI, int NI>
 __device__ __forceinline__ void flex_multiply(f32x16 (&acc)[MI][NI], const bf16_t *ta, const bf16_t *tb, int wm, int wn, int lane)
 {
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         bf16x8 av[MI], bv[NI];
@@ -370,7 +388,7 @@ __device__ __forceinline__ void flex_multiply(f32x16 (&acc)[MI][NI], const bf16_
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bv[j], av[i], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bv[j], av[i], FIRST && kk == 0 ? zero : acc[i][j], 0, 0, 0);
     }
 }
 // fp32: adds every 16 terms of a reduction step (of KT) to mid.
@@ -396,12 +414,7 @@ __device__ __forceinline__ void flex_multiply(f32x16 (&mid)[MI][NI], const float
                     for (int j = 0; j < NI; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[j][t], av[i][t], kk == 2 * part && t == 0 ? zero : acc[i][j], 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) mid[i][j][e] += acc[i][j][e];
+        flex_add(mid, acc);
     }
 }
 
@@ -437,15 +450,15 @@ template <typename E, int V, bool NT = true> __device__ __forceinline__ void fle
     }
 }
 
-template <typename T, int TM, int TN, int TEAMS>
+template <typename T, int TM, int TN, int TEAMS, bool FINE>
 struct FlexShape {
     static constexpr int WM = TM >= 64 ? 2 : 1, WN = TN >= 64 ? 2 : 1;     // wavefronts of a team along each side
     static constexpr int MI = TM / 32 / WM, NI = TN / 32 / WN;             // 32 x 32 blocks per wavefront
     static constexpr int TT = 64 * WM * WN, THREADS = TT * TEAMS;
     static constexpr int STAGES = TT == 64 ? 1 : 2;
-    // fp32: a step's MFMAs take longer than a load, so one step ahead is enough
-    static constexpr int SETS = 2;
-    static constexpr int MIN_WAVES = TT == 64 || MI * NI > 1   ? 2 : sizeof(T) == 4 ? 3 : 4;      // wavefronts per SIMD that the registers have to allow
+    static constexpr int SETS = 2;                     // reduction steps that the loads run ahead
+    static constexpr bool LEVELS = sizeof(T) == 4 || FINE;                 // sums in three levels
+    static constexpr int MIN_WAVES = TT == 64 || MI * NI > 1 ? 2 : LEVELS ? 3 : 4;      // wavefronts per SIMD that the registers have to allow
 
     static constexpr int CPITCH = TN + 4;
     static constexpr int C_BYTES = TM * CPITCH * 4;
@@ -454,7 +467,7 @@ constexpr int flex_max(int a, int b) { return a > b ? a : b; }
 template <typename T, int TM, int TN, int TEAMS, int KA, int KB>
 constexpr int flex_lds_bytes()
 {
-    typedef FlexShape<T, TM, TN, TEAMS> F;
+    typedef FlexShape<T, TM, TN, TEAMS, false> F;
     return flex_max(TEAMS * F::STAGES * (FlexStage<T, KA, TM, F::TT>::ELEMS + FlexStage<T, KB, TN, F::TT>::ELEMS) * (int)sizeof(T),
                     TEAMS * F::C_BYTES + F::THREADS * 4 + 64);
 }
@@ -487,10 +500,10 @@ __device__ __forceinline__ void flex_wave_sync()
 }
 
 // One workgroup's work on the product P: workgroup number wg of P.total_wg.
-template <typename T, int TM, int TN, int TEAMS, int KA, int KB, typename TOut, int EPI>
+template <typename T, int TM, int TN, int TEAMS, bool FINE, int KA, int KB, typename TOut, int EPI>
 __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int wg, unsigned char *lds)
 {
-    typedef FlexShape<T, TM, TN, TEAMS> F;
+    typedef FlexShape<T, TM, TN, TEAMS, FINE> F;
     typedef FlexLoader<T, KA, TM, F::TT> LA;
     typedef FlexLoader<T, KB, TN, F::TT> LB;
     constexpr int KT = flex_step<T>(F::TT), V = FlexType<T>::V, MI = F::MI, NI = F::NI;
@@ -518,7 +531,7 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
     la.init(P.a, ka, ma, m0, g, tid);
     lb.init(P.b, ka, P.n, n0, g, tid);
 
-    f32x16 acc[MI][NI], mid[MI][NI];                   // fp32 storage: the second and third level of partial sums are mid and acc
+    f32x16 acc[MI][NI], mid[MI][NI];                   // the sums; with levels: the third level's, and the second's
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -527,12 +540,12 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
             for (int e = 0; e < 16; ++e) { acc[i][j][e] = 0.f; mid[i][j][e] = 0.f; }
     const bool rows = ROWSUM && P.rowsum && n0 == 0;   // uniform
     float row_acc = 0.f, row_mid = 0.f;
-    int in_mid = 0;
+    int in_mid = 0;                                    // sixteenths of a second-level sum (256 terms) in mid
 
     T *stage0 = (T *)lds + team * F::STAGES * (LA::S::ELEMS + LB::S::ELEMS);
     const int steps = (ka.total + KT - 1) / KT, loops = (steps + TEAMS - 1) / TEAMS;
     auto c_of = [=](int i) { return (i * TEAMS + team) * KT; };
-    constexpr int SETS = F::SETS;                      // steps that the loads run ahead
+    constexpr int SETS = F::SETS;
     u32x4 ra[SETS][LA::S::NV], rb[SETS][LB::S::NV];
 #pragma unroll
     for (int d = 0; d < SETS; ++d) { la.fetch(ka, ra[d], c_of(d)); lb.fetch(ka, rb[d], c_of(d)); }
@@ -550,8 +563,15 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
         }
         if constexpr (F::TT > 64) __syncthreads();
         else flex_wave_sync();
-        if constexpr (sizeof(T) == 2) flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH>(acc, ta, tb, wm, wn, lane);
-        else flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH, KT>(mid, ta, tb, wm, wn, lane);
+        if constexpr (sizeof(T) == 4) {
+            flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH, KT>(mid, ta, tb, wm, wn, lane);
+        } else if constexpr (F::LEVELS) {
+            f32x16 part[MI][NI];
+            flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH, true>(part, ta, tb, wm, wn, lane);
+            flex_add(mid, part);
+        } else {
+            flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH, false>(acc, ta, tb, wm, wn, lane);
+        }
         if constexpr (ROWSUM) {
             if (rows) {
                 constexpr int PARTS = F::TT / TM;
@@ -562,18 +582,20 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
                 row_mid += t;
             }
         }
-        if constexpr (sizeof(T) == 4) {
-            in_mid += KT / 16;
+        if constexpr (F::LEVELS) {
+            in_mid += sizeof(T) == 4 ? KT / 16 : 4;
             if (in_mid == 16) {                        // uniform
+                flex_add(acc, mid);
 #pragma unroll
                 for (int a = 0; a < MI; ++a)
 #pragma unroll
                     for (int b = 0; b < NI; ++b)
 #pragma unroll
-                        for (int e = 0; e < 16; ++e) { acc[a][b][e] += mid[a][b][e]; mid[a][b][e] = 0.f; }
+                        for (int e = 0; e < 16; ++e) mid[a][b][e] = 0.f;
                 in_mid = 0;
-                row_acc += row_mid; row_mid = 0.f;
+                if (sizeof(T) == 4) { row_acc += row_mid; row_mid = 0.f; }
             }
+            if (sizeof(T) == 2 && (i & 63) == 63) { row_acc += row_mid; row_mid = 0.f; }      // (a step's 16 terms, 64 of those, the rest)
         }
         if constexpr (F::TT == 64) flex_wave_sync();
     };
@@ -585,14 +607,7 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
     }
     if (i < loops) step(0, i, true);
     row_acc += row_mid;
-    if constexpr (sizeof(T) == 4) {
-#pragma unroll
-        for (int a = 0; a < MI; ++a)
-#pragma unroll
-            for (int b = 0; b < NI; ++b)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[a][b][e] += mid[a][b][e];
-    }
+    if constexpr (F::LEVELS) flex_add(acc, mid);
     __syncthreads();
 
     // the finished tile goes through LDS, so that every global access of the epilogue is a run of whole rows
@@ -750,8 +765,8 @@ __device__ __forceinline__ int flex_xcd_order(int i, int count)     // see xcd_o
 
 // FORWARD: products in the forward layout (bias + activation, or plain store).  Otherwise: products in the input-gradient
 // layout (sigma' or plain store, kind 0) and in the weight-gradient layout (kind 1, float out), in any mix.
-template <typename T, int TM, int TN, int TEAMS, bool FORWARD>
-__global__ __launch_bounds__((FlexShape<T, TM, TN, TEAMS>::THREADS), (FlexShape<T, TM, TN, TEAMS>::MIN_WAVES)) void gemm_flex_kernel(FlexBatch batch)
+template <typename T, int TM, int TN, int TEAMS, bool FORWARD, bool FINE>
+__global__ __launch_bounds__((FlexShape<T, TM, TN, TEAMS, FINE>::THREADS), (FlexShape<T, TM, TN, TEAMS, FINE>::MIN_WAVES)) void gemm_flex_kernel(FlexBatch batch)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     if (batch.tail.partial && blockIdx.x == 0) {       // uniform
@@ -764,9 +779,9 @@ __global__ __launch_bounds__((FlexShape<T, TM, TN, TEAMS>::THREADS), (FlexShape<
     const FlexIn P = flex_args_at<FlexIn>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, in));
     if (local >= P.total_wg) return;
     const int wg = flex_xcd_order(local, P.total_wg);
-    if constexpr (FORWARD) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KC, T, EPI_BIAS_ACT>(P, j, wg, smem_raw);
-    else if (P.kind == 0) flex_workgroup<T, TM, TN, TEAMS, FLEX_KC, FLEX_KM, T, EPI_DACT>(P, j, wg, smem_raw);
-    else flex_workgroup<T, TM, TN, TEAMS, FLEX_KM, FLEX_KM, float, EPI_STORE>(P, j, wg, smem_raw);
+    if constexpr (FORWARD) flex_workgroup<T, TM, TN, TEAMS, FINE, FLEX_KC, FLEX_KC, T, EPI_BIAS_ACT>(P, j, wg, smem_raw);
+    else if (P.kind == 0) flex_workgroup<T, TM, TN, TEAMS, FINE, FLEX_KC, FLEX_KM, T, EPI_DACT>(P, j, wg, smem_raw);
+    else flex_workgroup<T, TM, TN, TEAMS, FINE, FLEX_KM, FLEX_KM, float, EPI_STORE>(P, j, wg, smem_raw);
 }
 
 }  // namespace phantom

@@ -75,6 +75,7 @@ struct Geo {
     int act, dtype, rank, layers;
     size_t esz;       // bytes per element of the storage type
     int vec;          // bf16: widest vector (8 or 4 elements) dividing si, so and k; 0: the kernels of gemm_flex.h only
+    bool fine;        // bf16: ... in their FINE form
 };
 
 // Checks the problem and fills in the shapes of layer `layer` (0-based).
@@ -111,6 +112,7 @@ ph_status make_geo(const ph_problem *pr, Geo &g, int layer = 0)
     g.act = pr->act; g.dtype = pr->dtype; g.rank = pr->rank; g.layers = pr->layers;
     g.esz = pr->dtype == PH_BF16 ? 2 : 4;
     g.vec = 0;
+    g.fine = pr->dtype == PH_BF16 && ((si | so | g.k) & 1);
     if (pr->dtype == PH_BF16) {
         for (int v = 8; v >= 4 && !g.vec; v >>= 1)
             if (si % v == 0 && so % v == 0 && (g.q == 0 || g.k % v == 0)) g.vec = v;
@@ -121,7 +123,10 @@ ph_status make_geo(const ph_problem *pr, Geo &g, int layer = 0)
     {
         const int64_t wide = std::max(si, so), slots = g.all ? g.p : g.q;
         const int64_t largest = std::max({g.B * wide, slots * g.B * g.k, so * si, slots * so * g.k, g.k * si});
-        if (largest > 0x7fffffff) g.vec = 0;
+        if (largest > 0x7fffffff) {
+            g.vec = 0;
+            g.fine = pr->dtype == PH_BF16;
+        }
         // they also divide a position among the peers' segments by k with a multiply (Axis::magic), exact while
         // position * k < 2^32
         if (g.q * g.k * g.k >= (int64_t)1 << 32) g.vec = 0;
@@ -883,10 +888,10 @@ FlexTile flex_tile_for(const Product *prods, int count, int groups)
     return tiles > 256 ? FLEX_64 : tiles > 24 ? FLEX_64_2 : FLEX_32_8;
 }
 
-template <typename T, int TM, int TN, int TEAMS, bool FORWARD>
+template <typename T, int TM, int TN, int TEAMS, bool FORWARD, bool FINE>
 ph_status launch_flex_kernel(const FlexBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
 {
-    auto kern = gemm_flex_kernel<T, TM, TN, TEAMS, FORWARD>;
+    auto kern = gemm_flex_kernel<T, TM, TN, TEAMS, FORWARD, FINE>;
     constexpr int LDS = FORWARD ? flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KC, FLEX_KC>()
                                 : flex_max(flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KC, FLEX_KM>(), flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KM, FLEX_KM>());
     static thread_local bool configured = false;
@@ -895,8 +900,17 @@ ph_status launch_flex_kernel(const FlexBatch &batch, unsigned total_wg, hipStrea
         if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
         configured = true;
     }
-    hipLaunchKernelGGL(kern, dim3(total_wg), dim3(FlexShape<T, TM, TN, TEAMS>::THREADS), LDS, st, batch);
+    hipLaunchKernelGGL(kern, dim3(total_wg), dim3(FlexShape<T, TM, TN, TEAMS, FINE>::THREADS), LDS, st, batch);
     return check_launch(what);
+}
+
+template <typename T, bool FORWARD, bool FINE>
+ph_status launch_flex_tile(const FlexBatch &batch, FlexTile tile, unsigned total_wg, hipStream_t st, const char *what)
+{
+    if (tile == FLEX_64) return launch_flex_kernel<T, 64, 64, 1, FORWARD, FINE>(batch, total_wg, st, what);
+    if constexpr (sizeof(T) == 2)
+        if (tile == FLEX_64_2) return launch_flex_kernel<T, 64, 64, 2, FORWARD, FINE>(batch, total_wg, st, what);
+    return launch_flex_kernel<T, 32, 32, 8, FORWARD, FINE>(batch, total_wg, st, what);
 }
 
 // Up to FLEX_MAX_PRODUCTS independent products in one launch.  forward: all in the forward layout; else any mix of the
@@ -904,13 +918,14 @@ ph_status launch_flex_kernel(const FlexBatch &batch, unsigned total_wg, hipStrea
 // launch's first workgroup.
 // mse_tiles: receives the number of tiles of the first product (one partial sum of the loss each).
 template <typename T>
-ph_status launch_flex(const Product *prods_in, int count_in, bool forward, int groups, const LossTail &tail, hipStream_t st,
+ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const Geo &g, const LossTail &tail, hipStream_t st,
                       const char *what, int *mse_tiles = nullptr)
 {
     Product prods[FLEX_MAX_PRODUCTS];
     int count = 0;
     for (int i = 0; i < count_in; ++i)
         if (prods_in[i].M > 0 && prods_in[i].N > 0) prods[count++] = prods_in[i];
+    const int groups = g.groups;
     if (count == 0 || groups <= 0) return PH_OK;
     const FlexTile tile = flex_tile_for<T>(prods, count, groups);
     const int t = tile == FLEX_32_8 ? 32 : 64;
@@ -945,16 +960,13 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, int g
     ProfScope prof(what, prods[0].M, prods[0].N, prods[0].K, groups, st, dim(1, &Product::M), dim(1, &Product::N), dim(1, &Product::K),
                    dim(2, &Product::M), dim(2, &Product::N), dim(2, &Product::K), dim(3, &Product::M), dim(3, &Product::N), dim(3, &Product::K));
     const unsigned total = (unsigned)next;
-    if (forward) {
-        if (tile == FLEX_64) return launch_flex_kernel<T, 64, 64, 1, true>(batch, total, st, what);
-        if constexpr (sizeof(T) == 2)
-            if (tile == FLEX_64_2) return launch_flex_kernel<T, 64, 64, 2, true>(batch, total, st, what);
-        return launch_flex_kernel<T, 32, 32, 8, true>(batch, total, st, what);
-    }
-    if (tile == FLEX_64) return launch_flex_kernel<T, 64, 64, 1, false>(batch, total, st, what);
+    // Sums of up to 128 terms per team need no levels (300 rows, two teams: 7.1e-8 with one running sum, 7.5e-8 in levels)
+    const int teams = tile == FLEX_64 ? 1 : tile == FLEX_64_2 ? 2 : 8;
+    bool fine = false;
+    for (int i = 0; i < count; ++i) fine = fine || (g.fine && prods[i].K > 128 * teams);
     if constexpr (sizeof(T) == 2)
-        if (tile == FLEX_64_2) return launch_flex_kernel<T, 64, 64, 2, false>(batch, total, st, what);
-    return launch_flex_kernel<T, 32, 32, 8, false>(batch, total, st, what);
+        if (fine) return forward ? launch_flex_tile<T, true, true>(batch, tile, total, st, what) : launch_flex_tile<T, false, true>(batch, tile, total, st, what);
+    return forward ? launch_flex_tile<T, true, false>(batch, tile, total, st, what) : launch_flex_tile<T, false, false>(batch, tile, total, st, what);
 }
 
 Epilogue epi_store()
@@ -1036,15 +1048,15 @@ ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tile
     const FwdProducts pr = make_fwd_products(g, f);
     if (g.all) {
         // every rank reads the other ranks' g: the compression of all ranks has to finish first
-        PH_TRY((launch_flex<T>(&pr.compress, 1, true, g.groups, LossTail{}, st, "compression")));
-        return launch_flex<T>(&pr.update, 1, true, g.groups, LossTail{}, st, "layer update", mse_tiles);
+        PH_TRY((launch_flex<T>(&pr.compress, 1, true, g, LossTail{}, st, "compression")));
+        return launch_flex<T>(&pr.update, 1, true, g, LossTail{}, st, "layer update", mse_tiles);
     }
     const Product both[2] = {pr.update, pr.compress};
     if (f.apart) {
-        PH_TRY((launch_flex<T>(&pr.update, 1, true, g.groups, LossTail{}, st, "layer update")));
-        return launch_flex<T>(&pr.compress, 1, true, g.groups, LossTail{}, st, "compression");
+        PH_TRY((launch_flex<T>(&pr.update, 1, true, g, LossTail{}, st, "layer update")));
+        return launch_flex<T>(&pr.compress, 1, true, g, LossTail{}, st, "compression");
     }
-    return launch_flex<T>(both, 2, true, g.groups, LossTail{}, st, g.q > 0 ? "layer update + compression" : "layer update", mse_tiles);
+    return launch_flex<T>(both, 2, true, g, LossTail{}, st, g.q > 0 ? "layer update + compression" : "layer update", mse_tiles);
 }
 
 ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
@@ -1258,13 +1270,13 @@ ph_status flex_layer_bwd(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStre
     pr.dw.km = pr.dc.km = true;
     pr.dw.rowsum = b.dbias;
     if (g.all && g.q > 0) {
-        PH_TRY((launch_flex<T>(&pr.send, 1, false, g.groups, LossTail{}, st, "error compression")));
+        PH_TRY((launch_flex<T>(&pr.send, 1, false, g, LossTail{}, st, "error compression")));
         PH_TRY(launch_reduce_scatter<T>(g, b.dG_send, b.dg_own, LossTail{}, st));
         const Product rest[3] = {pr.dw, pr.dc, pr.dx};
-        return launch_flex<T>(rest, 3, false, g.groups, LossTail{}, st, "weight + compressor + input gradients");
+        return launch_flex<T>(rest, 3, false, g, LossTail{}, st, "weight + compressor + input gradients");
     }
     const Product every[4] = {pr.dw, pr.dc, pr.dx, pr.send};
-    return launch_flex<T>(every, 4, false, g.groups, LossTail{}, st, "gradients | error compression");
+    return launch_flex<T>(every, 4, false, g, LossTail{}, st, "gradients | error compression");
 }
 
 ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t st)
@@ -1461,7 +1473,8 @@ ph_status forward_taps(const std::vector<Geo> &geos, const ph_step_args &a, cons
 template <typename T>
 ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const StepWs &w, hipStream_t st)
 {
-    const Geo &g = geos.back();       // what does not depend on the layer is read from the last one
+    Geo g = geos.back();              // what does not depend on the layer is read from the last one
+    for (const Geo &x : geos) g.fine = g.fine || x.fine;       // (a backward launch carries products of two layers)
     const int L = g.layers;
     const int64_t B = g.B, q = g.q;
     const bool train = a.mode != PH_STEP_FORWARD, update = a.mode == PH_STEP_TRAIN;
@@ -1493,7 +1506,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
         bool any = false;
         for (const Product &pr : next) any = any || (pr.M > 0 && pr.N > 0);
         if (!any) { next.clear(); return PH_OK; }
-        PH_TRY((launch_flex<T>(next.data(), (int)next.size(), false, g.groups, tail, st, what)));
+        PH_TRY((launch_flex<T>(next.data(), (int)next.size(), false, g, tail, st, what)));
         tail.partial = nullptr;
         next.clear();
         return PH_OK;
