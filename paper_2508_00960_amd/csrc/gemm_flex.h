@@ -27,6 +27,8 @@
 // 1.3e-7 : 7.2e-8, 4096 4.0e-7 : 9.7e-8, 65536 1.7e-6 : 2.9e-7.  Time (us): 5 layers of 1153, k 9, trained at batch 4096
 // 663 : 673, 3 layers of 751, k 11, at batch 1000 101 : 107.  The second accumulator takes the registers of one wavefront
 // per SIMD; within those of four it spills (one rank's layer call of 64, shard 512, k 16: 44 -> 71 us).
+// Such problems also take GELU and its derivative by erff rather than by the five-term formula of gelu_both: sigma' in float
+// is then off by 3.0e-8 (rms over |a| < 3) instead of 6e-8 (4 layers of 1025, k 33, forward at batch 8192, with the levels: 329 -> 374 us).
 #pragma once
 #include "common.h"
 #include "elementwise.h"
@@ -676,7 +678,10 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
             if constexpr (sizeof(T) == 2) {
                 if (ep.act == ACT_GELU) {              // uniform
 #pragma unroll
-                    for (int u = 0; u < V; ++u) gelu_both(pre.x[u], x.x[u], deriv.x[u]);
+                    for (int u = 0; u < V; ++u) {
+                        if constexpr (FINE) { x.x[u] = act_apply(ACT_GELU, pre.x[u]); deriv.x[u] = act_deriv(ACT_GELU, pre.x[u]); }
+                        else gelu_both(pre.x[u], x.x[u], deriv.x[u]);
+                    }
                 } else {
                     piecewise_both(ep.act, x.x, deriv.x);
                 }

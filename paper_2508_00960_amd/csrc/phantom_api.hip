@@ -962,7 +962,7 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
     const unsigned total = (unsigned)next;
     // Sums of up to 128 terms per team need no levels (300 rows, two teams: 7.1e-8 with one running sum, 7.5e-8 in levels)
     const int teams = tile == FLEX_64 ? 1 : tile == FLEX_64_2 ? 2 : 8;
-    bool fine = false;
+    bool fine = g.fine && prods[0].ep.mode == EPI_BIAS_ACT && prods[0].ep.act == ACT_GELU;
     for (int i = 0; i < count; ++i) fine = fine || (g.fine && prods[i].K > 128 * teams);
     if constexpr (sizeof(T) == 2)
         if (fine) return forward ? launch_flex_tile<T, true, true>(batch, tile, total, st, what) : launch_flex_tile<T, false, true>(batch, tile, total, st, what);

@@ -72,3 +72,31 @@ def test_bias_gradient_of_a_very_long_batch():
 def test_step_every_stage(n, p, k, B, L, act, rank, widths, ks):
     print(f"case odd stages n={n} p={p} k={k} B={B} L={L} {act} rank={rank} widths={widths}", flush=True)
     check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=rank, widths=widths, ks=ks), seed=9, lr=0.02)
+
+
+@pytest.mark.parametrize("p", [1, 2])
+def test_gelu_derivative_of_an_odd_width(p):
+    """A training step keeps sigma' of its first layer in float, right behind y_0 at the start of the workspace (256-byte
+    steps).  With one neuron per rank and a weight of 1 it is sigma' of the network's input, free of any other rounding."""
+    print(f"case odd gelu p={p}", flush=True)
+    B = 1 << 16
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    a = ((torch.rand((B, 1), device="cuda", generator=gen) * 2 - 1) * 3).bfloat16()
+    zeros = lambda *shape: torch.zeros(shape, device="cuda", dtype=torch.bfloat16)
+    kk = 1 if p > 1 else 0
+    one = torch.ones((1, 1), device="cuda", dtype=torch.bfloat16)
+    prob = ph.make_problem(p, p, kk, B, 2, "gelu", "bf16", 0)
+    ws = workspace(ph.workspace_bytes(prob))
+    peers = lambda *shape: [zeros(*shape), zeros(*shape)] if p > 1 else None
+    loss = torch.zeros(4, device="cuda")
+    ph.ffn_step(prob, a, zeros(B, 1), [one, one], peers(kk, 1), peers(p - 1, 1, kk), [zeros(1), zeros(1)], G=peers(p - 1, B, kk),
+                dg_own=peers(B, kk), loss=loss, mode="no_update", workspace=ws)
+    torch.cuda.synchronize()
+    at = -(-B * 2 // 256) * 256
+    got = ws[at:at + 4 * B].view(torch.float32).double()
+    x = a.double().flatten()
+    want = 0.5 * torch.special.erfc(-x / 2 ** 0.5) + x * torch.exp(-x * x / 2) / (2 * torch.pi) ** 0.5
+    rms = float((got - want).pow(2).mean().sqrt())
+    print(f"sigma' rms {rms:.2e} max {float((got - want).abs().max()):.2e}", flush=True)
+    # erff and the sum of its two parts: an ulp or two of numbers below 1, rms 3e-8; the five-term formula adds 6e-8 of its own
+    assert rms <= 4.5e-8
