@@ -110,7 +110,8 @@ def check_stages(prob, seed=0, lr=1e-3, mode="train", rows=None):
         close("Y", f"Y[{l}]", torch.from_numpy(y_gpu), Y)
         A_l.append(A)
         X = y_gpu                                   # the next layer's operand: the GPU's own stored y_l
-    assert torch.equal(Y_out, taps["Y"][L - 1])
+    close("Y", "Y_out", torch.from_numpy(host(Y_out)), Y)       # what the caller gets ...
+    assert torch.equal(Y_out, taps["Y"][L - 1])                 # ... is what the backward pass reads
     if not train:
         return worst
 
