@@ -1,12 +1,14 @@
-"""Steps with more 128 x 128 tiles than compute units in one-team workgroups (all ranks), and one rank's steps with more 128 x 128 tiles than gemm_flex.h takes, at the smallest sizes that still reach each launch of
-the step: the compressions of all layers together, all layers' gradients in one launch (equal layers: blocks in the
-kernel arguments; different ones: a table), compressor gradients in one to four pieces, a launch per layer, and more layers
-than one list of clears holds.  Every stage against the oracle, batches ragged."""
+"""Steps with more 128 x 128 tiles than compute units in one-team workgroups (all ranks), and one rank's steps and layer calls
+with more 128 x 128 tiles than gemm_flex.h takes, at the smallest sizes that still reach each launch: the compressions of all
+layers together, all layers' gradients in one launch (equal layers: blocks in the kernel arguments; different ones: a
+table), compressor gradients in one to four pieces, a launch per layer, and more layers than one list of clears holds.
+Against the oracle, batches ragged."""
 import pytest
 
 import phantom_inputs as pin
 
 from stage_check import check_stages
+from test_gpu_parity import run_layer_one_rank
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +41,14 @@ def test_one_team_workgroups(n, p, k, B, L, act, mode):
     print(f"case one team n={n} p={p} k={k} B={B} L={L} {act} {mode}", flush=True)
     prob = pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=-1 if p > 1 else 0)
     check_stages(prob, seed=7, lr=0.02, mode=mode)
+
+
+@pytest.mark.parametrize("n,p,k,B,act,rank", [
+    (8192, 8, 32, 3210, "relu", 3),                # 26 x 8 tiles: the compression inside the update's loop
+    (8192, 8, 68, 3210, "gelu", 0),                # 4-element vectors, a compression of its own
+    (16384, 8, 16, 2100, "gelu", 7),               # two-tile workgroups: the compression behind the epilogue
+    (1536, 1, 0, 2200, "identity", 0),             # dense
+])
+def test_layer_calls_of_one_rank(n, p, k, B, act, rank):
+    print(f"case many tiles layer n={n} p={p} k={k} B={B} {act} rank={rank}", flush=True)
+    run_layer_one_rank(pin.Problem(n=n, p=p, k=k, batch=B, layers=1, act=act, dtype="bf16", rank=rank), seed=4)

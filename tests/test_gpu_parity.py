@@ -35,17 +35,17 @@ ONE_RANK_CASES = [
     (64, 1, 0, 19, "relu", "f32", 0),             # p = 1: a plain dense layer
     (512, 4, 16, 192, "relu", "bf16", 3),
     (1056, 8, 24, 200, "gelu", "bf16", 5),        # shard 132: ragged in every tile dimension
-    (520, 4, 3, 67, "relu", "bf16", 0),           # k not a multiple of any vector width
+    (520, 4, 3, 67, "relu", "bf16", 0),           # odd k
     (2048, 16, 64, 300, "gelu", "bf16", 7),
     (96, 1, 0, 50, "gelu", "bf16", 0),
     (512, 2, 256, 160, "relu", "bf16", 1),        # k = n/p
-    (1024, 4, 4, 300, "relu", "bf16", 1),         # k = 4: 8-byte vectors
-    (1032, 4, 6, 260, "gelu", "bf16", 2),         # shard 258, k = 6: 4-byte vectors
-    (2048, 8, 32, 1100, "relu", "bf16", 0),       # several tiles in every dimension, split reduction
+    (1024, 4, 4, 300, "relu", "bf16", 1),         # k = 4
+    (1032, 4, 6, 260, "gelu", "bf16", 2),         # shard 258, k = 6: no vector divides them
+    (2048, 8, 32, 1100, "relu", "bf16", 0),       # several tiles in every dimension
     (1536, 4, 16, 520, "identity", "bf16", 3),    # shard 384 = 3 tiles
     (2048, 8, 32, 4100, "gelu", "bf16", 0),       # few tiles, long batch (65 reduction steps in the weight gradients)
-    (1032, 4, 6, 3000, "relu", "bf16", 1),        # the same with 4-byte vectors and ragged tiles
-    (256, 1, 0, 4100, "relu", "bf16", 0),         # p = 1, 4 tiles, 65 reduction steps: weight gradients in split pieces (atomic adds)
+    (1032, 4, 6, 3000, "relu", "bf16", 1),        # the same with ragged tiles and sizes that no vector divides
+    (256, 1, 0, 4100, "relu", "bf16", 0),         # p = 1, 4 tiles, 65 reduction steps
     (520, 1, 0, 2100, "gelu", "bf16", 0),         # the same, ragged tiles (shard 520)
 ]
 
@@ -116,7 +116,7 @@ RECTANGULAR_CASES = [
     (1024, 512, 4, 16, 200, "relu", "bf16", 1),        # narrowing: shard 256 -> 128
     (528, 1056, 4, 24, 300, "gelu", "bf16", 3),        # widening, shards 132 -> 264: ragged in every tile dimension
     (2048, 1024, 8, 32, 4100, "gelu", "bf16", 0),      # long batch
-    (1032, 520, 4, 6, 260, "relu", "bf16", 2),         # shards 258 -> 130, k = 6: 4-byte vectors
+    (1032, 520, 4, 6, 260, "relu", "bf16", 2),         # shards 258 -> 130, k = 6
 ]
 
 
@@ -312,6 +312,7 @@ def test_step_smooth_activations(n, p, k, B, L, act, dtype, rank):
 
 @pytest.mark.parametrize("n,p,k,B,L,act,rank", [
     (2048, 8, 32, 4100, 2, "gelu", 0),       # one rank, long batch
+    (8192, 8, 32, 2100, 2, "gelu", 0),       # one rank, 128 x 128 tiles
     (1024, 8, 16, 136, 3, "gelu", -1),       # all ranks on the device
 ])
 def test_step_without_gradient_outputs(n, p, k, B, L, act, rank):
@@ -341,8 +342,8 @@ def test_step_without_gradient_outputs(n, p, k, B, L, act, rank):
     ((288, 160, 96), (5, 3), 4, 37, "identity", "f32", 2),
     ((1024, 2048, 512, 1024), (16, 32, 8), 8, 136, "gelu", "bf16", -1),     # all ranks: thin compression, fused output error, riders
     ((2048, 1024, 3072), (32, 16), 16, 200, "gelu", "bf16", 0),             # one rank
-    ((1032, 520, 1032), (6, 2), 4, 70, "identity", "bf16", 3),              # 4-byte vectors
-    ((1056, 528, 1056), (24, 8), 8, 72, "gelu", "bf16", -1),                # shards 132, 66, 132: 4-byte vectors in the middle
+    ((1032, 520, 1032), (6, 2), 4, 70, "identity", "bf16", 3),              # sizes that no vector divides
+    ((1056, 528, 1056), (24, 8), 8, 72, "gelu", "bf16", -1),                # shards 132, 66, 132: the one in the middle
 ])
 def test_step_layers_of_different_widths(widths, ks, p, B, act, dtype, rank):
     """Section IV, first paragraph: widths n_l and phantom widths k_l per layer."""
@@ -354,7 +355,7 @@ def test_step_layers_of_different_widths(widths, ks, p, B, act, dtype, rank):
 
 
 @pytest.mark.parametrize("n,p,k,B,L,dtype,rank", [
-    (2048, 16, 16, 300, 2, "bf16", 3),       # one rank: nothing but the weight-gradient launch can finish the loss
+    (2048, 16, 16, 300, 2, "bf16", 3),       # one rank
     (1024, 8, 16, 136, 2, "bf16", -1),       # all ranks: the reduce-scatter does
     (512, 1, 0, 200, 2, "bf16", 0),          # a dense stack
     (288, 4, 5, 37, 2, "f32", 1),

@@ -1,6 +1,6 @@
 """The same step run again and again on the same inputs gives the same bits.
 
-One rank's weight gradients are cut along the batch into pieces that run on different compute units; the piece that
+One rank's compressor gradients are cut along the batch into pieces that run on different compute units; the piece that
 finishes last adds the others' results to its own, in the order of the pieces, and (training steps) applies the SGD
 update right there.  Which piece comes last changes from run to run; the result may not.  A piece that read another
 piece's result before it was complete, or a stale copy of it, would show here as a bit that differs between calls."""
@@ -16,9 +16,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,p,k,B,L,act,repeats", [
-    (16384, 16, 64, 4096, 3, "gelu", 24),      # configuration 4's shapes: 128 + 8 tiles cut into 2 and 8 pieces
-    (4096, 16, 16, 4300, 2, "gelu", 24),       # 4 pieces each, the last one ragged
-    (2048, 8, 32, 2050, 3, "relu", 24),        # 2 and 4 pieces, three layers: every launch of the backward pass carries pieces
+    (16384, 16, 64, 4096, 3, "gelu", 24),      # configuration 4's shapes: 8 tiles of compressor gradients per layer in 4 pieces
+    (4096, 16, 16, 4300, 2, "gelu", 24),       # few tiles (gemm_flex.h): two teams per tile, nothing cut
+    (2048, 8, 32, 2050, 3, "relu", 24),
+    (8192, 8, 32, 2100, 2, "relu", 24),        # in 2 pieces, the last one ragged
+    (4096, 8, 128, 4099, 3, "gelu", 24),       # in 4, and compressions of all layers in one launch
 ])
 def test_repeated_steps_give_identical_bits(n, p, k, B, L, act, repeats):
     print(f"case repeat n={n} p={p} k={k} B={B} L={L} {act}", flush=True)
