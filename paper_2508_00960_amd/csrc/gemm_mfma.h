@@ -16,7 +16,7 @@
 //          compression; delta, X, G in the weight gradients).  LDS tile [64][128 + 32]; the MFMA
 //          operand is built by two ds_read_b64_tr_b16 (the gfx950 transposing LDS read: within 16
 //          lanes, lanes 4j..4j+3 supply row j of a 4 x 16 block, lane i receives column i).
-// The peers' segments (G_i, D_i) are addressed in place through the View; VEC (8, 4 or 2
+// The peers' segments (G_i, D_i) are addressed in place through the View; VEC (8 or 4
 // elements) is the widest vector that never straddles a segment boundary.
 //
 // Address arithmetic is kept off the vector ALU as far as possible (it competes with the MFMAs for
@@ -75,7 +75,6 @@ constexpr int mfma_lds_bytes(int mode) { return mode == TILE_SOLO ? MFMA_LDS_BYT
 template <int VEC> struct VecOf;
 template <> struct VecOf<8> { typedef u32x4 type; };
 template <> struct VecOf<4> { typedef u32x2 type; };
-template <> struct VecOf<2> { typedef uint32_t type; };
 
 // a global-memory load that the compiler cannot mistake for a generic (flat) access
 template <typename V>
@@ -1376,9 +1375,7 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_tail_kernel(MfmaTailBatch tb
         if (tb.dual) mfma_workgroup<LD_KC, LD_KM, VEC, VEC, __bf16, true, EPI_STORE>(P, xcd_order(id, 0, tb.head_wg));
         else mfma_workgroup<LD_KC, LD_KM, VEC, VEC, __bf16, false, EPI_STORE>(P, xcd_order(id, 0, tb.head_wg));
     } else if (id < tb.loss_first) {
-        // The XCD-aware order within each product, and within each slab of pieces of a product whose reduction is cut
-        // (all first pieces, then all second ones, ...: a piece waits for the one before it, which must not sit
-        // behind it in the dispatch order)
+        // the XCD-aware order within each product
         int wg = id - tb.tail_first;
         const bool second = wg >= tb.tail0_wg;
         if (second) wg -= tb.tail0_wg;

@@ -669,7 +669,7 @@ ph_status launch_product_table(const ProductTable *table, int grid, hipStream_t 
     return check_launch(what);
 }
 
-// The same launch for layers of one shape, without a table (dw, dc: by layer; dc empty without compressors).
+// The same launch for layers of one shape, without a table (dw, dc: by layer; without compressors the dc have no rows).
 ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::vector<Product> &dc, int pieces, float *parts,
                                    unsigned *arrived, const LossTail &tail, hipStream_t st, const char *what)
 {
@@ -1130,7 +1130,6 @@ struct BwdArgs {
     float *dx_colsum;          // step only: zeroed [groups, s]; the input-gradient product adds the column sums
                                //   of what it stores, i.e. the layer below's bias gradient (Eq. (bpb))
     bool dbias_ready;          // step only: dbias already holds the column sums of delta
-    bool dbias_zeroed;         // step only: dbias is zero on entry
     bool send_done;            // step only: this layer's error compression was launched by the layer above (below)
     const void *below_Dw;      // step only, all ranks: D of the layer below; its error compression (dX -> dG_send)
     const Geo *below_g;        //   (that layer's shapes)
@@ -1303,7 +1302,7 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
         int chunks = (int)std::max<int64_t>(1, std::min<int64_t>(256 / ((int64_t)strips * g.groups), B / 128));
         const int rows_per_chunk = (int)((B + chunks - 1) / chunks);
         chunks = (int)((B + rows_per_chunk - 1) / rows_per_chunk);
-        if (chunks > 1 && !b.dbias_zeroed && !b.dbias_ready) {
+        if (chunks > 1 && !b.dbias_ready) {
             ProfScope prof("clear bias gradient", 0, (int64_t)g.groups * so, 0, 1, st);
             hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks_for((int64_t)g.groups * so)), dim3(256), 0, st, b.dbias,
                                (int64_t)g.groups * so);

@@ -64,14 +64,6 @@ __device__ __forceinline__ Loc locate(const Axis &ax, int idx, int skip)
     return l;
 }
 
-// element offset and region of (r, c) given the two locators
-__device__ __forceinline__ int64_t join(const Loc &lr, const Loc &lc, int &region)
-{
-    region = lr.region > lc.region ? lr.region : lc.region;
-    if (region < 0) region = 0;
-    return region ? lr.off1 + lc.off1 : lr.off0 + lc.off0;
-}
-
 // ---- host-side constructors -------------------------------------------------
 inline Axis axis_plain(int64_t mult0, int64_t mult1)
 {
@@ -127,9 +119,6 @@ inline View view_rowseg_t(const void *head, int64_t ld0, int head_cols, int64_t 
     return v;
 }
 
-}  // namespace phantom
-
-namespace phantom {
 // two row-major matrices stacked along the reduction index and read transposed:
 // element (r, c) = c < split ? top[c*ld0 + r] : bottom[(c-split)*ld1 + r]
 inline View view_colstack(const void *top, int64_t ld0, int split, int64_t gtop,

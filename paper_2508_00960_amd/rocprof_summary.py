@@ -226,7 +226,7 @@ def traffic(args):
     print("#  the saved sigma' or ReLU bits, the target, the output error, and a rider's tensors are not in that figure)")
     for k, v in F.items():
         fam = family_of(k[0])[0]
-        if fam in ("rs", "sgd", "fill", "thin") and k in W:
+        if fam in ("rs", "fill", "thin") and k in W:
             f_raw = sum(v["FETCH_SIZE"]) / len(v["FETCH_SIZE"])
             w_raw = sum(W[k]["WRITE_SIZE"]) / len(W[k]["WRITE_SIZE"])
             print(f"# {short(k[0])} ({k[1]} workgroups): fetch {f_raw * 1024 * sf:.0f} B, write {w_raw * 1024 * sw:.0f} B per launch")
