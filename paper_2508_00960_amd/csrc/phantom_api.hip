@@ -385,12 +385,11 @@ inline unsigned blocks_for(int64_t count, int per_block = 256, int cap = 8192)
 // Does this bf16 problem run on the kernels of gemm_flex.h rather than the 128 x 128 ones?  Widths or phantom widths that
 // no 8- or 4-element vector divides always do.  Otherwise where a layer's output has so few 128 x 128 tiles that they leave
 // compute units idle: 64 x 64 tiles then spread over four times as many workgroups, and the backward pass has fewer launches.
-// Measured (us, 128 x 128 kernels against these): 3 layers of 1024 with batch 1000 trained, 64 tiles, 158 : 130; 4 layers
-// forward, 32 / 64 / 128 tiles, 76 : 59, 78 : 62, 80 : 77; 3 layers of 1024 trained at batch 2000, 128 tiles, 169 : 179; 256
-// tiles and more lose everywhere (8 layers of 1024 at batch 4096: 719 : 907).  At 128 tiles the weight gradients
-// decide: with a batch longer than the layer is wide they have few tiles and a long reduction (512 wide, batch 4000:
-// 151 : 195), otherwise many (2048 wide, batch 1000: 254 : 234).
-// A layer's backward call saves two launches more: up to 192 tiles (1000 wide, batch 3000: 91 : 81).
+// Measured (us, 128 x 128 kernels : these; p = 8, k = 32): 3 layers of 1024 trained at batch 1000, 64 tiles, 141 : 107; 4 layers
+// forward at 16 / 64 / 96 / 128 / 256 tiles, 69 : 43, 71 : 56, 71 : 65, 71 : 71, 94 : 116; 3 layers of 1024 trained at 128 tiles
+// 155 : 150, at 256 209 : 246.  At 128 tiles the weight gradients decide: with a batch longer than the layer is wide they have
+// few tiles and a long reduction (512 wide, batch 4000: 135 : 162), otherwise many (2048 wide, batch 1000: 237 : 222).
+// A layer's backward call saves two launches more: up to 192 tiles (1024 wide, batch 3072, forward and backward: 77 : 65).
 // All ranks on the device: the 128 x 128 kernels' launches carry the next layer's error compression and sum the
 // reduce-scatter on read.
 bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call = false)
@@ -485,11 +484,12 @@ MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
 // More tiles than compute units: two workgroups of one tile each per compute unit (TILE_SOLO), or one of two tiles that
 // share their B operand (TILE_DUAL)?  All workgroups of a round are in the same phase, so the memory idles during DUAL's
 // loop and the matrix cores during its epilogue; SOLO's overlap, for a third more bytes staged.  It wins where the loop is
-// short against the epilogue.  Weight gradients with the update (10 to 14 bytes of weights per element; us per step,
-// DUAL : SOLO): batch 256 and 32 ranks of 1024 485 : 446, batch 1024 and 64 ranks of 128 631 : 561, dense 4096 656 : 610,
-// batch 1536 dense 365 : 350, but batch 2048 and 64 ranks of 256 1261 : 1282 and 4096 dense 781 : 803.  Input gradients (one
-// or four bytes of sigma' per element): 264 long 1282 : 1269, 528 long 632 : 631, 1036 long 419 : 429.  Plain stores:
-// 128 long 561 : 532, 256 long 474 : 470, 512 long 632 : 639.  The forward layout loses at 760 already (488 : 498).
+// short against the epilogue.  Step times (us, no launch in SOLO : every launch that can be : this rule):
+//   weight gradients with the update (10 to 14 bytes of weights per element), reduction 256 to 1536 long: 32 ranks of 1024 at batch
+//   256 505 : 447 : 448, 64 ranks of 256 at 512 567 : 527 : 526, 64 ranks of 128 at 1024 856 : 709 : 709, dense 4 x 4096 at 1024
+//   649 : 618 : 620 and at 1536 812 : 814 : 795; longer: dense at 2048 932 : 940 : 932, at 4096 1645 : 1693 : 1645;
+//   gradients alone: 64 ranks of 256 at 512 480 : 458 : 458, dense at 1024 577 : 536 : 537.
+// The forward layout loses at 760 already (488 : 498).
 template <typename TOut>
 bool solo_tiles(const GemmPlan &plan, const Product *prods, int count)
 {
@@ -867,8 +867,9 @@ FlexOperand flex_operand_of(const View &v, bool km, const FlexAxis &k, const Fle
 
 // Tile of a launch, by how many tiles of 64 x 64 it has.  More than one per compute unit: 64 x 64 with one team of four
 // wavefronts, several workgroups per unit.  Fewer: two teams that share the reduction (a lone workgroup otherwise spends
-// half of a step waiting: 3 layers of 512 trained at batch 1000, 112 -> 92 us).  Very few: 32 x 32 and
-// eight teams of one wavefront (6 layers of 1024 at batch 48, 17 tiles: 80 -> 62 us).
+// half of a step waiting).  Very few: 32 x 32 and eight teams of one wavefront.  Measured with each tile throughout (us,
+// 64 x 64 one team : two : 32 x 32): forward and backward call of 1024 wide at batch 1024 37 : 44 : 110, 3 layers of 512 trained at
+// batch 1000 88 : 76 : 153, 6 layers of 1024 forward at batch 512 84 : 74 : 117 and at batch 48 80 : 70 : 48.
 // fp32 adds its terms in the order of the reduction index (gemm_flex.h) and so has one team, except where eight teams
 // take one group of 16 terms each, the first level of its sums.
 enum FlexTile { FLEX_64, FLEX_64_2, FLEX_32_8 };

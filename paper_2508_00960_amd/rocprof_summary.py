@@ -5,7 +5,10 @@
                                                            --bench out/pmc_fetch_c4.json
     python -m paper_2508_00960_amd.rocprof_summary mfma    --workload c4 --dir out/pmc_mfma_c4 --bench out/pmc_mfma_c4.json
 
-Each mode prints the summary (redirect it into profiles/ffn_step_<workload>_<kind>.txt).  The directories are what
+    python -m paper_2508_00960_amd.rocprof_summary passes  --case "bf16 train deep" --passes 40     (the program to be traced)
+    python -m paper_2508_00960_amd.rocprof_summary case    --case "bf16 train deep" --passes 40 --dir out/case
+
+The last two are for the cases of perf/cases.py, which need no bench.py.  Each mode prints the summary (redirect it into profiles/ffn_step_<workload>_<kind>.txt).  The directories are what
 `rocprofv3 --output-format csv -d <dir> -o <workload>` wrote; --bench is the JSON line bench.py printed in the same
 run.  Kernel dispatches are matched to the names bench.py gives its launches by kernel family (which template of
 the library), launches per step, and number of workgroups; nothing here knows a workload's shapes.
@@ -181,6 +184,43 @@ def trace(args):
           f"{dom['achieved']} {dom['unit']} = {dom['frac']:.3f} of the {dom['bound']} peak")
 
 
+def passes(args):
+    import torch
+    from perf import cases
+    case = {c["name"]: c for c in cases.listed()}[args.case]
+    state = cases.prepare(case, 1)
+    torch.cuda.synchronize()
+    for _ in range(args.passes):
+        cases.run(state)
+    torch.cuda.synchronize()
+
+
+def case(args):
+    own = [r for r in csv.DictReader(open(one_file(args.dir, "kernel_trace.csv"))) if family_of(r["Kernel_Name"])[0] is not None]
+    own.sort(key=lambda r: int(r["Start_Timestamp"]))
+    per_pass = len(own) // args.passes
+    if per_pass * args.passes != len(own):
+        raise SystemExit(f"{len(own)} dispatches are no multiple of {args.passes} passes")
+    own = own[per_pass * (args.passes // 4):]                # the first quarter warms up
+    n = len(own) // per_pass
+    agg, order = collections.defaultdict(list), []
+    for r in own:
+        wgs = (int(r["Grid_Size_X"]) * int(r["Grid_Size_Y"]) * int(r["Grid_Size_Z"])) // \
+              (int(r["Workgroup_Size_X"]) * int(r["Workgroup_Size_Y"]) * int(r["Workgroup_Size_Z"]))
+        key = (r["Kernel_Name"], wgs)
+        if key not in agg:
+            order.append(key)
+        agg[key].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
+    busy = sum(sum(v) for v in agg.values()) / n
+    wall = (int(own[-1]["End_Timestamp"]) - int(own[0]["Start_Timestamp"])) / 1e3 / n
+    print(f"## {args.case}: {per_pass} launches a pass, {busy:.1f} us in kernels, {wall:.1f} us from one pass's first kernel to the next's (under the profiler)")
+    print("#  kernel | workgroups | launches a pass | average us | us a pass | % of the kernels' time")
+    for key in order:
+        v = agg[key]
+        print(f"{short(key[0]):<72} | {key[1]:>6} | {len(v) / n:>4.4g} | {sum(v) / len(v):>7.2f} | {sum(v) / n:>7.2f} | {100 * sum(v) / n / busy:>5.1f}")
+    print()
+
+
 def counters(directory):
     rows = list(csv.DictReader(open(one_file(directory, "counter_collection.csv"))))
     agg = collections.defaultdict(lambda: collections.defaultdict(list))
@@ -255,15 +295,17 @@ def mfma(args):
 
 def main():
     ap = argparse.ArgumentParser()
-    ap.add_argument("mode", choices=["trace", "traffic", "mfma"])
-    ap.add_argument("--workload", required=True)
+    ap.add_argument("mode", choices=["trace", "traffic", "mfma", "passes", "case"])
+    ap.add_argument("--workload")
+    ap.add_argument("--case")
+    ap.add_argument("--passes", type=int, default=40)
     ap.add_argument("--dir")
     ap.add_argument("--fetch")
     ap.add_argument("--write")
-    ap.add_argument("--bench", required=True)
+    ap.add_argument("--bench")
     ap.add_argument("--command", default="", help="the rocprofv3 command line that produced the input, to be quoted in the summary")
     args = ap.parse_args()
-    {"trace": trace, "traffic": traffic, "mfma": mfma}[args.mode](args)
+    {"trace": trace, "traffic": traffic, "mfma": mfma, "passes": passes, "case": case}[args.mode](args)
 
 
 if __name__ == "__main__":
