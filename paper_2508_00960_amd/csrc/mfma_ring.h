@@ -146,17 +146,21 @@ __device__ __forceinline__ const __bf16 *ring_uniform(const __bf16 *p)
     return (const __bf16 *)(uintptr_t)((uint64_t)ring_uniform((uint32_t)(v >> 32)) << 32 | ring_uniform((uint32_t)v));
 }
 
-// 64 lanes x 16 bytes from base + off (bytes) of each lane to the LDS address lds_at + AHEAD (uniform) + 16 * lane
+// 64 lanes x 16 bytes from base + off (bytes) of each lane to the LDS address lds_at + AHEAD (uniform) + 16 * lane.
+// (The compiler reserves M0 and warns that it will not keep a value in it across the statements, which is what naming it is for.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int AHEAD> __device__ __forceinline__ void ring_load(const __bf16 *base, uint32_t off, uint32_t lds_at)
 {
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(ring_uniform(lds_at)), "v"(off), "s"(ring_uniform(base)), "n"(AHEAD) : "memory", "scc");
+                 :: "s"(ring_uniform(lds_at)), "v"(off), "s"(ring_uniform(base)), "n"(AHEAD) : "memory", "scc", "m0");
 }
 template <int AHEAD> __device__ __forceinline__ void ring_load(const __bf16 *p, uint32_t lds_at)
 {
     asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :: "s"(ring_uniform(lds_at)), "v"(p), "n"(AHEAD) : "memory", "scc");
+                 :: "s"(ring_uniform(lds_at)), "v"(p), "n"(AHEAD) : "memory", "scc", "m0");
 }
+#pragma clang diagnostic pop
 // f(std::integral_constant<int, j>) for j = 0 .. N - 1
 template <int N, typename F, int J = 0> __device__ __forceinline__ void ring_each(F &&f)
 {
