@@ -3,8 +3,10 @@ from __future__ import annotations
 
 import hashlib
 import os
+import re
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -18,6 +20,82 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+
+
+LLVM = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(HIPCC))), "llvm", "bin")
+
+
+def device_code(library: str) -> str:
+    """Disassembly of the kernels in a library that was built here."""
+    with tempfile.TemporaryDirectory() as tmp:
+        fat, obj = os.path.join(tmp, "fat"), os.path.join(tmp, "obj")
+        run = lambda tool, *args: subprocess.run([os.path.join(LLVM, tool), *args], check=True, capture_output=True, text=True).stdout
+        run("llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", library, os.path.join(tmp, "copy"))
+        run("clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={fat}", f"--output={obj}")
+        return run("llvm-objdump", "-d", "--no-show-raw-insn", "--symbolize-operands", obj)
+
+
+def _scalar_registers(operand: str):
+    m = re.fullmatch(r"s\[(\d+):(\d+)\]", operand)
+    if m:
+        return range(int(m[1]), int(m[2]) + 1)
+    m = re.fullmatch(r"s(\d+)", operand)
+    return (int(m[1]),) if m else {"m0": ("m0",), "vcc": ("vcc_lo", "vcc_hi"), "vcc_lo": ("vcc_lo",), "vcc_hi": ("vcc_hi",)}.get(operand, ())
+
+
+def missing_wait_states(disassembly: str):
+    """[what is wrong] where a scalar register is read by a vector-memory instruction sooner than five wait states after a vector
+    instruction wrote it, or M0 is written right ahead of a direct-to-LDS load.  The compiler keeps these distances (CDNA3 ISA,
+    "Manually Inserted Wait States") for its own instructions and not for those of an inline assembly statement (mfma_ring.h)."""
+    code = []                   # (operation, operands, label or None, the line)
+    function = ""
+    for line in disassembly.splitlines():
+        text = line.split("//")[0].strip()
+        m = re.fullmatch(r"(?:[0-9a-f]+ )?<(.+)>:", text)
+        if m:
+            function = function if re.fullmatch(r"L\d+", m[1]) else m[1]
+            code.append((None, (), (function, m[1]), line))
+        elif text and function:
+            words = re.split(r"[,\s]+", text)
+            code.append((words[0], words[1:], function, text))
+    wrong = []
+    into, changed = {}, True    # label -> {register: wait states since the write}, the least over all ways there
+    while changed:
+        changed, wrong, age = False, [], {}
+        for op, operands, where, text in code:
+            if op is None:
+                known = into.setdefault(where, {})
+                if where[0] == where[1]:
+                    age = {}
+                for r, waited in age.items():
+                    if waited < known.get(r, 5):
+                        known[r], changed = waited, True
+                age = dict(known)
+                continue
+            if op.startswith(("global_", "buffer_", "flat_", "scratch_")):
+                read = {r for w in operands for r in _scalar_registers(w)}
+                wrong += [f"{where}: {text}: a vector instruction wrote s{r} {age[r]} wait states before" for r in read if age.get(r, 5) < 5]
+                if "_lds_" in op and age.get("m0", 5) < 1:
+                    wrong.append(f"{where}: {text}: M0 was written by the instruction before")
+            waits = int(operands[0], 0) + 1 if op == "s_nop" else 1
+            age = {r: waited + waits for r, waited in age.items() if waited + waits < 5}
+            if op.startswith("v_"):
+                second = operands[1:2] if "_co_" in op or op.startswith(("v_mad_u64_u32", "v_mad_i64_i32", "v_div_scale")) else []
+                age.update({r: 0 for w in operands[:1] + second for r in _scalar_registers(w)})
+            elif op.startswith("s_") and operands:
+                for r in _scalar_registers(operands[0]):
+                    age.pop(r, None)
+                    if r == "m0":
+                        age[r] = 0
+            m = re.search(r"<?(L\d+)>?$", text) if "branch" in op else None
+            if m:
+                known = into.setdefault((where, m[1]), {})
+                for r, waited in age.items():
+                    if waited < known.get(r, 5):
+                        known[r], changed = waited, True
+            if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                age = {}
+    return wrong
 
 
 def sources():
@@ -39,6 +117,10 @@ def build_library(verbose: bool = True) -> str:
         print(err, file=sys.stderr)
     if proc.returncode != 0:
         raise RuntimeError(f"hipcc failed ({proc.returncode}):\n{err}")
+    wrong = missing_wait_states(device_code(LIB))
+    if wrong:
+        os.remove(LIB)
+        raise RuntimeError("the compiler left too few wait states ahead of inline assembly:\n" + "\n".join(wrong[:20]))
     return LIB
 
 

@@ -147,6 +147,10 @@ __device__ __forceinline__ const __bf16 *ring_uniform(const __bf16 *p)
 }
 
 // 64 lanes x 16 bytes from base + off (bytes) of each lane to the LDS address lds_at + AHEAD (uniform) + 16 * lane.
+// A base that a vector instruction brought to scalar registers (v_readfirstlane, the reload of a spilled one) must be five wait states old,
+// which the compiler sees to for its own loads alone: the build looks for such a distance in the finished code (build.py,
+// missing_wait_states) and fails on one.  A scalar move of the base inside the statement would do without the check; with one per load 8 layers
+// of 1024 trained at batch 4096 took 703 us for 688, with one per step and operand layers of 1408 at 158 47.5 for 46.8.
 // (The compiler reserves M0 and warns that it will not keep a value in it across the statements, which is what naming it is for.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
