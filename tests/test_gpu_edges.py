@@ -18,8 +18,12 @@ pytestmark = pytest.mark.gpu
     (592, 4, 4, 63, 2, "relu", -1, "train"),         # shard 148: the straddling tile is the last one; part of a step
     (592, 4, 12, 64, 2, "gelu", -1, "no_update"),    # one whole step
     (1072, 4, 28, 130, 3, "relu", -1, "train"),      # shard 268, two steps and a part, an odd number for the two teams
-    (4784, 4, 32, 600, 2, "gelu", 1, "train"),       # shard 1196, one rank
-    (5464, 2, 12, 333, 2, "relu", 0, "train"),       # shard 2732: two tiles per workgroup
+    (4784, 4, 32, 600, 2, "gelu", 1, "train"),       # shard 1196, one rank; so few tiles that gemm_flex.h takes them, as in the next
+    (5464, 2, 12, 333, 2, "relu", 0, "train"),
+    (4784, 4, 32, 1300, 2, "gelu", 1, "train"),      # one rank on the 128 x 128 kernels: two teams on a tile
+    (4216, 2, 12, 1600, 1, "relu", 0, "train"),      # shard 2108, 306 tiles: two tiles per workgroup
+    (4216, 2, 12, 1400, 1, "relu", 1, "train"),      # ... one team per workgroup (a batch of at most 1536)
+    (6336, 16, 12, 1600, 1, "gelu", -1, "no_update"),        # shard 396, all ranks, 320 + 64 tiles: two per workgroup
 ])
 def test_straddling_tiles_of_weight_gradients(n, p, k, B, L, act, rank, mode):
     print(f"case straddling n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode}", flush=True)

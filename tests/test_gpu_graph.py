@@ -63,8 +63,10 @@ def assert_same(what, got, want, tol):
 
 
 @pytest.mark.parametrize("n,p,k,B,L,act,dtype,rank,mode", [
-    (1024, 8, 32, 256, 3, "relu", "bf16", -1, "train"),       # all ranks: riders on the weight-gradient launches
+    (1024, 8, 32, 256, 3, "relu", "bf16", -1, "train"),       # all ranks, few tiles (gemm_flex.h)
     (1024, 8, 32, 256, 3, "relu", "bf16", -1, "no_update"),
+    (2048, 8, 16, 1600, 3, "relu", "bf16", -1, "train"),      # all ranks, 128 x 128 tiles: riders on the weight-gradient launches
+    (2048, 8, 16, 1600, 3, "relu", "bf16", -1, "no_update"),
     (2048, 16, 32, 384, 3, "gelu", "bf16", 0, "train"),        # one rank, few tiles (gemm_flex.h)
     (2048, 16, 32, 2304, 2, "gelu", "bf16", 0, "train"),       # ... long batch
     (8192, 8, 32, 2100, 2, "gelu", "bf16", 0, "train"),        # one rank, 128 x 128 tiles: all layers' gradients in one launch, in pieces

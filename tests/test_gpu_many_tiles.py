@@ -32,10 +32,12 @@ def test_step_every_stage(n, p, k, B, L, act, rank, mode, widths, ks):
 
 
 @pytest.mark.parametrize("n,p,k,B,L,act,mode", [
-    (2048, 64, 16, 72, 2, "relu", "train"),        # weight gradients and error compression in one-team workgroups; shard 32
+    (2048, 64, 16, 72, 2, "relu", "train"),        # shard 32, so few tiles that gemm_flex.h takes them ...
+    (2048, 64, 16, 400, 2, "relu", "train"),       # ... and more: weight gradients with the update, and the error compression, of 64 ranks
     (8192, 64, 12, 100, 2, "gelu", "no_update"),   # 4-element vectors
     (4096, 16, 16, 2100, 2, "relu", "train"),      # the input gradient; 34 tile rows, the last ragged
-    (4096, 1, 0, 200, 2, "gelu", "train"),         # dense
+    (4096, 1, 0, 200, 2, "gelu", "train"),         # dense, few tiles (gemm_flex.h) ...
+    (2176, 1, 0, 1000, 2, "gelu", "train"),        # ... and more: 289 weight-gradient tiles
 ])
 def test_one_team_workgroups(n, p, k, B, L, act, mode):
     print(f"case one team n={n} p={p} k={k} B={B} L={L} {act} {mode}", flush=True)

@@ -47,13 +47,16 @@ def run_step(prob, over, mode):
     ("X0", "forward", 128, 2, 8, 96, 1, "relu", "f32", 0),
     ("X0", "forward", 260, 2, 9, 200, 1, "gelu", "bf16", 1),           # odd phantom width
     ("X0", "forward", 4096, 2, 64, 2100, 1, "relu", "bf16", 0),        # 128 x 128 tiles
-    ("X0", "forward", 2048, 4, 16, 300, 1, "relu", "bf16", -1),        # all ranks
+    ("X0", "forward", 2048, 4, 16, 300, 1, "relu", "bf16", -1),        # all ranks, few tiles
+    ("X0", "forward", 2048, 4, 16, 1700, 1, "relu", "bf16", -1),       # ... 128 x 128 tiles
     ("X0", "train", 128, 2, 8, 96, 2, "gelu", "f32", 0),               # the first layer's weight gradient reads X0 last
     ("X0", "train", 2048, 4, 16, 300, 2, "relu", "bf16", -1),
+    ("X0", "train", 2048, 4, 16, 1700, 2, "relu", "bf16", -1),
     ("T", "train", 128, 2, 8, 96, 2, "relu", "f32", -1),
     ("T", "no_update", 260, 2, 9, 200, 2, "gelu", "bf16", 0),
     ("T", "train", 4096, 2, 64, 2100, 2, "gelu", "bf16", 0),
     ("T", "train", 2048, 4, 16, 300, 2, "relu", "bf16", -1),
+    ("T", "train", 2048, 4, 16, 1700, 2, "relu", "bf16", -1),
     ("G", "train", 128, 2, 64, 96, 2, "relu", "f32", 0),               # the first layer's peer buffer, as wide as the output
 ])
 def test_step_output_over_an_input(over, mode, n, p, k, B, L, act, dtype, rank):

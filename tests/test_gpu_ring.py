@@ -56,8 +56,11 @@ def test_layer_one_rank(n, p, k, B, act):
     (1040, 1, 0, 200, 3, "relu", 0, "train"),                # dense
     (2560, 8, 32, 1154, 2, "relu", -1, "train"),             # 128 x 128: the summed block in a stage of its own behind the head's
     (2048, 8, 64, 1665, 2, "gelu", -1, "no_update"),         # ... a full stage
-    (8192, 8, 24, 2100, 2, "gelu", 0, "train"),              # one rank, two-tile workgroups, irregular segments
+    (8192, 8, 24, 2100, 2, "gelu", 0, "train"),              # one rank on the 128 x 128 kernels, irregular segments
     (8256, 8, 16, 2100, 2, "relu", 3, "train"),              # ... irregular shard 1032
+    (8256, 8, 24, 3600, 2, "gelu", 5, "train"),              # ... both, and more than 256 tiles: two to a workgroup
+    (8192, 8, 24, 4200, 2, "relu", 0, "forward"),            # ... forward only, the compression behind the epilogue
+    (8256, 8, 24, 3600, 2, "relu", 1, "forward"),            # ... beside it
     (1024, 8, 16, 64, 3, "relu", 2, "train"),                # four tiles a layer: the ring backward, too
     (64, 8, 8, 33, 2, "gelu", 0, "train"),                   # ... one
     (8192, 8, 64, 225, 2, "gelu", 1, "forward"),             # a forward reduction of 1472 in 256 tiles of 32 x 32

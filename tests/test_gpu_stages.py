@@ -44,7 +44,7 @@ def test_config5_forward_every_layer_full_size(k):
 
 
 @pytest.mark.parametrize("n,p,k,B,L,act,dtype,rank,mode", [
-    (1024, 8, 16, 136, 3, "relu", "bf16", -1, "train"),        # ReLU, several bf16 layers, all ranks (sum-on-read reduce-scatter)
+    (1024, 8, 16, 136, 3, "relu", "bf16", -1, "train"),        # ReLU, several bf16 layers, all ranks, few tiles (gemm_flex.h)
     (2048, 16, 32, 200, 4, "relu", "bf16", 0, "train"),        # ReLU, one rank
     (2048, 16, 8, 2100, 2, "relu", "bf16", -1, "train"),       # 272 output tiles: two-tile workgroups with the output error in the update
     # one rank with few tiles (gemm_flex.h; the launches of one rank with more are in test_gpu_many_tiles.py)
@@ -66,8 +66,11 @@ def test_step_every_stage(n, p, k, B, L, act, dtype, rank, mode):
 
 
 @pytest.mark.parametrize("widths,ks,p,B,act,dtype,rank", [
-    ((1024, 2048, 512, 1024), (16, 32, 8), 8, 136, "relu", "bf16", -1),
+    ((1024, 2048, 512, 1024), (16, 32, 8), 8, 136, "relu", "bf16", -1),        # few tiles (gemm_flex.h)
     ((2048, 1024, 3072), (32, 16), 16, 200, "gelu", "bf16", 0),
+    # 128 x 128 tiles, all ranks: the error compression of a layer of another shape rides with the weight gradients
+    ((1024, 2048, 512, 1024), (16, 16, 8), 8, 1600, "relu", "bf16", -1),       # sum on read
+    ((4096, 2048, 4096), (16, 8), 16, 800, "gelu", "bf16", -1),                # the reduce-scatter kernel
 ])
 def test_step_every_stage_layers_of_different_widths(widths, ks, p, B, act, dtype, rank):
     print(f"case stages widths={widths} ks={ks} p={p} B={B} {act} {dtype} rank={rank}", flush=True)
