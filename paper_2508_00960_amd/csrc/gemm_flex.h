@@ -850,7 +850,11 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
     if constexpr (F::LEVELS) flex_add(acc, mid);
     FlexOut Q;
     const size_t q_at = offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out);
-    constexpr int PASSES = (TM * TN / V + F::THREADS - 1) / F::THREADS, AHEAD = PASSES <= 2 ? PASSES : 0;
+    // Reads ahead of the epilogue, its passes unrolled.  Not the FINE forward epilogue of a 64 x 64 tile: erff and expf, inlined for every pass of
+    // a loop that runs once, are fetched cold (all 8 ranks of 405 at batch 615 with GELU, 560 workgroups: 24.6 us a launch, 23.4 without; 16 ranks
+    // of 133 trained at batch 534 253.1 : 247.2 us a step).
+    constexpr int PASSES = (TM * TN / V + F::THREADS - 1) / F::THREADS;
+    constexpr int AHEAD = PASSES <= 2 && !(FINE && EPI == EPI_BIAS_ACT && TM == 64) ? PASSES : 0;
     FlexAhead<T, (AHEAD > 0 ? AHEAD : 1)> ahead;
     if constexpr (AHEAD > 0) Q = args_at<FlexOut>(q_at);
     if constexpr (AHEAD > 0) flex_request<T, TM, TN, F::THREADS, false, ROWSUM, TOut, EPI>(ahead, P, Q, g, tm, tn, rows);
