@@ -852,9 +852,12 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
     const size_t q_at = offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out);
     // Reads ahead of the epilogue, its passes unrolled.  Not the FINE forward epilogue of a 64 x 64 tile: erff and expf, inlined for every pass of
     // a loop that runs once, are fetched cold (all 8 ranks of 405 at batch 615 with GELU, 560 workgroups: 24.6 us a launch, 23.4 without; 16 ranks
-    // of 133 trained at batch 534 253.1 : 247.2 us a step).
+    // of 133 trained at batch 534 253.1 : 247.2 us a step).  Nor two passes of the input-gradient layout, whose launches carry the error
+    // compression: it stores cut vectors element by element and reads nothing (gradients of 32 ranks of 256 + 22 at batch 663 527.8 : 512.8,
+    // 64 ranks of 234 + 8 trained at 1532 1775 : 1766; 3 layers of 750 + 10 trained at 1000 lose, 90.1 : 91.2).
     constexpr int PASSES = (TM * TN / V + F::THREADS - 1) / F::THREADS;
-    constexpr int AHEAD = PASSES <= 2 && !(FINE && EPI == EPI_BIAS_ACT && TM == 64) ? PASSES : 0;
+    constexpr bool DEARER = (FINE && EPI == EPI_BIAS_ACT && TM == 64) || (PASSES == 2 && EPI == EPI_DACT);
+    constexpr int AHEAD = PASSES <= 2 && !DEARER ? PASSES : 0;
     FlexAhead<T, (AHEAD > 0 ? AHEAD : 1)> ahead;
     if constexpr (AHEAD > 0) Q = args_at<FlexOut>(q_at);
     if constexpr (AHEAD > 0) flex_request<T, TM, TN, F::THREADS, false, ROWSUM, TOut, EPI>(ahead, P, Q, g, tm, tn, rows);
