@@ -394,24 +394,34 @@ inline unsigned blocks_for(int64_t count, int per_block = 256, int cap = 8192)
 //   a layer's backward call saves two launches more where the tiles are cheap: forward + backward of 1024 at 256 / 384 / 512 tiles 93 : 76,
 //   119 : 106, 153 : 135; of 512 at 256 118 : 88; of 2048 at 128 / 192 / 512 78 : 68, 85 : 91, 184 : 197; 64 ranks, 1024 wide, k 64 (reduction
 //   5056) at 256 190 : 220;
-//   all ranks on the device, whose 128 x 128 launches carry the next layer's error compression and sum the reduce-scatter on read: 8 ranks of 256
-//   at 64 / 128 / 192 / 256 tiles 160 : 133, 150 : 133, 184 : 160, 208 : 214; of 512 at 128 / 160 / 192 / 256 193 : 175, 199 : 192, 206 : 202,
-//   231 : 264; 32 ranks of 128 at 64 153 : 124; 64 ranks of 128 at 128 / 192 272 : 272, 235 : 237.
+//   all ranks on the device, whose 128 x 128 launches carry the next layer's error compression and sum the reduce-scatter on read; lines in tiles of
+//   64 x 64, of which a compute unit holds three.  A pass with a backward part up to 768: 8 ranks of 256 + 32 at 256 / 512 / 768 tiles (batch 512 /
+//   1024 / 1536) 152 : 122, 190 : 167, 216 : 187; of 512 + 32 at 512 / 768 185 : 170, 215 : 200; 16 of 128 + 32 at 768 183 : 174; 32 of 128 + 16 at
+//   640 / 768 217 : 212, 234 : 235; 64 of 128 + 8 at 512 / 768 224 : 220, 285 : 286; a layer's backward call of 8 of 512 + 32 at 768 48 : 39.  Less the
+//   longer the peers' part is against the shard, which smaller tiles read more often: 32 of 128 + 24 at 768 210 : 226, 16 of 128 + 64 236 : 247,
+//   64 of 128 + 16 243 : 269, 64 of 64 + 8 at 384 180 : 162, 32 of 128 + 32 at 512 / 768 190 : 193, 227 : 254; 64 of 64 + 16 at 320 213 : 201, of 128 + 32
+//   at 256 / 512 268 : 232, 323 : 335, + 64 at 512 548 : 637.
+//   Forward alone up to 512, as with one rank: 4 layers of 64 ranks of 128 + 8 at 512 / 768 74.6 : 70, 76.6 : 87, 32 of 128 + 16 63.4 : 58.7, 66 : 70, 8 of
+//   512 + 32 69.7 : 65.6, 71.3 : 74.9; 8 of 256 + 32 is the exception, at 768 64.2 : 63.  With more than 32 phantom neurons the compression has two column
+//   blocks there, or no kernel of its own: 8 of 256 + 40 at 640 73 : 70, 2 of 512 + 64 at 768 71 : 66, 4 of 1024 + 64 104 : 89, 8 of 512 + 128 109 : 99,
+//   32 of 128 + 64 at 640 120 : 118, but 64 of 128 + 48 at 640 161 : 178.
 // 4-element vectors, which take the renumbering kernel, keep the lines that were measured for it: 96 and 128 tiles, 192 for a layer's call.
 bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call = false)
 {
     int64_t tiles = 0;
-    bool wide = true, narrow = true, ring = true;
+    bool wide = true, narrow = true, ring = true, all_fit = true;
     for (const Geo &g : geos) {
         if (g.vec == 0) return true;
         tiles = std::max(tiles, tiles_of(g.B, g.so) * g.groups);
         ring = ring && g.vec == 8;
         wide = wide && g.B <= (ring ? 2 : 1) * g.so;
         narrow = narrow && g.so <= 1024 && g.Kc <= 2048;
+        const int64_t peers = g.q * g.k, small = ((g.B + 63) / 64) * ((g.so + 63) / 64) * g.groups;
+        all_fit = all_fit && small <= (backward ? (peers <= 4 * g.so ? 768 : peers <= 8 * g.so ? 512 : 384) : g.k > 32 && peers <= 16 * g.so ? 768 : 512);
     }
     static const char *force = tuning_env("PHANTOM_FLEX");
     if (force) return force[0] == '1';
-    if (geos[0].all) return ring && tiles <= 192;
+    if (geos[0].all) return ring && all_fit;
     if (single_call && !ring) return tiles <= 192;
     if (single_call) return tiles <= (backward && narrow ? 512 : 128);
     return tiles <= (!backward || wide ? 128 : 96);

@@ -31,9 +31,14 @@ LARGE = [
     (6400, 32, 40, 390, "relu"),     # shard 200
     (5248, 16, 64, 530, "identity"), # shard 328, whole segments in a stage that the head block shifts
 ]
+# between the lines of use_flex for all ranks: forward on the one kind of kernels, backward on the other
+BETWEEN = [
+    (1024, 8, 16, 2100, "relu"),     # 528 tiles of 64 x 64: 128 x 128 ones forward, 64 x 64 backward
+    (2048, 16, 64, 1030, "gelu"),    # 544, peers' part 7.5 times the shard, 64 phantom neurons: the other way round
+]
 
 
-@pytest.mark.parametrize("n,p,k,B,act", SMALL + LARGE)
+@pytest.mark.parametrize("n,p,k,B,act", SMALL + LARGE + BETWEEN)
 def test_layer_all_ranks(n, p, k, B, act):
     print(f"case ring layer n={n} p={p} k={k} B={B} {act}", flush=True)
     run_layer_all_ranks(pin.Problem(n=n, p=p, k=k, batch=B, layers=1, act=act, dtype="bf16", rank=-1))
@@ -63,6 +68,8 @@ def test_layer_one_rank(n, p, k, B, act):
     (8256, 8, 24, 3600, 2, "relu", 1, "forward"),            # ... beside it
     (1024, 8, 16, 64, 3, "relu", 2, "train"),                # four tiles a layer: the ring backward, too
     (64, 8, 8, 33, 2, "gelu", 0, "train"),                   # ... one
+    (1024, 8, 16, 2100, 2, "gelu", -1, "forward"),           # all ranks, between the lines, as above
+    (2048, 16, 64, 1030, 2, "relu", -1, "train"),
     (8192, 8, 64, 225, 2, "gelu", 1, "forward"),             # a forward reduction of 1472 in 256 tiles of 32 x 32
     (8192, 8, 64, 257, 2, "relu", 1, "forward"),             # ... of 64 x 64, two teams
 ])
