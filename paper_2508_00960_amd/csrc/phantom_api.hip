@@ -893,9 +893,13 @@ FlexOperand flex_operand_of(const View &v, bool km, const FlexAxis &k, const Fle
 // half of a step waiting).  Very few: 32 x 32 and eight teams of one wavefront.  Measured with each tile throughout (us,
 // 64 x 64 one team : two : 32 x 32): forward and backward call of 1024 wide at batch 1024 37 : 44 : 110, 3 layers of 512 trained at
 // batch 1000 88 : 76 : 153, 6 layers of 1024 forward at batch 512 84 : 74 : 117 and at batch 48 80 : 70 : 48.
-// On the ring (8-element vectors) a backward pass never takes 32 x 32 tiles (one rank of 128 + 16 trained at batch 64, 4 layers, 74 : 56), a
-// forward one those that fit one round of workgroups where the reduction is long: 6 layers of 1024 + 448 at batch 96 / 192 / 256 57 : 50, 57 : 51,
-// 57 : 79, 4 of 2048 + 448 at 64 / 128 52 : 40, 52 : 64, but 6 of 512 + 224 at 64 / 256 47 : 50, 46 : 51.
+// 8-element vectors, whose 64 x 64 tiles run on the ring, take 32 x 32 ones where they fit one round of workgroups and the reduction is so long that
+// eight teams gain more than the renumbering costs: 960 forward, or 512, which eight teams have in one whole step each (ring : 32 x 32; 6 layers): dense
+// 384 / 512 / 640 / 896 / 960 / 1024 wide at batch 64 35.4 : 39.3, 38.2 : 31.4, 41.3 : 47.9, 45.5 : 46.6, 47 : 46.1, 48 : 39.9, 512 at batch 512 39 : 32.6; 512 + 448
+// at 64 47.3 : 45.7, 1024 + 448 at 192 57 : 51, at 256 57 : 79, 2048 + 448 at 64 / 128 52 : 40, 52 : 64; all 8 ranks of 512 + 32 (the compression) at 512 66 : 61.
+// Backward, where the launch ends with its weight gradients, 1024 and at most 96 tiles of 32 x 32 (3 layers trained): dense 64 wide at batch
+// 512 / 1024 / 2048 / 8192 41.7 : 42.7, 49 : 49.5, 64.2 : 59.7, 156 : 118, 256 wide at 1024 / 4096 52.4 : 52.6, 100 : 85 (at most 24 tiles of 64 x 64: 101), 512 + 56 at
+// 8192 168 : 150; 128 + 16 at batch 64, whatever its tiles, 56 : 74.
 // fp32 adds its terms in the order of the reduction index (gemm_flex.h) and so has one team, except where eight teams
 // take one group of 16 terms each, the first level of its sums.
 enum FlexTile { FLEX_64, FLEX_64_2, FLEX_32_8 };
@@ -908,12 +912,12 @@ FlexTile flex_tile_for(const Product *prods, int count, int groups, bool forward
         tiles += ((prods[i].M + 63) / 64) * ((prods[i].N + 63) / 64) * groups;
         small += ((prods[i].M + 31) / 32) * ((prods[i].N + 31) / 32) * groups;
         const int64_t pad = prods[i].km ? 0 : ((prods[i].K - prods[i].a.c.split) / std::max(prods[i].a.c.seg, 1) + 1) * (FlexType<T>::V - 1);
-        longest = std::max(longest, prods[i].K + (prods[i].a.c.decides ? pad : 0));      // (at most; the numbering pads pieces to vectors)
+        longest = std::max(longest, prods[i].K + (prods[i].a.c.decides && !ring ? pad : 0));      // (at most; the numbering pads pieces to vectors)
     }
     static const char *force = tuning_env("PHANTOM_FLEX_TILE");
     if (force) return (FlexTile)atoi(force);
     if (sizeof(T) == 4) return tiles <= 128 && longest <= 8 * 16 ? FLEX_32_8 : FLEX_64;
-    const bool few = ring ? forward && small <= 256 && longest >= 1024 : tiles <= 24;
+    const bool few = !ring ? tiles <= 24 : forward ? small <= 256 && (longest >= 960 || longest == 8 * 64) : small <= 96 && longest >= 1024;
     return tiles > 256 ? FLEX_64 : few ? FLEX_32_8 : FLEX_64_2;
 }
 

@@ -70,6 +70,13 @@ def test_layer_one_rank(n, p, k, B, act):
     (64, 8, 8, 33, 2, "gelu", 0, "train"),                   # ... one
     (1024, 8, 16, 2100, 2, "gelu", -1, "forward"),           # all ranks, between the lines, as above
     (2048, 16, 64, 1030, 2, "relu", -1, "train"),
+    # 32 x 32 tiles, eight teams: weight gradients of 1024 rows and more, forward reductions of 512, and of 960 and more
+    (256, 4, 8, 1100, 2, "relu", 2, "train"),
+    (128, 1, 0, 2050, 2, "gelu", 0, "train"),
+    (256, 4, 16, 1024, 2, "relu", -1, "no_update"),
+    (512, 1, 0, 100, 2, "gelu", 0, "forward"),
+    (2048, 4, 8, 72, 2, "relu", -1, "train"),                # (the compressions of all ranks)
+    (1792, 2, 64, 70, 2, "relu", 1, "forward"),
     (8192, 8, 64, 225, 2, "gelu", 1, "forward"),             # a forward reduction of 1472 in 256 tiles of 32 x 32
     (8192, 8, 64, 257, 2, "relu", 1, "forward"),             # ... of 64 x 64, two teams
 ])
