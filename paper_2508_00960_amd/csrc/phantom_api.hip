@@ -897,9 +897,10 @@ FlexOperand flex_operand_of(const View &v, bool km, const FlexAxis &k, const Fle
 // eight teams gain more than the renumbering costs: 960 forward, or 512, which eight teams have in one whole step each (ring : 32 x 32; 6 layers): dense
 // 384 / 512 / 640 / 896 / 960 / 1024 wide at batch 64 35.4 : 39.3, 38.2 : 31.4, 41.3 : 47.9, 45.5 : 46.6, 47 : 46.1, 48 : 39.9, 512 at batch 512 39 : 32.6; 512 + 448
 // at 64 47.3 : 45.7, 1024 + 448 at 192 57 : 51, at 256 57 : 79, 2048 + 448 at 64 / 128 52 : 40, 52 : 64; all 8 ranks of 512 + 32 (the compression) at 512 66 : 61.
-// Backward, where the launch ends with its weight gradients, 1024 and at most 96 tiles of 32 x 32 (3 layers trained): dense 64 wide at batch
+// Backward, where the launch ends with its weight gradients, beyond 768 and at most 96 tiles of 32 x 32 (3 layers trained): dense 64 wide at batch
 // 512 / 1024 / 2048 / 8192 41.7 : 42.7, 49 : 49.5, 64.2 : 59.7, 156 : 118, 256 wide at 1024 / 4096 52.4 : 52.6, 100 : 85 (at most 24 tiles of 64 x 64: 101), 512 + 56 at
-// 8192 168 : 150; 128 + 16 at batch 64, whatever its tiles, 56 : 74.
+// 8192 168 : 150; 128 + 16 at batch 64, whatever its tiles, 56 : 74.  Eight teams are eight partial sums, two of the ring's four: error of the weight
+// gradients against 64 bits (2-norm), dense 256 at 256 / 768 / 1000 / 4096 rows 4.7e-8 : 4.9e-8, 6.7e-8 : 6.9e-8, 7.2e-8 : 6.7e-8, 1.0e-7 : 7.3e-8.
 // fp32 adds its terms in the order of the reduction index (gemm_flex.h) and so has one team, except where eight teams
 // take one group of 16 terms each, the first level of its sums.
 enum FlexTile { FLEX_64, FLEX_64_2, FLEX_32_8 };
@@ -917,7 +918,7 @@ FlexTile flex_tile_for(const Product *prods, int count, int groups, bool forward
     static const char *force = tuning_env("PHANTOM_FLEX_TILE");
     if (force) return (FlexTile)atoi(force);
     if (sizeof(T) == 4) return tiles <= 128 && longest <= 8 * 16 ? FLEX_32_8 : FLEX_64;
-    const bool few = !ring ? tiles <= 24 : forward ? small <= 256 && (longest >= 960 || longest == 8 * 64) : small <= 96 && longest >= 1024;
+    const bool few = !ring ? tiles <= 24 : forward ? small <= 256 && (longest >= 960 || longest == 8 * 64) : small <= 96 && longest > 768;
     return tiles > 256 ? FLEX_64 : few ? FLEX_32_8 : FLEX_64_2;
 }
 
