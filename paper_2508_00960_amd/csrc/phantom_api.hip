@@ -401,10 +401,11 @@ inline unsigned blocks_for(int64_t count, int per_block = 256, int cap = 8192)
 //   longer the peers' part is against the shard, which smaller tiles read more often: 32 of 128 + 24 at 768 210 : 226, 16 of 128 + 64 236 : 247,
 //   64 of 128 + 16 243 : 269, 64 of 64 + 8 at 384 180 : 162, 32 of 128 + 32 at 512 / 768 190 : 193, 227 : 254; 64 of 64 + 16 at 320 213 : 201, of 128 + 32
 //   at 256 / 512 268 : 232, 323 : 335, + 64 at 512 548 : 637.
-//   Forward alone up to 512, as with one rank: 4 layers of 64 ranks of 128 + 8 at 512 / 768 74.6 : 70, 76.6 : 87, 32 of 128 + 16 63.4 : 58.7, 66 : 70, 8 of
-//   512 + 32 69.7 : 65.6, 71.3 : 74.9; 8 of 256 + 32 is the exception, at 768 64.2 : 63.  With more than 32 phantom neurons the compression has two column
-//   blocks there, or no kernel of its own: 8 of 256 + 40 at 640 73 : 70, 2 of 512 + 64 at 768 71 : 66, 4 of 1024 + 64 104 : 89, 8 of 512 + 128 109 : 99,
-//   32 of 128 + 64 at 640 120 : 118, but 64 of 128 + 48 at 640 161 : 178.
+//   Forward alone up to 768 where the peers' part is at most twice the shard: 4 layers of 8 ranks of 256 + 32 at 512 / 768 59 : 56, 64.4 : 62.4, of 512 + 32 69 :
+//   60, 70.8 : 66.9 (with GELU 81 : 72), 2 of 2048 + 32 at 768 140 : 132, 16 of 128 + 16 57.6 : 59.8 (with GELU 67.5 : 65.4); beyond, up to 512: 32 of 128 + 16 at
+//   512 / 768 63 : 58, 65.8 : 69.8, 64 of 128 + 8 74.8 : 70, 77 : 87.5.  With more than 32 phantom neurons the compression has two column blocks
+//   there, or no kernel of its own: 8 of 256 + 40 at 640 72.5 : 70, 4 of 1024 + 64 at 768 103 : 88, 8 of 512 + 128 107 : 97, 32 of 128 + 64 at 640
+//   117 : 115, but 64 of 128 + 48 at 640 164 : 179.
 // 4-element vectors, which take the renumbering kernel, keep the lines that were measured for it: 96 and 128 tiles, 192 for a layer's call.
 bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call = false)
 {
@@ -417,7 +418,8 @@ bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call = fa
         wide = wide && g.B <= (ring ? 2 : 1) * g.so;
         narrow = narrow && g.so <= 1024 && g.Kc <= 2048;
         const int64_t peers = g.q * g.k, small = ((g.B + 63) / 64) * ((g.so + 63) / 64) * g.groups;
-        all_fit = all_fit && small <= (backward ? (peers <= 4 * g.so ? 768 : peers <= 8 * g.so ? 512 : 384) : g.k > 32 && peers <= 16 * g.so ? 768 : 512);
+        all_fit = all_fit && small <= (backward ? (peers <= 4 * g.so ? 768 : peers <= 8 * g.so ? 512 : 384)
+                                                : peers <= 2 * g.so || (g.k > 32 && peers <= 16 * g.so) ? 768 : 512);
     }
     static const char *force = tuning_env("PHANTOM_FLEX");
     if (force) return force[0] == '1';

@@ -36,7 +36,7 @@ LARGE = [
 ]
 # between the lines of use_flex for all ranks: forward on the one kind of kernels, backward on the other
 BETWEEN = [
-    (1024, 8, 16, 2100, "relu"),     # 528 tiles of 64 x 64: 128 x 128 ones forward, 64 x 64 backward
+    (1024, 16, 16, 2100, "relu"),    # 528 tiles of 64 x 64, peers' part 3.75 times the shard: 128 x 128 ones forward, 64 x 64 backward
     (2048, 16, 64, 1030, "gelu"),    # 544, peers' part 7.5 times the shard, 64 phantom neurons: the other way round
 ]
 
@@ -71,7 +71,7 @@ def test_layer_one_rank(n, p, k, B, act):
     (8256, 8, 24, 3600, 2, "relu", 1, "forward"),            # ... beside it
     (1024, 8, 16, 64, 3, "relu", 2, "train"),                # four tiles a layer: the ring backward, too
     (64, 8, 8, 33, 2, "gelu", 0, "train"),                   # ... one
-    (1024, 8, 16, 2100, 2, "gelu", -1, "forward"),           # all ranks, between the lines, as above
+    (1024, 16, 16, 2100, 2, "gelu", -1, "forward"),          # all ranks, between the lines, as above
     (2048, 16, 64, 1030, 2, "relu", -1, "train"),
     # 32 x 32 tiles, eight teams: weight gradients of more than 768 rows, forward reductions of 512, and of 960 and more
     (256, 4, 8, 1100, 2, "relu", 2, "train"),
