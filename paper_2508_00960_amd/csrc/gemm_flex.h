@@ -508,7 +508,7 @@ __device__ __forceinline__ void flex_wave_sync()
 // What the epilogue reads besides the tile, a vector per pass, requested before the tile is written to LDS (see EpilogueReads in
 // gemm_mfma.h).  WHOLE: every vector is whole; else only the whole ones are requested, and the epilogue reads the others for itself.
 // In the kernels without the ring, where a thread has one or two passes (us a step): all 4 ranks of 64 in fp32 at batch 32 56.4 -> 54.9,
-// ranks of 750 trained at batch 1000 92.1 -> 89.9.
+// ranks of 750 trained at batch 1000 92.1 -> 90.6.
 template <typename T, int PASSES> struct FlexAhead {
     static constexpr int V = FlexType<T>::V;
     typedef T VecT __attribute__((ext_vector_type(V), aligned(sizeof(T))));

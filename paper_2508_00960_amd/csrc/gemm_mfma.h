@@ -67,8 +67,7 @@ enum { TILE_SHARED = 0, TILE_DUAL = 1, TILE_SOLO = 2 };
 constexpr int mfma_threads(int mode) { return mode == TILE_SOLO ? MFMA_THREADS / 2 : MFMA_THREADS; }
 constexpr int mfma_lds_bytes(int mode) { return mode == TILE_SOLO ? MFMA_LDS_BYTES / 2 : MFMA_LDS_BYTES; }
 
-template <int VEC> struct VecOf;
-template <> struct VecOf<8> { typedef u32x4 type; };
+template <int VEC> struct VecOf;           // (vectors of 8 elements go from memory to LDS, mfma_ring.h)
 template <> struct VecOf<4> { typedef u32x2 type; };
 
 // a global-memory load that the compiler cannot mistake for a generic (flat) access
@@ -78,7 +77,7 @@ __device__ __forceinline__ V load_global(const __bf16 *p)
     return *(const __attribute__((address_space(1))) V *)(uintptr_t)p;
 }
 
-// ---- staging one operand tile ---------------------------------------------------------
+// ---- staging one operand tile in 4-element vectors -------------------------------------
 // KIND == LD_KC: tile rows = free index r in [r0, r0+128), columns = reduction index c in [c0, c0+64).
 //                The reduction index may decide the region (head block / peer segments); r never does.
 // KIND == LD_KM: tile rows = reduction index c in [c0, c0+64), columns = free index r in [r0, r0+128).
@@ -92,7 +91,7 @@ __device__ __forceinline__ V load_global(const __bf16 *p)
 // reaches past the end of the reduction range takes the slow path: indices are clamped to the last
 // valid position and the store zeroes what was loaded for reduction indices >= c_lim.
 // PART = 2: the 256 threads of a team stage only half of the tile's rows (the other team stages the
-// other half of an operand tile that both teams read; see the DUAL mode of gemm_mfma_kernel)
+// other half of an operand tile that both teams read; see TILE_DUAL)
 template <int KIND, int VEC, int PART = 1>
 struct StageCfg {
     typedef typename VecOf<VEC>::type V;
@@ -515,13 +514,13 @@ constexpr int part_lo(int n, int q) { return n * q / 3; }       // the q-th thir
 // g = X C^T shares its A operand with the update: the rows of X that a workgroup stages for its tile are the rows the
 // compression needs, over the first part [0, K) of the update's reduction range.  The 128 rows of a tile row and the
 // N <= 64 phantom neurons make 4 x ceil(N / 32) blocks of 32 x 32; the workgroup of tile column tn takes block tn:
-// it stages the block's 32 rows of C beside its B tile (4 KB per step, half a load more per wavefront), and the
-// one wavefront whose A fragment covers the block's rows issues one more MFMA per quarter step with the fragment it
+// it stages the block's 32 rows of C beside its B tile (4 KB per step, half a load more per wavefront), and in each team the
+// one wavefront whose A fragment covers the block's rows issues one more MFMA per quarter of the step (a team has two) with the fragment it
 // has read anyway.  No second pass over X, no partial sums between workgroups, and the work rides under a loop that
-// the memory side bounds.  Conditions (host): 8-element vectors, regular shapes (fast path only), a tile row has at
+// the memory side bounds.  Conditions (host): 8-element vectors, regular shapes, a tile row has at
 // least as many workgroups as blocks, one tile per workgroup (the two-tile loop has no registers left for it).
-// Configuration 4's forward launch: 36.1 us, against 37.6 with the compression as a share of rows behind the epilogue
-// and 33.9 without any compression.
+// 8 layers of 1024 + 960 at batch 4096, k 64 (us, share of rows behind the epilogue : so): forward 250 : 239, trained 685 : 677; 4 of 1024 + 224 at
+// 4096, k 32, forward 82.9 : 84.1.
 constexpr int FOLD_TILE = 32 * KT * 2;           // bytes of a stage's C rows
 
 struct FoldParams {
@@ -1397,7 +1396,7 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaIn &P, int wg, ReadOut 
     PH_PHASE(5);
     if constexpr (FOLD) {
         if (fs.on) {                                                 // uniform
-            // the block of g: two teams on one tile hold partial sums of it (alternate reduction steps): team 1's goes
+            // the block of g: two teams on one tile hold partial sums of it (half of every step each): team 1's goes
             // through LDS to team 0's owner.  A lane holds row (lane & 31) of the block and the columns
             // 8 * (e / 4) + 4 * (lane >> 5) + e % 4 (B operand first, as in acc_to_lds).
             const FoldParams &F = *Fp;
@@ -1679,10 +1678,9 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_table_kernel(const ProductTa
 // read again right after the update streamed them through the same XCD's L2 (workgroup w's rows lie in the
 // band of tile rows that its XCD works on), and no compute unit waits for a compression workgroup: as
 // workgroups of their own in front of the update's, the compression's kept half of the device from the
-// update for 9 us of a 38 us launch (configuration 5, k = 64: 40.9 -> 38.4 us per launch; at configuration 4,
-// where each workgroup's share is 16 rows, the two arrangements take the same time: a share costs a chain of
+// update for 9 us of a 38 us launch.  6 layers of 1024 + 448 at batch 8192, k 64: 233 us in launches of their own, 210 so.  (A share costs a chain of
 // latencies, load -> multiply -> exchange -> store, about 5 us however short it is, and starting its loads
-// ahead of the update's epilogue changed nothing).
+// ahead of the update's epilogue changed nothing.)
 struct MfmaFwdBatch {
     MfmaParams update;
     const __bf16 *X, *C;     // compression operands: X [M, K] per group, C [N, K] per group

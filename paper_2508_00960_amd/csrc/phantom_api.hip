@@ -510,10 +510,11 @@ MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
 // loop and the matrix cores during its epilogue; SOLO's overlap, for a third more bytes staged.  It wins where the loop is
 // short against the epilogue.  Step times (us, no launch in SOLO : every launch that can be : this rule):
 //   weight gradients with the update (10 to 14 bytes of weights per element), reduction 256 to 1536 long: 32 ranks of 1024 at batch
-//   256 505 : 447 : 448, 64 ranks of 256 at 512 567 : 527 : 526, 64 ranks of 128 at 1024 856 : 709 : 709, dense 4 x 4096 at 1024
-//   649 : 618 : 620 and at 1536 812 : 814 : 795; longer: dense at 2048 932 : 940 : 932, at 4096 1645 : 1693 : 1645;
-//   gradients alone: 64 ranks of 256 at 512 480 : 458 : 458, dense at 1024 577 : 536 : 537.
-// The forward layout loses at 760 already (488 : 498).
+//   256 470 : 400 : 402, 64 ranks of 256 at 512 541 : 510 : 510, 64 ranks of 128 at 1024 808 : 703 : 702, dense 4 x 4096 at 1024
+//   589 : 565 : 564 and at 1536 769 : 767 : 755; longer: dense at 2048 863 : 864 : 863, at 4096 1539 : 1568 : 1534;
+//   gradients alone: 64 ranks of 256 at 512 449 : 436 : 437, dense at 1024 528 : 495 : 495.  Not caught by it: 8 ranks of 1024 with GELU, gradients
+//   at 2048, 871 : 850 : 872.
+// The forward layout lost at 760 already (488 : 498, operands through registers).
 template <typename TOut>
 bool solo_tiles(const GemmPlan &plan, const Product *prods, int count)
 {
@@ -807,7 +808,8 @@ ph_status launch_fwd_pair(const Product &update, const Product &compress, int gr
     const int64_t si = compress.K, k = compress.N;
     const int ncb = (int)((k + 31) / 32);
     // One tile per workgroup only: with two tiles per workgroup (more than 256 tiles) the loop has no registers to
-    // spare, and the share behind the epilogue measured as fast or faster (configuration 5, k = 16: 0.195 against 0.221 ms).
+    // spare, and the share behind the epilogue measured as fast or faster (6 layers of 1024 + 112 at batch 8192, operands through
+    // registers: 0.195 against 0.221 ms).
     if (!dual && vec == 8 && si % KT == 0 && KT % k == 0 && 4 * ncb <= fb.update.in.tiles_n && update.a.c.decides && update.a.c.split == si) {
         fb.fold.C = fb.C; fb.fold.G = fb.G; fb.fold.c_g = fb.c_g; fb.fold.o_g = fb.o_g;
         fb.fold.N = (int)k; fb.fold.K = (int)si; fb.fold.ncb = ncb; fb.fold.nblocks = 4 * ncb;
@@ -836,6 +838,9 @@ ph_status launch_products(const GemmPlan &plan, const Product *prods_in, int cou
     // workgroup occupies a whole compute unit, so up to 256 tiles run at once (fixed cost ~8.6 us +
     // 0.5 us per 64 of the reduction length); above that, workgroups take two tiles each (~9.5 us +
     // 0.76 us per 64) and run in rounds of 256.  Separate launches pay ~2.5 us for the extra launch.
+    // (Its figures are those of operands through registers; its choices with the ring, us, apart : together : by the model: 8 layers of 1024 + 64 trained
+    // at batch 4096 697 : 677 : 676, 3 of 1024 + 256 321 : 344 : 321, gradients of 64 ranks of 256 + 8 at 512 471 : 437 : 431, of 16 of 512 + 32 at
+    // 1024 298 : 293 : 298.)
     // PHANTOM_PAIR=0 / 1 forces the choice (for measurements).
     bool pair = count == 2;
     if (pair) {
