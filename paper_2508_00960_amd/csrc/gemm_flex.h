@@ -20,6 +20,7 @@
 // single (unpacked) vector FMAs reach, and a lane's operand is one float, so LDS has an eighth of the bf16 kernel's
 // traffic per cycle and the matrix pipe alone bounds the loop.  Sums in three levels (16 terms, 16 of those, the
 // rest), terms in order: one running fp32 sum over a batch of some thousand rows drifts past 1e-5 of a weight gradient.
+// Widths that 4 divides, reductions of up to 2048 terms: in three bf16 parts instead (below).
 //
 // FINE, bf16: sums in three levels there too (64 terms, 4 of those, the rest).  For problems with an odd width or phantom
 // width, or a tensor beyond 2^31 elements; the others' sums are one running sum per team, as on the 128 x 128 kernels.
@@ -333,7 +334,8 @@ struct FlexLoader {
         for (int j = 0; j < S::NV; ++j) regs[j] = flex_load((const T *)(uintptr_t)q[j]);
     }
 
-    __device__ __forceinline__ void store(const FlexAxis &ax, u32x4 (&regs)[S::NV], T *tile, int c0) const
+    // The vectors of the tile that starts at c0, shifted and masked
+    __device__ __forceinline__ void settle(const FlexAxis &ax, u32x4 (&regs)[S::NV], int c0) const
     {
         if (!whole(ax, c0)) {                          // uniform
             const Col k = column(ax, c0);
@@ -344,6 +346,11 @@ struct FlexLoader {
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+    }
+
+    __device__ __forceinline__ void store(const FlexAxis &ax, u32x4 (&regs)[S::NV], T *tile, int c0) const
+    {
+        settle(ax, regs, c0);
         if constexpr (KIND == FLEX_KC && sizeof(T) == 4) {
             T *dst = tile + row * S::PITCH + (col & ~7) + ((col >> 1) & 2);
 #pragma unroll
@@ -519,7 +526,7 @@ template <typename T, int PASSES> struct FlexAhead {
 };
 
 template <typename T, int TM, int TN, int THREADS, bool WHOLE, bool ROWSUM, typename TOut, int EPI, int PASSES>
-__device__ __forceinline__ void flex_request(FlexAhead<T, PASSES> &R, const FlexIn &P, const FlexOut &Q, int g, int tm, int tn, bool rows)
+__device__ __forceinline__ void flex_request(FlexAhead<T, PASSES> &R, const FlexIn &P, const FlexOut &Q, int g, int tm, int tn, bool rows, int i0 = 0)
 {
     typedef typename FlexAhead<T, PASSES>::VecT VecT;
     typedef typename FlexAhead<T, PASSES>::VecF VecF;
@@ -530,12 +537,12 @@ __device__ __forceinline__ void flex_request(FlexAhead<T, PASSES> &R, const Flex
     // (addresses clamped into the tile's valid part)
     const int n = min(tn * TN + ((int)threadIdx.x % PER_ROW) * V, P.n.total - V);
     const int m0 = tm * TM + (int)threadIdx.x / PER_ROW;
-    auto row = [&](int i) { return (int64_t)min(m0 + i * (THREADS / PER_ROW), P.M - 1); };
+    auto row = [&](int i) { return (int64_t)min(m0 + (i0 + i) * (THREADS / PER_ROW), P.M - 1); };
     const FlexLoc l = flex_locate(P.n, n, Q.o_seg_stride, NO_SKIP);
     const bool whole = WHOLE || l.len - l.in_piece >= V;
     if constexpr (ROWSUM) {
         const int m = tm * TM + (int)threadIdx.x;
-        if (rows && sgd.bias_w && (int)threadIdx.x < TM && m < P.M)
+        if (rows && i0 == 0 && sgd.bias_w && (int)threadIdx.x < TM && m < P.M)
             R.row = gload<float>((sizeof(T) == 2 ? sgd.bias_master : (float *)sgd.bias_w) + (int64_t)g * P.M + m);
     }
     if (!whole || (TM * PER_ROW < THREADS && (int)threadIdx.x >= TM * PER_ROW)) return;
@@ -581,10 +588,11 @@ template <typename T, int PASSES> __device__ __forceinline__ void flex_arrived(F
 }
 
 // What a workgroup of THREADS threads does with its finished tile: TEAMS partial sums of it at ctile (C_BYTES apart), and with rows the
-// parts of A's row sums in extra (THREADS floats).  AHEAD: the passes whose reads are in R (WHOLE as there); 0: none, it reads for itself.
-template <typename T, int TM, int TN, int TEAMS, int THREADS, bool FINE, bool WHOLE, bool ROWSUM, typename TOut, int EPI, int AHEAD>
+// parts of A's row sums in extra (PARTS floats).  AHEAD: the passes whose reads are in R (WHOLE as there), the first ones of the tile; the next ones'
+// are requested as R's are used.  0: none, it reads for itself.
+template <typename T, int TM, int TN, int TEAMS, int THREADS, bool FINE, bool WHOLE, bool ROWSUM, typename TOut, int EPI, int AHEAD, int PARTS = THREADS>
 __device__ __forceinline__ void flex_epilogue(const FlexIn &P, const FlexOut &Q, int g, int tm, int tn, const float *ctile, float *extra, bool rows,
-                                              const FlexAhead<T, (AHEAD > 0 ? AHEAD : 1)> &R)
+                                              FlexAhead<T, (AHEAD > 0 ? AHEAD : 1)> &R)
 {
     typedef FlexTileShape<TM, TN> F;
     constexpr int V = FlexType<T>::V;
@@ -594,8 +602,13 @@ __device__ __forceinline__ void flex_epilogue(const FlexIn &P, const FlexOut &Q,
     if constexpr (ROWSUM) {
         if (rows && (int)threadIdx.x < TM && m0 + (int)threadIdx.x < P.M) {
             float t = 0.f;
+            if constexpr (PARTS >= 8 * TM) {
+#pragma unroll
+                for (int r = threadIdx.x; r < PARTS; r += 4 * TM) t += (extra[r] + extra[r + TM]) + (extra[r + 2 * TM] + extra[r + 3 * TM]);
+            } else {
 #pragma unroll 4
-            for (int r = threadIdx.x; r < THREADS; r += TM) t += extra[r];        // parts of a team, then the next team
+                for (int r = threadIdx.x; r < PARTS; r += TM) t += extra[r];      // parts of a team, then the next team
+            }
             const int64_t at = (int64_t)g * P.M + m0 + threadIdx.x;
             gstore<float>(Q.rowsum + at, t);
             if (sgd.bias_w) {
@@ -619,17 +632,24 @@ __device__ __forceinline__ void flex_epilogue(const FlexIn &P, const FlexOut &Q,
         for (int u = 0; u < V; ++u) r.x[u] = (float)vec[u];
         return r;
     };
-    constexpr int UNROLL = AHEAD > 0 ? AHEAD : 1;
-#pragma unroll UNROLL
-    for (int i = 0; i < (TM * PER_ROW + THREADS - 1) / THREADS; ++i) {
-        const int v = (int)threadIdx.x + i * THREADS;
+    constexpr int GROUP = AHEAD > 0 ? AHEAD : 1, PASSES = (TM * PER_ROW + THREADS - 1) / THREADS;
+    static_assert(PASSES % GROUP == 0, "whole groups");
+#pragma unroll 1
+    for (int i0 = 0; i0 < PASSES; i0 += GROUP) {
+    const FlexAhead<T, GROUP> now = R;
+    if constexpr (AHEAD > 0 && PASSES > GROUP) {
+        if (i0 + GROUP < PASSES) flex_request<T, TM, TN, THREADS, WHOLE, ROWSUM, TOut, EPI>(R, P, Q, g, tm, tn, rows, i0 + GROUP);
+    }
+#pragma unroll
+    for (int h = 0; h < GROUP; ++h) {
+        const int v = (int)threadIdx.x + (i0 + h) * THREADS;
         if (TM * PER_ROW % THREADS && v >= TM * PER_ROW) break;
         const int row = v / PER_ROW, col = (v % PER_ROW) * V, m = m0 + row, n = n0 + col;
         if (m >= P.M || n >= P.n.total) continue;
         const FlexLoc l = flex_locate(P.n, n, Q.o_seg_stride, NO_SKIP);
         const int valid = WHOLE ? V : min(V, l.len - l.in_piece);
         const bool have = AHEAD > 0 && valid == V;     // (WHOLE: known to the compiler)
-        const typename FlexAhead<T, (AHEAD > 0 ? AHEAD : 1)>::Pass &read = R.pass[AHEAD > 0 ? i : 0];
+        const typename FlexAhead<T, GROUP>::Pass &read = now.pass[h];
         FlexRow<V> x;
 #pragma unroll
         for (int h = 0; h < V / 4; ++h) {
@@ -643,7 +663,7 @@ __device__ __forceinline__ void flex_epilogue(const FlexIn &P, const FlexOut &Q,
         FlexRow<V> deriv;
         if (EPI == EPI_BIAS_ACT && ep.mode == EPI_BIAS_ACT) {
             FlexRow<V> bias;
-            if (have) bias = ready(R.bias);
+            if (have) bias = ready(now.bias);
             else bias = flex_read<T, V>((const T *)ep.bias + g * ep.bias_g + n, valid);
             FlexRow<V> pre;
 #pragma unroll
@@ -730,6 +750,7 @@ __device__ __forceinline__ void flex_epilogue(const FlexIn &P, const FlexOut &Q,
             }
             flex_write<T, V, false>((T *)ep.mse_delta + aux_at, dl, valid);
         }
+    }
     }
     if (EPI == EPI_BIAS_ACT && ep.mode == EPI_BIAS_ACT && ep.mse_target) {             // uniform
 #pragma unroll
@@ -883,6 +904,371 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
     if constexpr (AHEAD > 0) flex_arrived(ahead);
     else Q = args_at<FlexOut>(q_at);
     flex_epilogue<T, TM, TN, TEAMS, F::THREADS, FINE, false, ROWSUM, TOut, EPI, AHEAD>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
+}
+
+// ---- fp32 in three bf16 parts -----------------------------------------------------------------------------------------
+// A float is the exact sum of three bf16 numbers, hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid, so a product of floats is nine
+// products of bf16 numbers, of which the three smallest (mid lo, lo mid, lo lo: 2^-27 of the whole and less, of either sign) lie below what one
+// rounding of a float sum costs.  The other six run on v_mfma_f32_32x32x16_bf16: 16 terms take 192 clocks of the matrix pipe against 512 on
+// v_mfma_f32_32x32x2_f32, with one rounding of hi hi for 16 terms instead of 16.
+// Error against 64 bits (2-norm, fp32 instructions : so): 8 ranks of 512 + 32 at batch 1024, output 1.10e-7 : 7.5e-8, gradient of L 1.14e-7 : 8.6e-8;
+// 1024 wide, reduction 1216, 1.10e-7 : 7.9e-8; with every operand positive, output 5.8e-8 : 5.8e-8, gradients at 1024 rows 5.0e-8 : 5.7e-8.
+// A sum that overflows, or has an infinity among its operands (whose parts do not add up to it), leaves an infinity in the sum of hi hi: the
+// workgroup then starts again on the fp32 instructions.  A NaN passes through.
+// What bounds it.  Per SIMD and 32 reduction indices of a 128 x 128 tile: matrix pipe 1536 clocks, splitting and its writes some 240 vector
+// instructions, which the matrix pipe hides about half of, LDS 1400 clocks; 2700 in all.  Without the splitting the launch below takes 34 us, without the
+// LDS writes 36, without the operand reads 37.
+// Launches (us, fp32 instructions : so), 8 ranks of 512 + 32 at batch 1024: update 69.9 : 41.0, input gradient 52.9 : 31.0, weight + compressor
+// gradients with the error compression below 101 : 72, compression 17.8 : 15.9.  Steps: 4 such layers trained with ReLU, whose forward pass stays on the
+// fp32 instructions (flex_fwd), 965 : 756, with GELU at batch 512 585 : 476; 3 of 16 ranks of 256 + 32 with ReLU 726 : 586; 2 layers of 1024 + 224, one
+// rank, forward at batch 4096 247 : 169, at 1024 103 : 67.
+struct FlexParts { u32x2 p[3]; };                      // four consecutive elements
+__device__ __forceinline__ FlexParts flex_parts(u32x4 v)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    FlexParts r;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        f32x2 x = {__uint_as_float(v[2 * h]), __uint_as_float(v[2 * h + 1])};
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+            union { bf16x2 b; uint32_t u; } t;
+            t.b = __builtin_convertvector(x, bf16x2);
+            r.p[part][h] = t.u;
+            if (part < 2) { x[0] -= __uint_as_float(t.u << 16); x[1] -= __uint_as_float(t.u & 0xffff0000u); }
+        }
+    }
+    return r;
+}
+
+// A tile of TILE x TILE, wavefronts of 64 x 32 (TILE 128, eight) or 32 x 32 (64, four).  A stage holds 32 reduction indices of both operands, each
+// as three parts of TILE x 32 bf16 numbers without padding.  The 16-byte vectors of a row are permuted such that the operand reads fall on
+// different banks: FLEX_KC (rows of 32 reduction indices) vector v of row r sits at v ^ ((r >> 2) & 3), FLEX_KM (rows of TILE free indices) as on
+// the ring (ring_swizzle).
+template <int TILE> struct FlexSplit {
+    static constexpr int KT = 32, WN = TILE / 32, THREADS = 128 * WN, MI = TILE / 64;          // 2 x WN wavefronts of MI blocks, one below the other
+    static constexpr int PART = TILE * KT * 2, STAGE = 6 * PART;                               // bytes
+    static constexpr int SETS = TILE == 128 ? 1 : 2;                                           // steps that the loads run ahead of the split
+    static constexpr int MIN_WAVES = 2;
+};
+template <int TILE, int KA, int KB>
+constexpr int flex_split_lds_bytes()
+{
+    typedef FlexSplit<TILE> F;
+    const int again = (FlexStage<float, KA, TILE, F::THREADS>::ELEMS + FlexStage<float, KB, TILE, F::THREADS>::ELEMS) * 4;
+    return flex_max(flex_max(2 * F::STAGE, again), FlexTileShape<TILE, TILE>::C_BYTES + 4 * F::THREADS * 4 + 64);
+}
+// where four elements from column col (a multiple of 4) of row `row` of a part go; a lane's place in it as a matrix instruction's operand: rows
+// rbase .. rbase + 31, first 16 reduction indices; the operand of sub-step kk
+template <int KIND, int TILE> __device__ __forceinline__ int split_at(int row, int col)
+{
+    if (KIND == FLEX_KC) return row * (FlexSplit<TILE>::KT * 2) + (((col >> 3) ^ ((row >> 2) & 3)) << 4) + ((col & 4) << 1);
+    return row * (TILE * 2) + (((col >> 3) ^ ring_swizzle<LD_KM, TILE>(row)) << 4) + ((col & 4) << 1);
+}
+template <int KIND, int TILE> __device__ __forceinline__ int split_lane_at(int rbase, int lane)
+{
+    if (KIND == FLEX_KC) return split_at<FLEX_KC, TILE>(rbase + (lane & 31), (lane >> 5) * 8);
+    return ring_lane_at<LD_KM, TILE>(rbase, lane);
+}
+template <int KIND, int TILE> __device__ __forceinline__ bf16x8 split_operand(uint32_t part, int at, int block, int kk)
+{
+    if (KIND == FLEX_KC) return *lds_at<const bf16x8>(part + (at ^ (kk << 5)) + block * (32 * FlexSplit<TILE>::KT * 2));
+    return ring_operand<LD_KM, TILE>(part, at, block, kk);
+}
+
+// Loads an operand's tiles where 4 divides the widths and phantom widths and 32 bits hold a rank's byte offsets: every vector is then whole, the
+// numbering is the memory's own, and a step inside the head block takes a scalar base and offsets that never change.
+// CUT: the reduction index may be cut (FLEX_KM; with FLEX_KC it may).
+template <int KIND, int TF, int TT, bool CUT>
+struct FlexWhole {
+    typedef FlexStage<float, KIND, TF, TT> S;
+    static constexpr int KT = S::KT;
+    const char *base0, *base1;                 // KM: of this thread's free position
+    uint32_t off0[S::NV], off1[S::NV];         // bytes.  KC: of row j, in region 0 with the thread's column.  KM: of row j from the step's first
+    int col, row, seg, seg_stride, skip;
+    uint32_t magic, ld0, ld1;                  // ld: bytes
+    int split, lim, plain_lim;                 // the reduction index: start of region 1 (or none), its end, end of the simple steps
+
+    __device__ __forceinline__ void init(const FlexOperand &op, const FlexAxis &ax, const FlexAxis &fax, int f0, int g, int tid)
+    {
+        base0 = (const char *)op.p0 + g * op.g0 * 4;
+        base1 = (const char *)op.p1 + g * op.g1 * 4;
+        col = (tid % S::PER_ROW) * 4;
+        row = tid / S::PER_ROW;
+        seg = ax.seg; seg_stride = (int)op.seg_stride; skip = op.skip0 + g * op.skip_g; magic = ax.magic;
+        split = ax.seg > 0 ? ax.head : 0x7fffffff;
+        lim = ax.seg > 0 ? ax.total : ax.head;
+        plain_lim = min(split, lim);
+        ld0 = (uint32_t)op.ld0 * 4u; ld1 = (uint32_t)op.ld1 * 4u;
+        if (KIND == FLEX_KC) {
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                const uint32_t r = (uint32_t)(f0 + min(row + j * S::ROW_STEP, fax.head - 1 - f0));
+                off0[j] = r * ld0 + (uint32_t)col * 4u;
+                off1[j] = r * ld1;
+            }
+        } else {
+            const FlexLoc l = flex_locate(fax, min(f0 + col, fax.total - 4), seg_stride, skip);
+            base0 = (const char *)(uintptr_t)flex_pick<int64_t>(l.region, (int64_t)(uintptr_t)base0, (int64_t)(uintptr_t)base1) + l.off * 4;
+            base1 += l.off * 4;
+            ld0 = flex_pick(l.region, ld0, ld1);
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) off0[j] = (uint32_t)(row + j * S::ROW_STEP) * ld0;
+        }
+    }
+
+    __device__ __forceinline__ void fetch(u32x4 (&regs)[S::NV], int c0 /* uniform */) const
+    {
+        const char *q[S::NV];
+        if (c0 + KT <= plain_lim) {                    // uniform
+            const char *base = base0 + (KIND == FLEX_KC ? (uint64_t)((uint32_t)c0 * 4u) : (uint64_t)(uint32_t)c0 * ld0);
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) q[j] = base + off0[j];
+        } else if (KIND == FLEX_KC) {
+            const int c = min(c0 + col, lim - 4);
+            const bool tail = c >= split;
+            const uint32_t t = tail ? (uint32_t)(c - split) : 0u;
+            uint32_t i = __umulhi(t, magic);
+            i -= i * (uint32_t)seg > t ? 1u : 0u;
+            const int slot = (int)i + ((int)i >= skip ? 1 : 0);
+            const int64_t at = tail ? ((int64_t)slot * seg_stride + (int)(t - i * (uint32_t)seg)) * 4 : (int64_t)(c - col) * 4;
+            const int64_t base = (int64_t)(uintptr_t)(tail ? base1 : base0) + at;
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                const uint32_t o0 = off0[j], o1 = off1[j];
+                q[j] = (const char *)(uintptr_t)(base + (tail ? o1 : o0));
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                const int c = min(c0 + row + j * S::ROW_STEP, lim - 1);
+                const bool tail = CUT && c >= split;
+                q[j] = (tail ? base1 : base0) + (int64_t)(uint32_t)(tail ? c - split : c) * (tail ? ld1 : ld0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < S::NV; ++j) regs[j] = gload<u32x4>(q[j]);
+    }
+
+    // zeros in the place of what lies behind the end
+    __device__ __forceinline__ void settle(u32x4 (&regs)[S::NV], int c0) const
+    {
+        if (c0 + KT > lim) {                           // uniform
+#pragma unroll
+            for (int j = 0; j < S::NV; ++j) {
+                const int c = KIND == FLEX_KC ? c0 + col : c0 + row + j * S::ROW_STEP;
+                regs[j] = c < lim ? regs[j] : u32x4{0u, 0u, 0u, 0u};
+            }
+        }
+    }
+};
+
+// The products that overflow, or have an operand that is not finite, on v_mfma_f32_32x32x2_f32 as in flex_workgroup: parts of an infinity do
+// not add up to it.  One LDS stage.
+template <int TILE, int KA, int KB, int MI>
+__device__ __forceinline__ void flex_split_again(const FlexIn &P, const FlexAxis &ma, int m0, int n0, int g, f32x16 (&acc)[MI][1], float *lds, int wm, int wn, int lane)
+{
+    typedef FlexLoader<float, KA, TILE, FlexSplit<TILE>::THREADS> LA;
+    typedef FlexLoader<float, KB, TILE, FlexSplit<TILE>::THREADS> LB;
+    constexpr int KT = LA::KT;
+    const FlexAxis &ka = P.k;
+    LA la;
+    LB lb;
+    la.init(P.a, ka, ma, m0, g, (int)threadIdx.x);
+    lb.init(P.b, ka, P.n, n0, g, (int)threadIdx.x);
+    f32x16 mid[MI][1];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { acc[i][0][e] = 0.f; mid[i][0][e] = 0.f; }
+    float *ta = lds, *tb = lds + LA::S::ELEMS;
+#pragma unroll 1
+    for (int c0 = 0; c0 < ka.total; c0 += KT) {
+        u32x4 ra[LA::S::NV], rb[LB::S::NV];
+        la.fetch(ka, ra, c0);
+        lb.fetch(ka, rb, c0);
+        __syncthreads();
+        la.store(ka, ra, ta, c0);
+        lb.store(ka, rb, tb, c0);
+        __syncthreads();
+        flex_multiply<KA, KB, LA::S::PITCH, LB::S::PITCH, KT>(mid, ta, tb, wm, wn, lane);
+        if ((c0 / KT) % (256 / KT) == 256 / KT - 1) {  // uniform
+            flex_add(acc, mid);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mid[i][0][e] = 0.f;
+        }
+    }
+    flex_add(acc, mid);
+}
+
+template <int TILE, int KA, int KB, int EPI>
+__device__ __forceinline__ void flex_split_workgroup(const FlexIn &P, int product, int wg, unsigned char *lds)
+{
+    typedef FlexSplit<TILE> F;
+    constexpr int THREADS = F::THREADS, KT = F::KT, MI = F::MI;
+    constexpr bool ROWSUM = KA == FLEX_KM && KB == FLEX_KM;
+    typedef FlexWhole<KA, TILE, THREADS, false> LA;
+    typedef FlexWhole<KB, TILE, THREADS, !ROWSUM> LB;
+    typedef FlexTileShape<TILE, TILE> C;
+    static_assert(LA::KT == KT && LB::KT == KT && LA::S::NV == 2 && LB::S::NV == 2, "");
+
+    const FlexTileAt at = flex_tile_at<true>(P, wg);
+    const int g = at.g, tm = at.tm, tn = at.tn;
+    const int m0 = tm * TILE, n0 = tn * TILE;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave / F::WN) * MI * 32, wn = (wave % F::WN) * 32;
+    FlexAxis ma{};                                     // the row index: never cut
+    ma.head = P.M; ma.head_pad = (P.M + 3) / 4 * 4; ma.total = ma.head_pad;
+    LA la;
+    LB lb;
+    la.init(P.a, P.k, ma, m0, g, tid);
+    lb.init(P.b, P.k, P.n, n0, g, tid);
+
+    // Sums: hi hi of 128 terms (four steps, one rounding for 16 terms) in part, those in acc; the other five products, 2^-8 and less of the whole,
+    // in one running sum
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 acc[MI][1], part[MI], low[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) acc[i][0] = low[i] = zero;
+    const bool rows = ROWSUM && P.rowsum && n0 == 0;   // uniform
+    float row_acc[4] = {0.f, 0.f, 0.f, 0.f}, row_part[4] = {0.f, 0.f, 0.f, 0.f};      // of this thread's four columns of A: 8 terms, the rest
+
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(LdsBytes)lds;
+    const int steps = (la.lim + KT - 1) / KT;
+    u32x4 ra[F::SETS][2], rb[F::SETS][2];              // the tiles of the next steps on their way
+    auto fetch = [&](int set, int i) { la.fetch(ra[set], i * KT); lb.fetch(rb[set], i * KT); };
+    const uint32_t put_a = split_at<KA, TILE>(la.row, la.col), put_b = 3 * F::PART + split_at<KB, TILE>(lb.row, lb.col);
+    constexpr int STEP_A = LA::S::ROW_STEP * (KA == FLEX_KC ? KT : TILE) * 2, STEP_B = LB::S::ROW_STEP * (KB == FLEX_KC ? KT : TILE) * 2;
+    static_assert(LA::S::ROW_STEP % 16 == 0 && LB::S::ROW_STEP % 16 == 0, "the permutation of a thread's vectors is the same for both");
+    // one of the thread's four vectors of a tile (two of A, two of B) to a stage
+    auto put = [&](int set, auto vc, uint32_t stage) {
+        constexpr int v = decltype(vc)::value;
+        const FlexParts x = flex_parts(v < 2 ? ra[set][v & 1] : rb[set][v & 1]);
+        const uint32_t to = stage + (v < 2 ? put_a + v * STEP_A : put_b + (v & 1) * STEP_B);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *lds_at<u32x2>(to + q * F::PART) = x.p[q];
+    };
+    auto settle = [&](int set, int i) {
+        la.settle(ra[set], i * KT);
+        lb.settle(rb[set], i * KT);
+        if constexpr (ROWSUM) {
+            if (rows) {                                // uniform
+#pragma unroll
+                for (int u = 0; u < 4; ++u) row_part[u] += __uint_as_float(ra[set][0][u]) + __uint_as_float(ra[set][1][u]);
+                if (i % 4 == 3) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) { row_acc[u] += row_part[u]; row_part[u] = 0.f; }
+                }
+            }
+        }
+    };
+    const int read_a = split_lane_at<KA, TILE>(wm, lane), read_b = split_lane_at<KB, TILE>(wn, lane);
+    struct Operands { bf16x8 a[MI][3], b[3]; };
+    auto read = [&](Operands &f, uint32_t stage, int kk) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) f.a[i][q] = split_operand<KA, TILE>(stage + q * F::PART, read_a, i, kk);
+            f.b[q] = split_operand<KB, TILE>(stage + (3 + q) * F::PART, read_b, 0, kk);
+        }
+    };
+    // product number n of six (hi hi second: the others' sums are one chain); fresh: part starts anew
+    auto multiply = [&](const Operands &f, auto nc, auto fresh) {
+        constexpr int n = decltype(nc)::value;
+        constexpr int qa = n == 0 ? 2 : n == 3 || n == 4 ? 1 : 0, qb = n == 2 ? 2 : n == 3 || n == 5 ? 1 : 0;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            if constexpr (n == 1) part[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[0], f.a[i][0], decltype(fresh)::value ? zero : part[i], 0, 0, 0);
+            else low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[qb], f.a[i][qa], low[i], 0, 0, 0);
+        }
+    };
+    // On entry to step i its tile is in stage i % 2 and the operands of its first half in f; tile i + 1 (set (i + 1) % SETS), and with two sets
+    // tile i + 2, is in registers or on its way there.  The barrier lies between the halves: by then everybody has read the step's operands and written the
+    // next tile.
+    Operands f, h;
+#define PH_PIN __builtin_amdgcn_sched_barrier(0)
+    auto step = [&](auto set /* of tile i + 1 */, int i, auto fresh) {
+        constexpr int SET = decltype(set)::value;
+        const uint32_t cur = lds0 + (i & 1) * F::STAGE, next = lds0 + (~i & 1) * F::STAGE;
+        read(h, cur, 1);
+        settle(SET, i + 1);
+        PH_PIN;
+        ring_each<6>([&](auto n) {
+            multiply(f, n, fresh);
+            if constexpr (decltype(n)::value < 4) put(SET, n, next);
+            PH_PIN;
+        });
+        fetch(SET, i + 1 + F::SETS);
+        __syncthreads();
+        read(f, next, 0);
+        PH_PIN;
+        ring_each<6>([&](auto n) { multiply(h, n, std::integral_constant<bool, false>{}); });
+    };
+#undef PH_PIN
+    fetch(0, 0);
+    if constexpr (F::SETS == 2) fetch(1, 1);
+    settle(0, 0);
+    ring_each<4>([&](auto v) { put(0, v, lds0); });
+    fetch(0, F::SETS);
+    __syncthreads();
+    read(f, lds0, 0);
+    // (tiles past the end of the range are zeros, read from its last rows)
+    // (128 x 128: unrolled as the other is, the weight-gradient layout has no registers for it and spills, 71 us -> 83 for 352 tiles; 64 x 64: as a
+    // loop within a loop 2-4 % slower)
+    typedef std::integral_constant<int, 0> Set0;
+    typedef std::integral_constant<int, F::SETS - 1> Set1;
+    const std::integral_constant<bool, false> on{};
+#pragma unroll 1
+    for (int i = 0; i < steps; i += 4) {
+        if constexpr (F::SETS == 2) {
+            step(Set1{}, i, std::integral_constant<bool, true>{});
+            step(Set0{}, i + 1, on);
+            if (i + 2 < steps) {                       // uniform
+                step(Set1{}, i + 2, on);
+                step(Set0{}, i + 3, on);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < MI; ++j) part[j] = zero;
+#pragma unroll 1
+            for (int t = i; t < min(i + 4, steps); ++t) step(Set0{}, t, on);
+        }
+#pragma unroll
+        for (int j = 0; j < MI; ++j) acc[j][0] += part[j];
+    }
+    float most = 0.f;                                  // (a NaN is passed over)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) most = fmaxf(most, fabsf(acc[i][0][e]));
+        acc[i][0] += low[i];
+    }
+    if (__syncthreads_or(most == __builtin_inff())) flex_split_again<TILE, KA, KB>(P, ma, m0, n0, g, acc, (float *)lds, wm, wn, lane);       // uniform
+
+    const FlexOut Q = args_at<FlexOut>(offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out));
+    constexpr int AHEAD = EPI == EPI_BIAS_ACT ? 1 : 4;
+    FlexAhead<float, AHEAD> ahead;
+    flex_request<float, TILE, TILE, THREADS, true, ROWSUM, float, EPI>(ahead, P, Q, g, tm, tn, rows);
+    __syncthreads();
+    float *const ctile = (float *)lds;
+    float *const extra = (float *)(lds + C::C_BYTES);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 v = {acc[i][0][4 * q], acc[i][0][4 * q + 1], acc[i][0][4 * q + 2], acc[i][0][4 * q + 3]};
+            *(f32x4 *)(ctile + (wm + 32 * i + (lane & 31)) * C::CPITCH + wn + 8 * q + 4 * (lane >> 5)) = v;
+        }
+    // a thread's sums of its four columns: the epilogue adds those of the rows of threads
+    if constexpr (ROWSUM) {
+        if (rows) *(f32x4 *)(extra + la.row * TILE + la.col) = f32x4{row_acc[0] + row_part[0], row_acc[1] + row_part[1], row_acc[2] + row_part[2], row_acc[3] + row_part[3]};
+    }
+    __syncthreads();
+    flex_arrived(ahead);
+    flex_epilogue<float, TILE, TILE, 1, THREADS, false, true, ROWSUM, float, EPI, AHEAD, 4 * THREADS>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
 }
 
 // ---- bf16 in 16-byte vectors: the ring of mfma_ring.h ----------------------------------------------------------------
@@ -1059,6 +1445,25 @@ __global__ __launch_bounds__((FlexShape<T, TM, TN, TEAMS, FINE>::THREADS), (Flex
     if constexpr (FORWARD) flex_workgroup<T, TM, TN, TEAMS, FINE, FLEX_KC, FLEX_KC, T, EPI_BIAS_ACT>(P, j, wg, smem_raw);
     else if (P.kind == 0) flex_workgroup<T, TM, TN, TEAMS, FINE, FLEX_KC, FLEX_KM, T, EPI_DACT>(P, j, wg, smem_raw);
     else flex_workgroup<T, TM, TN, TEAMS, FINE, FLEX_KM, FLEX_KM, float, EPI_STORE>(P, j, wg, smem_raw);
+}
+
+template <int TILE, bool FORWARD>
+__global__ __launch_bounds__(FlexSplit<TILE>::THREADS, FlexSplit<TILE>::MIN_WAVES) void gemm_flex_split_kernel(FlexBatch batch)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    if (batch.tail.partial && blockIdx.x == 0) {       // uniform
+        finish_loss(batch.tail, (float *)smem_raw);
+        __syncthreads();
+    }
+    int j = 0;
+    while (j + 1 < batch.count && (int)blockIdx.x >= batch.first_wg[j + 1]) ++j;       // uniform
+    const int local = (int)blockIdx.x - batch.first_wg[j];
+    const FlexIn P = args_at<FlexIn>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, in));
+    if (local >= P.total_wg) return;
+    const int wg = flex_xcd_order(local, P.total_wg);
+    if constexpr (FORWARD) flex_split_workgroup<TILE, FLEX_KC, FLEX_KC, EPI_BIAS_ACT>(P, j, wg, smem_raw);
+    else if (P.kind == 0) flex_split_workgroup<TILE, FLEX_KC, FLEX_KM, EPI_DACT>(P, j, wg, smem_raw);
+    else flex_split_workgroup<TILE, FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
 }
 
 template <int TEAMS, int RING, bool FORWARD>

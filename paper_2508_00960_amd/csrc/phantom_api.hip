@@ -76,6 +76,7 @@ struct Geo {
     size_t esz;       // bytes per element of the storage type
     int vec;          // bf16: widest vector (8 or 4 elements) dividing si, so and k; 0: the kernels of gemm_flex.h only
     bool fine;        // bf16: ... in their FINE form
+    bool whole;       // fp32: 4 divides si, so and k, and 32 bits hold a byte offset inside a rank's share of a tensor (FlexWhole)
 };
 
 // Checks the problem and fills in the shapes of layer `layer` (0-based).
@@ -123,6 +124,7 @@ ph_status make_geo(const ph_problem *pr, Geo &g, int layer = 0)
     {
         const int64_t wide = std::max(si, so), slots = g.all ? g.p : g.q;
         const int64_t largest = std::max({g.B * wide, slots * g.B * g.k, so * si, slots * so * g.k, g.k * si});
+        g.whole = pr->dtype == PH_F32 && si % 4 == 0 && so % 4 == 0 && g.k % 4 == 0 && largest < (int64_t)1 << 30 && g.q * g.k * g.k < (int64_t)1 << 32;
         if (largest > 0x7fffffff) {
             g.vec = 0;
             g.fine = pr->dtype == PH_BF16;
@@ -908,23 +910,42 @@ FlexOperand flex_operand_of(const View &v, bool km, const FlexAxis &k, const Fle
 // 512 / 1024 / 2048 / 8192 41.7 : 42.7, 49 : 49.5, 64.2 : 59.7, 156 : 118, 256 wide at 1024 / 4096 52.4 : 52.6, 100 : 85 (at most 24 tiles of 64 x 64: 101), 512 + 56 at
 // 8192 168 : 150; 128 + 16 at batch 64, whatever its tiles, 56 : 74.  Eight teams are eight partial sums, two of the ring's four: error of the weight
 // gradients against 64 bits (2-norm), dense 256 at 256 / 768 / 1000 / 4096 rows 4.7e-8 : 4.9e-8, 6.7e-8 : 6.9e-8, 7.2e-8 : 6.7e-8, 1.0e-7 : 7.3e-8.
-// fp32 adds its terms in the order of the reduction index (gemm_flex.h) and so has one team, except where eight teams
-// take one group of 16 terms each, the first level of its sums.
-enum FlexTile { FLEX_64, FLEX_64_2, FLEX_32_8 };
+// fp32: reductions of at most 128 terms and few tiles on 32 x 32 tiles, eight teams with one group of 16 terms each, the first level of that kernel's
+// sums.  Where 4 divides the widths and the reduction is at most 2048 long, in three bf16 parts: 128 x 128 tiles, one to a compute unit, or 64 x 64
+// ones, two to a unit, which split every operand twice as often.  A model of both in ns: 12000 and 37 a term of the rounds (rounded up to the
+// shortest product's length) and 6000 if there is more than one; 5000 and 23 a term of one tile, or 15 (weight gradients 17) a term of a compute
+// unit's share if that is more.  Measured (us, 64 : 128; 2 layers of 1024 + 224 forward, reduction 1248, at 144 / 180 / 252 / 288 / 360 / 432 tiles of
+// 128 x 128) 96 : 111, 116 : 111, 163 : 125, 174 : 205, 210 : 228, 252 : 230; weight gradients of 8 ranks of 512 + 32 at batch 1024 with the next
+// layer's error compression (224 + 128 tiles) 75 : 72.
+// Longer reductions, where two levels of sums lose to three, and other widths stay on the fp32 matrix instructions.
+enum FlexTile { FLEX_64, FLEX_64_2, FLEX_32_8, FLEX_SPLIT_64, FLEX_SPLIT_128 };      // (FLEX_SPLIT: fp32 in three bf16 parts)
 
 template <typename T>
-FlexTile flex_tile_for(const Product *prods, int count, int groups, bool forward, bool ring)
+FlexTile flex_tile_for(const Product *prods, int count, int groups, bool forward, bool ring, bool whole)
 {
     int64_t tiles = 0, small = 0, longest = 0;         // of 64 x 64, of 32 x 32
+    int64_t large_tiles = 0, work = 0, large = 0, longest_k = 0, shortest = INT64_MAX;      // tiles of 128 x 128; terms of all 64 x 64 ones, of all 128 x 128 ones, of the products
     for (int i = 0; i < count; ++i) {
         tiles += ((prods[i].M + 63) / 64) * ((prods[i].N + 63) / 64) * groups;
         small += ((prods[i].M + 31) / 32) * ((prods[i].N + 31) / 32) * groups;
+        work += ((prods[i].M + 63) / 64) * ((prods[i].N + 63) / 64) * groups * prods[i].K;
+        const int64_t t128 = ((prods[i].M + 127) / 128) * ((prods[i].N + 127) / 128) * groups;
+        large_tiles += t128;
+        large += t128 * prods[i].K;
+        longest_k = std::max(longest_k, prods[i].K); shortest = std::min(shortest, prods[i].K);
         const int64_t pad = prods[i].km ? 0 : ((prods[i].K - prods[i].a.c.split) / std::max(prods[i].a.c.seg, 1) + 1) * (FlexType<T>::V - 1);
         longest = std::max(longest, prods[i].K + (prods[i].a.c.decides && !ring ? pad : 0));      // (at most; the numbering pads pieces to vectors)
     }
     static const char *force = tuning_env("PHANTOM_FLEX_TILE");
     if (force) return (FlexTile)atoi(force);
-    if (sizeof(T) == 4) return tiles <= 128 && longest <= 8 * 16 ? FLEX_32_8 : FLEX_64;
+    if (sizeof(T) == 4) {
+        if (tiles <= 128 && longest <= 8 * 16) return FLEX_32_8;
+        if (longest > 2048 || !whole) return FLEX_64;
+        const bool fits = large_tiles <= 256;
+        const int64_t rounds = fits ? longest_k : std::max(longest_k, (large + 256 * shortest - 1) / (256 * shortest) * shortest);
+        const int64_t ns_128 = 12000 + 37 * rounds + (fits ? 0 : 6000), ns_64 = 5000 + std::max(23 * longest_k, (prods[0].km ? 17 : 15) * work / 256);
+        return ns_128 < ns_64 ? FLEX_SPLIT_128 : FLEX_SPLIT_64;
+    }
     const bool few = !ring ? tiles <= 24 : forward ? small <= 256 && (longest >= 960 || longest == 8 * 64) : small <= 96 && longest > 768;
     return tiles > 256 ? FLEX_64 : few ? FLEX_32_8 : FLEX_64_2;
 }
@@ -945,12 +966,32 @@ ph_status launch_flex_kernel(const FlexBatch &batch, unsigned total_wg, hipStrea
     return check_launch(what);
 }
 
+template <int TILE, bool FORWARD>
+ph_status launch_flex_split(const FlexBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
+{
+    auto kern = gemm_flex_split_kernel<TILE, FORWARD>;
+    constexpr int LDS = FORWARD ? flex_split_lds_bytes<TILE, FLEX_KC, FLEX_KC>()
+                                : flex_max(flex_split_lds_bytes<TILE, FLEX_KC, FLEX_KM>(), flex_split_lds_bytes<TILE, FLEX_KM, FLEX_KM>());
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
+        configured = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(total_wg), dim3(FlexSplit<TILE>::THREADS), LDS, st, batch);
+    return check_launch(what);
+}
+
 template <typename T, bool FORWARD, bool FINE>
 ph_status launch_flex_tile(const FlexBatch &batch, FlexTile tile, unsigned total_wg, hipStream_t st, const char *what)
 {
     if (tile == FLEX_64) return launch_flex_kernel<T, 64, 64, 1, FORWARD, FINE>(batch, total_wg, st, what);
     if constexpr (sizeof(T) == 2)
         if (tile == FLEX_64_2) return launch_flex_kernel<T, 64, 64, 2, FORWARD, FINE>(batch, total_wg, st, what);
+    if constexpr (sizeof(T) == 4) {
+        if (tile == FLEX_SPLIT_128) return launch_flex_split<128, FORWARD>(batch, total_wg, st, what);
+        if (tile == FLEX_SPLIT_64) return launch_flex_split<64, FORWARD>(batch, total_wg, st, what);
+    }
     return launch_flex_kernel<T, 32, 32, 8, FORWARD, FINE>(batch, total_wg, st, what);
 }
 
@@ -983,8 +1024,8 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
         if (prods_in[i].M > 0 && prods_in[i].N > 0) prods[count++] = prods_in[i];
     const int groups = g.groups;
     if (count == 0 || groups <= 0) return PH_OK;
-    const FlexTile tile = flex_tile_for<T>(prods, count, groups, forward, g.vec == 8);
-    const int t = tile == FLEX_32_8 ? 32 : 64;
+    const FlexTile tile = flex_tile_for<T>(prods, count, groups, forward, g.vec == 8, g.whole);
+    const int t = tile == FLEX_32_8 ? 32 : tile == FLEX_SPLIT_128 ? 128 : 64;
     constexpr int V = FlexType<T>::V;
     FlexBatch batch{};
     batch.count = count;
@@ -1063,6 +1104,7 @@ struct FwdArgs {
     const struct OutputError *mse;   // step only, last layer: form the MSE output error in the update's epilogue
     ClearList *clear;                // step only: buffers to clear; a launch that can do it on its way empties the list
     std::vector<Product> *later;     // step only, one rank: takes a compression that would leave compute units idle (launch_many)
+    bool forward_only;               // step only: there is no backward pass
 };
 
 // What the last layer's update needs to leave the output error of the MSE loss behind (Epilogue::mse_*).
@@ -1119,9 +1161,13 @@ FwdProducts make_fwd_products(const Geo &g, const FwdArgs &f)
 
 // Forward through gemm_flex.h.  mse_tiles: with f.mse, the number of partial sums of the loss it leaves.
 template <typename T>
-ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tiles = nullptr)
+ph_status flex_fwd(const Geo &layer, const FwdArgs &f, hipStream_t st, int *mse_tiles = nullptr)
 {
-    const FwdProducts pr = make_fwd_products(g, f);
+    const FwdProducts pr = make_fwd_products(layer, f);
+    // Not in three bf16 parts where a backward pass takes ReLU' from the sums: one that rounding alone puts on the other side of 0 changes a row of
+    // the gradients (8 ranks of 512 + 32, 4 layers, batch 1024: some 2 of 17 million a step, 1e-4 of a weight's size), so these sums keep their order.
+    Geo g = layer;
+    g.whole = g.whole && (g.act != PH_ACT_RELU || f.forward_only);
     if (g.all) {
         // every rank reads the other ranks' g: the compression of all ranks has to finish first
         PH_TRY((launch_flex<T>(&pr.compress, 1, true, g, LossTail{}, st, "compression")));
@@ -1552,6 +1598,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
     for (const Geo &x : geos) {                                // (a backward launch carries products of two layers)
         g.fine = g.fine || x.fine;
         g.vec = std::min(g.vec, x.vec);
+        g.whole = g.whole && x.whole;
     }
     const int L = g.layers;
     const int64_t B = g.B, q = g.q;
@@ -1570,7 +1617,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
         f.Lw = a.Lw[l]; f.Cw = q ? a.Cw[l] : nullptr; f.Dw = q ? a.Dw[l] : nullptr; f.bias = a.bias[l];
         f.G = (q && !g.all) ? a.G[l] : nullptr;
         f.Y = w.Y[(size_t)l]; f.g_own = w.G[(size_t)l]; f.A_save = train ? w.A[(size_t)l] : nullptr;
-        f.a_f32 = !save_deriv; f.a_deriv = save_deriv;
+        f.a_f32 = !save_deriv; f.a_deriv = save_deriv; f.forward_only = !train;
         f.mse = train && l == L - 1 ? &oe : nullptr;
         PH_TRY(flex_fwd<T>(geos[(size_t)l], f, st, f.mse ? &mse_tiles : nullptr));
     }
