@@ -90,6 +90,6 @@ __device__ __forceinline__ int div_by(int x, int d, uint32_t magic)
     const uint32_t q = __umulhi((uint32_t)x, magic);       // at most one too high
     return d == 1 ? x : (int)(q - (q * (uint32_t)d > (uint32_t)x ? 1u : 0u));
 }
-inline uint32_t div_magic(int d) { return d > 1 ? (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d) : 0u; }
+__host__ __device__ constexpr uint32_t div_magic(int d) { return d > 1 ? (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d) : 0u; }
 
 }  // namespace phantom

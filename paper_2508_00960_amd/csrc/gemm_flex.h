@@ -1308,8 +1308,9 @@ __device__ __forceinline__ RingOperand flex_ring_init(const FlexOperand &op, con
     return s;
 }
 
-template <int TEAMS, int RING, int KA, int KB, typename TOut, int EPI>
-__device__ __forceinline__ void flex_ring_workgroup(const FlexIn &P, int product, int wg, unsigned char *lds)
+// read_out(): the epilogue's part of the parameters, read behind the reduction.
+template <int TEAMS, int RING, int KA, int KB, typename TOut, int EPI, typename ReadOut>
+__device__ __forceinline__ void flex_ring_workgroup(const FlexIn &P, ReadOut read_out, int wg, unsigned char *lds)
 {
     constexpr int TILE = FLEX_RING_TILE, WAVES = 4 * TEAMS;
     constexpr int A_BYTES = TILE * KT * 2, STAGE = 2 * A_BYTES;
@@ -1397,7 +1398,7 @@ __device__ __forceinline__ void flex_ring_workgroup(const FlexIn &P, int product
     }
     __syncthreads();
 
-    const FlexOut Q = args_at<FlexOut>(offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out));
+    const FlexOut Q = read_out();
     constexpr int PASSES = TILE * TILE / 8 / (WAVES * 64);
     FlexAhead<bf16_t, PASSES> ahead;
     flex_request<bf16_t, TILE, TILE, WAVES * 64, true, ROWSUM, TOut, EPI>(ahead, P, Q, g, tm, tn, rows);
@@ -1480,9 +1481,52 @@ __global__ __launch_bounds__(TEAMS * 256, TEAMS == 1 ? 3 : 2) void gemm_flex_rin
     const FlexIn P = args_at<FlexIn>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, in));
     if (local >= P.total_wg) return;
     const int wg = flex_xcd_order(local, P.total_wg);
-    if constexpr (FORWARD) flex_ring_workgroup<TEAMS, RING, LD_KC, LD_KC, bf16_t, EPI_BIAS_ACT>(P, j, wg, smem_raw);
-    else if (P.kind == 0) flex_ring_workgroup<TEAMS, RING, LD_KC, LD_KM, bf16_t, EPI_DACT>(P, j, wg, smem_raw);
-    else flex_ring_workgroup<TEAMS, RING, LD_KM, LD_KM, float, EPI_STORE>(P, j, wg, smem_raw);
+    auto out = [=]() { return args_at<FlexOut>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, out)); };
+    if constexpr (FORWARD) flex_ring_workgroup<TEAMS, RING, LD_KC, LD_KC, bf16_t, EPI_BIAS_ACT>(P, out, wg, smem_raw);
+    else if (P.kind == 0) flex_ring_workgroup<TEAMS, RING, LD_KC, LD_KM, bf16_t, EPI_DACT>(P, out, wg, smem_raw);
+    else flex_ring_workgroup<TEAMS, RING, LD_KM, LD_KM, float, EPI_STORE>(P, out, wg, smem_raw);
+}
+
+// One rank's compressions g = C y of several layers with at most 64 phantom neurons (8 divides them and the widths) in one launch, behind the
+// forward pass: nothing on the rank waits for them.  A tile of 64 rows streams its rows of X once; the launch is bound by that, 64 MB for 8 layers
+// of 1024 at batch 4096.
+constexpr int COMPRESS_LAYERS = 32;
+struct CompressMany {
+    struct Layer {
+        const void *X, *C;   // [M, K], [N, K]
+        void *G;             // [M, N]
+        int M, N, K;
+        uint32_t magic_tiles, magic_last;      // see FlexIn
+    } at[COMPRESS_LAYERS];
+    int count;
+    int first_wg[COMPRESS_LAYERS + 1];         // multiples of 8
+};
+static_assert(sizeof(CompressMany) <= 3840, "travels as kernel arguments (4 KB with the hidden ones)");
+
+__global__ __launch_bounds__(256, 3) void compress_many_kernel(CompressMany many)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    int j = 0;
+    while (j + 1 < many.count && (int)blockIdx.x >= many.first_wg[j + 1]) ++j;         // uniform
+    const int local = (int)blockIdx.x - many.first_wg[j];
+    const CompressMany::Layer l = args_at<CompressMany::Layer>(offsetof(CompressMany, at) + (size_t)j * sizeof(CompressMany::Layer));
+    FlexIn P{};
+    P.M = l.M;
+    P.tiles_m = (l.M + FLEX_RING_TILE - 1) / FLEX_RING_TILE; P.tiles_n = 1; P.total_wg = P.tiles_m;
+    if (local >= P.total_wg) return;
+    P.magic_tiles = l.magic_tiles; P.magic_band = div_magic(FLEX_RASTER); P.magic_last = l.magic_last;
+    P.a.p0 = l.X; P.b.p0 = l.C;
+    P.a.ld0 = P.b.ld0 = l.K;
+    P.a.skip0 = P.b.skip0 = NO_SKIP;
+    P.k.head = P.k.head_pad = P.k.total = l.K;
+    P.n.head = P.n.head_pad = P.n.total = l.N;
+    auto out = [=]() {
+        FlexOut Q{};
+        Q.o0 = l.G; Q.o_ld0 = l.N;
+        Q.ep.mode = EPI_STORE;
+        return Q;
+    };
+    flex_ring_workgroup<1, 3, LD_KC, LD_KC, bf16_t, EPI_STORE>(P, out, flex_xcd_order(local, P.total_wg), smem_raw);
 }
 
 }  // namespace phantom

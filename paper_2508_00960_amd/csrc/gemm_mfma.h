@@ -34,7 +34,7 @@
 //   gemm_mfma_uniform_kernel, gemm_mfma_table_kernel
 //                          one rank: the weight + compressor gradients of all layers, with parameter blocks in the kernel
 //                          arguments (layers of the same shapes) or in device memory
-//   gemm_mfma_many_kernel  one rank: the compressions of all layers
+//   gemm_mfma_many_kernel  one rank: the compressions of all layers, more than 64 phantom neurons
 //   gemm_mfma_tail_kernel  weight + compressor gradients with riders of other layouts (the error compression of
 //                          the layer below, the loss)
 //   gemm_mfma_fwd_kernel   a rank's layer update with the thin compression shared out over its workgroups
@@ -519,8 +519,8 @@ constexpr int part_lo(int n, int q) { return n * q / 3; }       // the q-th thir
 // has read anyway.  No second pass over X, no partial sums between workgroups, and the work rides under a loop that
 // the memory side bounds.  Conditions (host): 8-element vectors, regular shapes, a tile row has at
 // least as many workgroups as blocks, one tile per workgroup (the two-tile loop has no registers left for it).
-// 8 layers of 1024 + 960 at batch 4096, k 64 (us, share of rows behind the epilogue : so): forward 250 : 239, trained 685 : 677; 4 of 1024 + 224 at
-// 4096, k 32, forward 82.9 : 84.1.
+// For a single layer, as a layer call has it: 4.9 us of a launch (1024 + 960 at batch 4096, k 64), and a launch of its own takes 8.  A step of two layers
+// or more compresses all of them behind the forward pass (compress_many_kernel): forward of 8 such layers 221 -> 199 us, of 2 55.3 -> 52.3.
 constexpr int FOLD_TILE = 32 * KT * 2;           // bytes of a stage's C rows
 
 struct FoldParams {
@@ -1045,12 +1045,18 @@ __device__ __forceinline__ void epilogue_pieces_from_lds(const MfmaIn &P, const 
 // layer update with the compression, the error compression with the input gradient, the weight
 // gradients with the compressor gradient): their workgroups run side by side instead of one thin
 // launch waiting for the other.
+struct MfmaRiders {      // what a launch of gemm_mfma_kernel may do on its way
+    ClearList clear;     // forward layout: buffers that later launches of a training step add into
+    LossTail tail;       // weight-gradient layout: the first workgroup finishes the loss (partial == NULL: nothing to do)
+};
 struct MfmaBatch {
     MfmaParams p[2];
     int count;
     int total_wg;
     int first_wg;        // = p[0].total_wg
+    MfmaRiders ride;
 };
+static_assert(sizeof(MfmaBatch) <= 3840, "a batch travels as kernel arguments (4 KB with the hidden ones)");
 
 
 // Reads the epilogue's part of the parameter block that starts at a byte offset of the kernel's argument.
@@ -1435,6 +1441,15 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaIn &P, int wg, ReadOut 
 template <int KA, int KB, int VA, int VB, typename TOut, bool PAIR, int MODE, int EPI>
 __global__ __launch_bounds__(mfma_threads(MODE), MODE == TILE_SOLO ? 2 : 1) void gemm_mfma_kernel(MfmaBatch batch)
 {
+    // (launches of their own took 4.8 us: dense 4 x 4096 trained at batch 1024, which has both, 573 -> 563 us a step)
+    if constexpr (EPI == EPI_BIAS_ACT) clear_rider(batch.ride.clear, (int)blockIdx.x, (int)gridDim.x, mfma_threads(MODE));
+    if constexpr (sizeof(TOut) == 4) {
+        if (blockIdx.x == 0 && batch.ride.tail.partial) {      // uniform
+            extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+            finish_loss(batch.ride.tail, (float *)smem_raw);
+            __syncthreads();
+        }
+    }
     int wg = xcd_order(blockIdx.x, 0, batch.total_wg);
     const bool second = PAIR && wg >= batch.first_wg;
     if (second) wg -= batch.first_wg;
@@ -1680,7 +1695,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_table_kernel(const ProductTa
 // workgroups of their own in front of the update's, the compression's kept half of the device from the
 // update for 9 us of a 38 us launch.  6 layers of 1024 + 448 at batch 8192, k 64: 233 us in launches of their own, 210 so.  (A share costs a chain of
 // latencies, load -> multiply -> exchange -> store, about 5 us however short it is, and starting its loads
-// ahead of the update's epilogue changed nothing.)
+// ahead of the update's epilogue changed nothing.)  Steps of two layers or more with 8-element vectors do without: see compress_many_kernel, 6 such layers
+// 223 -> 190 us.
 struct MfmaFwdBatch {
     MfmaParams update;
     const __bf16 *X, *C;     // compression operands: X [M, K] per group, C [N, K] per group

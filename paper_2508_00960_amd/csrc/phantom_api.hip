@@ -530,7 +530,7 @@ bool solo_tiles(const GemmPlan &plan, const Product *prods, int count)
 
 // bf16 operands on the matrix cores: one product, or two of the same layout side by side in one launch
 template <typename TOut>
-ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int groups, hipStream_t st, const char *what)
+ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int groups, const MfmaRiders &ride, hipStream_t st, const char *what)
 {
     const Product &first = prods[0];
     const int64_t tiles = tiles_of(first.M, first.N) * groups;
@@ -548,6 +548,7 @@ ph_status launch_mfma(const GemmPlan &plan, const Product *prods, int count, int
     batch.p[0] = mfma_params(first, groups, 1, dual);
     batch.total_wg = batch.p[0].in.total_wg;
     batch.first_wg = batch.p[0].in.total_wg;
+    batch.ride = ride;
     if (count == 2) {
         batch.p[1] = mfma_params(prods[1], groups, 1, dual);
         batch.total_wg += batch.p[1].in.total_wg;
@@ -822,10 +823,10 @@ ph_status launch_fwd_pair(const Product &update, const Product &compress, int gr
 }
 
 // Runs one product, or two independent ones of the same kind (names: `what` for the pair, `what_first` / `what_second`
-// when they run as launches of their own).
+// when they run as launches of their own).  ride: taken along by the first launch.
 template <typename TIn, typename TOut>
 ph_status launch_products(const GemmPlan &plan, const Product *prods_in, int count_in, int groups, hipStream_t st,
-                          const char *what, const char *what_first = nullptr, const char *what_second = nullptr)
+                          const char *what, const char *what_first = nullptr, const char *what_second = nullptr, const MfmaRiders &ride = MfmaRiders{})
 {
     Product prods[2];
     const char *names[2];
@@ -859,10 +860,10 @@ ph_status launch_products(const GemmPlan &plan, const Product *prods_in, int cou
         static const char *force = tuning_env("PHANTOM_PAIR");
         if (force) pair = force[0] == '1';
     }
-    if (pair || count == 1) return launch_mfma<TOut>(plan, prods, count, groups, st, count == 2 ? what : names[0]);
+    if (pair || count == 1) return launch_mfma<TOut>(plan, prods, count, groups, ride, st, count == 2 ? what : names[0]);
     GemmPlan single = plan;
-    PH_TRY(launch_mfma<TOut>(single, &prods[0], 1, groups, st, names[0]));
-    return launch_mfma<TOut>(single, &prods[1], 1, groups, st, names[1]);
+    PH_TRY(launch_mfma<TOut>(single, &prods[0], 1, groups, ride, st, names[0]));
+    return launch_mfma<TOut>(single, &prods[1], 1, groups, MfmaRiders{}, st, names[1]);
 }
 
 // ---- products of any shape and storage type (gemm_flex.h) ------------------------------------
@@ -1086,6 +1087,25 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
     return forward ? launch_flex_tile<T, true, false>(batch, tile, total, st, what) : launch_flex_tile<T, false, false>(batch, tile, total, st, what);
 }
 
+// The compressions of several layers of one rank in one launch (compress_many_kernel).
+ph_status launch_compressions(const std::vector<Product> &prods, hipStream_t st, const char *what)
+{
+    for (size_t at = 0; at < prods.size(); at += COMPRESS_LAYERS) {
+        CompressMany many{};
+        many.count = (int)std::min<size_t>(COMPRESS_LAYERS, prods.size() - at);
+        for (int i = 0; i < many.count; ++i) {
+            const Product &pr = prods[at + i];
+            const int tiles = (int)((pr.M + FLEX_RING_TILE - 1) / FLEX_RING_TILE);
+            many.at[i] = {pr.a.p0, pr.b.p0, pr.o.p0, (int)pr.M, (int)pr.N, (int)pr.K, div_magic(tiles), div_magic(tiles % FLEX_RASTER)};
+            many.first_wg[i + 1] = many.first_wg[i] + ((tiles + 7) & ~7);
+        }
+        ProfScope prof(what, prods[at].M, prods[at].N, prods[at].K, many.count, st);
+        hipLaunchKernelGGL(compress_many_kernel, dim3((unsigned)many.first_wg[many.count]), dim3(256), (flex_ring_lds<1, 3>()), st, many);
+        PH_TRY(check_launch(what));
+    }
+    return PH_OK;
+}
+
 Epilogue epi_store()
 {
     Epilogue e{};
@@ -1103,7 +1123,8 @@ struct FwdArgs {
     bool a_bits;  // step only, ReLU: A_save receives one bit per element (stored output > 0)
     const struct OutputError *mse;   // step only, last layer: form the MSE output error in the update's epilogue
     ClearList *clear;                // step only: buffers to clear; a launch that can do it on its way empties the list
-    std::vector<Product> *later;     // step only, one rank: takes a compression that would leave compute units idle (launch_many)
+    std::vector<Product> *later;     // step only, one rank: takes a compression that would leave compute units idle (launch_many, or
+                                     //   launch_compressions where it is thin)
     bool forward_only;               // step only: there is no backward pass
 };
 
@@ -1221,19 +1242,21 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
     // one rank: the peers' g are inputs, so the rank's own compression runs beside the update when the two
     // fit the device together
     const int64_t tiles_both = (tiles_of(B, so) + tiles_of(B, k)) * g.groups;
+    const auto riders = [&]() { MfmaRiders r{}; r.clear = take_clear(); return r; };
     if (thin && tiles_both > 256) {
-        static const char *force = tuning_env("PHANTOM_FWD_PAIR");         // =0: two launches (for measurements)
-        if (!(force && force[0] == '0'))
-            return launch_fwd_pair(update, compress, g.groups, g.vec, take_clear(), st, "layer update + thin compression");
-        PH_TRY(launch_thin());
-        return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update");
+        static const char *force = tuning_env("PHANTOM_FWD_PAIR");         // =0: with the update (for measurements)
+        if (f.later && g.vec == 8 && !(force && force[0] == '0')) {
+            f.later->push_back(compress);
+            return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update", nullptr, nullptr, riders());
+        }
+        return launch_fwd_pair(update, compress, g.groups, g.vec, take_clear(), st, "layer update + thin compression");
     }
     if (f.later && q > 0 && k > THIN_MAX_N) {
         f.later->push_back(compress);
-        return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update");
+        return launch_products<T, T>(plan, &update, 1, g.groups, st, "layer update", nullptr, nullptr, riders());
     }
     Product both[2] = {update, compress};
-    return launch_products<T, T>(plan, both, 2, g.groups, st, "layer update + compression", "layer update", "compression");
+    return launch_products<T, T>(plan, both, 2, g.groups, st, "layer update + compression", "layer update", "compression", riders());
 }
 
 // ---- backward of one layer (Eq. (deltaL), (backprop), (bpb)-(bpD)) ---------------------------
@@ -1517,10 +1540,12 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
             return PH_OK;
         }
     }
+    MfmaRiders ride{};
+    ride.tail = take_tail();
     Product grads[2] = {dw, dc};
     // (send_rides never gets here: its launch above carries the error compression)
     return launch_products<T, float>(GemmPlan{LD_KM, LD_KM, g.vec}, grads, q > 0 ? 2 : 1, g.groups, st,
-                                     "weight + compressor gradients", "weight gradients", "compressor gradient");
+                                     "weight + compressor gradients", "weight gradients", "compressor gradient", ride);
 }
 
 ph_status check_fwd_args(const Geo &g, const FwdArgs &f)
@@ -1776,11 +1801,14 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
                   false, !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr, &clear, g.all || L == 1 ? nullptr : &later};
         PH_TRY(fwd_impl(geos[(size_t)l], f, st));
     }
+    std::vector<Product> thin;
+    later.erase(std::remove_if(later.begin(), later.end(), [&](const Product &pr) { if (pr.N <= THIN_MAX_N) thin.push_back(pr); return pr.N <= THIN_MAX_N; }), later.end());
     if (!later.empty()) {
         int vec = 8;
         for (const Geo &x : geos) vec = std::min(vec, x.vec);
         PH_TRY(launch_many(later, vec, st, "compressions of all layers"));
     }
+    if (!thin.empty()) PH_TRY(launch_compressions(thin, st, "compressions of all layers"));
     PH_TRY(forward_taps<T>(geos, a, w, st));
     if (!train) return PH_OK;
 

@@ -31,7 +31,7 @@ FAMILIES = [
     (("gemm_mfma_fwd_kernel",), "fwd", ("layer update + thin compression",)),
     (("gemm_mfma_tail_kernel",), "tail", ("weight + compressor gradients |",)),
     (("gemm_mfma_table_kernel", "gemm_mfma_uniform_kernel"), "table", ("weight + compressor gradients of all layers",)),
-    (("gemm_mfma_many_kernel",), "many", ("compression",)),
+    (("gemm_mfma_many_kernel", "compress_many_kernel"), "many", ("compression",)),
     (("table_upload_kernel",), "upload", ("parameter table",)),
     (("gemm_mfma_kernel<0, 0", "gemm_mfma_kernelILi0ELi0E"), "kc_kc", ("layer update", "compression")),
     (("gemm_mfma_kernel<0, 1", "gemm_mfma_kernelILi0ELi1E"), "kc_km", ("input gradient", "error compression")),
@@ -40,7 +40,7 @@ FAMILIES = [
     (("reduce_scatter_kernel",), "rs", ("reduce-scatter",)),
     (("colsum_kernel",), "colsum", ("bias gradient",)),
     (("loss_kernel",), "loss", ("loss",)),
-    (("gemm_flex_kernel", "gemm_flex_ring_kernel"), "flex", ("layer update", "compression", "input gradient", "error compression", "weight + compressor gradients",
+    (("gemm_flex_kernel", "gemm_flex_ring_kernel", "gemm_flex_split_kernel"), "flex", ("layer update", "compression", "input gradient", "error compression", "weight + compressor gradients",
                                      "gradients")),
     (("delta_kernel",), "delta", ("local error",)),
     (("fill_zero_kernel", "clear_kernel"), "fill", ("clear",)),
