@@ -919,9 +919,8 @@ __device__ __forceinline__ void flex_workgroup(const FlexIn &P, int product, int
 // instructions, which the matrix pipe hides about half of, LDS 1400 clocks; 2700 in all.  Without the splitting the launch below takes 34 us, without the
 // LDS writes 36, without the operand reads 37.
 // Launches (us, fp32 instructions : so), 8 ranks of 512 + 32 at batch 1024: update 69.9 : 41.0, input gradient 52.9 : 31.0, weight + compressor
-// gradients with the error compression below 101 : 72, compression 17.8 : 15.9.  Steps: 4 such layers trained with ReLU, whose forward pass stays on the
-// fp32 instructions (flex_fwd), 965 : 756, with GELU at batch 512 585 : 476; 3 of 16 ranks of 256 + 32 with ReLU 726 : 586; 2 layers of 1024 + 224, one
-// rank, forward at batch 4096 247 : 169, at 1024 103 : 67.
+// gradients with the error compression below 101 : 72, compression 17.8 : 15.9.  Steps: 4 such layers trained with GELU at batch 512 585 : 476 (ReLU
+// training stays on the fp32 instructions, see flex_fwd); 2 layers of 1024 + 224, one rank, forward at batch 4096 247 : 169, at 1024 103 : 67.
 struct FlexParts { u32x2 p[3]; };                      // four consecutive elements
 __device__ __forceinline__ FlexParts flex_parts(u32x4 v)
 {
