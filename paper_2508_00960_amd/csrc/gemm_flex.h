@@ -1270,6 +1270,287 @@ __device__ __forceinline__ void flex_split_workgroup(const FlexIn &P, int produc
     flex_epilogue<float, TILE, TILE, 1, THREADS, false, true, ROWSUM, float, EPI, AHEAD, 4 * THREADS>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
 }
 
+// ---- fp32 in whole vectors ------------------------------------------------------------------------------------------------
+// What stays on the fp32 matrix instructions (ReLU training, reductions beyond 2048) where 4 divides the widths and phantom widths: the sums of
+// flex_workgroup, term by term in the same order, so the same bits.
+// What bounds it: v_mfma_f32_32x32x2_f32 and the vector ALU do not run beside each other, whichever wavefronts they come from (8 ranks of
+// 512 + 32 at batch 1024, update: 94000 clocks of matrix instructions a SIMD; with 145, 100 and 64 other vector instructions a wavefront and step,
+// whose own four clocks each make 53000, 37000 and 23000, the compute units were busy for 160000, 150000 and 140000).  So a step keeps little more
+// than the 32 additions of its sums: loads take a scalar base and offsets that stay, LDS addresses stay too.
+// Both operands lie in LDS as rows of 32 reduction indices per free index, so that an operand read is 16 bytes for either kind, unpadded: of each
+// eight reduction positions first the even ones (one 16-byte unit), then the odd (see flex_operand); unit u of row r sits at u ^ flex_f32_swizzle(r),
+// where 16 rows' reads cover all 64 banks.  A thread has two vectors that differ by one free index (FLEX_KC) or by two
+// reduction indices (FLEX_KM), so that what it writes are pairs of words.
+// 32 KB of stages and 128 registers: four workgroups of 64 x 64 to a compute unit.
+// Trained (us, flex_workgroup : so): 4 layers of 8 ranks of 512 + 32 at batch 1024 952 : 842, 2 of 8 of 512 + 64 at 300 296 : 264, 2 of 16 of 256 + 32 at 400
+// 261 : 237, 3 of 4 of 256 + 8 at 1024 224 : 218.
+constexpr int F32_KT = 32, F32_ROW = F32_KT * 4, F32_TILE = 64 * F32_ROW, F32_STAGE = 2 * F32_TILE;       // bytes
+constexpr int F32_LDS_BYTES = flex_max(2 * F32_STAGE, FlexTileShape<64, 64>::C_BYTES + 256 * 4 + 64);
+__device__ __forceinline__ int flex_f32_swizzle(int row) { return ((row >> 1) & 7) ^ ((row >> 4) & 1); }
+
+// CUT: FLEX_KM, the reduction index may be cut (FLEX_KC: it may).
+template <int KIND, bool CUT>
+struct FlexF32Loader {
+    const char *base0, *base1;                 // uniform
+    uint32_t off0[2], off1[2];                 // bytes, of the thread's vectors in region 0 and 1 at reduction start 0 (FLEX_KM: of the first)
+    uint32_t free_off;                         // FLEX_KM: bytes, of the thread's free position
+    bool own1;                                 // FLEX_KM: the tile straddles the cut, and the thread's free position lies in region 1
+    uint32_t ld0, ld1;                         // bytes
+    int c;                                     // reduction index of the first vector inside a step (FLEX_KM: the second's is two higher)
+    int seg, seg_stride, skip, split, lim, plain_lim;      // split: start of region 1 (or none); plain_lim: end of the steps in region 0
+    uint32_t magic;
+    int col_seg, col_in_seg;                   // FLEX_KC, a step holds several segments: the thread's
+    bool regular;                              // FLEX_KC: steps do not straddle the cut, and segments hold steps or steps segments
+    uint32_t even, odd;                        // LDS bytes of what it writes
+
+    __device__ __forceinline__ void init(const FlexOperand &op, const FlexAxis &ax, const FlexAxis &fax, int f0, int g, int tid)
+    {
+        base0 = (const char *)op.p0 + g * op.g0 * 4;
+        base1 = (const char *)op.p1 + g * op.g1 * 4;
+        seg = ax.seg; seg_stride = (int)op.seg_stride; skip = op.skip0 + g * op.skip_g; magic = ax.magic;
+        split = ax.seg > 0 ? ax.head : 0x7fffffff;
+        lim = ax.seg > 0 ? ax.total : ax.head;
+        plain_lim = min(split, lim);
+        ld0 = (uint32_t)op.ld0 * 4u; ld1 = (uint32_t)op.ld1 * 4u;
+        int row, unit, word;
+        if (KIND == FLEX_KC) {
+            const int col = c = (tid & 7) * 4;
+            row = (tid >> 3) * 2; unit = col >> 3 << 1; word = (col & 4) >> 1;
+            regular = seg <= 0 || (split % F32_KT == 0 && (F32_KT % seg == 0 || seg % F32_KT == 0));
+            col_seg = 0; col_in_seg = col;
+            if (regular && seg > 0 && seg < F32_KT) {
+                col_seg = col / seg;
+                col_in_seg = col - col_seg * seg;
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t r = (uint32_t)min(f0 + row + j, fax.head - 1);
+                off0[j] = r * ld0 + (uint32_t)col * 4u;
+                off1[j] = r * ld1;
+            }
+        } else {
+            // reduction indices 8 (pair / 4) + 4 (pair / 2 % 2) + pair % 2 and two further; half a wavefront writes for 8 rows of 128 bytes, 4 pairs each
+            const int pair = (tid >> 6) * 4 + (tid >> 3 & 3);
+            row = ((tid & 7) + (tid >> 5 & 1) * 8) * 4; unit = (pair >> 2) * 2 + (pair & 1); word = pair & 2;
+            const FlexLoc l = flex_locate(fax, min(f0 + row, fax.total - 4), seg_stride, skip);
+            const bool straddles = fax.seg > 0 && f0 < fax.head && f0 + 64 > fax.head, tail = fax.seg > 0 && f0 >= fax.head;      // uniform
+            if (tail) { base0 = base1; ld0 = ld1; }
+            if (straddles) plain_lim = 0;
+            own1 = straddles && l.region;
+            free_off = (uint32_t)l.off * 4u;
+            c = (pair >> 2) * 8 + (pair & 2) * 2 + (pair & 1);
+            off0[0] = (uint32_t)c * ld0 + free_off;
+            off1[0] = (uint32_t)c * ld1 + free_off;
+        }
+        even = (uint32_t)(row * F32_ROW + ((unit ^ flex_f32_swizzle(row)) << 4) + word * 4);
+        odd = even ^ 16u;
+    }
+
+    // (The comments in assembly keep the branches' loads apart: the compiler would join them behind the branches, where their addresses are 64-bit
+    // vector values.)
+    __device__ __forceinline__ void fetch(u32x4 (&regs)[2], int c0 /* uniform */) const
+    {
+        if (c0 + F32_KT <= plain_lim) {                // uniform, like every branch here
+            const char *base = base0 + (KIND == FLEX_KC ? (uint64_t)((uint32_t)c0 * 4u) : (uint64_t)(uint32_t)c0 * ld0);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) regs[j] = KIND == FLEX_KC ? gload<u32x4>(base + off0[j]) : gload<u32x4>(base + (uint64_t)(2 * j) * ld0 + off0[0]);
+            asm volatile("; region 0");
+        } else if (KIND == FLEX_KC && regular && c0 + F32_KT <= lim) {
+            const uint32_t t0 = (uint32_t)(c0 - split);
+            uint32_t i0 = __umulhi(t0, magic);
+            i0 -= i0 * (uint32_t)seg > t0 ? 1u : 0u;
+            const int rem = (int)(t0 - i0 * (uint32_t)seg);
+            const char *base = base1;
+            uint32_t add = (uint32_t)c * 4u;
+            if (seg >= F32_KT) {
+                const int slot = (int)i0 + ((int)i0 >= skip ? 1 : 0);
+                base += ((int64_t)slot * seg_stride + rem) * 4;
+            } else {
+                const int i = (int)i0 + col_seg, slot = i + (i >= skip ? 1 : 0);
+                add = (uint32_t)(slot * seg_stride + col_in_seg) * 4u;
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) regs[j] = gload<u32x4>(base + (off1[j] + add));
+            asm volatile("; segments");
+        } else if (KIND == FLEX_KC) {
+            const int at = min(c0 + c, lim - 4);
+            const bool tail = at >= split;
+            const uint32_t t = tail ? (uint32_t)(at - split) : 0u;
+            uint32_t i = __umulhi(t, magic);
+            i -= i * (uint32_t)seg > t ? 1u : 0u;
+            const int slot = (int)i + ((int)i >= skip ? 1 : 0);
+            const int64_t from = tail ? ((int64_t)slot * seg_stride + (int)(t - i * (uint32_t)seg)) * 4 : (int64_t)(at - c) * 4;
+            const int64_t base = (int64_t)(uintptr_t)(tail ? base1 : base0) + from;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t o0 = off0[j], o1 = off1[j];
+                regs[j] = gload<u32x4>((const char *)(uintptr_t)(base + (tail ? o1 : o0)));
+            }
+            asm volatile("; any");
+        } else if (CUT && c0 >= split && c0 + F32_KT <= lim) {
+            const char *base = base1 + (uint64_t)(uint32_t)(c0 - split) * ld1;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) regs[j] = gload<u32x4>(base + (uint64_t)(2 * j) * ld1 + off1[0]);
+            asm volatile("; region 1");
+        } else {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int at = min(c0 + c + 2 * j, lim - 1);
+                const bool tail = CUT && at >= split;
+                const char *base = tail || own1 ? base1 : base0;
+                regs[j] = gload<u32x4>(base + ((int64_t)(tail ? at - split : at) * (tail || own1 ? ld1 : ld0) + free_off));
+            }
+            asm volatile("; any");
+        }
+    }
+
+    // zeros in the place of what lies behind the end
+    __device__ __forceinline__ void settle(u32x4 (&regs)[2], int c0) const
+    {
+        if (c0 + F32_KT > lim) {                       // uniform
+#pragma unroll
+            for (int j = 0; j < 2; ++j) regs[j] = c0 + c + (KIND == FLEX_KC ? 0 : 2 * j) < lim ? regs[j] : u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+
+    // (inline assembly: from the stores the compiler makes 8-byte ones, and moves words together for them.  It does not count these on
+    // their way: flex_f32_barrier.)
+    __device__ __forceinline__ void put(const u32x4 (&regs)[2], uint32_t tile) const
+    {
+        const uint32_t e = tile + even, o = tile + odd;
+#define PH_PAIR(at, x, y, row) asm volatile("ds_write2_b32 %0, %1, %2 offset0:%3 offset1:%4" :: "v"(at), "v"(x), "v"(y), "n"((row) * (F32_ROW / 4)), "n"((row) * (F32_ROW / 4) + 1) : "memory")
+        if (KIND == FLEX_KC) {                         // row's words 0 2 | 1 3
+            PH_PAIR(e, regs[0][0], regs[0][2], 0);
+            PH_PAIR(o, regs[0][1], regs[0][3], 0);
+            PH_PAIR(e, regs[1][0], regs[1][2], 1);
+            PH_PAIR(o, regs[1][1], regs[1][3], 1);
+        } else {                                       // (rows 2 and 3 of four have the swizzle's next value)
+            PH_PAIR(e, regs[0][0], regs[1][0], 0);
+            PH_PAIR(e, regs[0][1], regs[1][1], 1);
+            PH_PAIR(o, regs[0][2], regs[1][2], 2);
+            PH_PAIR(o, regs[0][3], regs[1][3], 3);
+        }
+#undef PH_PAIR
+    }
+};
+__device__ __forceinline__ void flex_f32_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// SETS: steps that the loads run ahead.  2, and a step's operand reads ahead of its matrix instructions: for launches whose few workgroups wait for
+// them (the registers of two workgroups to a compute unit).
+template <int SETS, int KA, int KB, int EPI>
+__device__ __forceinline__ void flex_f32_workgroup(const FlexIn &P, int product, int wg, unsigned char *lds)
+{
+    constexpr int TILE = 64, THREADS = 256, KT = F32_KT;
+    constexpr bool ROWSUM = KA == FLEX_KM && KB == FLEX_KM;
+    typedef FlexTileShape<TILE, TILE> C;
+
+    const FlexTileAt at = flex_tile_at<true>(P, wg);
+    const int g = at.g, tm = at.tm, tn = at.tn;
+    const int m0 = tm * TILE, n0 = tn * TILE;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    FlexAxis ma{};                                     // the row index: never cut
+    ma.head = P.M; ma.head_pad = (P.M + 3) / 4 * 4; ma.total = ma.head_pad;
+    FlexF32Loader<KA, false> la;
+    FlexF32Loader<KB, !ROWSUM> lb;
+    la.init(P.a, P.k, ma, m0, g, tid);
+    lb.init(P.b, P.k, P.n, n0, g, tid);
+
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 acc = zero;                                 // the third level's sums
+    const bool rows = ROWSUM && P.rowsum && n0 == 0;   // uniform
+    float row_acc = 0.f, row_mid = 0.f;                // of column tid % 64 of A
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(LdsBytes)lds;
+    const int steps = (la.lim + KT - 1) / KT;
+    // the operands of the reduction positions 0 .. 7; 8 kk further at the XOR of kk << 5
+    auto place = [&](int rbase) {
+        const int row = rbase + (lane & 31);
+        return (uint32_t)(row * F32_ROW + (((lane >> 5) ^ flex_f32_swizzle(row)) << 4));
+    };
+    uint32_t at_a[KT / 8], at_b[KT / 8];
+#pragma unroll
+    for (int kk = 0; kk < KT / 8; ++kk) { at_a[kk] = lds0 + (place(wm) ^ (kk << 5)); at_b[kk] = lds0 + (place(wn) ^ (kk << 5)); }
+    u32x4 ra[SETS][2], rb[SETS][2];
+#pragma unroll
+    for (int d = 0; d < SETS; ++d)
+        if (d < steps) {                               // uniform
+            la.fetch(ra[d], d * KT);
+            lb.fetch(rb[d], d * KT);
+        }
+    auto step = [&](auto stage, int i, f32x16 &mid) {
+        constexpr int AT = decltype(stage)::value * F32_STAGE, SET = decltype(stage)::value % SETS;
+        la.settle(ra[SET], i * KT);
+        lb.settle(rb[SET], i * KT);
+        la.put(ra[SET], lds0 + AT);
+        lb.put(rb[SET], lds0 + AT + F32_TILE);
+        if (i + SETS < steps) {                        // uniform
+            la.fetch(ra[SET], (i + SETS) * KT);
+            lb.fetch(rb[SET], (i + SETS) * KT);
+        }
+        flex_f32_barrier();                            // (the stage's readers of two steps ago have passed the barrier between)
+        f32x4 av[KT / 8], bv[KT / 8];
+        auto read = [&](int kk) { av[kk] = *lds_at<const f32x4>(at_a[kk] + AT); bv[kk] = *lds_at<const f32x4>(at_b[kk] + AT + F32_TILE); };
+        if constexpr (SETS == 2) {
+#pragma unroll
+            for (int kk = 0; kk < KT / 8; ++kk) read(kk);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int part = 0; part < KT / 16; ++part) {
+            f32x16 sum;
+#pragma unroll
+            for (int kk = 2 * part; kk < 2 * part + 2; ++kk) {
+                if constexpr (SETS == 1) read(kk);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[kk][t], av[kk][t], kk == 2 * part && t == 0 ? zero : sum, 0, 0, 0);
+            }
+            mid += sum;
+        }
+        if constexpr (ROWSUM) {
+            if (rows) {
+                float t = 0.f;
+#pragma unroll
+                for (int r = 0; r < KT / 4; ++r) {
+                    const int c = wave + r * 4, unit = (c >> 3) * 2 + (c & 1);
+                    t += *lds_at<const float>(lds0 + AT + lane * F32_ROW + ((unit ^ flex_f32_swizzle(lane)) << 4) + ((c & 7) >> 1) * 4);
+                }
+                row_mid += t;
+            }
+        }
+    };
+    // (two loops: with the second level's end in one, the compiler made it 48 selects in every step)
+#pragma unroll 1
+    for (int i0 = 0; i0 < steps; i0 += 8) {            // a second-level sum holds 256 terms
+        f32x16 mid = zero;
+        row_mid = 0.f;
+        const int end = min(i0 + 8, steps);
+#pragma unroll 1
+        for (int i = i0; i < end; i += 2) {
+            step(std::integral_constant<int, 0>{}, i, mid);
+            if (i + 1 < end) step(std::integral_constant<int, 1>{}, i + 1, mid);
+        }
+        acc += mid;
+        row_acc += row_mid;
+    }
+
+    const FlexOut Q = args_at<FlexOut>(offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out));
+    constexpr int AHEAD = EPI == EPI_BIAS_ACT ? 1 : 4;
+    FlexAhead<float, AHEAD> ahead;
+    flex_request<float, TILE, TILE, THREADS, true, ROWSUM, float, EPI>(ahead, P, Q, g, tm, tn, rows);
+    __syncthreads();
+    float *const ctile = (float *)lds;
+    float *const extra = (float *)(lds + C::C_BYTES);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 v = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        *(f32x4 *)(ctile + (wm + (lane & 31)) * C::CPITCH + wn + 8 * q + 4 * (lane >> 5)) = v;
+    }
+    if (rows) extra[tid] = row_acc;
+    __syncthreads();
+    flex_arrived(ahead);
+    flex_epilogue<float, TILE, TILE, 1, THREADS, false, true, ROWSUM, float, EPI, AHEAD>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
+}
+
 // ---- bf16 in 16-byte vectors: the ring of mfma_ring.h ----------------------------------------------------------------
 // Problems whose widths and phantom widths 8 divides need neither the renumbering nor masked vectors.  A workgroup owns a 64 x 64 tile, each
 // wavefront of a team a quadrant of it; two teams share it as in the kernel above, each with every other tile of the reduction range in stages
@@ -1464,6 +1745,25 @@ __global__ __launch_bounds__(FlexSplit<TILE>::THREADS, FlexSplit<TILE>::MIN_WAVE
     if constexpr (FORWARD) flex_split_workgroup<TILE, FLEX_KC, FLEX_KC, EPI_BIAS_ACT>(P, j, wg, smem_raw);
     else if (P.kind == 0) flex_split_workgroup<TILE, FLEX_KC, FLEX_KM, EPI_DACT>(P, j, wg, smem_raw);
     else flex_split_workgroup<TILE, FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
+}
+
+template <bool FORWARD, bool MANY>
+__global__ __launch_bounds__(256, MANY ? 4 : 2) void gemm_flex_f32_kernel(FlexBatch batch)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    if (batch.tail.partial && blockIdx.x == 0) {       // uniform
+        finish_loss(batch.tail, (float *)smem_raw);
+        __syncthreads();
+    }
+    int j = 0;
+    while (j + 1 < batch.count && (int)blockIdx.x >= batch.first_wg[j + 1]) ++j;       // uniform
+    const int local = (int)blockIdx.x - batch.first_wg[j];
+    const FlexIn P = args_at<FlexIn>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, in));
+    if (local >= P.total_wg) return;
+    const int wg = flex_xcd_order(local, P.total_wg);
+    if constexpr (FORWARD) flex_f32_workgroup<(MANY ? 1 : 2), FLEX_KC, FLEX_KC, EPI_BIAS_ACT>(P, j, wg, smem_raw);
+    else if (P.kind == 0) flex_f32_workgroup<(MANY ? 1 : 2), FLEX_KC, FLEX_KM, EPI_DACT>(P, j, wg, smem_raw);
+    else flex_f32_workgroup<(MANY ? 1 : 2), FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
 }
 
 template <int TEAMS, int RING, bool FORWARD>

@@ -77,6 +77,7 @@ struct Geo {
     int vec;          // bf16: widest vector (8 or 4 elements) dividing si, so and k; 0: the kernels of gemm_flex.h only
     bool fine;        // bf16: ... in their FINE form
     bool whole;       // fp32: 4 divides si, so and k, and 32 bits hold a byte offset inside a rank's share of a tensor (FlexWhole)
+    bool parts;       // fp32: ... and products may run in three bf16 parts (flex_step, flex_fwd)
 };
 
 // Checks the problem and fills in the shapes of layer `layer` (0-based).
@@ -132,6 +133,7 @@ ph_status make_geo(const ph_problem *pr, Geo &g, int layer = 0)
         // they also divide a position among the peers' segments by k with a multiply (Axis::magic), exact while
         // position * k < 2^32
         if (g.q * g.k * g.k >= (int64_t)1 << 32) g.vec = 0;
+        g.parts = g.whole;
     }
     // index arithmetic inside the kernels uses 32-bit row/column numbers and a 3-D grid
     if (g.B > (1 << 22) || si > (1 << 22) || so > (1 << 22) || g.Kc > (1 << 24) || so + g.q * g.k > (1 << 24) || g.p > 65535)
@@ -922,7 +924,7 @@ FlexOperand flex_operand_of(const View &v, bool km, const FlexAxis &k, const Fle
 enum FlexTile { FLEX_64, FLEX_64_2, FLEX_32_8, FLEX_SPLIT_64, FLEX_SPLIT_128 };      // (FLEX_SPLIT: fp32 in three bf16 parts)
 
 template <typename T>
-FlexTile flex_tile_for(const Product *prods, int count, int groups, bool forward, bool ring, bool whole)
+FlexTile flex_tile_for(const Product *prods, int count, int groups, bool forward, bool ring, bool parts)
 {
     int64_t tiles = 0, small = 0, longest = 0;         // of 64 x 64, of 32 x 32
     int64_t large_tiles = 0, work = 0, large = 0, longest_k = 0, shortest = INT64_MAX;      // tiles of 128 x 128; terms of all 64 x 64 ones, of all 128 x 128 ones, of the products
@@ -941,7 +943,7 @@ FlexTile flex_tile_for(const Product *prods, int count, int groups, bool forward
     if (force) return (FlexTile)atoi(force);
     if (sizeof(T) == 4) {
         if (tiles <= 128 && longest <= 8 * 16) return FLEX_32_8;
-        if (longest > 2048 || !whole) return FLEX_64;
+        if (longest > 2048 || !parts) return FLEX_64;
         const bool fits = large_tiles <= 256;
         const int64_t rounds = fits ? longest_k : std::max(longest_k, (large + 256 * shortest - 1) / (256 * shortest) * shortest);
         const int64_t ns_128 = 12000 + 37 * rounds + (fits ? 0 : 6000), ns_64 = 5000 + std::max(23 * longest_k, (prods[0].km ? 17 : 15) * work / 256);
@@ -980,6 +982,15 @@ ph_status launch_flex_split(const FlexBatch &batch, unsigned total_wg, hipStream
         configured = true;
     }
     hipLaunchKernelGGL(kern, dim3(total_wg), dim3(FlexSplit<TILE>::THREADS), LDS, st, batch);
+    return check_launch(what);
+}
+
+template <bool FORWARD, bool MANY>
+ph_status launch_flex_f32(const FlexBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
+{
+    constexpr int LDS = F32_LDS_BYTES;
+    static_assert(4 * LDS <= 160 * 1024, "four workgroups share a compute unit");
+    hipLaunchKernelGGL((gemm_flex_f32_kernel<FORWARD, MANY>), dim3(total_wg), dim3(256), LDS, st, batch);
     return check_launch(what);
 }
 
@@ -1025,7 +1036,7 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
         if (prods_in[i].M > 0 && prods_in[i].N > 0) prods[count++] = prods_in[i];
     const int groups = g.groups;
     if (count == 0 || groups <= 0) return PH_OK;
-    const FlexTile tile = flex_tile_for<T>(prods, count, groups, forward, g.vec == 8, g.whole);
+    const FlexTile tile = flex_tile_for<T>(prods, count, groups, forward, g.vec == 8, g.parts);
     const int t = tile == FLEX_32_8 ? 32 : tile == FLEX_SPLIT_128 ? 128 : 64;
     constexpr int V = FlexType<T>::V;
     FlexBatch batch{};
@@ -1081,6 +1092,14 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
                 return forward ? launch_flex_ring<2, 2, true>(batch, total, st, what) : launch_flex_ring<2, 2, false>(batch, total, st, what);
             }
             return forward ? launch_flex_ring<1, 3, true>(batch, total, st, what) : launch_flex_ring<1, 3, false>(batch, total, st, what);
+        }
+    if constexpr (sizeof(T) == 4)
+        if (tile == FLEX_64 && g.whole) {
+            // Up to two workgroups to a compute unit the launch waits for loads and operand reads, not for the matrix pipe (us a step of this kernel with
+            // neither far ahead : so): 3 layers of 4 ranks of 256 + 8 trained at batch 1024, 256 to 384 workgroups, 251 : 218, of 4 of 400 + 20 at 700 302 : 277.
+            static const char *force = tuning_env("PHANTOM_F32_MANY");     // =0 / 1 (for measurements)
+            if (force ? force[0] == '1' : total > 512) return forward ? launch_flex_f32<true, true>(batch, total, st, what) : launch_flex_f32<false, true>(batch, total, st, what);
+            return forward ? launch_flex_f32<true, false>(batch, total, st, what) : launch_flex_f32<false, false>(batch, total, st, what);
         }
     if constexpr (sizeof(T) == 2)
         if (fine) return forward ? launch_flex_tile<T, true, true>(batch, tile, total, st, what) : launch_flex_tile<T, false, true>(batch, tile, total, st, what);
@@ -1188,7 +1207,7 @@ ph_status flex_fwd(const Geo &layer, const FwdArgs &f, hipStream_t st, int *mse_
     // Not in three bf16 parts where a backward pass takes ReLU' from the sums: one that rounding alone puts on the other side of 0 changes a row of
     // the gradients (8 ranks of 512 + 32, 4 layers, batch 1024: some 2 of 17 million a step, 1e-4 of a weight's size), so these sums keep their order.
     Geo g = layer;
-    g.whole = g.whole && (g.act != PH_ACT_RELU || f.forward_only);
+    g.parts = g.parts && (g.act != PH_ACT_RELU || f.forward_only);
     if (g.all) {
         // every rank reads the other ranks' g: the compression of all ranks has to finish first
         PH_TRY((launch_flex<T>(&pr.compress, 1, true, g, LossTail{}, st, "compression")));
@@ -1630,7 +1649,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
     const bool train = a.mode != PH_STEP_FORWARD, update = a.mode == PH_STEP_TRAIN;
     // The update of ReLU training keeps the order of its terms as well (see flex_fwd): weights that differ in the last place move sums of the next step
     // across 0 (gradients in parts, two steps of those 4 layers: in 7 of 40 runs some weight more than 1e-4 of its size off; 756 us a step for 965).
-    g.whole = g.whole && !(update && g.act == PH_ACT_RELU);
+    g.parts = g.whole && !(update && g.act == PH_ACT_RELU);
     const bool gelu = g.act == PH_ACT_GELU, save_deriv = gelu && std::is_same<T, bf16_t>::value;
     // delta_l is read until the launch after the next one is out: three buffers in turn
     void *const deltas[3] = {w.dYa, w.dYb, w.bwd.delta};
