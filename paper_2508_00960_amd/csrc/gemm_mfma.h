@@ -1600,8 +1600,8 @@ struct UniformGradients {
 };
 static_assert(sizeof(UniformGradients) <= 3840, "travels as kernel arguments (4 KB with the hidden ones)");
 
-template <int VEC>
-__global__ __launch_bounds__(512, 1) void gemm_mfma_uniform_kernel(UniformGradients u)
+template <int VEC, bool SOLO>
+__global__ __launch_bounds__(SOLO ? 256 : 512, SOLO ? 2 : 1) void gemm_mfma_uniform_kernel(UniformGradients u)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int id = (int)blockIdx.x;
@@ -1638,7 +1638,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_uniform_kernel(UniformGradie
         }
         return Q;
     };
-    if (weights && u.dw_dual) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, true, EPI_STORE>(P, xcd_order(local, 0, P.total_wg), read_out);
+    if constexpr (SOLO) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, TILE_SOLO, EPI_STORE>(P, xcd_order(local, 0, P.total_wg), read_out);
+    else if (weights && u.dw_dual) mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, true, EPI_STORE>(P, xcd_order(local, 0, P.total_wg), read_out);
     else mfma_workgroup<LD_KM, LD_KM, VEC, VEC, float, false, EPI_STORE>(P, xcd_order(local, 0, P.total_wg), read_out);
 }
 

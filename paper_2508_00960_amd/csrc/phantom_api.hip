@@ -273,8 +273,8 @@ struct StepWs {
                                                     //   it at the start of a step, left zero by every launch that uses them
     int64_t arrived_words;
     float *parts;                                   // deferred weight gradients (one rank): the pieces' results of the cut
-    ProductTable *table;                            //   compressor gradients, the launch's parameter table, and every
-    std::vector<void *> delta_of;                   //   layer's delta [B, so_l]
+    ProductTable *table;                            //   compressor gradients, the launch's parameter table (DEFER_SMALL), and
+    std::vector<void *> delta_of;                   //   every layer's delta [B, so_l]
     BwdWs bwd;
 };
 
@@ -290,17 +290,37 @@ bool relu_bits_ok(const std::vector<Geo> &geos, size_t l)
 
 inline int64_t tiles_of(int64_t M, int64_t N) { return ((M + MT - 1) / MT) * ((N + MT - 1) / MT); }
 
-// One rank's backward pass over two or more layers keeps every layer's delta and runs all weight + compressor
-// gradients in one launch at its end (gemm_mfma_table_kernel) where a layer's own would leave compute units idle:
-// bf16 with 8-element vectors and at most 256 weight-gradient tiles in every layer.  (All ranks on the device:
-// the weight gradients' launches carry the next error compression and the update on the compute units they leave
-// idle, and putting them off made configuration 2 slower, 0.272 against 0.260 ms; a single layer has nothing to gain.)
-bool deferred_weight_gradients(const std::vector<Geo> &geos)
+bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call = false);
+
+bool all_alike(const std::vector<Geo> &geos)
 {
-    if (geos.size() < 2 || 2 * geos.size() > (size_t)TABLE_PRODUCTS) return false;
-    for (const Geo &g : geos)
-        if (g.all || g.dtype != PH_BF16 || g.vec != 8 || tiles_of(g.so, g.Kc) > 256) return false;
-    return true;
+    return std::all_of(geos.begin(), geos.end(), [&](const Geo &g) { return g.si == geos[0].si && g.so == geos[0].so && g.k == geos[0].k; });
+}
+
+// One rank's backward pass over two or more layers keeps every layer's delta and runs all weight + compressor
+// gradients in one launch at its end (gemm_mfma_uniform_kernel, gemm_mfma_table_kernel): bf16 with 8-element vectors.
+// A layer with at most 256 weight-gradient tiles would leave compute units idle in a launch of its own.  Larger ones (layers alike): within one
+// launch a tile's epilogue runs beside others' loops to the end, where each layer's own launch ended with all its compute units in the update.
+// Us a step, a launch per layer : one: 4 layers of 4096 trained at batch 1024 575 : 539, 3 of 3072 with GELU at 1500 425 : 384, 3 of 2048 + 192 at 2048
+// 304 : 263, at 4096 475 : 413, 2 of 4096 at 4096 712 : 703.  Their deltas then lie where a launch per layer has its buffers (carve_step), so that
+// no step needs more workspace for it; where they do not fit there, each layer keeps its launch.
+// (All ranks on the device: the weight gradients' launches carry the next error compression and the update on the compute units they leave
+// idle, and putting them off made configuration 2 slower, 0.272 against 0.260 ms; a single layer has nothing to gain.)
+enum Deferral { DEFER_NONE, DEFER_SMALL, DEFER_LARGE };
+Deferral deferred_weight_gradients(const std::vector<Geo> &geos)
+{
+    const size_t L = geos.size();
+    if (L < 2 || 2 * L > (size_t)TABLE_PRODUCTS) return DEFER_NONE;
+    bool large = false;
+    for (const Geo &g : geos) {
+        if (g.all || g.dtype != PH_BF16 || g.vec != 8) return DEFER_NONE;
+        large = large || tiles_of(g.so, g.Kc) > 256;
+    }
+    if (!large) return DEFER_SMALL;
+    const Geo &g = geos[0];
+    if (L > (size_t)UNIFORM_LAYERS || !all_alike(geos) || use_flex(geos, true)) return DEFER_NONE;
+    const int64_t delta = (g.B * g.so * (int64_t)g.esz + 255) & ~(int64_t)255, beside = 4 * (g.so * g.Kc + g.k * g.si);
+    return ((int64_t)L - 3) * delta <= beside ? DEFER_LARGE : DEFER_NONE;
 }
 
 // The compressor gradient [k, si] of a layer has few tiles with a long reduction (configuration 4: 8 tiles of 64
@@ -316,6 +336,7 @@ int compressor_gradient_pieces(const Geo &g)
 int64_t cut_tiles(const std::vector<Geo> &geos)
 {
     int64_t tiles = 0;
+    if (deferred_weight_gradients(geos) != DEFER_SMALL) return 0;
     for (const Geo &g : geos)
         if (g.q > 0 && compressor_gradient_pieces(g) > 1) tiles += tiles_of(g.k, g.si);
     return tiles;
@@ -350,15 +371,20 @@ StepWs carve_step(Arena &a, const std::vector<Geo> &geos)
     w.dYb = a.take(groups * B * act_max * g0.esz);
     w.dG_send = g0.q > 0 ? a.take(groups * g0.q * B * k_max * g0.esz) : nullptr;
     w.dg_own = g0.q > 0 ? a.take(groups * B * k_max * g0.esz) : nullptr;
+    size_t second = 0;                                 // where the second set starts
     for (int set = 0; set < 2; ++set) {
+        second = (a.used + 255) & ~(size_t)255;
         w.dLw[set] = (float *)a.take(groups * lw_max * 4);
         w.dCw[set] = (float *)a.take(groups * cw_max * 4 + 16);
         w.dDw[set] = (float *)a.take(groups * dw_max * 4 + 16);
     }
-    w.arrived_words = deferred_weight_gradients(geos) ? cut_tiles(geos) : 0;
+    const Deferral deferral = deferred_weight_gradients(geos);
+    w.arrived_words = cut_tiles(geos);
     w.dbias = (float *)a.take((size_t)(dbias_total + w.arrived_words) * 4);
     w.arrived = w.dbias ? (unsigned *)(w.dbias + dbias_total) : nullptr;
-    if (deferred_weight_gradients(geos)) {
+    w.parts = nullptr;
+    w.table = nullptr;
+    if (deferral == DEFER_SMALL) {
         size_t slots = 0;
         for (const Geo &g : geos) {
             w.delta_of.push_back(a.take((size_t)g.B * g.so * g.esz));
@@ -366,14 +392,16 @@ StepWs carve_step(Arena &a, const std::vector<Geo> &geos)
         }
         w.parts = (float *)a.take(std::max<size_t>(slots, 1) * MT * MT * sizeof(float));
         w.table = (ProductTable *)a.take(sizeof(ProductTable));
-    } else {
-        w.parts = nullptr;
-        w.table = nullptr;
     }
     // one partial sum of the loss per output tile of the last layer, at the smallest tile (32 x 32)
     const Geo &gL = geos.back();
     w.mse_partial = (float *)a.take((size_t)((gL.B + 31) / 32) * (size_t)((gL.so + 31) / 32 * g0.groups) * sizeof(float));
     w.bwd.delta = a.take(groups * B * act_max * g0.esz);
+    if (deferral == DEFER_LARGE) {
+        Arena beside{a.base, second};                  // (the gradients of all layers that nobody wants lie in the first set)
+        for (size_t l = 0; l < geos.size(); ++l)
+            w.delta_of.push_back(l == 0 ? w.dYa : l == 1 ? w.dYb : l == 2 ? w.bwd.delta : beside.take(B * (size_t)g0.so * g0.esz));
+    }
     return w;
 }
 
@@ -411,7 +439,7 @@ inline unsigned blocks_for(int64_t count, int per_block = 256, int cap = 8192)
 //   there, or no kernel of its own: 8 of 256 + 40 at 640 72.5 : 70, 4 of 1024 + 64 at 768 103 : 88, 8 of 512 + 128 107 : 97, 32 of 128 + 64 at 640
 //   117 : 115, but 64 of 128 + 48 at 640 164 : 179.
 // 4-element vectors, which take the renumbering kernel, keep the lines that were measured for it: 96 and 128 tiles, 192 for a layer's call.
-bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call = false)
+bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call)
 {
     int64_t tiles = 0;
     bool wide = true, narrow = true, ring = true, all_fit = true;
@@ -699,7 +727,28 @@ ph_status launch_product_table(const ProductTable *table, int grid, hipStream_t 
     return check_launch(what);
 }
 
+template <bool SOLO>
+ph_status launch_uniform_kernel(const UniformGradients &u, const Product &dw, const Product &dc, hipStream_t st, const char *what)
+{
+    auto kern = gemm_mfma_uniform_kernel<8, SOLO>;
+    constexpr int MODE = SOLO ? TILE_SOLO : TILE_DUAL, LDS = mfma_lds_bytes(MODE);
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
+        configured = true;
+    }
+    ProfScope prof(what, dw.M, dw.N, dw.K, u.layers, st, dc.M, dc.N, dc.K);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(u.layers * (u.dc_wg + u.dw_wg))), dim3(mfma_threads(MODE)), LDS, st, u);
+    return check_launch(what);
+}
+
 // The same launch for layers of one shape, without a table (dw, dc: by layer; without compressors the dc have no rows).
+// More tiles than compute units: one tile to a workgroup, two workgroups to a compute unit (TILE_SOLO), where that takes no more rounds of
+// the chip than two tiles to a workgroup, whose compressor gradients are cut and start the launch: there the epilogues of the first
+// round run beside the second's loops.  (Not with whole rounds of long reductions, where loops are most of the time.)  Us a step, two tiles : SOLO: 4 layers of 4096 trained at batch 1024 558 : 539, 2 at 3072 601 : 597, at 4096 699 :
+// 703; 3 of 2048 + 192 at 2048 280 : 263, at 4096 434 : 413; 8 of 512 + 960 at 4096 359 : 348; 4 of 2048 at 1500 244 : 236.  A round more: 8 of
+// 1024 + 960 at 4096 (1088 tiles) 637 : 665, at 2560 468 : 485.
 ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::vector<Product> &dc, int pieces, float *parts,
                                    unsigned *arrived, const LossTail &tail, hipStream_t st, const char *what)
 {
@@ -708,7 +757,12 @@ ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::ve
     UniformGradients u{};
     int64_t tiles = tiles_of(dw[0].M, dw[0].N) * L;
     if (two) tiles += tiles_of(dc[0].M, dc[0].N) * L;
-    u.dw_dual = tiles > 256;
+    const int64_t pairs = ((dw[0].M + 2 * MT - 1) / (2 * MT)) * ((dw[0].N + MT - 1) / MT) * L;
+    bool solo = tiles > 256 && (tiles + 511) / 512 <= (pairs + 255) / 256 && (dw[0].K <= 3072 || pairs % 256 != 0);
+    static const char *force = tuning_env("PHANTOM_UNIFORM_SOLO");         // =0 / 1 (for measurements)
+    if (force) solo = force[0] == '1';
+    if (solo) pieces = 1;
+    u.dw_dual = tiles > 256 && !solo;
     u.dw = mfma_params(dw[0], 1, 1, u.dw_dual);
     u.dw_wg = (u.dw.in.total_wg + 7) & ~7;
     if (two) {
@@ -728,16 +782,7 @@ ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::ve
         u.at[l].out = {w.o.p0, w.o.p1, c.o.p0, w.sgd.master0, w.sgd.master1, c.sgd.master0, w.sgd.bias_master, w.sgd.w0, w.sgd.w1, c.sgd.w0,
                        w.sgd.bias_w, w.sgd.bias_grad};
     }
-    auto kern = gemm_mfma_uniform_kernel<8>;
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES, hipGetErrorString(e));
-        configured = true;
-    }
-    ProfScope prof(what, dw[0].M, dw[0].N, dw[0].K, L, st, dc[0].M, dc[0].N, dc[0].K);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(L * (u.dc_wg + u.dw_wg))), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, u);
-    return check_launch(what);
+    return solo ? launch_uniform_kernel<true>(u, dw[0], dc[0], st, what) : launch_uniform_kernel<false>(u, dw[0], dc[0], st, what);
 }
 
 // Up to MANY_PRODUCTS products of the forward layout with a plain store, in one launch.
@@ -1770,7 +1815,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     // sum of the loss per tile: two launches less than a kernel for the error and one for the column sums.
     const int64_t out_tiles = tiles_of(B, g.so) * g.groups;
     // (one rank with deferred weight gradients keeps every layer's delta: the last layer's goes to its own buffer)
-    const bool deferred = train && w.table && deferred_weight_gradients(geos);
+    const Deferral deferral = train ? deferred_weight_gradients(geos) : DEFER_NONE;
+    const bool deferred = deferral != DEFER_NONE;
     void *delta_top = deferred ? w.delta_of[(size_t)L - 1] : w.dYa;
     OutputError oe{a.T, delta_top, w.mse_partial, 1.0f / (float)B, dbias_of(L - 1)};
 
@@ -1781,9 +1827,7 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     // units as those come free; the SGD update of L, C, D and the bias in the epilogues, the loss by the first workgroup.
     int table_grid = 0;
     std::vector<Product> all_dw, all_dc;               // by layer
-    const bool uniform = L <= UNIFORM_LAYERS && std::all_of(geos.begin(), geos.end(), [&](const Geo &x) {
-        return x.si == g.si && x.so == g.so && x.k == g.k;
-    });
+    const bool uniform = L <= UNIFORM_LAYERS && all_alike(geos);
     const LossTail table_tail{w.mse_partial, (int)out_tiles, 0.5f / (float)B, a.loss};
     if (deferred) {
         for (int l = 0; l < L; ++l) {
@@ -1888,7 +1932,7 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     }
     if (deferred) {
         const char *what = update ? "weight + compressor gradients of all layers + SGD | loss" : "weight + compressor gradients of all layers | loss";
-        if (uniform) PH_TRY(launch_uniform_gradients(all_dw, all_dc, compressor_gradient_pieces(g), w.parts, w.arrived, table_tail, st, what));
+        if (uniform) PH_TRY(launch_uniform_gradients(all_dw, all_dc, deferral == DEFER_SMALL ? compressor_gradient_pieces(g) : 1, w.parts, w.arrived, table_tail, st, what));
         else PH_TRY(launch_product_table(w.table, table_grid, st, what, all_dw.back(), all_dc.back(), L));
     }
     return PH_OK;

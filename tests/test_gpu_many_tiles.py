@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (4096, 8, 16, 3150, 9, "relu", 0, "train", None, None),            # in three, nine layers
     (4096, 8, 128, 4099, 3, "relu", 7, "train", None, None),           # in four; k > 64: compressions of all layers together
     (8192, 8, 68, 1630, 2, "gelu", 0, "train", None, None),            # 4-element vectors: a launch per layer
-    (16384, 8, 16, 1100, 2, "relu", 0, "train", None, None),           # 272 weight-gradient tiles per layer: a launch per layer
+    (16384, 8, 16, 1100, 2, "relu", 0, "train", None, None),           # 272 weight-gradient tiles per layer
     (4096, 8, 16, 3150, 17, "relu", 0, "no_update", None, None),       # more layers than the table holds
     (8192, 8, 32, 2100, 2, "relu", 0, "train", (8192, 4096, 12288), (32, 16)),       # layers that differ
     (2816, 2, 1408, 1990, 5, "relu", 0, "train", None, None),          # k = n/p: 605 tiles of compressor gradients in pieces
@@ -54,3 +54,12 @@ def test_one_team_workgroups(n, p, k, B, L, act, mode):
 def test_layer_calls_of_one_rank(n, p, k, B, act, rank):
     print(f"case many tiles layer n={n} p={p} k={k} B={B} {act} rank={rank}", flush=True)
     run_layer_one_rank(pin.Problem(n=n, p=p, k=k, batch=B, layers=1, act=act, dtype="bf16", rank=rank), seed=4)
+
+
+@pytest.mark.parametrize("n,p,k,B,L,act,mode", [
+    (4096, 2, 8, 1100, 4, "relu", "train"),          # 1088 + 64 tiles: one a workgroup; a fourth delta beside the first set of gradients
+    (18432, 9, 256, 1030, 2, "gelu", "no_update"),   # 1024 + 64: two a workgroup
+])
+def test_all_gradients_of_large_layers_together(n, p, k, B, L, act, mode):
+    print(f"case large layers n={n} p={p} k={k} B={B} L={L} {act} {mode}", flush=True)
+    check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=0), seed=5, lr=0.02, mode=mode)
