@@ -201,4 +201,81 @@ __global__ __launch_bounds__(256) void copy_kernel(const T *__restrict__ src, T 
     for (; i < count; i += stride) dst[i] = src[i];
 }
 
+// Copies of bf16 matrices whose rows of `len` elements become rows of `plen`, a multiple of 8, with zeros behind them: 16 bytes per thread.
+// len is even, so that every row starts on a word.  Bound by the launch: 9 MB for 6 layers of 7 peers' G [8192, 4] and D [1024, 4] to 8.
+constexpr int PAD_ENTRIES = 64;
+struct PadList {
+    struct Entry {
+        const void *src;
+        void *dst;
+        int vectors, len, plen, first_block;
+    } at[PAD_ENTRIES];
+    int count;
+};
+static_assert(sizeof(PadList) <= 3840, "travels as kernel arguments (4 KB with the hidden ones)");
+
+__global__ __launch_bounds__(256) void pad_kernel(PadList list)
+{
+    int j = 0;
+    while (j + 1 < list.count && (int)blockIdx.x >= list.at[j + 1].first_block) ++j;      // uniform
+    const PadList::Entry e = list.at[j];
+    const int v = ((int)blockIdx.x - e.first_block) * 256 + (int)threadIdx.x;
+    if (v >= e.vectors) return;
+    const int per_row = e.plen / 8, row = v / per_row, col = (v - row * per_row) * 8;
+    typedef uint32_t Words __attribute__((ext_vector_type(4)));
+    typedef uint32_t AnyWords __attribute__((ext_vector_type(4), aligned(4)));
+    const uint32_t *src = (const uint32_t *)e.src + ((int64_t)row * e.len + col) / 2;
+    Words x;
+    if (col + 8 <= e.len) {
+        x = *(const AnyWords *)src;
+    } else {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) x[h] = col + 2 * h < e.len ? src[h] : 0u;
+    }
+    ((Words *)e.dst)[v] = x;
+}
+
+// What becomes of float gradients in rows of `plen` with `len` (even) elements that count: out <- the gradient (NULL: not wanted), and
+// SGD on the weights as the epilogues do it (master == NULL: none).  Two elements per thread.
+struct UnpadList {
+    struct Entry {
+        const float *grad;
+        float *out, *master;
+        void *w;
+        int pairs, len, plen, first_block;
+    } at[PAD_ENTRIES / 2];
+    int count;
+    float lr;
+};
+static_assert(sizeof(UnpadList) <= 3840, "travels as kernel arguments (4 KB with the hidden ones)");
+
+__global__ __launch_bounds__(256) void unpad_gradients_kernel(UnpadList list)
+{
+    int j = 0;
+    while (j + 1 < list.count && (int)blockIdx.x >= list.at[j + 1].first_block) ++j;      // uniform
+    const UnpadList::Entry e = list.at[j];
+    const int v = ((int)blockIdx.x - e.first_block) * 256 + (int)threadIdx.x;
+    if (v >= e.pairs) return;
+    typedef float F2 __attribute__((ext_vector_type(2)));
+    typedef bf16_t B2 __attribute__((ext_vector_type(2)));
+    const int per_row = e.len / 2, row = v / per_row, col = (v - row * per_row) * 2;
+    const F2 g = *(const F2 *)(e.grad + (int64_t)row * e.plen + col);
+    if (e.master) {                                    // uniform
+        F2 m = ((F2 *)e.master)[v];
+        m[0] -= list.lr * g[0];
+        m[1] -= list.lr * g[1];
+        ((F2 *)e.master)[v] = m;
+        ((B2 *)e.w)[v] = B2{(bf16_t)m[0], (bf16_t)m[1]};
+    }
+    if (e.out) ((F2 *)e.out)[v] = g;                   // uniform
+}
+
+// dst [rows, len] <- the first len columns of src [rows, plen]
+template <typename T>
+__global__ __launch_bounds__(256) void unpad_copy_kernel(const T *src, T *dst, int64_t rows, int len, int plen)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows * len; i += stride) dst[i] = src[i / len * plen + i % len];
+}
+
 }  // namespace phantom

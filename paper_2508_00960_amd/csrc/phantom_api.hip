@@ -70,6 +70,7 @@ inline const char *tuning_env(const char *name)
 // the problem gives per-layer widths).
 struct Geo {
     int64_t p, k, B, si, so, q, Kc;
+    int64_t k_given;  // the caller's phantom width: k, or less where the step runs on padded copies (padded_geos)
     int groups;       // ranks held on this GPU: 1 or p
     bool all;         // all-ranks mode
     int act, dtype, rank, layers;
@@ -107,7 +108,7 @@ ph_status make_geo(const ph_problem *pr, Geo &g, int layer = 0)
         return fail(PH_ERR_INVALID_ARG, "layer %d: k = %lld must lie in [1, n/p = %lld]", layer, (long long)k,
                     (long long)std::max(si, so));
     g.p = pr->p; g.B = pr->batch; g.si = si; g.so = so; g.q = pr->p - 1;
-    g.k = g.q > 0 ? k : 0;
+    g.k = g.k_given = g.q > 0 ? k : 0;
     g.Kc = si + g.q * g.k;
     g.all = pr->rank < 0;
     g.groups = g.all ? (int)pr->p : 1;
@@ -1361,6 +1362,16 @@ ph_status tap_copy(void *dst, const void *src, int64_t count, hipStream_t st)
     return check_launch("copy");
 }
 
+// copy of a step's tensor with rows of g.k elements into the caller's, with rows of g.k_given
+template <typename T>
+ph_status tap_rows(const Geo &g, void *dst, const void *src, int64_t rows, hipStream_t st)
+{
+    if (g.k == g.k_given) return tap_copy<T>(dst, src, rows * g.k, st);
+    if (!dst || !src || rows <= 0) return PH_OK;
+    hipLaunchKernelGGL((unpad_copy_kernel<T>), dim3(blocks_for(rows * g.k_given)), dim3(256), 0, st, (const T *)src, (T *)dst, rows, (int)g.k_given, (int)g.k);
+    return check_launch("copy");
+}
+
 // error compression: dG_send[i] = delta . D_i   ([B, so] x [so, k] for every peer, one product over N = q*k);
 // w_out, kk: the output width and phantom width of the layer whose delta (dl) and D these are
 Product error_compression_product(int64_t B, int64_t q, void *dG_send, const void *dl, const void *Dw, int64_t w_out, int64_t kk)
@@ -1543,11 +1554,11 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
     const bool send_rides = riders && !g.all && !b.dX && q > 0 && !b.defer && !b.sgd_w.w0;
 
     const GemmPlan plan_x{LD_KC, LD_KM, g.vec};
-    const int64_t send_count = (int64_t)g.groups * q * B * k;
+    const int64_t send_rows = (int64_t)g.groups * q * B;
     if (g.all) {
         // the input gradient needs dg_own, which is the sum of what all ranks send: three launches
         if (!b.send_done) PH_TRY((launch_products<T, T>(plan_x, &send, 1, g.groups, st, "error compression")));
-        PH_TRY(tap_copy<T>(b.tap_dG_send, b.dG_send, send_count, st));
+        PH_TRY(tap_rows<T>(g, b.tap_dG_send, b.dG_send, send_rows, st));
         // Reduce-scatter as a sum on read: the input gradient's loader sums the p-1 senders' slices while it stages
         // the one reduction tile that holds dg_own, and writes dg_own out for the compressor gradient.  Conditions:
         // the block starts on a tile boundary of the reduction index and fits one tile (so a multiple of 64,
@@ -1568,7 +1579,7 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
         Product both[2] = {dx, send};
         PH_TRY((launch_products<T, T>(plan_x, both, 2, g.groups, st, "input gradient + error compression",
                                       "input gradient", "error compression")));
-        PH_TRY(tap_copy<T>(b.tap_dG_send, b.dG_send, send_count, st));
+        PH_TRY(tap_rows<T>(g, b.tap_dG_send, b.dG_send, send_rows, st));
     }
 
     if (b.below_done) *b.below_done = false;
@@ -1600,7 +1611,7 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
                                            : "weight + compressor gradients | loss",
                                send_rides && used > 256));
             if (b.below_done) *b.below_done = with_head && !send_rides;
-            if (send_rides) PH_TRY(tap_copy<T>(b.tap_dG_send, b.dG_send, send_count, st));
+            if (send_rides) PH_TRY(tap_rows<T>(g, b.tap_dG_send, b.dG_send, send_rows, st));
             return PH_OK;
         }
     }
@@ -1647,17 +1658,19 @@ ph_status check_ws(void *ws, size_t have, size_t want)
 
 // The update of layer l in the epilogues that finish its gradients (Section VI: plain SGD), `weights` (L, D and the bias) or
 // C; keep: the gradients are stored too.
-SgdInPlace sgd_of(const ph_step_args &a, int l, int64_t q, bool weights, const float *bias_grad)
+SgdInPlace sgd_of(const ph_step_args &a, int l, const Geo &g, bool weights, const float *bias_grad)
 {
     auto at = [l](auto *const *arr) { return arr ? arr[l] : nullptr; };
+    // (on padded copies the epilogues leave the gradients of D and C, which unpad_gradients_kernel takes from there)
+    const bool peers = g.q > 0 && g.k == g.k_given;
     SgdInPlace s{};
     s.lr = a.lr;
     if (weights) {
         s.master0 = at(a.Lw_master); s.w0 = a.Lw[l];
-        s.master1 = q ? at(a.Dw_master) : nullptr; s.w1 = q ? a.Dw[l] : nullptr;
-        s.keep_grad = a.dLw || a.dDw;
+        s.master1 = peers ? at(a.Dw_master) : nullptr; s.w1 = peers ? a.Dw[l] : nullptr;
+        s.keep_grad = a.dLw || (peers && a.dDw);
         s.bias_master = at(a.bias_master); s.bias_w = a.bias[l]; s.bias_grad = bias_grad;
-    } else if (q) {
+    } else if (peers) {
         s.master0 = at(a.Cw_master); s.w0 = a.Cw[l];
         s.keep_grad = a.dCw != nullptr;
     }
@@ -1672,7 +1685,7 @@ ph_status forward_taps(const std::vector<Geo> &geos, const ph_step_args &a, cons
     for (size_t l = 0; l < geos.size(); ++l) {
         const Geo &g = geos[l];
         if (a.taps->Y) PH_TRY(tap_copy<T>(a.taps->Y[l], w.Y[l], (int64_t)g.groups * g.B * g.so, st));
-        if (a.taps->g_own && g.q) PH_TRY(tap_copy<T>(a.taps->g_own[l], w.G[l], (int64_t)g.groups * g.B * g.k, st));
+        if (a.taps->g_own && g.q) PH_TRY(tap_rows<T>(g, a.taps->g_own[l], w.G[l], (int64_t)g.groups * g.B, st));
     }
     return PH_OK;
 }
@@ -1744,18 +1757,18 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
         b.dbias = dbias_of(l);
         b.dG_send = w.dG_send;
         if (update) {
-            b.sgd_w = sgd_of(a, l, q, true, b.dbias);
-            b.sgd_c = sgd_of(a, l, q, false, nullptr);
+            b.sgd_w = sgd_of(a, l, geos[(size_t)l], true, b.dbias);
+            b.sgd_c = sgd_of(a, l, geos[(size_t)l], false, nullptr);
         }
         BwdProducts pr = make_bwd_products(gl, b, delta_of(l));
         pr.dw.km = pr.dc.km = true;
         pr.dw.rowsum = b.dbias;
-        const int64_t send_count = (int64_t)g.groups * q * B * gl.k;
+        const int64_t send_rows = (int64_t)g.groups * q * B;
         void *tap_send = (a.taps && a.taps->dG_send && q) ? a.taps->dG_send[l] : nullptr;
         if (g.all && q > 0) {
             next.push_back(pr.send);
             PH_TRY(go("error compression | gradients above"));
-            PH_TRY(tap_copy<T>(tap_send, b.dG_send, send_count, st));
+            PH_TRY(tap_rows<T>(gl, tap_send, b.dG_send, send_rows, st));
             PH_TRY(launch_reduce_scatter<T>(gl, b.dG_send, b.dg_own, LossTail{}, st));
             PH_TRY(tap_copy<T>(a.taps && a.taps->dg_own ? a.taps->dg_own[l] : nullptr, b.dg_own, (int64_t)g.groups * B * gl.k, st));
             next.push_back(pr.dx);
@@ -1764,7 +1777,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
             next.push_back(pr.dx);
             next.push_back(pr.send);
             PH_TRY(go("input gradient + error compression | gradients above"));
-            PH_TRY(tap_copy<T>(tap_send, b.dG_send, send_count, st));
+            PH_TRY(tap_rows<T>(gl, tap_send, b.dG_send, send_rows, st));
         }
         if (a.taps && a.taps->delta && l > 0) PH_TRY(tap_copy<T>(a.taps->delta[l - 1], b.dX, (int64_t)g.groups * B * gl.si, st));
         next.push_back(pr.dw);
@@ -1841,8 +1854,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
             b.dCw = q ? (a.dCw ? a.dCw[l] : w.dCw[0]) : nullptr;
             b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[0]) : nullptr;
             if (update) {
-                b.sgd_w = sgd_of(a, l, q, true, dbias_of(l));
-                b.sgd_c = sgd_of(a, l, q, false, nullptr);
+                b.sgd_w = sgd_of(a, l, geos[(size_t)l], true, dbias_of(l));
+                b.sgd_c = sgd_of(a, l, geos[(size_t)l], false, nullptr);
             }
             const BwdProducts all = make_bwd_products(geos[(size_t)l], b, w.delta_of[(size_t)l]);
             all_dw.push_back(all.dw);
@@ -1910,8 +1923,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
         b.dG_send = w.dG_send;
         // SGD on this layer in the epilogues of its gradients: every launch that reads its weights is out by then
         if (update && !deferred) {
-            b.sgd_w = sgd_of(a, l, q, true, b.dbias);
-            b.sgd_c = sgd_of(a, l, q, false, nullptr);
+            b.sgd_w = sgd_of(a, l, geos[(size_t)l], true, b.dbias);
+            b.sgd_c = sgd_of(a, l, geos[(size_t)l], false, nullptr);
         }
         const Geo &gl = geos[(size_t)l];
         if (a.taps) {
@@ -1936,6 +1949,147 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
         else PH_TRY(launch_product_table(w.table, table_grid, st, what, all_dw.back(), all_dc.back(), L));
     }
     return PH_OK;
+}
+
+// ---- one rank's step on padded phantom widths --------------------------------------------------------
+// Phantom widths that 8 does not divide cost 8-byte vectors through registers (4 divides them), or the renumbering kernels of gemm_flex.h.  One rank's
+// bf16 step whose widths 8 divides therefore runs on copies of D, C, G and dg_own in which every phantom width is rounded up to a multiple
+// of 8, the rest zeros: one launch ahead of the step, and in training one behind it that takes the gradients of D and C from their
+// padded places and updates these weights.  The zeros meet zeros in every product that leaves the rank or the layer, also where a tensor holds
+// infinities.  (All ranks on the device would read each other's padded g, zeros times what may be infinite; odd phantom widths keep the levels of sums
+// that the FINE kernels give them.)
+// The layers' shapes on padded copies; empty where a step cannot run on them.
+std::vector<Geo> padded_geos(const ph_problem *prob, const std::vector<Geo> &geos)
+{
+    std::vector<Geo> out;
+    auto up = [](int64_t k) { return (k + 7) & ~(int64_t)7; };
+    bool any = false;
+    for (const Geo &g : geos) {
+        if (g.all || g.q == 0 || g.dtype != PH_BF16 || g.fine || g.si % 8 || g.so % 8) return out;
+        any = any || g.k % 8;
+    }
+    if (!any || geos.size() > (size_t)PAD_ENTRIES / 4) return out;
+    std::vector<int64_t> ks;
+    for (const Geo &g : geos) ks.push_back(up(g.k));
+    ph_problem padded = *prob;
+    padded.k = up(prob->k);
+    if (prob->widths) padded.ks = ks.data();
+    if (make_geos(&padded, out) != PH_OK) { g_err[0] = 0; out.clear(); }
+    for (size_t l = 0; l < out.size(); ++l) {
+        out[l].k_given = geos[l].k;
+        if (out[l].vec != 8) { out.clear(); break; }
+    }
+    return out;
+}
+
+// Are they worth the launches?  Where the 128 x 128 kernels then run, or the peers' part is long, which the renumbering kernels go through vector by vector,
+// or the step is.  Measured (us, on the caller's tensors : on copies).  128 x 128 kernels: 6 layers of 1024 forward at batch 8192, k 4 198 : 169, k 10 275 :
+// 169; 2 of 1024 + 3750 at 2000 214 : 92; 8 of 1024 + 28 trained at 4096 828 : 554, 4 of 1024 + 750 with GELU 495 : 348, 3 of 2048 + 300 at 2048 391 :
+// 307.  Sums of the peers' parts over the layers: 8 ranks of 256 + 100 forward at 1500, 2 layers (1400) 31 : 26, 16 of 1024 + 100 at 128 (6000)
+// 113 : 59, 32 of 512 + 18 trained at 512, 4 layers (2232) 121 : 97, 16 of 256 + 36 at 600, 3 layers (1620) 77 : 72, 32 of 256 + 10 at 256, 4 layers
+// (1240) 77.6 : 77.6, 8 of 1024 + 20 at 300, 2 layers (280) 59 : 61.5.  Steps of 64 x 64 tiles (a backward pass counts twice): 6 layers of 1024 + 84 forward at
+// 2048 (53000) 101 : 91, 4 of 1024 + 28 trained at 1024 (50000) 132 : 125; 4 of 512 + 28 forward at 1024 (4300) 32.8 : 35.5, 3 of 2048 + 108 at 256 (12900)
+// 39.9 : 46.3.
+bool padding_pays(const std::vector<Geo> &padded, bool train)
+{
+    if (padded.empty()) return false;
+    static const char *force = tuning_env("PHANTOM_PAD");              // =0 / 1 (for measurements)
+    if (force) return force[0] == '1';
+    int64_t peers = 0, steps = 0;
+    for (const Geo &g : padded) {
+        peers += g.q * g.k_given;
+        steps += ((g.B + 63) / 64) * ((g.so + 63) / 64) * ((g.Kc + 63) / 64);
+    }
+    return !use_flex(padded, train) || peers >= 1280 || steps * (train ? 3 : 1) >= 30000;
+}
+
+struct PadWs {
+    std::vector<void *> G, C, D, dg;               // per layer, NULL where the caller's tensors are used
+    std::vector<float *> dC, dD;
+};
+
+PadWs carve_pad(Arena &a, const std::vector<Geo> &padded)
+{
+    PadWs w;
+    for (const Geo &g : padded) {
+        const bool on = g.k != g.k_given;
+        auto take = [&](int64_t elems, size_t size) { return on ? a.take((size_t)elems * size) : nullptr; };
+        w.G.push_back(take(g.q * g.B * g.k, g.esz));
+        w.C.push_back(take(g.k * g.si, g.esz));
+        w.D.push_back(take(g.q * g.so * g.k, g.esz));
+        w.dg.push_back(take(g.B * g.k, g.esz));
+        w.dC.push_back((float *)take(g.k * g.si, 4));
+        w.dD.push_back((float *)take(g.q * g.so * g.k, 4));
+    }
+    return w;
+}
+
+size_t padded_ws_bytes(const std::vector<Geo> &padded)
+{
+    Arena a{nullptr, 0};
+    carve_step(a, padded);
+    carve_pad(a, padded);
+    return a.used;
+}
+
+ph_status step_on_padded(const std::vector<Geo> &geos, const ph_step_args &given, const StepWs &w, const PadWs &x, hipStream_t st)
+{
+    const size_t L = geos.size();
+    const bool train = given.mode != PH_STEP_FORWARD, update = given.mode == PH_STEP_TRAIN;
+    std::vector<void *> Cw, Dw;
+    std::vector<const void *> G, dg;
+    std::vector<float *> dC, dD;
+    PadList in{};
+    int blocks = 0;
+    auto pad = [&](const void *src, void *dst, int64_t rows, int64_t len, int64_t plen) {
+        PadList::Entry &e = in.at[in.count++];
+        e = {src, dst, (int)(rows * (plen / 8)), (int)len, (int)plen, blocks};
+        blocks += (e.vectors + 255) / 256;
+    };
+    for (size_t l = 0; l < L; ++l) {
+        const Geo &g = geos[l];
+        const bool on = g.k != g.k_given;
+        Cw.push_back(on ? x.C[l] : given.Cw[l]);
+        Dw.push_back(on ? x.D[l] : given.Dw[l]);
+        G.push_back(on ? x.G[l] : given.G[l]);
+        dg.push_back(!train ? nullptr : on ? x.dg[l] : given.dg_own[l]);
+        dC.push_back(on ? x.dC[l] : given.dCw ? given.dCw[l] : w.dCw[l & 1]);
+        dD.push_back(on ? x.dD[l] : given.dDw ? given.dDw[l] : w.dDw[l & 1]);
+        if (!on) continue;
+        pad(given.G[l], x.G[l], g.q * g.B, g.k_given, g.k);
+        pad(given.Dw[l], x.D[l], g.q * g.so, g.k_given, g.k);
+        pad(given.Cw[l], x.C[l], 1, g.k_given * g.si, g.k * g.si);
+        if (train) pad(given.dg_own[l], x.dg[l], g.B, g.k_given, g.k);
+    }
+    {
+        ProfScope prof("pad", 0, (int64_t)blocks * 2048, 0, 1, st);
+        hipLaunchKernelGGL(pad_kernel, dim3((unsigned)blocks), dim3(256), 0, st, in);
+        PH_TRY(check_launch("pad"));
+    }
+    ph_step_args a = given;
+    a.Cw = Cw.data(); a.Dw = Dw.data(); a.G = G.data();
+    a.dg_own = train ? dg.data() : nullptr;
+    a.dCw = dC.data(); a.dDw = dD.data();
+    PH_TRY(use_flex(geos, train) ? flex_step<bf16_t>(geos, a, w, st) : step_impl(geos, a, w, st));
+    UnpadList out{};
+    out.lr = given.lr;
+    blocks = 0;
+    auto unpad = [&](const float *grad, float *keep, float *master, void *weight, int64_t rows, int64_t len, int64_t plen) {
+        if (!keep && !update) return;
+        UnpadList::Entry &e = out.at[out.count++];
+        e = {grad, keep, update ? master : nullptr, weight, (int)(rows * (len / 2)), (int)len, (int)plen, blocks};
+        blocks += (e.pairs + 255) / 256;
+    };
+    for (size_t l = 0; train && l < L; ++l) {
+        const Geo &g = geos[l];
+        if (g.k == g.k_given) continue;
+        unpad(x.dD[l], given.dDw ? given.dDw[l] : nullptr, update ? given.Dw_master[l] : nullptr, given.Dw[l], g.q * g.so, g.k_given, g.k);
+        unpad(x.dC[l], given.dCw ? given.dCw[l] : nullptr, update ? given.Cw_master[l] : nullptr, given.Cw[l], 1, g.k_given * g.si, g.k * g.si);
+    }
+    if (out.count == 0) return PH_OK;
+    ProfScope prof("update of D and C", 0, (int64_t)blocks * 512, 0, 1, st);
+    hipLaunchKernelGGL(unpad_gradients_kernel, dim3((unsigned)blocks), dim3(256), 0, st, out);
+    return check_launch("update of D and C");
 }
 
 ph_status check_ptr_array(const void *const *arr, int L, const char *name)
@@ -2021,7 +2175,8 @@ ph_status phantom_workspace_bytes(const ph_problem *prob, size_t *bytes)
         if (!bytes) return fail(PH_ERR_INVALID_ARG, "bytes is NULL");
         Arena a{nullptr, 0};
         carve_step(a, geos);       // the step's layout contains the backward's; the forward needs none
-        *bytes = a.used + 256;
+        const std::vector<Geo> padded = padded_geos(prob, geos);
+        *bytes = std::max(a.used, padding_pays(padded, true) || padding_pays(padded, false) ? padded_ws_bytes(padded) : 0) + 256;
         return PH_OK;
     });
 }
@@ -2145,16 +2300,20 @@ bool output_overlaps_input(const std::vector<Geo> &geos, const ph_step_args &a)
     return any;
 }
 
-ph_status run_step(const std::vector<Geo> &geos, const ph_step_args *args, void *workspace, void *hip_stream)
+// ws_bytes: with less than the padded copies need (callers of a fixed workspace) the step runs on the caller's tensors.
+ph_status run_step(const ph_problem *prob, const std::vector<Geo> &geos, const ph_step_args *args, void *workspace, size_t ws_bytes, void *hip_stream)
 {
+    std::vector<Geo> padded = padded_geos(prob, geos);
+    if (!padding_pays(padded, args->mode != PH_STEP_FORWARD) || padded_ws_bytes(padded) > ws_bytes) padded.clear();
     Arena a{(char *)workspace, 0};
-    StepWs w = carve_step(a, geos);
+    StepWs w = carve_step(a, padded.empty() ? geos : padded);
     hipStream_t st = (hipStream_t)hip_stream;
     // The last layer writes the network output where the caller wants it, unless other workgroups or later launches still
     // read what lies there: then it writes the workspace, and the output is copied when the step is over.
     const bool copy = args->Y_out && output_overlaps_input(geos, *args);
     if (args->Y_out && !copy) w.Y.back() = args->Y_out;
-    if (geos[0].dtype == PH_F32) PH_TRY(flex_step<float>(geos, *args, w, st));
+    if (!padded.empty()) PH_TRY(step_on_padded(padded, *args, w, carve_pad(a, padded), st));
+    else if (geos[0].dtype == PH_F32) PH_TRY(flex_step<float>(geos, *args, w, st));
     else PH_TRY(use_flex(geos, args->mode != PH_STEP_FORWARD) ? flex_step<bf16_t>(geos, *args, w, st) : step_impl(geos, *args, w, st));
     if (!copy) return PH_OK;
     const Geo &last = geos.back();
@@ -2202,7 +2361,7 @@ ph_status phantom_ffn_step(const ph_problem *prob, const ph_step_args *args, voi
         size_t ws_need = 0;
         PH_TRY(check_step_args(prob, args, geos, ws_need));
         PH_TRY(check_ws(workspace, workspace_bytes, ws_need));
-        return run_step(geos, args, workspace, hip_stream);
+        return run_step(prob, geos, args, workspace, workspace_bytes, hip_stream);
     });
 }
 
@@ -2219,7 +2378,7 @@ ph_status phantom_ffn_step_static(const ph_problem *prob, const ph_step_args *ar
                                           "use phantom_ffn_step with a workspace of the caller's", ws_need, STATIC_WS_BYTES);
         void *ws = nullptr;
         PH_TRY(scratch_of_current_device(&ws));
-        return run_step(geos, args, ws, hip_stream);
+        return run_step(prob, geos, args, ws, STATIC_WS_BYTES, hip_stream);
     });
 }
 

@@ -44,7 +44,9 @@ FAMILIES = [
                                      "gradients")),
     (("delta_kernel",), "delta", ("local error",)),
     (("fill_zero_kernel", "clear_kernel"), "fill", ("clear",)),
+    (("unpad_gradients_kernel",), "unpad", ("update of D and C",)),
     (("copy_kernel",), "copy", ()),
+    (("pad_kernel",), "pad", ("pad",)),
 ]
 
 
