@@ -201,9 +201,10 @@ __global__ __launch_bounds__(256) void copy_kernel(const T *__restrict__ src, T 
     for (; i < count; i += stride) dst[i] = src[i];
 }
 
-// Copies of bf16 matrices whose rows of `len` elements become rows of `plen`, a multiple of 8, with zeros behind them: 16 bytes per thread.
+// Copies of bf16 matrices (or of float ones, as twice the columns) whose rows of `len` elements become rows of `plen`, a multiple of 8, with zeros behind
+// them: 16 bytes per thread.
 // len is even, so that every row starts on a word.  Bound by the launch: 9 MB for 6 layers of 7 peers' G [8192, 4] and D [1024, 4] to 8.
-constexpr int PAD_ENTRIES = 64;
+constexpr int PAD_ENTRIES = 112;
 struct PadList {
     struct Entry {
         const void *src;
@@ -235,21 +236,22 @@ __global__ __launch_bounds__(256) void pad_kernel(PadList list)
     ((Words *)e.dst)[v] = x;
 }
 
-// What becomes of float gradients in rows of `plen` with `len` (even) elements that count: out <- the gradient (NULL: not wanted), and
-// SGD on the weights as the epilogues do it (master == NULL: none).  Two elements per thread.
+// Back from rows of `plen` floats with `len` (even) that count: out <- the gradient (NULL: not wanted), master <- the updated fp32 weights and
+// w <- the same in bf16 (master == NULL: no update).  Two elements per thread.
 struct UnpadList {
     struct Entry {
         const float *grad;
-        float *out, *master;
+        float *out;
+        const float *updated;
+        float *master;
         void *w;
         int pairs, len, plen, first_block;
     } at[PAD_ENTRIES / 2];
     int count;
-    float lr;
 };
 static_assert(sizeof(UnpadList) <= 3840, "travels as kernel arguments (4 KB with the hidden ones)");
 
-__global__ __launch_bounds__(256) void unpad_gradients_kernel(UnpadList list)
+__global__ __launch_bounds__(256) void unpad_kernel(UnpadList list)
 {
     int j = 0;
     while (j + 1 < list.count && (int)blockIdx.x >= list.at[j + 1].first_block) ++j;      // uniform
@@ -259,15 +261,13 @@ __global__ __launch_bounds__(256) void unpad_gradients_kernel(UnpadList list)
     typedef float F2 __attribute__((ext_vector_type(2)));
     typedef bf16_t B2 __attribute__((ext_vector_type(2)));
     const int per_row = e.len / 2, row = v / per_row, col = (v - row * per_row) * 2;
-    const F2 g = *(const F2 *)(e.grad + (int64_t)row * e.plen + col);
+    const int64_t from = (int64_t)row * e.plen + col;
     if (e.master) {                                    // uniform
-        F2 m = ((F2 *)e.master)[v];
-        m[0] -= list.lr * g[0];
-        m[1] -= list.lr * g[1];
+        const F2 m = *(const F2 *)(e.updated + from);
         ((F2 *)e.master)[v] = m;
         ((B2 *)e.w)[v] = B2{(bf16_t)m[0], (bf16_t)m[1]};
     }
-    if (e.out) ((F2 *)e.out)[v] = g;                   // uniform
+    if (e.out) ((F2 *)e.out)[v] = *(const F2 *)(e.grad + from);      // uniform
 }
 
 // dst [rows, len] <- the first len columns of src [rows, plen]

@@ -41,8 +41,7 @@ struct Epilogue {
 // belongs to, laid out like the output's two regions.  w0 == nullptr: none.
 struct SgdInPlace {
     float *master0, *master1;    // bf16 storage: fp32 master copies: master -= lr * gradient.  NULL with fp32 storage.
-    void *w0, *w1;               // bf16: compute copies, w = bf16(master).  fp32: w -= lr * gradient.  w1 == NULL, bf16: the gradients of
-                                 //   region 1 are stored instead
+    void *w0, *w1;               // bf16: compute copies, w = bf16(master).  fp32: w -= lr * gradient
     float lr;
     int keep_grad;               // also store the gradient (the caller wants to see it)
     float *bias_master;          // weight gradients only: the layer's bias [M], likewise

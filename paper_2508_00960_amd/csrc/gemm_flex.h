@@ -566,7 +566,7 @@ __device__ __forceinline__ void flex_request(FlexAhead<T, PASSES> &R, const Flex
         }
     } else {
         if (sgd.w0) {
-            float *const m0_ = sizeof(T) == 2 ? sgd.master0 : (float *)sgd.w0, *const m1_ = sizeof(T) == 4 ? (float *)sgd.w1 : sgd.w1 ? sgd.master1 : (float *)Q.o1;
+            float *const m0_ = sizeof(T) == 2 ? sgd.master0 : (float *)sgd.w0, *const m1_ = sizeof(T) == 2 ? sgd.master1 : (float *)sgd.w1;
             const float *base = l.region ? m1_ + g * Q.o_g1 + l.off : m0_ + g * Q.o_g0 + l.off;
             const int64_t ld = flex_pick<int64_t>(l.region, Q.o_ld0, Q.o_ld1);
 #pragma unroll
@@ -709,9 +709,9 @@ __device__ __forceinline__ void flex_epilogue(const FlexIn &P, const FlexOut &Q,
         }
         const int64_t o_at = l.region ? g * Q.o_g1 + (int64_t)m * Q.o_ld1 + l.off : g * Q.o_g0 + (int64_t)m * Q.o_ld0 + l.off;
         if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
-            void *const w0 = sgd.w0, *const w1 = sgd.w1;
-            void *const w = l.region ? w1 : w0;
-            if (w) {
+            if (sgd.w0) {                              // uniform
+                void *const w0 = sgd.w0, *const w1 = sgd.w1;
+                void *const w = l.region ? w1 : w0;
                 if constexpr (sizeof(T) == 2) {
                     float *const m0 = sgd.master0, *const m1 = sgd.master1;
                     float *const master = (l.region ? m1 : m0) + o_at;

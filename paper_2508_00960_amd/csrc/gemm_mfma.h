@@ -669,8 +669,7 @@ struct EpilogueReads {
         if constexpr (MASTERS) {
             if (Q.sgd.w0) {                                    // uniform
                 const Loc lc = locate(Q.o.c, n, Q.o.skip0 + g * Q.o.skip_g);
-                const float *const second = Q.sgd.w1 ? Q.sgd.master1 : (const float *)Q.o.p1;
-                const float *base = lc.region > 0 ? second + g * Q.o.g1 + lc.off1 : Q.sgd.master0 + g * Q.o.g0 + lc.off0;
+                const float *base = lc.region > 0 ? Q.sgd.master1 + g * Q.o.g1 + lc.off1 : Q.sgd.master0 + g * Q.o.g0 + lc.off0;
                 const int64_t ld = lc.region > 0 ? Q.o.r.mult1 : Q.o.r.mult0;
 #pragma unroll
                 for (int h = 0; h < GROUP; ++h) masters[h] = gload<FlV>(base + (int64_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
@@ -818,7 +817,7 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaIn &P, const MfmaOut
 #pragma unroll
         for (int u = 0; u < VEC; ++u) o[u] = from_f32<TOut>(x[u]);
         if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
-            if (region ? Q.sgd.w1 : Q.sgd.w0) {   // Section VI's plain SGD on the finished gradient
+            if (Q.sgd.w0) {                       // uniform: Section VI's plain SGD on the finished gradient
                 const int64_t at = dst - (region ? o1 : o0);
                 float *master = (region ? Q.sgd.master1 : Q.sgd.master0) + g * (region ? Q.o.g1 : Q.o.g0) + at;
                 __bf16 *w = (__bf16 *)(region ? Q.sgd.w1 : Q.sgd.w0) + g * (region ? Q.o.g1 : Q.o.g0) + at;

@@ -1658,19 +1658,17 @@ ph_status check_ws(void *ws, size_t have, size_t want)
 
 // The update of layer l in the epilogues that finish its gradients (Section VI: plain SGD), `weights` (L, D and the bias) or
 // C; keep: the gradients are stored too.
-SgdInPlace sgd_of(const ph_step_args &a, int l, const Geo &g, bool weights, const float *bias_grad)
+SgdInPlace sgd_of(const ph_step_args &a, int l, int64_t q, bool weights, const float *bias_grad)
 {
     auto at = [l](auto *const *arr) { return arr ? arr[l] : nullptr; };
-    // (on padded copies the epilogues leave the gradients of D and C, which unpad_gradients_kernel takes from there)
-    const bool peers = g.q > 0 && g.k == g.k_given;
     SgdInPlace s{};
     s.lr = a.lr;
     if (weights) {
         s.master0 = at(a.Lw_master); s.w0 = a.Lw[l];
-        s.master1 = peers ? at(a.Dw_master) : nullptr; s.w1 = peers ? a.Dw[l] : nullptr;
-        s.keep_grad = a.dLw || (peers && a.dDw);
+        s.master1 = q ? at(a.Dw_master) : nullptr; s.w1 = q ? a.Dw[l] : nullptr;
+        s.keep_grad = a.dLw || a.dDw;
         s.bias_master = at(a.bias_master); s.bias_w = a.bias[l]; s.bias_grad = bias_grad;
-    } else if (peers) {
+    } else if (q) {
         s.master0 = at(a.Cw_master); s.w0 = a.Cw[l];
         s.keep_grad = a.dCw != nullptr;
     }
@@ -1757,8 +1755,8 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
         b.dbias = dbias_of(l);
         b.dG_send = w.dG_send;
         if (update) {
-            b.sgd_w = sgd_of(a, l, geos[(size_t)l], true, b.dbias);
-            b.sgd_c = sgd_of(a, l, geos[(size_t)l], false, nullptr);
+            b.sgd_w = sgd_of(a, l, q, true, b.dbias);
+            b.sgd_c = sgd_of(a, l, q, false, nullptr);
         }
         BwdProducts pr = make_bwd_products(gl, b, delta_of(l));
         pr.dw.km = pr.dc.km = true;
@@ -1854,8 +1852,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
             b.dCw = q ? (a.dCw ? a.dCw[l] : w.dCw[0]) : nullptr;
             b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[0]) : nullptr;
             if (update) {
-                b.sgd_w = sgd_of(a, l, geos[(size_t)l], true, dbias_of(l));
-                b.sgd_c = sgd_of(a, l, geos[(size_t)l], false, nullptr);
+                b.sgd_w = sgd_of(a, l, q, true, dbias_of(l));
+                b.sgd_c = sgd_of(a, l, q, false, nullptr);
             }
             const BwdProducts all = make_bwd_products(geos[(size_t)l], b, w.delta_of[(size_t)l]);
             all_dw.push_back(all.dw);
@@ -1923,8 +1921,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
         b.dG_send = w.dG_send;
         // SGD on this layer in the epilogues of its gradients: every launch that reads its weights is out by then
         if (update && !deferred) {
-            b.sgd_w = sgd_of(a, l, geos[(size_t)l], true, b.dbias);
-            b.sgd_c = sgd_of(a, l, geos[(size_t)l], false, nullptr);
+            b.sgd_w = sgd_of(a, l, q, true, b.dbias);
+            b.sgd_c = sgd_of(a, l, q, false, nullptr);
         }
         const Geo &gl = geos[(size_t)l];
         if (a.taps) {
@@ -1954,8 +1952,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
 // ---- one rank's step on padded phantom widths --------------------------------------------------------
 // Phantom widths that 8 does not divide cost 8-byte vectors through registers (4 divides them), or the renumbering kernels of gemm_flex.h.  One rank's
 // bf16 step whose widths 8 divides therefore runs on copies of D, C, G and dg_own in which every phantom width is rounded up to a multiple
-// of 8, the rest zeros: one launch ahead of the step, and in training one behind it that takes the gradients of D and C from their
-// padded places and updates these weights.  The zeros meet zeros in every product that leaves the rank or the layer, also where a tensor holds
+// of 8, the rest zeros: one launch ahead of the step, and in training one behind it that takes the gradients and the updated weights of D
+// and C from their padded places.  The zeros meet zeros in every product that leaves the rank or the layer, also where a tensor holds
 // infinities.  (All ranks on the device would read each other's padded g, zeros times what may be infinite; odd phantom widths keep the levels of sums
 // that the FINE kernels give them.)
 // The layers' shapes on padded copies; empty where a step cannot run on them.
@@ -1968,7 +1966,7 @@ std::vector<Geo> padded_geos(const ph_problem *prob, const std::vector<Geo> &geo
         if (g.all || g.q == 0 || g.dtype != PH_BF16 || g.fine || g.si % 8 || g.so % 8) return out;
         any = any || g.k % 8;
     }
-    if (!any || geos.size() > (size_t)PAD_ENTRIES / 4) return out;
+    if (!any || geos.size() > (size_t)PAD_ENTRIES / 6) return out;
     std::vector<int64_t> ks;
     for (const Geo &g : geos) ks.push_back(up(g.k));
     ph_problem padded = *prob;
@@ -1977,7 +1975,7 @@ std::vector<Geo> padded_geos(const ph_problem *prob, const std::vector<Geo> &geo
     if (make_geos(&padded, out) != PH_OK) { g_err[0] = 0; out.clear(); }
     for (size_t l = 0; l < out.size(); ++l) {
         out[l].k_given = geos[l].k;
-        if (out[l].vec != 8) { out.clear(); break; }
+        if (out[l].vec != 8 || out[l].k * out[l].si >= (int64_t)1 << 29) { out.clear(); break; }      // (PadList counts a C's elements in 32 bits)
     }
     return out;
 }
@@ -2005,7 +2003,7 @@ bool padding_pays(const std::vector<Geo> &padded, bool train)
 
 struct PadWs {
     std::vector<void *> G, C, D, dg;               // per layer, NULL where the caller's tensors are used
-    std::vector<float *> dC, dD;
+    std::vector<float *> dC, dD, mC, mD;           // (masters: mC, mD)
 };
 
 PadWs carve_pad(Arena &a, const std::vector<Geo> &padded)
@@ -2020,6 +2018,8 @@ PadWs carve_pad(Arena &a, const std::vector<Geo> &padded)
         w.dg.push_back(take(g.B * g.k, g.esz));
         w.dC.push_back((float *)take(g.k * g.si, 4));
         w.dD.push_back((float *)take(g.q * g.so * g.k, 4));
+        w.mC.push_back((float *)take(g.k * g.si, 4));
+        w.mD.push_back((float *)take(g.q * g.so * g.k, 4));
     }
     return w;
 }
@@ -2038,9 +2038,10 @@ ph_status step_on_padded(const std::vector<Geo> &geos, const ph_step_args &given
     const bool train = given.mode != PH_STEP_FORWARD, update = given.mode == PH_STEP_TRAIN;
     std::vector<void *> Cw, Dw;
     std::vector<const void *> G, dg;
-    std::vector<float *> dC, dD;
+    std::vector<float *> dC, dD, mC, mD;
     PadList in{};
     int blocks = 0;
+    // rows of `len` 2-byte elements (a float counts as two)
     auto pad = [&](const void *src, void *dst, int64_t rows, int64_t len, int64_t plen) {
         PadList::Entry &e = in.at[in.count++];
         e = {src, dst, (int)(rows * (plen / 8)), (int)len, (int)plen, blocks};
@@ -2052,44 +2053,48 @@ ph_status step_on_padded(const std::vector<Geo> &geos, const ph_step_args &given
         Cw.push_back(on ? x.C[l] : given.Cw[l]);
         Dw.push_back(on ? x.D[l] : given.Dw[l]);
         G.push_back(on ? x.G[l] : given.G[l]);
-        dg.push_back(!train ? nullptr : on ? x.dg[l] : given.dg_own[l]);
-        dC.push_back(on ? x.dC[l] : given.dCw ? given.dCw[l] : w.dCw[l & 1]);
-        dD.push_back(on ? x.dD[l] : given.dDw ? given.dDw[l] : w.dDw[l & 1]);
+        if (train) dg.push_back(on ? x.dg[l] : given.dg_own[l]);
+        if (given.dCw) dC.push_back(on ? x.dC[l] : given.dCw[l]);
+        if (given.dDw) dD.push_back(on ? x.dD[l] : given.dDw[l]);
+        if (update) mC.push_back(on ? x.mC[l] : given.Cw_master[l]);
+        if (update) mD.push_back(on ? x.mD[l] : given.Dw_master[l]);
         if (!on) continue;
         pad(given.G[l], x.G[l], g.q * g.B, g.k_given, g.k);
         pad(given.Dw[l], x.D[l], g.q * g.so, g.k_given, g.k);
         pad(given.Cw[l], x.C[l], 1, g.k_given * g.si, g.k * g.si);
         if (train) pad(given.dg_own[l], x.dg[l], g.B, g.k_given, g.k);
+        if (update) pad(given.Dw_master[l], x.mD[l], g.q * g.so, 2 * g.k_given, 2 * g.k);
+        if (update) pad(given.Cw_master[l], x.mC[l], 1, 2 * g.k_given * g.si, 2 * g.k * g.si);
     }
     {
         ProfScope prof("pad", 0, (int64_t)blocks * 2048, 0, 1, st);
         hipLaunchKernelGGL(pad_kernel, dim3((unsigned)blocks), dim3(256), 0, st, in);
         PH_TRY(check_launch("pad"));
     }
+    auto arr = [](auto &v) { return v.empty() ? nullptr : v.data(); };
     ph_step_args a = given;
-    a.Cw = Cw.data(); a.Dw = Dw.data(); a.G = G.data();
-    a.dg_own = train ? dg.data() : nullptr;
-    a.dCw = dC.data(); a.dDw = dD.data();
+    a.Cw = Cw.data(); a.Dw = Dw.data(); a.G = G.data(); a.dg_own = arr(dg);
+    a.dCw = arr(dC); a.dDw = arr(dD);
+    a.Cw_master = arr(mC); a.Dw_master = arr(mD);
     PH_TRY(use_flex(geos, train) ? flex_step<bf16_t>(geos, a, w, st) : step_impl(geos, a, w, st));
     UnpadList out{};
-    out.lr = given.lr;
     blocks = 0;
-    auto unpad = [&](const float *grad, float *keep, float *master, void *weight, int64_t rows, int64_t len, int64_t plen) {
+    auto unpad = [&](const float *grad, float *keep, const float *from, float *master, void *weight, int64_t rows, int64_t len, int64_t plen) {
         if (!keep && !update) return;
         UnpadList::Entry &e = out.at[out.count++];
-        e = {grad, keep, update ? master : nullptr, weight, (int)(rows * (len / 2)), (int)len, (int)plen, blocks};
+        e = {grad, keep, from, master, weight, (int)(rows * (len / 2)), (int)len, (int)plen, blocks};
         blocks += (e.pairs + 255) / 256;
     };
     for (size_t l = 0; train && l < L; ++l) {
         const Geo &g = geos[l];
         if (g.k == g.k_given) continue;
-        unpad(x.dD[l], given.dDw ? given.dDw[l] : nullptr, update ? given.Dw_master[l] : nullptr, given.Dw[l], g.q * g.so, g.k_given, g.k);
-        unpad(x.dC[l], given.dCw ? given.dCw[l] : nullptr, update ? given.Cw_master[l] : nullptr, given.Cw[l], 1, g.k_given * g.si, g.k * g.si);
+        unpad(x.dD[l], given.dDw ? given.dDw[l] : nullptr, x.mD[l], update ? given.Dw_master[l] : nullptr, given.Dw[l], g.q * g.so, g.k_given, g.k);
+        unpad(x.dC[l], given.dCw ? given.dCw[l] : nullptr, x.mC[l], update ? given.Cw_master[l] : nullptr, given.Cw[l], 1, g.k_given * g.si, g.k * g.si);
     }
     if (out.count == 0) return PH_OK;
-    ProfScope prof("update of D and C", 0, (int64_t)blocks * 512, 0, 1, st);
-    hipLaunchKernelGGL(unpad_gradients_kernel, dim3((unsigned)blocks), dim3(256), 0, st, out);
-    return check_launch("update of D and C");
+    ProfScope prof("D and C from padded rows", 0, (int64_t)blocks * 512, 0, 1, st);
+    hipLaunchKernelGGL(unpad_kernel, dim3((unsigned)blocks), dim3(256), 0, st, out);
+    return check_launch("D and C from padded rows");
 }
 
 ph_status check_ptr_array(const void *const *arr, int L, const char *name)

@@ -44,7 +44,7 @@ FAMILIES = [
                                      "gradients")),
     (("delta_kernel",), "delta", ("local error",)),
     (("fill_zero_kernel", "clear_kernel"), "fill", ("clear",)),
-    (("unpad_gradients_kernel",), "unpad", ("update of D and C",)),
+    (("unpad_kernel",), "unpad", ("D and C from padded rows",)),
     (("copy_kernel",), "copy", ()),
     (("pad_kernel",), "pad", ("pad",)),
 ]

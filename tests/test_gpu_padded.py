@@ -6,7 +6,7 @@ import torch
 import paper_2508_00960_amd as ph
 import phantom_inputs as pin
 
-from helpers import workspace
+from helpers import empty_f32, to_gpu, to_gpu_f32, workspace
 from stage_check import check_stages
 
 pytestmark = pytest.mark.gpu
@@ -26,6 +26,31 @@ def test_parity(n, p, k, B, L, act, mode, widths, ks):
     print(f"case padded n={n} p={p} k={k} B={B} L={L} {act} {mode}", flush=True)
     prob = pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=0, widths=widths, ks=ks)
     check_stages(prob, seed=8, lr=0.02, mode=mode)
+
+
+def test_gradients_that_nobody_takes():
+    """Layers alike on the copies, of which some need none, deltas where a launch per layer has its gradients: the weights come out the same, bit for
+    bit, whether or not the caller takes the gradients (the launches add the same terms in the same order)."""
+    print("case padded, gradients not taken", flush=True)
+    n, p, B, L, ks = 4096, 2, 1100, 4, (28, 32, 28, 32)
+    prob = pin.Problem(n=n, p=p, k=32, batch=B, layers=L, act="relu", dtype="bf16", rank=0, widths=(n,) * (L + 1), ks=ks)
+    data = pin.one_rank_step_inputs(prob, 3)
+    pc = ph.make_problem(n, p, 32, B, L, "relu", "bf16", 0, widths=prob.widths, ks=ks)
+    names = ("Lw", "Cw", "Dw", "bias")
+    outs = []
+    for taken in (True, False):
+        W = {nm: [to_gpu(P[nm], "bf16") for P in data["layers"]] for nm in names}
+        M = {nm: [to_gpu_f32(P[nm]) for P in data["layers"]] for nm in names}
+        Gd = {nm: [empty_f32(P[nm].shape) for P in data["layers"]] if taken else None for nm in names}
+        ph.ffn_step(pc, to_gpu(data["X0"], "bf16"), to_gpu(data["T"], "bf16"), W["Lw"], W["Cw"], W["Dw"], W["bias"], Lw_master=M["Lw"], Cw_master=M["Cw"],
+                    Dw_master=M["Dw"], bias_master=M["bias"], G=[to_gpu(P["G"], "bf16") for P in data["layers"]],
+                    dg_own=[to_gpu(P["dg_own"], "bf16") for P in data["layers"]], dLw=Gd["Lw"], dCw=Gd["Cw"], dDw=Gd["Dw"], dbias=Gd["bias"],
+                    loss=empty_f32((4,)), lr=0.02, mode="train", workspace=workspace(ph.workspace_bytes(pc)))
+        torch.cuda.synchronize()
+        outs.append(M)
+    for nm in ("Lw", "Cw", "Dw"):                      # (the bias gradients are added with atomics)
+        for l in range(L):
+            assert torch.equal(outs[0][nm][l], outs[1][nm][l]), (nm, l)
 
 
 def test_infinities():
