@@ -1729,8 +1729,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma_fwd_kernel(MfmaFwdBatch fb)
         const int last = min(first + fb.thin_rows, fb.M);
         for (int m0 = first; m0 < last; m0 += THIN_ROWS) {           // uniform
             __syncthreads();                                         // the epilogue, or the block before, is done with LDS
-            if (fb.N <= 32) thin_workgroup<1, 8>(fb.X, fb.C, fb.G, last, fb.N, fb.K, fb.x_g, fb.c_g, fb.o_g, m0, grp, (float *)smem_raw);
-            else thin_workgroup<2, 8>(fb.X, fb.C, fb.G, last, fb.N, fb.K, fb.x_g, fb.c_g, fb.o_g, m0, grp, (float *)smem_raw);
+            if (fb.N <= 32) thin_workgroup<2, 8>(fb.X, fb.C, fb.G, last, fb.N, fb.K, fb.x_g, fb.c_g, fb.o_g, m0, grp, (float *)smem_raw);
+            else thin_workgroup<4, 8>(fb.X, fb.C, fb.G, last, fb.N, fb.K, fb.x_g, fb.c_g, fb.o_g, m0, grp, (float *)smem_raw);
         }
     }
 }

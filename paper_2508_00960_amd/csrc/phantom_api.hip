@@ -1284,12 +1284,9 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
     auto launch_thin = [&]() -> ph_status {
         ProfScope prof("compression", B, k, si, g.groups, st);
         dim3 grid((unsigned)((B + THIN_ROWS - 1) / THIN_ROWS), (unsigned)g.groups);
-        if (k <= 32)
-            hipLaunchKernelGGL((thin_product_kernel<1>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
-                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, take_clear());
-        else
-            hipLaunchKernelGGL((thin_product_kernel<2>), grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
-                               (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, take_clear());
+        auto kern = k <= 16 ? thin_product_kernel<1> : k <= 32 ? thin_product_kernel<2> : thin_product_kernel<4>;
+        hipLaunchKernelGGL(kern, grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw, (__bf16 *)f.g_own, (int)B, (int)k, (int)si,
+                           B * si, k * si, B * k, take_clear());
         return check_launch("compression");
     };
     // (this layer's update adds into the buffers itself if it is the last one)

@@ -4,9 +4,12 @@
 // As a tile of the general product it has few workgroups (one per 128 rows: 64 for an 8192-row batch)
 // and every one of them walks the whole reduction range, so three quarters of the device wait for
 // 14 us.  Here a workgroup owns 32 rows and all n; its eight wavefronts split the reduction range and
-// feed the MFMAs straight from global memory (a lane's operand is 16 contiguous bytes of one row; the
-// four 16-byte pieces of a 128-byte line are used by consecutive steps of the same wavefront, from L1),
-// then add their partial sums through LDS.  C (k x s, at most 128 KB) is read by every workgroup, from L2.
+// feed the MFMAs straight from global memory, then add their partial sums through LDS.  C (k x s, at most 128 KB) is
+// read by every workgroup, from L2.
+// What bounds it: the loads of operands in the MFMA's layout, 16 contiguous bytes of a row per lane.  On
+// v_mfma_f32_16x16x32_bf16 an instruction covers 64 bytes of 16 rows, where v_mfma_f32_32x32x16_bf16 covers 32 bytes of 32,
+// and up to 16 phantom neurons read half as much of C.  Us a step (32x32x16 : so): gradients of 64 ranks of 256 + 8, 4 layers at
+// batch 512, 465 : 458; 8 ranks of 512 + 32 and 1024 + 64 in turn, 4 layers trained at 1024, 370 : 363.
 #pragma once
 #include "common.h"
 #include "elementwise.h"    // ClearList
@@ -20,10 +23,10 @@ constexpr int THIN_MAX_N = 64;
 constexpr int THIN_WAVES = 8;       // wavefronts per workgroup of the stand-alone kernel
 
 typedef __bf16 thin_bf16x8 __attribute__((ext_vector_type(8)));
-typedef float thin_f32x16 __attribute__((ext_vector_type(16)));
+typedef float thin_f32x4 __attribute__((ext_vector_type(4)));
 
-// One workgroup's share: rows [m0, m0 + 32) of group grp.  NF = number of 32-wide column blocks (1: N <= 32,
-// 2: N <= 64); WAVES wavefronts split the K / 16 reduction chunks (K is a multiple of 16); part: WAVES * NF * 1024
+// One workgroup's share: rows [m0, m0 + 32) of group grp.  NF = number of 16-wide column blocks (N <= 16 NF);
+// WAVES wavefronts split the reduction range (K is a multiple of 16) in chunks of 32; part: WAVES * NF * 512
 // floats of LDS.  x_g, c_g, o_g: element offsets per group.
 // M: end of the rows this call may read and store (the matrix's row count, or the end of a shorter share of a
 // 32-row block: the MFMA rows beyond it repeat the last one and are dropped).
@@ -32,69 +35,88 @@ __device__ __forceinline__ void thin_workgroup(const __bf16 *__restrict__ X, con
                                                __bf16 *__restrict__ G, int M, int N, int K, int64_t x_g, int64_t c_g,
                                                int64_t o_g, int m0, int grp, float *part)
 {
+    constexpr int MF = THIN_ROWS / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const __bf16 *x = X + grp * x_g, *c = C + grp * c_g;
     __bf16 *out = G + grp * o_g;
-    auto part_at = [part](int w, int f, int e, int l) -> float & { return part[((w * NF + f) * 16 + e) * 64 + l]; };
+    // [wavefront][row block][column block][accumulator][lane], turned such that a wavefront that reads whole rows meets every bank once
+    auto part_at = [part](int w, int r, int f, int e, int l) -> float & { return part[(((w * MF + r) * NF + f) * 4 + e) * 64 + ((l + 16 * (f + NF * e)) & 63)]; };
 
-    // this wavefront's share of the K / 16 reduction chunks
-    const int chunks = K >> 4;
+    // this wavefront's share of the whole chunks; the last one takes the half that may be left
+    const int chunks = K >> 5;
     const int c_lo = (int)((int64_t)chunks * wave / WAVES), c_hi = (int)((int64_t)chunks * (wave + 1) / WAVES);
-    // MFMA operand of a lane: row (lane & 31), 8 consecutive reduction indices starting at 8 * (lane >> 5).
+    // MFMA operand of a lane: row (lane & 15), 8 consecutive reduction indices starting at 8 * (lane >> 4).
     // Rows past the end read the last row; what they produce is never stored.
-    const int half = (lane >> 5) * 8;
-    const __bf16 *xrow = x + (int64_t)min(m0 + (lane & 31), M - 1) * K + half;
-    const __bf16 *crow[NF];
+    const int quarter = (lane >> 4) * 8;
+    const __bf16 *xrow[MF], *crow[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) crow[f] = c + (int64_t)min(f * 32 + (lane & 31), N - 1) * K + half;
+    for (int r = 0; r < MF; ++r) xrow[r] = x + (int64_t)min(m0 + r * 16 + (lane & 15), M - 1) * K + quarter;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) crow[f] = c + (int64_t)min(f * 16 + (lane & 15), N - 1) * K + quarter;
 
-    thin_f32x16 acc[NF];
+    thin_f32x4 acc[MF][NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
+    for (int r = 0; r < MF; ++r)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[f][e] = 0.f;
-    // eight chunks' loads in flight together, then four, then one at a time (a 1024-wide shard gives a wavefront exactly eight)
+        for (int f = 0; f < NF; ++f) acc[r][f] = thin_f32x4{0.f, 0.f, 0.f, 0.f};
+    // four chunks' loads in flight together, then two, then one (a 1024-wide shard gives a wavefront exactly four)
     int ch = c_lo;
     auto batch = [&](auto count) {
-        constexpr int N = decltype(count)::value;
-        thin_bf16x8 a[N], b[NF][N];
+        constexpr int U = decltype(count)::value;
+        thin_bf16x8 a[MF][U], b[NF][U];
 #pragma unroll
-        for (int u = 0; u < N; ++u) {
-            a[u] = *(const thin_bf16x8 *)(xrow + (ch + u) * 16);
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
-            for (int f = 0; f < NF; ++f) b[f][u] = *(const thin_bf16x8 *)(crow[f] + (ch + u) * 16);
+            for (int r = 0; r < MF; ++r) a[r][u] = *(const thin_bf16x8 *)(xrow[r] + (ch + u) * 32);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) b[f][u] = *(const thin_bf16x8 *)(crow[f] + (ch + u) * 32);
         }
 #pragma unroll
-        for (int u = 0; u < N; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[f][u], acc[f], 0, 0, 0);
-        ch += N;
+            for (int r = 0; r < MF; ++r)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) acc[r][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][u], b[f][u], acc[r][f], 0, 0, 0);
+        ch += U;
     };
-    while (ch + 8 <= c_hi) batch(std::integral_constant<int, 8>{});
-    if (ch + 4 <= c_hi) batch(std::integral_constant<int, 4>{});
-    for (; ch < c_hi; ++ch) {
-        const thin_bf16x8 a = *(const thin_bf16x8 *)(xrow + ch * 16);
+    while (ch + 4 <= c_hi) batch(std::integral_constant<int, 4>{});
+    if (ch + 2 <= c_hi) batch(std::integral_constant<int, 2>{});
+    if (ch < c_hi) batch(std::integral_constant<int, 1>{});
+    if ((K & 16) && wave == WAVES - 1) {               // uniform: the upper 16 indices of the chunk do not exist
+        const int at = quarter < 16 ? chunks * 32 : chunks * 32 - 16;      // (in bounds: read by their neighbours' lanes too)
+        const auto half = [&](const __bf16 *row) {
+            thin_bf16x8 v = *(const thin_bf16x8 *)(row + at);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            const thin_bf16x8 b = *(const thin_bf16x8 *)(crow[f] + ch * 16);
-            acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[f], 0, 0, 0);
+            for (int i = 0; i < 8; ++i) v[i] = quarter < 16 ? v[i] : (__bf16)0.f;
+            return v;
+        };
+        thin_bf16x8 b[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) b[f] = half(crow[f]);
+#pragma unroll
+        for (int r = 0; r < MF; ++r) {
+            const thin_bf16x8 a = half(xrow[r]);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) acc[r][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[f], acc[r][f], 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
+    for (int r = 0; r < MF; ++r)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) part_at(wave, f, e, lane) = acc[f][e];
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part_at(wave, r, f, e, lane) = acc[r][f][e];
     __syncthreads();
 
-    // accumulator e of lane l in column block f is element (row 8*(e/4) + 4*(l>>5) + e%4, column 32*f + (l&31))
-    for (int o = threadIdx.x; o < THIN_ROWS * NF * 32; o += WAVES * 64) {
-        const int row = o / (NF * 32), col = o - row * (NF * 32);
+    // accumulator e of lane l in blocks r, f is element (row 16 r + 4 (l >> 4) + e, column 16 f + (l & 15))
+    for (int o = threadIdx.x; o < THIN_ROWS * NF * 16; o += WAVES * 64) {
+        const int row = o / (NF * 16), col = o - row * (NF * 16);
         const int m = m0 + row;
         if (m >= M || col >= N) continue;
-        const int f = col >> 5, e = (row >> 3) * 4 + (row & 3), l = (col & 31) + 32 * ((row >> 2) & 1);
+        const int r = row >> 4, f = col >> 4, e = row & 3, l = (col & 15) + 16 * ((row >> 2) & 3);
         float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) sum += part_at(w, f, e, l);
+        for (int w = 0; w < WAVES; ++w) sum += part_at(w, r, f, e, l);
         out[(int64_t)m * N + col] = (__bf16)sum;
     }
 }
@@ -108,7 +130,7 @@ __global__ __launch_bounds__(THIN_WAVES * 64) void thin_product_kernel(const __b
                                                           ClearList clear)
 {
     clear_rider(clear, (int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y), THIN_WAVES * 64);
-    __shared__ float part[THIN_WAVES * NF * 16 * 64];  // [wavefront][column block][accumulator][lane]
+    __shared__ float part[THIN_WAVES * NF * 512];
     thin_workgroup<NF, THIN_WAVES>(X, C, G, M, N, K, x_g, c_g, o_g, blockIdx.x * THIN_ROWS, blockIdx.y, part);
 }
 

@@ -63,3 +63,17 @@ def test_layer_calls_of_one_rank(n, p, k, B, act, rank):
 def test_all_gradients_of_large_layers_together(n, p, k, B, L, act, mode):
     print(f"case large layers n={n} p={p} k={k} B={B} L={L} {act} {mode}", flush=True)
     check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=0), seed=5, lr=0.02, mode=mode)
+
+
+@pytest.mark.parametrize("n,p,k,B,L,act,rank,mode", [
+    (4160, 4, 8, 1100, 1, "relu", -1, "no_update"),       # shard 1040: half a chunk of the reduction is left; one block of 16 columns, half of it empty
+    (4160, 4, 12, 1100, 1, "gelu", -1, "forward"),        # 4-element vectors in the update
+    (2176, 4, 16, 2001, 1, "relu", -1, "forward"),        # shard 544: chunks that the wavefronts share unevenly; a last block of 17 rows
+    (2112, 4, 24, 2000, 2, "relu", -1, "no_update"),      # shard 528, two blocks
+    (4160, 4, 64, 1100, 1, "relu", -1, "forward"),        # four blocks
+    (4128, 2, 40, 2100, 1, "relu", 0, "forward"),         # one rank's step of one layer: behind the update's epilogue, shares of 16 rows
+    (4128, 2, 24, 2100, 1, "relu", 1, "forward"),
+])
+def test_thin_compression(n, p, k, B, L, act, rank, mode):
+    print(f"case thin n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode}", flush=True)
+    check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="bf16", rank=rank), seed=13, lr=0.02, mode=mode)
