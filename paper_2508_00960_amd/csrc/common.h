@@ -87,6 +87,22 @@ __device__ __forceinline__ Part args_at(size_t offset)
     return out.p;
 }
 
+// Reads one word of every 64 bytes of a piece of the kernel's argument, so that a later args_at finds it in the scalar cache.
+template <typename Part>
+__device__ __forceinline__ void touch_args(size_t offset)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef const uint32_t __attribute__((address_space(4))) *ArgWords;
+    const ArgWords in = (ArgWords)((const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+    constexpr int LINES = (int)(sizeof(Part) + 63) / 64;
+    uint32_t w[LINES];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) w[i] = in[min(i * 16, (int)(sizeof(Part) / 4) - 1)];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) asm volatile("" :: "s"(w[i]));
+#endif
+}
+
 // x / d with magic = ceil(2^32 / d) (0 for d = 1), x below 2^31: a few scalar instructions in the place of some thirty
 __device__ __forceinline__ int div_by(int x, int d, uint32_t magic)
 {

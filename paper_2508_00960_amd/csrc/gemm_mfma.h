@@ -641,11 +641,10 @@ struct EpilogueReads {
     static constexpr int PASSES = MT * PER_ROW / THREADS, ROWS_PER_PASS = THREADS / PER_ROW;
     static_assert(THREADS % PER_ROW == 0, "a thread keeps its columns from pass to pass");
     static constexpr bool MSE = EPI == EPI_BIAS_ACT && sizeof(TOut) == 2;
-    // The master weights of an update: not with two tiles per workgroup, such launches fill the chip and are bound by the bytes of
-    // the update (dense 4096 x 4096: 642 -> 657 us with it).
-    static constexpr bool MASTERS = EPI == EPI_STORE && sizeof(TOut) == 4 && MODE != TILE_DUAL;
+    // The master weights of an update.
+    static constexpr bool MASTERS = EPI == EPI_STORE && sizeof(TOut) == 4;
     // passes that are unrolled together and whose reads are in flight together, a group ahead of their use
-    static constexpr int GROUP = EPI == EPI_DACT ? PASSES : MASTERS ? 4 : 2;
+    static constexpr int GROUP = EPI == EPI_DACT ? PASSES : MASTERS && MODE == TILE_DUAL ? 8 : MASTERS || MSE ? 4 : 2;
     static_assert(PASSES % GROUP == 0, "whole groups");
     union AuxU { FlV f; BfV h; unsigned bits; __device__ AuxU() {} };
     BfV bias;
@@ -654,25 +653,26 @@ struct EpilogueReads {
     FlV masters[MASTERS ? GROUP : 1];
 
     // the target's and the master weights' vectors of passes i0 .. i0 + GROUP - 1
-    // (addresses clamped into the tile's valid part instead of skipped: no branch per load)
+    // (addresses clamped into the tile's valid part instead of skipped: no branch per load.  Element offsets inside a group fit 32 bits.)
     __device__ __forceinline__ void group(const MfmaIn &P, const MfmaOut &Q, int g, int m0, int n0, int thread, int i0)
     {
         const int row = m0 + i0 * ROWS_PER_PASS + thread / PER_ROW, n = min(n0 + (thread % PER_ROW) * VEC, P.N - VEC);
         if constexpr (MSE) {
             const Epilogue &ep = Q.ep;
             if (ep.mode == EPI_BIAS_ACT && ep.mse_target) {    // uniform
+                const __bf16 *base = (const __bf16 *)ep.mse_target + g * ep.aux_g;
 #pragma unroll
                 for (int h = 0; h < GROUP; ++h)
-                    target[h] = gload<BfV>((const __bf16 *)ep.mse_target + g * ep.aux_g + (int64_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ep.aux_ld + n);
+                    target[h] = gload<BfV>(base + ((uint32_t)min(row + h * ROWS_PER_PASS, P.M - 1) * (uint32_t)ep.aux_ld + (uint32_t)n));
             }
         }
         if constexpr (MASTERS) {
             if (Q.sgd.w0) {                                    // uniform
                 const Loc lc = locate(Q.o.c, n, Q.o.skip0 + g * Q.o.skip_g);
                 const float *base = lc.region > 0 ? Q.sgd.master1 + g * Q.o.g1 + lc.off1 : Q.sgd.master0 + g * Q.o.g0 + lc.off0;
-                const int64_t ld = lc.region > 0 ? Q.o.r.mult1 : Q.o.r.mult0;
+                const uint32_t ld = (uint32_t)(lc.region > 0 ? Q.o.r.mult1 : Q.o.r.mult0);
 #pragma unroll
-                for (int h = 0; h < GROUP; ++h) masters[h] = gload<FlV>(base + (int64_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
+                for (int h = 0; h < GROUP; ++h) masters[h] = gload<FlV>(base + (uint32_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
             }
         }
     }
@@ -695,22 +695,23 @@ __device__ __forceinline__ void epilogue_request(EpilogueReads<VEC, TOut, MODE, 
         if (ep.mode == EPI_DACT && ep.aux) {
             // One straight run of loads per kind of aux: with the choice of kind and the bounds test inside the loop every pass was a
             // basic block of its own and the compiler waited for each pass's load before it issued the next one's.
-            int64_t at[Reads::PASSES];
+            uint32_t at[Reads::PASSES];
 #pragma unroll
             for (int i = 0; i < Reads::PASSES; ++i) {
                 const int v = thread + i * Reads::THREADS;
                 const int m = min(m0 + v / Reads::PER_ROW, P.M - 1), n = min(n0 + (v % Reads::PER_ROW) * VEC, P.N - VEC);
-                at[i] = g * ep.aux_g + (int64_t)m * ep.aux_ld + n;
+                at[i] = (uint32_t)m * (uint32_t)ep.aux_ld + (uint32_t)n;
             }
+            const int64_t first = g * ep.aux_g;                // (of groups: a multiple of aux_ld, which VEC divides)
             if (ep.aux_bits) {                         // uniform
 #pragma unroll
-                for (int i = 0; i < Reads::PASSES; ++i) R.aux[i].bits = gload<uint8_t>((const uint8_t *)ep.aux + (at[i] >> 3));
+                for (int i = 0; i < Reads::PASSES; ++i) R.aux[i].bits = gload<uint8_t>((const uint8_t *)ep.aux + (first >> 3) + (at[i] >> 3));
             } else if (ep.aux_deriv) {
 #pragma unroll
-                for (int i = 0; i < Reads::PASSES; ++i) R.aux[i].f = gload_nt<FlV>((const float *)ep.aux + at[i]);   // read once
+                for (int i = 0; i < Reads::PASSES; ++i) R.aux[i].f = gload_nt<FlV>((const float *)ep.aux + first + at[i]);   // read once
             } else {
 #pragma unroll
-                for (int i = 0; i < Reads::PASSES; ++i) R.aux[i].h = gload<BfV>((const __bf16 *)ep.aux + at[i]);
+                for (int i = 0; i < Reads::PASSES; ++i) R.aux[i].h = gload<BfV>((const __bf16 *)ep.aux + first + at[i]);
             }
         }
     }
@@ -719,153 +720,208 @@ __device__ __forceinline__ void epilogue_request(EpilogueReads<VEC, TOut, MODE, 
 
 // rows [m0, m0+128) x columns [n0, n0+128) of the output = sum of the two teams' fp32 tiles in LDS, walked by
 // all 512 threads; one team per tile: the tile at ctile alone, walked by the team's 256 threads (thread = 0..255)
-template <int VEC, typename TOut, int MODE, int EPI>
+// Nothing runs beside it where a workgroup has its compute unit for itself, and the vector instructions bound it: with every choice taken pass by
+// pass, 64-bit products for every address, and sums and derivatives that nobody had asked for, they were some 120 for 8 elements; now 65.
+// Clocks, before : now: ReLU forward, two tiles 7350 : 4270, one 4610 : 2840; GELU 11200 : 5500; input gradient with sigma' in bf16, two tiles
+// 3670 : 1900, one 2470 : 1600.
+// What a wavefront stores in one instruction has no gaps: 16 bytes per thread, so 8 columns of bf16 and 4 of floats.  With 8 floats to a thread an
+// instruction wrote every other 16 bytes of its lines and the next one the rest, which the memory takes at half its rate.  Floats, halves : whole: GELU with
+// sigma' kept, 4096 x 1024 outputs 28.5 : 24.9 us a launch (epilogue 11700 : 8000 clocks); gradients 4096 x 4096 over 512 rows 44.2 : 31.3.
+// Passes, us, both steps: 8 layers of 1024 + 960 with GELU trained at batch 4096 631 : 587; gradients of 64 ranks of 256 + 16 at 512 467 : 454, 6 layers
+// of 1024 + 28 forward at 8192 183 : 175.
+enum { EPI_PIECEWISE, EPI_GELU, EPI_GELU_DERIV };      // EPI_BIAS_ACT: not GELU; GELU; GELU whose derivative is kept
+template <int VEC, typename TOut, int MODE, int EPI, int ACT>
 __device__ __forceinline__ void epilogue_from_lds(const MfmaIn &P, const MfmaOut &Q, int g, const float *ctile, int m0, int n0, int thread,
                                                   float *wave_sums, EpilogueReads<VEC, TOut, MODE, EPI> &R)
 {
     typedef EpilogueReads<VEC, TOut, MODE, EPI> Reads;
     constexpr bool SOLO = MODE != TILE_SHARED;         // one team per tile
-    constexpr int THREADS = Reads::THREADS, PER_ROW = Reads::PER_ROW, PASSES = Reads::PASSES, GROUP = Reads::GROUP;
+    constexpr int THREADS = Reads::THREADS, PER_ROW = Reads::PER_ROW, PASSES = Reads::PASSES, GROUP = Reads::GROUP, ROWS_PER_PASS = Reads::ROWS_PER_PASS;
     typedef typename PackOf<TOut, VEC>::type OutV;
     typedef typename Reads::BfV BfV;
     typedef typename Reads::FlV FlV;
-    TOut *o0 = (TOut *)Q.o.p0 + g * Q.o.g0, *o1 = (TOut *)Q.o.p1 + g * Q.o.g1;
-    const int skip_o = Q.o.skip0 + g * Q.o.skip_g;
     const Epilogue &ep = Q.ep;
+    // A thread's columns stay the same; its row moves down ROWS_PER_PASS a pass, and its addresses by the same amount (element
+    // offsets inside a group fit 32 bits).
+    const int col = (thread % PER_ROW) * VEC, n = n0 + col, row0 = thread / PER_ROW;
+    const int rows = n < P.N ? P.M - m0 - row0 : 0;    // pass i has a row of the output: i * ROWS_PER_PASS < rows
+    const Loc ln = locate(Q.o.c, n, Q.o.skip0 + g * Q.o.skip_g);
+    const bool tail = ln.region > 0;
+    const int64_t out_first = tail ? g * Q.o.g1 + ln.off1 : g * Q.o.g0 + ln.off0;
+    const uint32_t out_ld = (uint32_t)(tail ? Q.o.r.mult1 : Q.o.r.mult0);
+    TOut *const out = (TOut *)(tail ? Q.o.p1 : Q.o.p0) + out_first;
+    const uint32_t out_step = ROWS_PER_PASS * out_ld, aux_step = ROWS_PER_PASS * (uint32_t)ep.aux_ld;
+    uint32_t out_at = (uint32_t)(m0 + row0) * out_ld, aux_at = (uint32_t)(m0 + row0) * (uint32_t)ep.aux_ld + (uint32_t)n;
+    const int64_t aux_first = g * ep.aux_g;
+    const float *ct = ctile + row0 * CT_PITCH + col;
+    const bool mse = EPI == EPI_BIAS_ACT && sizeof(TOut) == 2 && ep.mode == EPI_BIAS_ACT && ep.mse_target;      // uniform
+    const bool sums = EPI != EPI_STORE && ep.colsum;                                                            // uniform
     float csum[VEC];                                   // this thread's share of the column sums (ep.colsum)
 #pragma unroll
     for (int u = 0; u < VEC; ++u) csum[u] = 0.f;
     float sq_sum = 0.f;                                // ... and of the squared output error (ep.mse_target)
 #pragma unroll 1
     for (int i0 = 0; i0 < PASSES; i0 += GROUP) {
-    const Reads now = R;                               // the group's target and master weights; the next group's are requested
-    if (i0 + GROUP < PASSES) R.group(P, Q, g, m0, n0, thread, i0 + GROUP);
+        const Reads now = R;                           // the group's target and master weights; the next group's are requested
+        if (i0 + GROUP < PASSES) R.group(P, Q, g, m0, n0, thread, i0 + GROUP);
+        // Every choice below is the same for the whole workgroup and taken once for the group, not pass by pass: its passes then run as one
+        // straight piece of code.  Rows past the output's end are computed like the others (from what the loaders repeat) and not stored.
+        float x[GROUP][VEC], deriv[GROUP][VEC];        // deriv: sigma'(pre-activation)
+        bool ok[GROUP];
 #pragma unroll
-    for (int h = 0; h < GROUP; ++h) {
-        const int i = i0 + h;
-        const int v = thread + i * THREADS;
-        const int row = v / PER_ROW, col = (v % PER_ROW) * VEC;
-        const int m = m0 + row, n = n0 + col;
-        if (m >= P.M || n >= P.N) continue;
-        float x[VEC];
-        {
-            const FlV c0 = *(const FlV *)(ctile + row * CT_PITCH + col);
+        for (int h = 0; h < GROUP; ++h) {
+            ok[h] = (i0 + h) * ROWS_PER_PASS < rows;
+            const float *from = ct + (i0 + h) * ROWS_PER_PASS * CT_PITCH;
+            const FlV c0 = *(const FlV *)from;
             if constexpr (SOLO) {
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) x[u] = c0[u];
+                for (int u = 0; u < VEC; ++u) x[h][u] = c0[u];
             } else {
-                const FlV c1 = *(const FlV *)(ctile + CT_ELEMS + row * CT_PITCH + col);
+                const FlV c1 = *(const FlV *)(from + CT_ELEMS);
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) x[u] = c0[u] + c1[u];
+                for (int u = 0; u < VEC; ++u) x[h][u] = c0[u] + c1[u];
             }
         }
-        const int64_t aux_at = g * ep.aux_g + (int64_t)m * ep.aux_ld + n;
-        float deriv[VEC];                              // EPI_BIAS_ACT: sigma'(pre-activation), for the output error
+        const auto store_aux = [&](const float (&v)[GROUP][VEC]) {             // in the storage type
+#pragma unroll
+            for (int h = 0; h < GROUP; ++h) {
+                BfV a;
+#pragma unroll
+                for (int u = 0; u < VEC; ++u) a[u] = (__bf16)v[h][u];
+                if (ok[h]) gstore<BfV>((__bf16 *)ep.aux + aux_first + (aux_at + h * aux_step), a);
+            }
+        };
         if (EPI == EPI_BIAS_ACT && ep.mode == EPI_BIAS_ACT) {
 #pragma unroll
-            for (int u = 0; u < VEC; ++u) x[u] += (float)now.bias[u];
-            if (ep.act == ACT_GELU) {                  // uniform
-                float pre[VEC];
+            for (int h = 0; h < GROUP; ++h)
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) {
-                    pre[u] = x[u];
-                    gelu_both(pre[u], x[u], deriv[u]);
-                }
-                if (ep.aux) {
-                    if (ep.aux_deriv) {
-                        // written once, read once by the backward pass much later: a streaming store keeps it from
-                        // pushing the operand panels that other workgroups still share out of L2
+                for (int u = 0; u < VEC; ++u) x[h][u] += (float)now.bias[u];
+            if constexpr (ACT != EPI_PIECEWISE) {
+                if (ACT == EPI_GELU && ep.aux) store_aux(x);
+#pragma unroll
+                for (int h = 0; h < GROUP; ++h)
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) {
+                        const float pre = x[h][u];
+                        gelu_both(pre, x[h][u], deriv[h][u]);
+                    }
+                if constexpr (ACT == EPI_GELU_DERIV) {
+                    // written once, read once by the backward pass much later: a streaming store keeps it from
+                    // pushing the operand panels that other workgroups still share out of L2
+#pragma unroll
+                    for (int h = 0; h < GROUP; ++h) {
                         FlV a;
 #pragma unroll
-                        for (int u = 0; u < VEC; ++u) a[u] = deriv[u];
-                        gstore_nt<FlV>((float *)ep.aux + aux_at, a);
-                    } else {
-                        BfV a;
-#pragma unroll
-                        for (int u = 0; u < VEC; ++u) a[u] = (__bf16)pre[u];
-                        gstore<BfV>((__bf16 *)ep.aux + aux_at, a);
+                        for (int u = 0; u < VEC; ++u) a[u] = deriv[h][u];
+                        if (ok[h]) gstore_nt<FlV>((float *)ep.aux + aux_first + (aux_at + h * aux_step), a);
                     }
                 }
             } else {
-                if (ep.aux && !ep.aux_bits) {
-                    BfV a;
+                if (ep.aux && !ep.aux_bits) store_aux(x);
+                if (ep.act == ACT_RELU) {
 #pragma unroll
-                    for (int u = 0; u < VEC; ++u) a[u] = (__bf16)x[u];
-                    gstore<BfV>((__bf16 *)ep.aux + aux_at, a);
+                    for (int h = 0; h < GROUP; ++h)
+#pragma unroll
+                        for (int u = 0; u < VEC; ++u) x[h][u] = __builtin_fmaxf(x[h][u], 0.f);      // (of a NaN: 0)
                 }
-                piecewise_both(ep.act, x, deriv);
             }
         } else if (EPI == EPI_DACT && ep.mode == EPI_DACT && ep.aux) {      // no aux: sigma' = 1, column sums only
-            const typename Reads::AuxU &av = now.aux[EPI == EPI_DACT ? h : 0];
             if (ep.aux_bits) {                         // one bit per element: ReLU' of the stored output
                 if constexpr (VEC == 8) {
 #pragma unroll
-                    for (int u = 0; u < VEC; ++u) x[u] = (av.bits >> u) & 1u ? x[u] : 0.f;
+                    for (int h = 0; h < GROUP; ++h)
+#pragma unroll
+                        for (int u = 0; u < VEC; ++u) x[h][u] = (now.aux[EPI == EPI_DACT ? h : 0].bits >> u) & 1u ? x[h][u] : 0.f;
                 }
             } else if (ep.aux_deriv) {                 // sigma' itself, float
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) x[u] *= av.f[u];
+                for (int h = 0; h < GROUP; ++h)
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) x[h][u] *= now.aux[EPI == EPI_DACT ? h : 0].f[u];
             } else {                                   // ReLU output in bf16
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) x[u] = (float)av.h[u] > 0.f ? x[u] : x[u] * 0.f;
+                for (int h = 0; h < GROUP; ++h)
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) x[h][u] = (float)now.aux[EPI == EPI_DACT ? h : 0].h[u] > 0.f ? x[h][u] : x[h][u] * 0.f;
             }
         }
-        const Loc ln = locate(Q.o.c, n, skip_o);
-        const int region = ln.region > 0 ? 1 : 0;
-        TOut *dst = (region ? o1 + ln.off1 : o0 + ln.off0) + (int64_t)m * (region ? Q.o.r.mult1 : Q.o.r.mult0);
-        OutV o;
+        OutV o[GROUP];
 #pragma unroll
-        for (int u = 0; u < VEC; ++u) o[u] = from_f32<TOut>(x[u]);
+        for (int h = 0; h < GROUP; ++h)
+#pragma unroll
+            for (int u = 0; u < VEC; ++u) o[h][u] = from_f32<TOut>(x[h][u]);
+        bool store = true;
         if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
-            if (Q.sgd.w0) {                       // uniform: Section VI's plain SGD on the finished gradient
-                const int64_t at = dst - (region ? o1 : o0);
-                float *master = (region ? Q.sgd.master1 : Q.sgd.master0) + g * (region ? Q.o.g1 : Q.o.g0) + at;
-                __bf16 *w = (__bf16 *)(region ? Q.sgd.w1 : Q.sgd.w0) + g * (region ? Q.o.g1 : Q.o.g0) + at;
-                const FlV before = Reads::MASTERS ? now.masters[Reads::MASTERS ? h : 0] : gload<FlV>(master);
-                FlV after;
-                BfV rounded;
+            if (Q.sgd.w0) {                            // uniform: Section VI's plain SGD on the finished gradient
+                float *const masters = (tail ? Q.sgd.master1 : Q.sgd.master0) + out_first;
+                __bf16 *const weights = (__bf16 *)(tail ? Q.sgd.w1 : Q.sgd.w0) + out_first;
+                store = Q.sgd.keep_grad;
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) {
-                    after[u] = before[u] - Q.sgd.lr * x[u];
-                    rounded[u] = (__bf16)after[u];
+                for (int h = 0; h < GROUP; ++h) {
+                    if (!ok[h]) continue;
+                    float *const master = masters + (out_at + h * out_step);
+                    const FlV before = now.masters[Reads::MASTERS ? h : 0];
+                    FlV after;
+                    BfV rounded;
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) {
+                        after[u] = before[u] - Q.sgd.lr * x[h][u];
+                        rounded[u] = (__bf16)after[u];
+                    }
+                    // (the master is next read a step later, by this epilogue; the bf16 copy by the next forward pass, which
+                    // found it in the last-level cache before a streaming store put it out of there: 1.8 us per forward launch)
+                    gstore_nt<FlV>(master, after);
+                    gstore<BfV>(weights + (out_at + h * out_step), rounded);
                 }
-                // (the master is next read a step later, by this epilogue; the bf16 copy by the next forward pass, which
-                // found it in the last-level cache before a streaming store put it out of there: 1.8 us per forward launch)
-                gstore_nt<FlV>(master, after);
-                gstore<BfV>(w, rounded);
-                if (!Q.sgd.keep_grad) continue;
             }
         }
-        // (outputs are written once and read by a later launch at the earliest: a streaming store leaves less for the
-        // write-back at the end of the kernel; 0.4 % of configuration 4's step, 2-4 % of the forward-only and small ones)
-        gstore_nt<OutV>(dst, o);
+        if (store) {                                   // uniform
+            // (outputs are written once and read by a later launch at the earliest: a streaming store leaves less for the
+            // write-back at the end of the kernel; 0.4 % of configuration 4's step, 2-4 % of the forward-only and small ones)
+#pragma unroll
+            for (int h = 0; h < GROUP; ++h)
+                if (ok[h]) gstore_nt<OutV>(out + (out_at + h * out_step), o[h]);
+        }
         if constexpr (EPI == EPI_BIAS_ACT && VEC == 8) {
             if (ep.mode == EPI_BIAS_ACT && ep.aux && ep.aux_bits) {     // uniform
-                unsigned bits = 0;
 #pragma unroll
-                for (int u = 0; u < VEC; ++u) bits |= ((float)o[u] > 0.f ? 1u : 0u) << u;
-                gstore<uint8_t>((uint8_t *)ep.aux + (aux_at >> 3), (uint8_t)bits);
+                for (int h = 0; h < GROUP; ++h) {
+                    unsigned bits = 0;
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) bits |= ((float)o[h][u] > 0.f ? 1u : 0u) << u;
+                    if (ok[h]) gstore<uint8_t>((uint8_t *)ep.aux + (aux_first >> 3) + ((aux_at + h * aux_step) >> 3), (uint8_t)bits);
+                }
             }
         }
-        if (EPI == EPI_BIAS_ACT && sizeof(TOut) == 2 && ep.mode == EPI_BIAS_ACT && ep.mse_target) {      // uniform
+        if (mse) {
             // the MSE output error of Eq. (deltaL) from the output as stored, rounded once
-            const BfV t = now.target[Reads::MSE ? h : 0];
-            BfV dl;
 #pragma unroll
-            for (int u = 0; u < VEC; ++u) {
-                const float diff = (float)o[u] - (float)t[u];
-                sq_sum += diff * diff;
-                float e = diff * ep.mse_inv_b;
-                if (ep.act != ACT_IDENTITY) e *= deriv[u];
-                dl[u] = (__bf16)e;
-                csum[u] += (float)dl[u];
+            for (int h = 0; h < GROUP; ++h) {
+                if (!ok[h]) continue;
+                const BfV t = now.target[Reads::MSE ? h : 0];
+                BfV dl;
+#pragma unroll
+                for (int u = 0; u < VEC; ++u) {
+                    const float diff = (float)o[h][u] - (float)t[u];
+                    sq_sum += diff * diff;
+                    float e = diff * ep.mse_inv_b;
+                    if (ACT != EPI_PIECEWISE) e *= deriv[h][u];
+                    else if (ep.act == ACT_RELU) e *= x[h][u] > 0.f ? 1.f : 0.f;
+                    dl[u] = (__bf16)e;
+                    csum[u] += (float)dl[u];
+                }
+                gstore<BfV>((__bf16 *)ep.mse_delta + aux_first + (aux_at + h * aux_step), dl);
             }
-            gstore<BfV>((__bf16 *)ep.mse_delta + aux_at, dl);
-        } else {
+        } else if (sums) {
 #pragma unroll
-            for (int u = 0; u < VEC; ++u) csum[u] += (float)o[u];
+            for (int h = 0; h < GROUP; ++h)
+                if (ok[h]) {
+#pragma unroll
+                    for (int u = 0; u < VEC; ++u) csum[u] += (float)o[h][u];
+                }
         }
-    }
+        out_at += GROUP * out_step;
+        aux_at += GROUP * aux_step;
     }
     if constexpr (EPI == EPI_STORE && sizeof(TOut) == 4) {
         if (Q.sgd.bias_master && n0 == 0 && thread < MT && m0 + thread < P.M) {
@@ -912,7 +968,7 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaIn &P, const MfmaOut
 }
 
 // The epilogue of one piece of a reduction that is cut into ksplit pieces without atomics (float output, plain store
-// semantics, 8 columns per thread, all 512 threads).  Every piece writes its 128 x 128 result to its own slot of
+// semantics, 4 columns per thread, all 512 threads).  Every piece writes its 128 x 128 result to its own slot of
 // Q.parts and then counts itself in Q.arrived[tile]; the piece that finds all others counted adds the slots up in the
 // order of the pieces (its own from registers), writes the output and leaves the word zero for the next launch.  The
 // sum does not depend on which piece comes last, and no workgroup ever waits for another.
@@ -925,7 +981,7 @@ __device__ __forceinline__ void epilogue_pieces_from_lds(const MfmaIn &P, const 
                                                          int m0, int n0, int thread)
 {
     typedef unsigned long long u64;
-    constexpr int VEC = 8, PER_ROW = MT / VEC, PASSES = MT * PER_ROW / MFMA_THREADS, WORDS = VEC / 2;
+    constexpr int VEC = 4, PER_ROW = MT / VEC, PASSES = MT * PER_ROW / MFMA_THREADS, WORDS = VEC / 2;
     constexpr int ROWS_PER_PASS = MFMA_THREADS / PER_ROW;
     constexpr int64_t SLOT = MT * MT / 2;              // 8-byte words per slot
     constexpr int GROUP = 2;                           // other pieces whose loads are in flight together
@@ -937,13 +993,9 @@ __device__ __forceinline__ void epilogue_pieces_from_lds(const MfmaIn &P, const 
     for (int i = 0; i < PASSES; ++i) {
         const int v = thread + i * MFMA_THREADS;
         const int row = v / PER_ROW, col = (v % PER_ROW) * VEC;
+        const f32x4 c0 = *(const f32x4 *)(ctile + row * CT_PITCH + col), c1 = *(const f32x4 *)(ctile + CT_ELEMS + row * CT_PITCH + col);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const f32x4 c0 = *(const f32x4 *)(ctile + row * CT_PITCH + col + 4 * h);
-            const f32x4 c1 = *(const f32x4 *)(ctile + CT_ELEMS + row * CT_PITCH + col + 4 * h);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[i][4 * h + u] = c0[u] + c1[u];
-        }
+        for (int u = 0; u < VEC; ++u) x[i][u] = c0[u] + c1[u];
     }
     u64 *slots = (u64 *)Q.parts + (int64_t)tile * P.ksplit * SLOT;
     u64 *mine = slots + ks * SLOT + thread;
@@ -1010,21 +1062,19 @@ __device__ __forceinline__ void epilogue_pieces_from_lds(const MfmaIn &P, const 
         if (Q.sgd.w0) {                           // uniform: Section VI's plain SGD on the finished gradient
             float *master = (region ? Q.sgd.master1 : Q.sgd.master0) + at;
             __bf16 *w = (__bf16 *)(region ? Q.sgd.w1 : Q.sgd.w0) + at;
-            const f32x4 m_lo = gload<f32x4>(master), m_hi = gload<f32x4>(master + 4);
-            float nm[VEC];
-            bf16x8 nw;
+            const f32x4 before = gload<f32x4>(master);
+            f32x4 after;
+            typename PackOf<__bf16, VEC>::type rounded;
 #pragma unroll
             for (int u = 0; u < VEC; ++u) {
-                nm[u] = (u < 4 ? m_lo[u] : m_hi[u - 4]) - Q.sgd.lr * t[i][u];
-                nw[u] = (__bf16)nm[u];
+                after[u] = before[u] - Q.sgd.lr * t[i][u];
+                rounded[u] = (__bf16)after[u];
             }
-            gstore_nt<f32x4>(master, f32x4{nm[0], nm[1], nm[2], nm[3]});
-            gstore_nt<f32x4>(master + 4, f32x4{nm[4], nm[5], nm[6], nm[7]});
-            gstore<bf16x8>(w, nw);
+            gstore_nt<f32x4>(master, after);
+            gstore<typename PackOf<__bf16, VEC>::type>(w, rounded);
             if (!Q.sgd.keep_grad) continue;
         }
         gstore_nt<f32x4>(dst, f32x4{t[i][0], t[i][1], t[i][2], t[i][3]});
-        gstore_nt<f32x4>(dst + 4, f32x4{t[i][4], t[i][5], t[i][6], t[i][7]});
     }
     if (thread == 0) __hip_atomic_store(Q.arrived + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1064,7 +1114,12 @@ struct OutFromArgs {
     size_t offset;
     __device__ __forceinline__ MfmaOut operator()() const { return args_at<MfmaOut>(offset + offsetof(MfmaParams, out)); }
 };
-__device__ __forceinline__ MfmaIn in_from_args(size_t offset) { return args_at<MfmaIn>(offset + offsetof(MfmaParams, in)); }
+// ... and the part that the reduction needs, with the epilogue's on its way to the scalar cache: first asked for behind the reduction, it took 700 clocks.
+__device__ __forceinline__ MfmaIn in_from_args(size_t offset)
+{
+    touch_args<MfmaOut>(offset + offsetof(MfmaParams, out));
+    return args_at<MfmaIn>(offset + offsetof(MfmaParams, in));
+}
 
 // DUAL: the two teams take two tiles that lie one above the other (rows m0 .. m0+127 and m0+128 .. m0+255)
 // instead of the reduction of one tile.  They share the B tile (each team stages half of its
@@ -1409,6 +1464,7 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaIn &P, int wg, ReadOut 
     f32x16 acc[2][2];
     if constexpr (VA == 8) reduce_in_ring<KA, KB, MODE, FOLD, LEVELS>(P, g, m0, n0, tn, k_begin, k_end, acc, fs, (uint32_t)(uintptr_t)(LdsBytes)smem_raw);
     else reduce_in_registers<KA, KB, VA, VB, MODE>(P, g, m0, n0, tm, k_begin, k_end, acc, smem_raw);
+    const MfmaOut Q = read_out();
     __syncthreads();
     PH_PHASE(3);
 
@@ -1417,17 +1473,29 @@ __device__ __forceinline__ void mfma_workgroup(const MfmaIn &P, int wg, ReadOut 
     float *ctile = (float *)smem_raw;
     constexpr bool PIECES = MODE == TILE_SHARED && !FOLD && EPI == EPI_STORE && sizeof(TOut) == 4 && VA == 8;
     const int thread = DUAL || SOLO ? tid : (int)threadIdx.x;
-    const MfmaOut Q = read_out();
     const bool piece = PIECES && Q.parts && P.ksplit > 1;            // uniform (one group: the host sees to that)
-    EpilogueReads<VA, TOut, MODE, EPI> reads;
-    if (!piece) epilogue_request(reads, P, Q, g, m0, n0, thread);
-    acc_to_lds(ctile + team * CT_ELEMS, acc, wm, wn, lane);
-    __syncthreads();
-    PH_PHASE(4);
-    if constexpr (PIECES)
-        if (piece) epilogue_pieces_from_lds(P, Q, rem, ks, ctile, (unsigned *)(ctile + 2 * CT_ELEMS), m0, n0, thread);
-    if (!piece)
-        epilogue_from_lds<VA, TOut, MODE, EPI>(P, Q, g, ctile + (DUAL || SOLO ? team * CT_ELEMS : 0), m0, n0, thread, ctile + (SOLO ? 1 : 2) * CT_ELEMS, reads);
+    auto finish = [&](auto vec, auto act) {
+        EpilogueReads<decltype(vec)::value, TOut, MODE, EPI> reads;
+        if (!piece) epilogue_request(reads, P, Q, g, m0, n0, thread);
+        acc_to_lds(ctile + team * CT_ELEMS, acc, wm, wn, lane);
+        __syncthreads();
+        PH_PHASE(4);
+        if constexpr (PIECES)
+            if (piece) epilogue_pieces_from_lds(P, Q, rem, ks, ctile, (unsigned *)(ctile + 2 * CT_ELEMS), m0, n0, thread);
+        if (!piece)
+            epilogue_from_lds<decltype(vec)::value, TOut, MODE, EPI, decltype(act)::value>(P, Q, g, ctile + (DUAL || SOLO ? team * CT_ELEMS : 0), m0, n0, thread,
+                                                                                            ctile + (SOLO ? 1 : 2) * CT_ELEMS, reads);
+    };
+    // 16 bytes per thread and store, see epilogue_from_lds (with 8 elements, GELU alone, whose derivative nobody wants, is 1 % faster than with 4)
+    typedef std::integral_constant<int, sizeof(TOut) == 4 ? 4 : VA> Wide;
+    typedef std::integral_constant<int, EPI_PIECEWISE> Piecewise;
+    if constexpr (EPI == EPI_BIAS_ACT) {
+        if (Q.ep.act != ACT_GELU) finish(Wide{}, Piecewise{});       // (uniform choices)
+        else if (Q.ep.aux && Q.ep.aux_deriv) finish(std::integral_constant<int, 4>{}, std::integral_constant<int, EPI_GELU_DERIV>{});
+        else finish(Wide{}, std::integral_constant<int, EPI_GELU>{});
+    } else {
+        finish(Wide{}, Piecewise{});
+    }
     PH_PHASE(5);
     if constexpr (FOLD) {
         if (fs.on) {                                                 // uniform
