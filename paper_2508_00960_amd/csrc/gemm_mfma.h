@@ -641,7 +641,9 @@ struct EpilogueReads {
     static constexpr int PASSES = MT * PER_ROW / THREADS, ROWS_PER_PASS = THREADS / PER_ROW;
     static_assert(THREADS % PER_ROW == 0, "a thread keeps its columns from pass to pass");
     static constexpr bool MSE = EPI == EPI_BIAS_ACT && sizeof(TOut) == 2;
-    // The master weights of an update.
+    // The master weights of an update: streaming reads, as nothing else reads them for the rest of the step.  Kept in L2, they push the operand tiles that
+    // other workgroups still share out of it (us a pass, kept : streaming: dense 4 x 4096 trained at batch 1024 541 : 503, 8 layers of 1024 + 960 at 4096
+    // 587 : 577, 8 ranks of 512 / 1024 337 : 326; a launch of 4096 x 4096 over 2048 rows alone, whose masters stay in the last-level cache, 93 : 97).
     static constexpr bool MASTERS = EPI == EPI_STORE && sizeof(TOut) == 4;
     // passes that are unrolled together and whose reads are in flight together, a group ahead of their use
     static constexpr int GROUP = EPI == EPI_DACT ? PASSES : MASTERS && MODE == TILE_DUAL ? 8 : MASTERS || MSE ? 4 : 2;
@@ -672,7 +674,7 @@ struct EpilogueReads {
                 const float *base = lc.region > 0 ? Q.sgd.master1 + g * Q.o.g1 + lc.off1 : Q.sgd.master0 + g * Q.o.g0 + lc.off0;
                 const uint32_t ld = (uint32_t)(lc.region > 0 ? Q.o.r.mult1 : Q.o.r.mult0);
 #pragma unroll
-                for (int h = 0; h < GROUP; ++h) masters[h] = gload<FlV>(base + (uint32_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
+                for (int h = 0; h < GROUP; ++h) masters[h] = gload_nt<FlV>(base + (uint32_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
             }
         }
     }
@@ -1062,7 +1064,7 @@ __device__ __forceinline__ void epilogue_pieces_from_lds(const MfmaIn &P, const 
         if (Q.sgd.w0) {                           // uniform: Section VI's plain SGD on the finished gradient
             float *master = (region ? Q.sgd.master1 : Q.sgd.master0) + at;
             __bf16 *w = (__bf16 *)(region ? Q.sgd.w1 : Q.sgd.w0) + at;
-            const f32x4 before = gload<f32x4>(master);
+            const f32x4 before = gload_nt<f32x4>(master);
             f32x4 after;
             typename PackOf<__bf16, VEC>::type rounded;
 #pragma unroll
