@@ -354,8 +354,8 @@ StepWs carve_step(Arena &a, const std::vector<Geo> &geos, bool forward = false)
     for (const Geo &g : geos) {
         const size_t act_bytes = (size_t)g.groups * g.B * g.so * g.esz;
         w.Y.push_back(a.take(act_bytes));
-        // GELU keeps per layer, in float: fp32 storage, the pre-activation; bf16 storage, sigma'(pre-activation)
-        w.A.push_back(!forward && g.act == PH_ACT_GELU ? a.take((size_t)g.groups * g.B * g.so * sizeof(float)) : nullptr);
+        // GELU keeps per layer but the last, in float: fp32 storage, the pre-activation; bf16 storage, sigma'(pre-activation)
+        w.A.push_back(!forward && g.act == PH_ACT_GELU && w.Y.size() < geos.size() ? a.take((size_t)g.groups * g.B * g.so * sizeof(float)) : nullptr);
         w.G.push_back(g.q > 0 ? a.take((size_t)g.groups * g.B * g.k * g.esz) : nullptr);   // all-ranks: [p,B,k]; one-rank: [B,k]
         act_max = std::max(act_max, (size_t)std::max(g.si, g.so));
         k_max = std::max(k_max, (size_t)g.k);
@@ -1672,7 +1672,8 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
         f.X = l > 0 ? w.Y[(size_t)l - 1] : a.X0;
         f.Lw = a.Lw[l]; f.Cw = q ? a.Cw[l] : nullptr; f.Dw = q ? a.Dw[l] : nullptr; f.bias = a.bias[l];
         f.G = (q && !g.all) ? a.G[l] : nullptr;
-        f.Y = w.Y[(size_t)l]; f.g_own = w.G[(size_t)l]; f.A_save = train ? w.A[(size_t)l] : nullptr;
+        // (nobody reads the last layer's: its update forms delta_L itself)
+        f.Y = w.Y[(size_t)l]; f.g_own = w.G[(size_t)l]; f.A_save = train && l < L - 1 ? w.A[(size_t)l] : nullptr;
         f.a_f32 = !save_deriv; f.a_deriv = save_deriv;
         f.mse = train && l == L - 1 ? &oe : nullptr;
         PH_TRY(flex_fwd<T>(geos[(size_t)l], f, st, f.mse ? &mse_tiles : nullptr));
@@ -1827,7 +1828,7 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     for (int l = 0; l < L; ++l) {
         const bool bits = train && w.relu_bits[(size_t)l] != nullptr;
         FwdArgs f{l > 0 ? w.Y[(size_t)l - 1] : a.X0, a.Lw[l], q ? a.Cw[l] : nullptr, q ? a.Dw[l] : nullptr, a.bias[l],
-                  (q && !g.all) ? a.G[l] : nullptr, w.Y[l], w.G[l], bits ? w.relu_bits[(size_t)l] : train ? w.A[l] : nullptr,
+                  (q && !g.all) ? a.G[l] : nullptr, w.Y[l], w.G[l], bits ? w.relu_bits[(size_t)l] : train && l < L - 1 ? w.A[l] : nullptr,      // (the last layer's update forms delta_L itself)
                   false, !save_deriv && !bits, save_deriv, bits, (train && l == L - 1) ? &oe : nullptr, &clear, g.all || L == 1 ? nullptr : &later};
         PH_TRY(fwd_impl(geos[(size_t)l], f, st));
     }
