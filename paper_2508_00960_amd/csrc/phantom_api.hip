@@ -17,6 +17,7 @@
 
 #include "common.h"
 #include "elementwise.h"
+#include "few_rows.h"
 #include "gemm_flex.h"
 #include "gemm_mfma.h"
 #include "thin_product.h"
@@ -1208,6 +1209,67 @@ FwdProducts make_fwd_products(const Geo &g, const FwdArgs &f)
     return pr;
 }
 
+// Does a layer's forward pass run on the kernel for few rows (few_rows.h), and how many blocks of 16 rows does a workgroup take?  0: no.
+// The fewest with which the launch is one round of workgroups, while a workgroup's operands (16 columns and those rows by the reduction) are
+// not so long that gemm_flex.h, whose larger tiles read less, is the faster one.  Measured, us, 6 layers forward (dense: 4), gemm_flex.h : 1 block : 2 : 4:
+// 1024 + 448 at batch 48 / 96 / 128 46.4 : 36.3 : 39.4 : 43.6, 48.5 : 64.6 : 41.6 : 45.8, 49.3 : 85 : 63.5 : 48.1; 1024 + 1792 at 32 / 96 / 128 67.1 : 54.4 : 61.3 : 64.8,
+// 67.6 : 98.6 : 59.8 : 68.7, 67.9 : 116 : 81.4 : 72.0; 512 + 960 at 96 / 192 47.2 : 36.2 : 39.0 : 43.3, 48.7 : 67 : 42.8 : 47.9; 512 + 3840 at 64 / 128 75.8 : 70.5 : 81.9 : 103,
+// 76.2 : 83.6 : 81.6 : 102; 256 + 48 at 384 / 768 36.3 : 37.9 : 26.6 : 27.4, 36.3 : 63.5 : 41.1 : 31.0; 1280 + 280 at 40 / 96 59.9 : 56.6 : 43.6 : 47.9, 62.3 : 83.5 : 64.1 : 50.4;
+// 2048 + 224 at 32 / 48 59.8 : 80 : 54.5 : 56.7, 59.2 : 87 : 83 : 60.9; 2048 + 1024 at 32 63.1 : 91 : 64.3 : 67.9; dense 512 at 128 21.9 : 16.2 : 17.1 : 19.9, 1024 at 64 / 128
+// 27.5 : 20.7 : 22.3 : 25.2, 27.8 : 35 : 23.6 : 25.8, 2048 at 32 / 64 / 128 34.8 : 31.4 : 33.1 : 34.7, 35.3 : 55 : 35.3 : 39.2, 36.0 : 103 : 62 : 41.8, 2560 at 16 34.0 : 36.5 : 37.1 : 39.3,
+// 4096 at 16 44.2 : 49.0 : 50.9 : 55.9.
+int few_rows_blocks(const Geo &g, const FwdArgs &f)
+{
+    if (g.all || g.vec != 8 || f.apart || f.mse || f.a_bits) return 0;
+    static const char *force = tuning_env("PHANTOM_FEW");              // =0, 1, 2 or 4 (for measurements)
+    if (force) return atoi(force);
+    const int64_t rows = (g.B + 15) / 16, columns = (g.so + 15) / 16 + (g.k + 15) / 16;
+    for (int blocks = 1; blocks <= 4; blocks *= 2)
+        if ((rows + blocks - 1) / blocks * columns <= 256) return (blocks + 1) * g.Kc <= (g.q > 0 ? 9000 : 6144) && (g.q > 0 || g.Kc <= 2048) ? blocks : 0;
+    return 0;
+}
+
+template <int ROWS>
+ph_status launch_few_rows_kernel(const FewBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
+{
+    constexpr int LDS = few_lds_bytes(ROWS);
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)few_rows_kernel<ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
+        configured = true;
+    }
+    hipLaunchKernelGGL(few_rows_kernel<ROWS>, dim3(total_wg), dim3(FEW_WAVES * 64), LDS, st, batch);
+    return check_launch(what);
+}
+
+ph_status launch_few_rows(const Geo &g, const FwdProducts &pr, int blocks, hipStream_t st)
+{
+    FewBatch batch{};
+    int next = 0;
+    for (const Product *p : {&pr.update, &pr.compress}) {
+        if (p->M == 0 || p->N == 0) continue;
+        FewProduct &P = batch.p[batch.count];
+        const bool cut = p->a.c.decides;
+        P.a0 = (const __bf16 *)p->a.p0; P.a1 = (const __bf16 *)p->a.p1; P.b0 = (const __bf16 *)p->b.p0; P.b1 = (const __bf16 *)p->b.p1;
+        P.out = p->o.p0; P.M = (int)p->M; P.N = (int)p->N; P.K = (int)p->K;
+        P.split = (int)g.si; P.seg = cut ? p->a.c.seg : 8; P.magic = div_magic(P.seg);
+        P.a_seg = (int)p->a.c.seg_stride; P.b_seg = (int)p->b.c.seg_stride;
+        if (p->ep.mode == EPI_BIAS_ACT) {
+            P.bias = (const __bf16 *)p->ep.bias; P.act = p->ep.act;
+            P.aux = p->ep.aux; P.aux_f32 = p->ep.aux_f32; P.aux_deriv = p->ep.aux_deriv;
+        }
+        P.tiles_n = (P.N + FEW_TILE - 1) / FEW_TILE; P.pitch = (P.tiles_n + 7) & ~7;
+        if (batch.count == 1) batch.first_wg = next;
+        next += (P.M + blocks * FEW_TILE - 1) / (blocks * FEW_TILE) * P.pitch;
+        ++batch.count;
+    }
+    const char *what = batch.count == 2 ? "layer update + compression" : "layer update";
+    ProfScope prof(what, pr.update.M, pr.update.N, pr.update.K, 1, st, pr.compress.M, pr.compress.N, pr.compress.K);
+    return blocks == 1 ? launch_few_rows_kernel<1>(batch, (unsigned)next, st, what) : blocks == 2 ? launch_few_rows_kernel<2>(batch, (unsigned)next, st, what)
+                       : launch_few_rows_kernel<4>(batch, (unsigned)next, st, what);
+}
+
 // Forward through gemm_flex.h.  mse_tiles: with f.mse, the number of partial sums of the loss it leaves.
 template <typename T>
 ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tiles = nullptr)
@@ -1219,6 +1281,8 @@ ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tile
         return launch_flex<T>(&pr.update, 1, true, g, LossTail{}, st, "layer update", mse_tiles);
     }
     const Product both[2] = {pr.update, pr.compress};
+    if constexpr (sizeof(T) == 2)
+        if (const int blocks = few_rows_blocks(g, f)) return launch_few_rows(g, pr, blocks, st);
     if (f.apart) {
         PH_TRY((launch_flex<T>(&pr.update, 1, true, g, LossTail{}, st, "layer update")));
         return launch_flex<T>(&pr.compress, 1, true, g, LossTail{}, st, "compression");
