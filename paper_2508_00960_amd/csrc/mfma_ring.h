@@ -12,6 +12,17 @@
 // Passes (us): 4 x 4096, 8 ranks, gradients 247.7 : 233.6; widths 4096 / 8192 415 : 385; 6 layers of 1024, k 256, forward 359 : 352;
 // 8 layers of 1024, k 64, trained at batch 4096 698 : 695; dense 4 x 4096 624 : 605.
 //
+// What stands between that and a step: whatever a wavefront waits for holds up its matrix instructions, and the two wavefronts of a SIMD wait for the same
+// things.  All loads of a stage issued behind the barrier fill the queue of the vector-memory path for 570 clocks; four operand reads in a row, issued by
+// eight wavefronts at once, return later than the four matrix instructions ahead of them end; every address worked out in between is an instruction the
+// matrix cores wait for.  So a step is a straight piece of code: one operand read ahead of each matrix instruction, the loads of a regular shape one by one
+// behind them, from a scalar base that moves by a constant for a run of tiles (RingCursor).  Bare products (us, operands and loads in bunches :
+// so): 8192 x 1024 x 2816 in two-tile workgroups 50.8 : 44.6, x 5632 96 : 88; 4096 x 1024 x 1984 two teams to a tile 22.5 : 20.0; input-gradient layout 8192 x 1024 x
+// 2048 39.3 : 33.5, 1024 x 4096 x 4096 41 : 35; weight gradients 8192 x 1024 over 4096 rows 71 : 60, 4096 x 4096 over 2048 in one-team workgroups 77 : 70.
+// Matrix instructions alone take 61 of the 96.
+// Steps (us, before : now): 6 layers of 1024 + 1792 forward at batch 8192 338 : 311, of 1024 + 28 165 : 159, 8 of 1024 + 960 with GELU trained at 4096 576 : 546,
+// dense 4 x 4096 at 1024 501 : 479, gradients of 8 ranks of 512 + 224 at 1024 208 : 200.
+//
 // A stage holds one step of 64 of both operands.  The loads of a stage are issued RING - 1 steps before it is read, by all
 // wavefronts that read it; each step has one barrier, placed before its last quarter of matrix instructions, and by then every
 // wavefront has read its operands of the stage into registers, so that the freed slot is filled again right behind the barrier and the
@@ -165,12 +176,12 @@ template <int AHEAD> __device__ __forceinline__ void ring_load(const __bf16 *p, 
                  :: "s"(ring_uniform(lds_at)), "v"(p), "n"(AHEAD) : "memory", "scc", "m0");
 }
 #pragma clang diagnostic pop
-// f(std::integral_constant<int, j>) for j = 0 .. N - 1
-template <int N, typename F, int J = 0> __device__ __forceinline__ void ring_each(F &&f)
+// f(std::integral_constant<int, j>) for j = J .. N - 1
+template <int N, int J = 0, typename F> __device__ __forceinline__ void ring_each(F &&f)
 {
     if constexpr (J < N) {
         f(std::integral_constant<int, J>{});
-        ring_each<N, F, J + 1>(static_cast<F &&>(f));
+        ring_each<N, J + 1>(static_cast<F &&>(f));
     }
 }
 
@@ -224,6 +235,57 @@ __device__ __forceinline__ void ring_fetch(const RingOperand &s, const uint32_t 
             ring_load<j * STRIDE>((const __bf16 *)(uintptr_t)((int64_t)(uintptr_t)(reg1 ? s.base1 : s.base0) + (reg1 ? o1 : o0) + rows * 2), tile);
         });
     }
+}
+
+// Where a regular shape's loads of full tiles come from, as the reduction range is walked down: a scalar base, and offsets of the thread that stay the
+// same for a run of tiles, in which the base moves by the same amount from tile to tile.
+template <int KIND, int WAVES, int TILE = MT>
+struct RingCursor {
+    const __bf16 *base;
+    uint32_t off[RingCfg<KIND, WAVES, TILE>::NV];
+    uint32_t step;           // bytes from a tile to the next lower one
+    int left;                // lower tiles of the run
+};
+
+// the run that the tile whose reduction index starts at c0 (uniform) begins
+template <int KIND, int WAVES, int TILE = MT>
+__device__ __forceinline__ void ring_run(RingCursor<KIND, WAVES, TILE> &at, const RingOperand &s, const uint32_t (&off0)[RingCfg<KIND, WAVES, TILE>::NV],
+                                             const uint32_t (&off1)[RingCfg<KIND, WAVES, TILE>::NV], int c0)
+{
+    typedef RingCfg<KIND, WAVES, TILE> C;
+    if (c0 < s.c_split) {                              // uniform, like every branch here
+        at.left = c0 >> 6;
+        at.step = KIND == LD_KC ? KT * 2u : KT * 2u * (uint32_t)s.c_mult0;
+        at.base = s.base0 + (KIND == LD_KC ? (unsigned)c0 : (unsigned)c0 * (unsigned)s.c_mult0);
+#pragma unroll
+        for (int j = 0; j < C::NV; ++j) at.off[j] = off0[j];
+    } else if (KIND == LD_KC) {
+        const unsigned t0 = (unsigned)(c0 - s.c_split);
+        const int i0 = (int)__umulhi(t0, s.c_magic), rem = (int)t0 - i0 * s.c_seg;     // first segment the tile touches; 0 unless a segment holds several tiles
+        const int i = i0 + s.col_seg, slot = i + (i >= s.c_skip ? 1 : 0);
+        const unsigned add = (unsigned)(slot * s.c_seg_stride + rem + s.col_in_seg) * 2u;
+#pragma unroll
+        for (int j = 0; j < C::NV; ++j) at.off[j] = off1[j] + add;
+        at.base = s.base1;
+        // a run ends with its segment, or where segments that a tile holds lie on either side of the skipped slot
+        if (s.c_seg > KT) {
+            at.left = rem >> 6;
+            at.step = KT * 2u;
+        } else {
+            const int held = (int)__umulhi(KT, s.c_magic);
+            at.left = (i0 >= s.c_skip ? (i0 - s.c_skip) * s.c_seg : i0 + held <= s.c_skip ? i0 * s.c_seg : 0) >> 6;
+            at.step = (uint32_t)(held * s.c_seg_stride) * 2u;
+        }
+    } else {
+        at.left = (c0 - s.c_split) >> 6;
+        at.step = KT * 2u * (uint32_t)s.c_mult1;
+        at.base = s.base1 + (unsigned)(c0 - s.c_split) * (unsigned)s.c_mult1;
+#pragma unroll
+        for (int j = 0; j < C::NV; ++j) at.off[j] = off1[j];
+    }
+    // (scalar registers from here on: a base that the loop moved there ahead of each load would be too young for it, see ring_load)
+    at.base = ring_uniform(at.base);
+    at.step = ring_uniform(at.step);
 }
 
 typedef __attribute__((address_space(3))) unsigned char *LdsBytes;

@@ -33,6 +33,11 @@ LARGE = [
     (4352, 32, 8, 400, "gelu"),      # shard 136
     (6400, 32, 40, 390, "relu"),     # shard 200
     (5248, 16, 64, 530, "identity"), # shard 328, whole segments in a stage that the head block shifts
+    # regular shapes: runs of stages whose loads move by a constant
+    (4096, 64, 8, 1300, "relu"),     # eight segments in a stage, the skipped slot at every place in one; a run ends on either side of it
+    (2048, 16, 32, 2000, "gelu"),    # two; shard 128
+    (2048, 8, 128, 1700, "relu"),    # a segment of two stages: a run each
+    (1536, 2, 768, 8200, "identity"), # ... of twelve
 ]
 # between the lines of use_flex for all ranks: forward on the one kind of kernels, backward on the other
 BETWEEN = [
