@@ -70,6 +70,7 @@ struct FlexIn {
     uint32_t magic_tiles, magic_band, magic_last;      // div_by: tiles_m * tiles_n, FLEX_RASTER * tiles_n, rows of the last band
     int kind;            // 0: A along the reduction index (forward and input-gradient layouts); 1: weight-gradient layout
     int rowsum;          // FlexOut::rowsum is wanted
+    SumOnRead rs;        // gemm_flex_f32_few_kernel: A's block dg_own is summed on read (src != nullptr)
 };
 // ... and what its epilogue needs
 struct FlexOut {
@@ -1181,6 +1182,142 @@ __device__ __forceinline__ void flex_f32_workgroup(const FlexIn &P, int product,
     flex_epilogue<float, TILE, TILE, 1, THREADS, false, true, ROWSUM, float, EPI, AHEAD>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
 }
 
+// ---- fp32 in whole vectors, few tiles and short reductions ------------------------------------------------------------------
+// Where 4 divides the widths and phantom widths, 32 x 32 tiles whose eight teams of one wavefront take one group of 16 terms each: the sums of
+// flex_workgroup, group by group in the same order, so the same bits.
+// What bounds it: a launch of 8 to 40 workgroups is a chain of latencies (parameters, one read of the operands, eight matrix instructions, the epilogue) and of
+// instructions that are fetched cold.  So nothing is in a loop, what the epilogue reads is requested with the operands, and a wavefront stages what it
+// alone reads: one barrier, ahead of the epilogue.
+// 2 layers of 4 ranks of 64 + 24 trained at batch 32, ten launches (us a step, flex_workgroup : so): 54.9 : 44.4.
+constexpr int F32_FEW_TERMS = 16, F32_FEW_KC = F32_FEW_TERMS + 4, F32_FEW_KM = 32;      // floats per LDS row
+constexpr int F32_FEW_STAGE = 2 * 32 * F32_FEW_KC * 4;                                  // bytes of a team's two operands
+constexpr int F32_FEW_LDS = 8 * F32_FEW_STAGE + 8 * FlexTileShape<32, 32>::C_BYTES + 512 * 4 + 64;
+
+// All ranks on the device, at most 8: dg_own is summed on read by the launch that needs it first, the senders in the order in which reduce_scatter_kernel
+// adds them, and stored by the workgroups of tile column 0 for the launches behind it (the same step, with two launches for the sums : without, 44.4 : 42.4).
+__device__ __forceinline__ u32x4 f32_few_sum(const SumOnRead &rs, int g, int64_t at /* element of the rank's dg_own */)
+{
+    constexpr int MOST = 7;                            // (the host allows at most 8 ranks)
+    f32x4 v[MOST];
+#pragma unroll
+    for (int a = 0; a < MOST; ++a) {
+        const int i = min(a, rs.p - 2), from = i < g ? i : i + 1, slot = g < from ? g : g - 1;      // the i-th sender other than g
+        v[a] = gload<f32x4>((const float *)(const void *)rs.src + ((int64_t)from * (rs.p - 1) + slot) * rs.per_slot + at);
+    }
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int a = 0; a < MOST; ++a)
+        if (a < rs.p - 1) sum += v[a];                 // uniform
+    union { f32x4 f; u32x4 u; } r;
+    r.f = sum;
+    return r.u;
+}
+
+// 32 free positions from f0 on x 16 reduction positions from c0 on, two vectors a lane.  Free positions past the end repeat the last ones (nothing is
+// stored of them), reduction positions past the end are zeros.
+// rs: NULL, or where the operand's block dg_own comes from (KC: what lies behind the cut of the reduction index; KM: all of it); keep: store it, too.
+template <int KIND>
+__device__ __forceinline__ void f32_few_fetch(u32x4 (&v)[2], const FlexOperand &op, const FlexAxis &ax, const FlexAxis &fax, int f0, int c0, int g, int lane,
+                                              const SumOnRead *rs = nullptr, bool keep = false)
+{
+    const float *p0 = (const float *)op.p0 + g * op.g0, *p1 = (const float *)op.p1 + g * op.g1;
+    const int skip = op.skip0 + g * op.skip_g, end = ax.seg > 0 ? ax.total : ax.head;
+    const float *at[2];
+    bool in[2], summed[2] = {false, false}, store[2] = {false, false};
+    int64_t own[2] = {0, 0};
+    const bool sums = rs && rs->src;                   // uniform
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (KIND == FLEX_KC) {
+            const int c = c0 + (lane & 3) * 4, r = min(f0 + (lane >> 2) + 16 * j, fax.head - 1);
+            in[j] = c < end;
+            const FlexLoc l = flex_locate(ax, in[j] ? c : 0, op.seg_stride, skip);
+            at[j] = (l.region ? p1 + r * op.ld1 : p0 + r * op.ld0) + l.off;
+            summed[j] = sums && in[j] && l.region;
+            store[j] = keep && summed[j] && f0 + (lane >> 2) + 16 * j < fax.head;
+            own[j] = r * op.ld1 + l.off;
+        } else {
+            int c = c0 + (lane >> 3) + 8 * j;
+            in[j] = c < end;
+            c = in[j] ? c : 0;
+            const FlexLoc l = flex_locate(fax, min(f0 + (lane & 7) * 4, fax.total - 4), op.seg_stride, skip);
+            const bool below = ax.seg > 0 && c >= ax.head, tail = below || (fax.seg > 0 && l.region);       // (one of the two indices is cut)
+            at[j] = (tail ? p1 + (int64_t)(c - (below ? ax.head : 0)) * op.ld1 : p0 + (int64_t)c * op.ld0) + l.off;
+            summed[j] = sums && in[j];
+            store[j] = keep && summed[j] && f0 + (lane & 7) * 4 < fax.head;
+            own[j] = (int64_t)c * op.ld0 + l.off;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (summed[j]) v[j] = f32_few_sum(*rs, g, own[j]);
+        else v[j] = gload<u32x4>(at[j]);
+        if (store[j]) gstore<u32x4>((float *)(void *)rs->out + (int64_t)g * rs->per_slot + own[j], v[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[j][u] = in[j] ? v[j][u] : 0u;
+}
+// ... to LDS, as flex_operand reads it
+template <int KIND>
+__device__ __forceinline__ void f32_few_store(const u32x4 (&v)[2], float *tile, int lane)
+{
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (KIND == FLEX_KC) {
+            const int col = (lane & 3) * 4;
+            float *to = tile + ((lane >> 2) + 16 * j) * F32_FEW_KC + (col & ~7) + ((col >> 1) & 2);
+            *(u32x2 *)to = u32x2{v[j][0], v[j][2]};
+            *(u32x2 *)(to + 4) = u32x2{v[j][1], v[j][3]};
+        } else {
+            *(u32x4 *)(tile + ((lane >> 3) + 8 * j) * F32_FEW_KM + (lane & 7) * 4) = v[j];
+        }
+    }
+}
+
+template <int KA, int KB, int EPI>
+__device__ __forceinline__ void flex_f32_few_workgroup(const FlexIn &P, int product, int wg, unsigned char *lds)
+{
+    typedef FlexTileShape<32, 32> F;
+    constexpr bool ROWSUM = KA == FLEX_KM && KB == FLEX_KM;
+    constexpr int PA = KA == FLEX_KC ? F32_FEW_KC : F32_FEW_KM, PB = KB == FLEX_KC ? F32_FEW_KC : F32_FEW_KM;
+    const FlexTileAt at = flex_tile_at<true>(P, wg);
+    const int g = at.g, tm = at.tm, tn = at.tn;
+    const int lane = threadIdx.x & 63, team = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    FlexAxis ma{};                                     // the row index: never cut
+    ma.head = P.M; ma.head_pad = ma.total = (P.M + 3) & ~3;
+    const bool rows = ROWSUM && P.rowsum && tn == 0;   // uniform
+    u32x4 va[2], vb[2];
+    f32_few_fetch<KA>(va, P.a, P.k, ma, tm * 32, team * F32_FEW_TERMS, g, lane, &P.rs, tn == 0);
+    f32_few_fetch<KB>(vb, P.b, P.k, P.n, tn * 32, team * F32_FEW_TERMS, g, lane);
+    const FlexOut Q = args_at<FlexOut>(offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out));
+    FlexAhead<float, 1> ahead;
+    flex_request<float, 32, 32, 512, true, ROWSUM, float, EPI>(ahead, P, Q, g, tm, tn, rows);
+    float *const ta = (float *)(lds + team * F32_FEW_STAGE), *const tb = ta + 32 * F32_FEW_KC;
+    f32_few_store<KA>(va, ta, lane);
+    f32_few_store<KB>(vb, tb, lane);
+    flex_wave_sync();
+    f32x16 sum[1][1];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sum[0][0][e] = 0.f;
+    flex_multiply<KA, KB, PA, PB, F32_FEW_TERMS>(sum, ta, tb, 0, 0, lane);
+    float *const ctile = (float *)(lds + 8 * F32_FEW_STAGE), *const extra = (float *)(lds + 8 * F32_FEW_STAGE + 8 * F::C_BYTES);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        *(f32x4 *)(ctile + team * (F::C_BYTES / 4) + (lane & 31) * F::CPITCH + 8 * q + 4 * (lane >> 5)) =
+            f32x4{sum[0][0][4 * q], sum[0][0][4 * q + 1], sum[0][0][4 * q + 2], sum[0][0][4 * q + 3]};
+    if (rows) {
+        float t = 0.f;
+#pragma unroll
+        for (int r = 0; r < F32_FEW_TERMS / 2; ++r) t += ta[((lane >> 5) + 2 * r) * F32_FEW_KM + (lane & 31)];
+        extra[threadIdx.x] = t;
+    }
+    __syncthreads();
+    flex_arrived(ahead);
+    flex_epilogue<float, 32, 32, 8, 512, false, true, ROWSUM, float, EPI, 1>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
+}
+
 // ---- bf16 in 16-byte vectors: the ring of mfma_ring.h ----------------------------------------------------------------
 // Problems whose widths and phantom widths 8 divides need neither the renumbering nor masked vectors.  A workgroup owns a 64 x 64 tile, each
 // wavefront of a team a quadrant of it; two teams share it as in the kernel above, each with every other tile of the reduction range in stages
@@ -1375,6 +1512,25 @@ __global__ __launch_bounds__(256, MANY ? 4 : 2) void gemm_flex_f32_kernel(FlexBa
     if constexpr (FORWARD) flex_f32_workgroup<(MANY ? 1 : 2), FLEX_KC, FLEX_KC, EPI_BIAS_ACT>(P, j, wg, smem_raw);
     else if (P.kind == 0) flex_f32_workgroup<(MANY ? 1 : 2), FLEX_KC, FLEX_KM, EPI_DACT>(P, j, wg, smem_raw);
     else flex_f32_workgroup<(MANY ? 1 : 2), FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
+}
+
+template <bool FORWARD>
+__global__ __launch_bounds__(512) void gemm_flex_f32_few_kernel(FlexBatch batch)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    if (batch.tail.partial && blockIdx.x == 0) {       // uniform
+        finish_loss(batch.tail, (float *)smem_raw);
+        __syncthreads();
+    }
+    int j = 0;
+    while (j + 1 < batch.count && (int)blockIdx.x >= batch.first_wg[j + 1]) ++j;       // uniform
+    const int local = (int)blockIdx.x - batch.first_wg[j];
+    const FlexIn P = args_at<FlexIn>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, in));
+    if (local >= P.total_wg) return;
+    const int wg = flex_xcd_order(local, P.total_wg);
+    if constexpr (FORWARD) flex_f32_few_workgroup<FLEX_KC, FLEX_KC, EPI_BIAS_ACT>(P, j, wg, smem_raw);
+    else if (P.kind == 0) flex_f32_few_workgroup<FLEX_KC, FLEX_KM, EPI_DACT>(P, j, wg, smem_raw);
+    else flex_f32_few_workgroup<FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
 }
 
 template <int TEAMS, int RING, bool FORWARD>

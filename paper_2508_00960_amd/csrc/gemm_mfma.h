@@ -340,18 +340,6 @@ __device__ __forceinline__ bf16x8 lds_operand(const __bf16 *tile, int rbase, int
     }
 }
 
-// Reduce-scatter as a sum on read (all ranks on the device; Algorithm 1, backward): the tail block of operand A
-// (the k columns behind a.c.split, dg_own in the input-gradient product) is not read from memory but summed
-// from what the other ranks sent, dg_own[g] = sum_{j != g} src[j][slot of g on j], src = dG_send [p, p-1, per_slot],
-// per_slot = rows * k.  The workgroups of tile column 0 also write the sums to out [p, per_slot] for later kernels.
-// src == nullptr: operand A is read as its View says.
-struct SumOnRead {
-    const __bf16 *src;
-    __bf16 *out;
-    int64_t per_slot;
-    int p, k;
-};
-
 struct MfmaIn {          // what a product's reduction needs ...
     View a, b;
     SumOnRead rs;

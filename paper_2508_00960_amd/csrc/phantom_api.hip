@@ -472,7 +472,7 @@ struct Product {
     View a, b, o;
     Epilogue ep;
     int64_t M, N, K;
-    SumOnRead rs;        // gemm_mfma kernels only: the tail block of a is summed on read (src != nullptr)
+    SumOnRead rs;        // the tail block of a (gemm_flex_f32_few_kernel, weight-gradient layout: all of it) is summed on read (src != nullptr; kernels that do it only)
     SgdInPlace sgd;      // weight gradients: the update applied by the epilogue that finishes them (w0 == nullptr: none)
     float *rowsum;       // gemm_flex kernels, weight gradients: receives the bias gradient (MfmaParams has no such thing)
     bool km;             // gemm_flex kernels: weight-gradient layout (both operands along their free index), float out
@@ -1009,6 +1009,19 @@ ph_status launch_flex_f32(const FlexBatch &batch, unsigned total_wg, hipStream_t
     return check_launch(what);
 }
 
+template <bool FORWARD>
+ph_status launch_flex_f32_few(const FlexBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
+{
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_flex_f32_few_kernel<FORWARD>, hipFuncAttributeMaxDynamicSharedMemorySize, F32_FEW_LDS);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, F32_FEW_LDS, hipGetErrorString(e));
+        configured = true;
+    }
+    hipLaunchKernelGGL(gemm_flex_f32_few_kernel<FORWARD>, dim3(total_wg), dim3(512), F32_FEW_LDS, st, batch);
+    return check_launch(what);
+}
+
 template <typename T, bool FORWARD, bool FINE>
 ph_status launch_flex_tile(const FlexBatch &batch, FlexTile tile, unsigned total_wg, hipStream_t st, const char *what)
 {
@@ -1031,6 +1044,17 @@ ph_status launch_flex_ring(const FlexBatch &batch, unsigned total_wg, hipStream_
     }
     hipLaunchKernelGGL(kern, dim3(total_wg), dim3(TEAMS * 256), LDS, st, batch);
     return check_launch(what);
+}
+
+// Does an fp32 launch run on gemm_flex_f32_few_kernel?  (Empty products count for nothing.)
+bool f32_few(const Product *prods, int count, const Geo &g, bool forward)
+{
+    if (g.dtype != PH_F32 || !g.whole || flex_tile_for<float>(prods, count, g.groups, forward, false) != FLEX_32_8) return false;
+    static const char *force = tuning_env("PHANTOM_F32_FEW");      // =0 (for measurements)
+    if (force && force[0] == '0') return false;
+    for (int i = 0; i < count; ++i)                    // (the rule of flex_tile_for: a team has one group of terms at most)
+        if (prods[i].M > 0 && prods[i].N > 0 && prods[i].K > 8 * F32_FEW_TERMS) return false;
+    return true;
 }
 
 // Up to FLEX_MAX_PRODUCTS independent products in one launch.  forward: all in the forward layout; else any mix of the
@@ -1065,6 +1089,7 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
         P.k = flex_axis(pr.km ? Axis{} : pr.a.c, pr.K, V);
         P.n = flex_axis(pr.o.c, pr.N, V);
         P.M = (int)pr.M;
+        P.rs = pr.rs;
         FlexAxis rows{};
         rows.head = P.M;
         P.a = flex_operand_of(pr.a, pr.km, P.k, rows, V);
@@ -1103,6 +1128,10 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
                 return forward ? launch_flex_ring<2, 2, true>(batch, total, st, what) : launch_flex_ring<2, 2, false>(batch, total, st, what);
             }
             return forward ? launch_flex_ring<1, 3, true>(batch, total, st, what) : launch_flex_ring<1, 3, false>(batch, total, st, what);
+        }
+    if constexpr (sizeof(T) == 4)
+        if (tile == FLEX_32_8) {
+            if (f32_few(prods, count, g, forward)) return forward ? launch_flex_f32_few<true>(batch, total, st, what) : launch_flex_f32_few<false>(batch, total, st, what);
         }
     if constexpr (sizeof(T) == 4)
         if (tile == FLEX_64 && g.whole) {
@@ -1785,10 +1814,21 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
             next.push_back(pr.send);
             PH_TRY(go("error compression | gradients above"));
             PH_TRY(tap_rows<T>(gl, tap_send, b.dG_send, send_rows, st));
-            PH_TRY(launch_reduce_scatter<T>(gl, b.dG_send, b.dg_own, LossTail{}, st));
-            PH_TRY(tap_copy<T>(a.taps && a.taps->dg_own ? a.taps->dg_own[l] : nullptr, b.dg_own, (int64_t)g.groups * B * gl.k, st));
+            // the launch that needs dg_own first sums it on read where it can: the input gradient, or (first layer) the compressor gradient's
+            const SumOnRead sum{(const __bf16 *)b.dG_send, (__bf16 *)b.dg_own, B * gl.k, (int)g.p, (int)gl.k};
+            const Product last[2] = {pr.dw, pr.dc};
+            const bool on_read = sizeof(T) == 4 && g.p <= 8 && (l > 0 ? f32_few(&pr.dx, 1, g, false) : f32_few(last, 2, g, false));
+            if (on_read) (l > 0 ? pr.dx : pr.dc).rs = sum;
+            else PH_TRY(launch_reduce_scatter<T>(gl, b.dG_send, b.dg_own, LossTail{}, st));
             next.push_back(pr.dx);
             PH_TRY(go("input gradient"));
+            if (on_read && l == 0) {
+                next.push_back(pr.dw);
+                next.push_back(pr.dc);
+                PH_TRY(go("weight + compressor gradients"));
+            }
+            PH_TRY(tap_copy<T>(a.taps && a.taps->dg_own ? a.taps->dg_own[l] : nullptr, b.dg_own, (int64_t)g.groups * B * gl.k, st));
+            if (on_read && l == 0) break;
         } else {
             next.push_back(pr.dx);
             next.push_back(pr.send);

@@ -20,3 +20,17 @@ pytestmark = pytest.mark.gpu
 def test_parity(n, p, k, B, L, rank):
     print(f"case f32 whole n={n} p={p} k={k} B={B} L={L} rank={rank}", flush=True)
     check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act="relu", dtype="f32", rank=rank), seed=12, lr=0.02, mode="train")
+
+
+@pytest.mark.parametrize("n,p,k,B,L,act,rank,mode", [
+    (256, 4, 8, 32, 2, "relu", -1, "train"),
+    (288, 4, 12, 127, 3, "gelu", -1, "train"),       # shard 72 + 36: tiles of eight and four columns left over; 127 terms in the weight gradients
+    (384, 4, 8, 128, 2, "relu", 1, "train"),         # one rank, 120 and 128 terms: all teams
+    (20, 5, 4, 2, 3, "gelu", -1, "no_update"),       # shard 4 = k: one team with terms, one vector to a piece
+    (64, 1, 0, 16, 2, "relu", 0, "train"),           # dense
+    (512, 8, 4, 36, 2, "identity", -1, "forward"),
+])
+def test_few_tiles_and_short_reductions(n, p, k, B, L, act, rank, mode):
+    """32 x 32 tiles, one group of 16 terms to each of eight teams."""
+    print(f"case f32 few n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode}", flush=True)
+    check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="f32", rank=rank), seed=12, lr=0.02, mode=mode)
