@@ -7,22 +7,24 @@ namespace phantom {
 
 // delta = dY * sigma'(S)   (Eq. (deltaL); the sigma' factor of Eq. (backprop)), 16 bytes per thread and pass.
 // S is the pre-activation (any activation) or, for ReLU, the layer output.
-template <typename T>
+// GELU is a kernel of its own: its erff and expf, inlined for every element, are what a launch of a few microseconds fetches cold.  2048 x 512 in bf16, ReLU,
+// with GELU's code beside it : without, 35.8 : 35.5 us for a layer's forward and backward call (512 + 1008).
+template <typename T, bool GELU>
 __global__ __launch_bounds__(256) void delta_kernel(const T *__restrict__ dY, const T *__restrict__ S,
-                                                   T *__restrict__ delta, int64_t count, int act)
+                                                   T *__restrict__ delta, int64_t count)
 {
-    constexpr int VEC = 16 / (int)sizeof(T);
+    constexpr int VEC = 16 / (int)sizeof(T), ACT = GELU ? ACT_GELU : ACT_RELU;
     typedef T TV __attribute__((ext_vector_type(VEC)));
     const int64_t stride = (int64_t)gridDim.x * blockDim.x, first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = first; i < count / VEC; i += stride) {
         TV d = ((const TV *)dY)[i];
         const TV s = ((const TV *)S)[i];
 #pragma unroll
-        for (int u = 0; u < VEC; ++u) d[u] = from_f32<T>(to_f32((T)d[u]) * act_deriv(act, to_f32((T)s[u])));
+        for (int u = 0; u < VEC; ++u) d[u] = from_f32<T>(to_f32((T)d[u]) * act_deriv(ACT, to_f32((T)s[u])));
         ((TV *)delta)[i] = d;
     }
     for (int64_t i = count / VEC * VEC + first; i < count; i += stride)
-        delta[i] = from_f32<T>(to_f32(dY[i]) * act_deriv(act, to_f32(S[i])));
+        delta[i] = from_f32<T>(to_f32(dY[i]) * act_deriv(ACT, to_f32(S[i])));
 }
 
 // The loss of a step is left as partial sums (one per tile of

@@ -1522,8 +1522,9 @@ ph_status local_error(const Geo &g, const BwdArgs &b, void *buffer, const void *
         return copy ? tap_copy<T>(buffer, b.dY, count, st) : PH_OK;
     }
     ProfScope prof("local error", 0, count, 0, 1, st);
-    hipLaunchKernelGGL((delta_kernel<T>), dim3(blocks_for(count, 256 * 16 / (int)sizeof(T))), dim3(256), 0, st,
-                       (const T *)b.dY, (const T *)b.S, (T *)buffer, count, g.act);
+    auto kern = g.act == PH_ACT_GELU ? delta_kernel<T, true> : delta_kernel<T, false>;
+    hipLaunchKernelGGL(kern, dim3(blocks_for(count, 256 * 16 / (int)sizeof(T))), dim3(256), 0, st,
+                       (const T *)b.dY, (const T *)b.S, (T *)buffer, count);
     *delta = buffer;
     return check_launch("local error");
 }
