@@ -1183,15 +1183,18 @@ __device__ __forceinline__ void flex_f32_workgroup(const FlexIn &P, int product,
 }
 
 // ---- fp32 in whole vectors, few tiles and short reductions ------------------------------------------------------------------
-// Where 4 divides the widths and phantom widths, 32 x 32 tiles whose eight teams of one wavefront take one group of 16 terms each: the sums of
+// Where 4 divides the widths and phantom widths, 32 x 32 tiles whose eight teams of one wavefront take one, two or four groups of 16 terms each: the sums of
 // flex_workgroup, group by group in the same order, so the same bits.
 // What bounds it: a launch of 8 to 40 workgroups is a chain of latencies (parameters, one read of the operands, eight matrix instructions, the epilogue) and of
 // instructions that are fetched cold.  So nothing is in a loop, what the epilogue reads is requested with the operands, and a wavefront stages what it
 // alone reads: one barrier, ahead of the epilogue.
 // 2 layers of 4 ranks of 64 + 24 trained at batch 32, ten launches (us a step, flex_workgroup : so): 54.9 : 44.4.
 constexpr int F32_FEW_TERMS = 16, F32_FEW_KC = F32_FEW_TERMS + 4, F32_FEW_KM = 32;      // floats per LDS row
-constexpr int F32_FEW_STAGE = 2 * 32 * F32_FEW_KC * 4;                                  // bytes of a team's two operands
-constexpr int F32_FEW_LDS = 8 * F32_FEW_STAGE + 8 * FlexTileShape<32, 32>::C_BYTES + 512 * 4 + 64;
+constexpr int F32_FEW_STAGE = 2 * 32 * F32_FEW_KC * 4;                                  // bytes of a group's two operands
+// A team's region: the tiles of its groups' sums, its operands over the last one's place
+constexpr int f32_few_region(int groups) { return (groups - 1) * FlexTileShape<32, 32>::C_BYTES + F32_FEW_STAGE; }
+constexpr int f32_few_lds(int groups) { return 8 * f32_few_region(groups) + 512 * 4 + 64; }
+constexpr int F32_FEW_GROUPS = 4;                      // a team's groups, at most
 
 // All ranks on the device, at most 8: dg_own is summed on read by the launch that needs it first, the senders in the order in which reduce_scatter_kernel
 // adds them, and stored by the workgroups of tile column 0 for the launches behind it (the same step, with two launches for the sums : without, 44.4 : 42.4).
@@ -1276,7 +1279,7 @@ __device__ __forceinline__ void f32_few_store(const u32x4 (&v)[2], float *tile, 
     }
 }
 
-template <int KA, int KB, int EPI>
+template <int GROUPS, int KA, int KB, int EPI>
 __device__ __forceinline__ void flex_f32_few_workgroup(const FlexIn &P, int product, int wg, unsigned char *lds)
 {
     typedef FlexTileShape<32, 32> F;
@@ -1288,34 +1291,61 @@ __device__ __forceinline__ void flex_f32_few_workgroup(const FlexIn &P, int prod
     FlexAxis ma{};                                     // the row index: never cut
     ma.head = P.M; ma.head_pad = ma.total = (P.M + 3) & ~3;
     const bool rows = ROWSUM && P.rowsum && tn == 0;   // uniform
-    u32x4 va[2], vb[2];
-    f32_few_fetch<KA>(va, P.a, P.k, ma, tm * 32, team * F32_FEW_TERMS, g, lane, &P.rs, tn == 0);
-    f32_few_fetch<KB>(vb, P.b, P.k, P.n, tn * 32, team * F32_FEW_TERMS, g, lane);
+    u32x4 va[GROUPS][2], vb[GROUPS][2];
+#pragma unroll
+    for (int i = 0; i < GROUPS; ++i) {
+        const int c0 = (team * GROUPS + i) * F32_FEW_TERMS;
+        f32_few_fetch<KA>(va[i], P.a, P.k, ma, tm * 32, c0, g, lane, &P.rs, tn == 0);
+        f32_few_fetch<KB>(vb[i], P.b, P.k, P.n, tn * 32, c0, g, lane);
+    }
     const FlexOut Q = args_at<FlexOut>(offsetof(FlexBatch, p) + (size_t)product * sizeof(FlexParams) + offsetof(FlexParams, out));
     FlexAhead<float, 1> ahead;
     flex_request<float, 32, 32, 512, true, ROWSUM, float, EPI>(ahead, P, Q, g, tm, tn, rows);
-    float *const ta = (float *)(lds + team * F32_FEW_STAGE), *const tb = ta + 32 * F32_FEW_KC;
-    f32_few_store<KA>(va, ta, lane);
-    f32_few_store<KB>(vb, tb, lane);
-    flex_wave_sync();
-    f32x16 sum[1][1];
+    constexpr int REGION = f32_few_region(GROUPS);
+    unsigned char *const mine = lds + team * REGION;
+    float *const ta = (float *)(mine + (GROUPS - 1) * F::C_BYTES), *const tb = ta + 32 * F32_FEW_KC;
+    float *const extra = (float *)(lds + 8 * REGION);
+    float row_acc = 0.f;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) sum[0][0][e] = 0.f;
-    flex_multiply<KA, KB, PA, PB, F32_FEW_TERMS>(sum, ta, tb, 0, 0, lane);
-    float *const ctile = (float *)(lds + 8 * F32_FEW_STAGE), *const extra = (float *)(lds + 8 * F32_FEW_STAGE + 8 * F::C_BYTES);
+    for (int i = 0; i < GROUPS; ++i) {
+        f32_few_store<KA>(va[i], ta, lane);
+        f32_few_store<KB>(vb[i], tb, lane);
+        flex_wave_sync();
+        f32x16 sum[1][1];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-        *(f32x4 *)(ctile + team * (F::C_BYTES / 4) + (lane & 31) * F::CPITCH + 8 * q + 4 * (lane >> 5)) =
-            f32x4{sum[0][0][4 * q], sum[0][0][4 * q + 1], sum[0][0][4 * q + 2], sum[0][0][4 * q + 3]};
-    if (rows) {
-        float t = 0.f;
+        for (int e = 0; e < 16; ++e) sum[0][0][e] = 0.f;
+        flex_multiply<KA, KB, PA, PB, F32_FEW_TERMS>(sum, ta, tb, 0, 0, lane);
+        if (rows) {
+            float t = 0.f;
 #pragma unroll
-        for (int r = 0; r < F32_FEW_TERMS / 2; ++r) t += ta[((lane >> 5) + 2 * r) * F32_FEW_KM + (lane & 31)];
-        extra[threadIdx.x] = t;
+            for (int r = 0; r < F32_FEW_TERMS / 2; ++r) t += ta[((lane >> 5) + 2 * r) * F32_FEW_KM + (lane & 31)];
+            row_acc += t;
+        }
+        flex_wave_sync();
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *(f32x4 *)((float *)(mine + i * F::C_BYTES) + (lane & 31) * F::CPITCH + 8 * q + 4 * (lane >> 5)) =
+                f32x4{sum[0][0][4 * q], sum[0][0][4 * q + 1], sum[0][0][4 * q + 2], sum[0][0][4 * q + 3]};
+        flex_wave_sync();
     }
+    if (rows) extra[threadIdx.x] = row_acc;
     __syncthreads();
     flex_arrived(ahead);
-    flex_epilogue<float, 32, 32, 8, 512, false, true, ROWSUM, float, EPI, 1>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
+    // the groups' sums, 16 of them to a second-level sum, over the first one's place (read again by the same thread alone)
+    float *const ctile = (float *)lds;
+    if (threadIdx.x < 256) {
+        const int word = ((int)threadIdx.x >> 3) * F::CPITCH + ((int)threadIdx.x & 7) * 4;
+        f32x4 total = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int h = 0; h < (8 * GROUPS + 15) / 16; ++h) {
+            f32x4 mid = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 16 * h; j < 16 * h + 16 && j < 8 * GROUPS; ++j) mid += *(const f32x4 *)((const float *)(lds + j / GROUPS * REGION + j % GROUPS * F::C_BYTES) + word);
+            total += mid;
+        }
+        *(f32x4 *)(ctile + word) = total;
+    }
+    flex_epilogue<float, 32, 32, 1, 512, false, true, ROWSUM, float, EPI, 1>(P, Q, g, tm, tn, ctile, extra, rows, ahead);
 }
 
 // ---- bf16 in 16-byte vectors: the ring of mfma_ring.h ----------------------------------------------------------------
@@ -1514,7 +1544,7 @@ __global__ __launch_bounds__(256, MANY ? 4 : 2) void gemm_flex_f32_kernel(FlexBa
     else flex_f32_workgroup<(MANY ? 1 : 2), FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
 }
 
-template <bool FORWARD>
+template <bool FORWARD, int GROUPS>
 __global__ __launch_bounds__(512) void gemm_flex_f32_few_kernel(FlexBatch batch)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -1528,9 +1558,9 @@ __global__ __launch_bounds__(512) void gemm_flex_f32_few_kernel(FlexBatch batch)
     const FlexIn P = args_at<FlexIn>(offsetof(FlexBatch, p) + (size_t)j * sizeof(FlexParams) + offsetof(FlexParams, in));
     if (local >= P.total_wg) return;
     const int wg = flex_xcd_order(local, P.total_wg);
-    if constexpr (FORWARD) flex_f32_few_workgroup<FLEX_KC, FLEX_KC, EPI_BIAS_ACT>(P, j, wg, smem_raw);
-    else if (P.kind == 0) flex_f32_few_workgroup<FLEX_KC, FLEX_KM, EPI_DACT>(P, j, wg, smem_raw);
-    else flex_f32_few_workgroup<FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
+    if constexpr (FORWARD) flex_f32_few_workgroup<GROUPS, FLEX_KC, FLEX_KC, EPI_BIAS_ACT>(P, j, wg, smem_raw);
+    else if (P.kind == 0) flex_f32_few_workgroup<GROUPS, FLEX_KC, FLEX_KM, EPI_DACT>(P, j, wg, smem_raw);
+    else flex_f32_few_workgroup<GROUPS, FLEX_KM, FLEX_KM, EPI_STORE>(P, j, wg, smem_raw);
 }
 
 template <int TEAMS, int RING, bool FORWARD>

@@ -1009,16 +1009,16 @@ ph_status launch_flex_f32(const FlexBatch &batch, unsigned total_wg, hipStream_t
     return check_launch(what);
 }
 
-template <bool FORWARD>
+template <bool FORWARD, int GROUPS>
 ph_status launch_flex_f32_few(const FlexBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
 {
     static thread_local bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_flex_f32_few_kernel<FORWARD>, hipFuncAttributeMaxDynamicSharedMemorySize, F32_FEW_LDS);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, F32_FEW_LDS, hipGetErrorString(e));
+        hipError_t e = hipFuncSetAttribute((const void *)(gemm_flex_f32_few_kernel<FORWARD, GROUPS>), hipFuncAttributeMaxDynamicSharedMemorySize, f32_few_lds(GROUPS));
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, f32_few_lds(GROUPS), hipGetErrorString(e));
         configured = true;
     }
-    hipLaunchKernelGGL(gemm_flex_f32_few_kernel<FORWARD>, dim3(total_wg), dim3(512), F32_FEW_LDS, st, batch);
+    hipLaunchKernelGGL((gemm_flex_f32_few_kernel<FORWARD, GROUPS>), dim3(total_wg), dim3(512), f32_few_lds(GROUPS), st, batch);
     return check_launch(what);
 }
 
@@ -1046,15 +1046,25 @@ ph_status launch_flex_ring(const FlexBatch &batch, unsigned total_wg, hipStream_
     return check_launch(what);
 }
 
-// Does an fp32 launch run on gemm_flex_f32_few_kernel?  (Empty products count for nothing.)
-bool f32_few(const Product *prods, int count, const Geo &g, bool forward)
+// Does an fp32 launch run on gemm_flex_f32_few_kernel, and how many groups of 16 terms does a team take?  0: no.  (Empty products count for nothing.)
+// Up to one workgroup to a compute unit with four groups (150 KB of LDS), two with one or two.  Trained, us a step, never : up to 128 workgroups : 256 : 512 with any
+// number of groups: 4 layers of 8 ranks of 512 + 224 at batch 1024 (the compressions) 836 : 837 : 810 : 809; 3 of 8 of 128 + 112 at 256 121 : 118 : 92 : 90, of 4 of
+// 256 + 96 at 256 155 : 139 : 116 : 107; 2 of 8 of 256 + 224 at 128 110 : 101 : 77 : 77, of 16 of 64 + 120 at 512 98 : 91 : 81 : 75, of 4 of 64 + 24 at 64 54.8 : 42.8 : 42.9 :
+// 42.8; 4 of 4 of 96 + 72 at 333 164 : 150 : 118 : 118.  Up to 1024: 2 of 4 of 400 + 60 at 512 134.7 (512) : 198, of 16 of 256 + 120 at 256 114 : 164.
+int f32_few_groups(const Product *prods, int count, const Geo &g)
 {
-    if (g.dtype != PH_F32 || !g.whole || flex_tile_for<float>(prods, count, g.groups, forward, false) != FLEX_32_8) return false;
-    static const char *force = tuning_env("PHANTOM_F32_FEW");      // =0 (for measurements)
-    if (force && force[0] == '0') return false;
-    for (int i = 0; i < count; ++i)                    // (the rule of flex_tile_for: a team has one group of terms at most)
-        if (prods[i].M > 0 && prods[i].N > 0 && prods[i].K > 8 * F32_FEW_TERMS) return false;
-    return true;
+    if (g.dtype != PH_F32 || !g.whole) return 0;
+    int64_t small = 0, longest = 0;
+    for (int i = 0; i < count; ++i) {
+        if (prods[i].M <= 0 || prods[i].N <= 0) continue;
+        small += ((prods[i].M + 31) / 32) * ((prods[i].N + 31) / 32) * g.groups;
+        longest = std::max(longest, prods[i].K);
+    }
+    if (longest > 8 * F32_FEW_TERMS * F32_FEW_GROUPS) return 0;
+    const int groups = longest <= 8 * F32_FEW_TERMS ? 1 : longest <= 16 * F32_FEW_TERMS ? 2 : 4;
+    static const char *force[] = {tuning_env("PHANTOM_F32_FEW1"), tuning_env("PHANTOM_F32_FEW2"), tuning_env("PHANTOM_F32_FEW4")};     // workgroups, at most (for measurements)
+    const char *most = force[groups / 2];
+    return small <= (most ? atoi(most) : groups == 1 ? 512 : groups == 2 ? 512 : 256) ? groups : 0;
 }
 
 // Up to FLEX_MAX_PRODUCTS independent products in one launch.  forward: all in the forward layout; else any mix of the
@@ -1071,7 +1081,8 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
         if (prods_in[i].M > 0 && prods_in[i].N > 0) prods[count++] = prods_in[i];
     const int groups = g.groups;
     if (count == 0 || groups <= 0) return PH_OK;
-    const FlexTile tile = flex_tile_for<T>(prods, count, groups, forward, g.vec == 8);
+    const int few = f32_few_groups(prods, count, g);
+    const FlexTile tile = few > 0 ? FLEX_32_8 : flex_tile_for<T>(prods, count, groups, forward, g.vec == 8);
     const int t = tile == FLEX_32_8 ? 32 : 64;
     constexpr int V = FlexType<T>::V;
     FlexBatch batch{};
@@ -1130,10 +1141,12 @@ ph_status launch_flex(const Product *prods_in, int count_in, bool forward, const
             return forward ? launch_flex_ring<1, 3, true>(batch, total, st, what) : launch_flex_ring<1, 3, false>(batch, total, st, what);
         }
     if constexpr (sizeof(T) == 4)
-        if (tile == FLEX_32_8) {
-            if (f32_few(prods, count, g, forward)) return forward ? launch_flex_f32_few<true>(batch, total, st, what) : launch_flex_f32_few<false>(batch, total, st, what);
+        if (few > 0) {
+            if (few == 1) return forward ? launch_flex_f32_few<true, 1>(batch, total, st, what) : launch_flex_f32_few<false, 1>(batch, total, st, what);
+            if (few == 2) return forward ? launch_flex_f32_few<true, 2>(batch, total, st, what) : launch_flex_f32_few<false, 2>(batch, total, st, what);
+            return forward ? launch_flex_f32_few<true, 4>(batch, total, st, what) : launch_flex_f32_few<false, 4>(batch, total, st, what);
         }
-    if constexpr (sizeof(T) == 4)
+   if constexpr (sizeof(T) == 4)
         if (tile == FLEX_64 && g.whole) {
             // Up to two workgroups to a compute unit the launch waits for loads and operand reads, not for the matrix pipe (us a step of this kernel with
             // neither far ahead : so): 3 layers of 4 ranks of 256 + 8 trained at batch 1024, 256 to 384 workgroups, 251 : 218, of 4 of 400 + 20 at 700 302 : 277.
@@ -1818,7 +1831,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
             // the launch that needs dg_own first sums it on read where it can: the input gradient, or (first layer) the compressor gradient's
             const SumOnRead sum{(const __bf16 *)b.dG_send, (__bf16 *)b.dg_own, B * gl.k, (int)g.p, (int)gl.k};
             const Product last[2] = {pr.dw, pr.dc};
-            const bool on_read = sizeof(T) == 4 && g.p <= 8 && (l > 0 ? f32_few(&pr.dx, 1, g, false) : f32_few(last, 2, g, false));
+            const bool on_read = sizeof(T) == 4 && g.p <= 8 && (l > 0 ? f32_few_groups(&pr.dx, 1, g) : f32_few_groups(last, 2, g)) > 0;
             if (on_read) (l > 0 ? pr.dx : pr.dc).rs = sum;
             else PH_TRY(launch_reduce_scatter<T>(gl, b.dG_send, b.dg_own, LossTail{}, st));
             next.push_back(pr.dx);

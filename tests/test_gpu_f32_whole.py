@@ -29,8 +29,15 @@ def test_parity(n, p, k, B, L, rank):
     (20, 5, 4, 2, 3, "gelu", -1, "no_update"),       # shard 4 = k: one team with terms, one vector to a piece
     (64, 1, 0, 16, 2, "relu", 0, "train"),           # dense
     (512, 8, 4, 36, 2, "identity", -1, "forward"),
+    (512, 4, 16, 130, 2, "gelu", -1, "train"),       # two groups to a team: 176 and 130 terms
+    (1008, 4, 4, 256, 2, "relu", -1, "train"),       # ... 264: four, the last of them in part; 256: two
+    (1024, 4, 64, 500, 2, "gelu", -1, "train"),      # four groups: 448 and 500 terms, 320 and 512 workgroups
+    (512, 1, 0, 512, 2, "relu", 0, "train"),         # dense, 512 terms: all groups of all teams
+    (768, 3, 120, 90, 3, "identity", 2, "train"),    # one rank
+    (1024, 8, 20, 300, 2, "relu", -1, "no_update"),  # reduce-scatter on read with segments of 20
+    (576, 9, 8, 100, 2, "gelu", -1, "train"),        # nine ranks: a launch for the sums
 ])
 def test_few_tiles_and_short_reductions(n, p, k, B, L, act, rank, mode):
-    """32 x 32 tiles, one group of 16 terms to each of eight teams."""
+    """32 x 32 tiles, one, two or four groups of 16 terms to each of eight teams."""
     print(f"case f32 few n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode}", flush=True)
     check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="f32", rank=rank), seed=12, lr=0.02, mode=mode)
