@@ -40,7 +40,7 @@ FAMILIES = [
     (("reduce_scatter_kernel",), "rs", ("reduce-scatter",)),
     (("colsum_kernel",), "colsum", ("bias gradient",)),
     (("loss_kernel",), "loss", ("loss",)),
-    (("gemm_flex_kernel", "gemm_flex_ring_kernel", "gemm_flex_f32_kernel"), "flex", ("layer update", "compression", "input gradient", "error compression", "weight + compressor gradients",
+    (("gemm_flex_kernel", "gemm_flex_ring_kernel", "gemm_flex_f32_kernel", "gemm_flex_f32_few_kernel", "few_rows_kernel"), "flex", ("layer update", "compression", "input gradient", "error compression", "weight + compressor gradients",
                                      "gradients")),
     (("delta_kernel",), "delta", ("local error",)),
     (("fill_zero_kernel", "clear_kernel"), "fill", ("clear",)),
