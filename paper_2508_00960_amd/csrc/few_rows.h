@@ -42,7 +42,7 @@ template <int ROWS>
 __global__ __launch_bounds__(FEW_WAVES * 64) void few_rows_kernel(FewBatch batch)
 {
     constexpr int AHEAD = few_ahead(ROWS), NL = ROWS + 1, CHUNK = NL * 1024;           // bytes of a chunk's operands
-    extern __shared__ unsigned char few_lds[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char few_lds[];
     const bool second = batch.count > 1 && (int)blockIdx.x >= batch.first_wg;
     const FewProduct &P = second ? batch.p[1] : batch.p[0];
     const int id = (int)blockIdx.x - (second ? batch.first_wg : 0);

@@ -1332,6 +1332,22 @@ ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tile
     return launch_flex<T>(both, 2, true, g, LossTail{}, st, g.q > 0 ? "layer update + compression" : "layer update", mse_tiles);
 }
 
+template <int NF>
+ph_status launch_thin_product(dim3 grid, const FwdArgs &f, int64_t B, int64_t k, int64_t si, const ClearList &clear, hipStream_t st)
+{
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)thin_product_kernel<NF>, hipFuncAttributeMaxDynamicSharedMemorySize, THIN_WAVES * thin_region(NF, NF == 4 ? 3 : THIN_AHEAD));
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "compression: cannot reserve its LDS: %s", hipGetErrorString(e));
+        configured = true;
+    }
+    // all chunks of 32 that a wavefront may have, up to four (three of 64 phantom neurons: 144 KB of LDS)
+    const int most = NF == 4 ? 3 : THIN_AHEAD, ahead = (int)std::max<int64_t>(1, std::min<int64_t>(most, (si / 16 + 2 * THIN_WAVES - 1) / (2 * THIN_WAVES)));
+    hipLaunchKernelGGL(thin_product_kernel<NF>, grid, dim3(THIN_WAVES * 64), THIN_WAVES * thin_region(NF, ahead), st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
+                       (__bf16 *)f.g_own, (int)B, (int)k, (int)si, B * si, k * si, B * k, ahead, clear);
+    return check_launch("compression");
+}
+
 ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
 {
     typedef bf16_t T;
@@ -1349,10 +1365,8 @@ ph_status fwd_impl(const Geo &g, const FwdArgs &f, hipStream_t st)
     auto launch_thin = [&]() -> ph_status {
         ProfScope prof("compression", B, k, si, g.groups, st);
         dim3 grid((unsigned)((B + THIN_ROWS - 1) / THIN_ROWS), (unsigned)g.groups);
-        auto kern = k <= 16 ? thin_product_kernel<1> : k <= 32 ? thin_product_kernel<2> : thin_product_kernel<4>;
-        hipLaunchKernelGGL(kern, grid, dim3(THIN_WAVES * 64), 0, st, (const __bf16 *)f.X, (const __bf16 *)f.Cw, (__bf16 *)f.g_own, (int)B, (int)k, (int)si,
-                           B * si, k * si, B * k, take_clear());
-        return check_launch("compression");
+        if (k <= 16) return launch_thin_product<1>(grid, f, B, k, si, take_clear(), st);
+        return k <= 32 ? launch_thin_product<2>(grid, f, B, k, si, take_clear(), st) : launch_thin_product<4>(grid, f, B, k, si, take_clear(), st);
     };
     // (this layer's update adds into the buffers itself if it is the last one)
     if (f.clear && f.mse && !(g.all && thin)) PH_TRY(launch_clear(*f.clear, st));
