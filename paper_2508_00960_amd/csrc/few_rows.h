@@ -4,7 +4,7 @@
 // What bounds it.  The weights are read once and multiplied by a handful of rows, so a launch is a chain of latencies: parameters, one read of
 // the operands, a few matrix instructions, the sum over wavefronts, the epilogue.  The tiles of gemm_flex.h walk the reduction in dependent steps with
 // a barrier each, and 32 x 32 of them are too few to occupy the chip: 48 rows of 1024 + 448 make 72 workgroups that read 188 KB each.  Here a workgroup owns 16
-// output columns and ROWS x 16 rows, its eight wavefronts split the reduction, and each requests up to FEW_AHEAD chunks of 32 reduction indices at
+// output columns and ROWS x 16 rows, its eight wavefronts split the reduction, and each requests up to few_ahead chunks of 32 reduction indices at
 // once, to LDS that it alone reads: no barrier before the sum over wavefronts.  (Loads of operands in the matrix cores' layout, whose
 // neighbouring lanes lie in different rows, run at a quarter of the rate.)
 // Us a pass, 6 layers forward at batch 48 (gemm_flex.h : direct loads : so): 1024 + 448 46.4 : 38.8 : 36.3, 256 + 112 36.2 : 26.7 : 26.2, 1024 + 1792

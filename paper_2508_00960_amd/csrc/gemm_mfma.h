@@ -1180,14 +1180,13 @@ __device__ __forceinline__ void reduce_in_ring(const MfmaIn &P, int g, int m0, i
     const int steps = (k_end - k_begin + KT - 1) / KT;
     auto c_of = [=](int i) { return k_begin + (steps - 1 - i) * KT; };          // tile processed in step i
     auto fetch_a = [&](int i, uint32_t stage) { ring_fetch<KA, WA>(sa, a_off0, a_off1, c_of(i), stage + a_at, wave_a); };
-    auto fetch_fold = [&](int i, uint32_t stage) {
-        // (always one load, so that every stage has the same number; behind X's part of the range it is not used)
-        const int c0 = c_of(i);
-        if (lane < 32) ring_load<0>(fs.base, fs.src_off + (unsigned)(fs.on && c0 < fs.limit ? c0 : 0) * 2u, stage + E_AT + wave8 * 512);
-    };
     auto fetch_b = [&](int i, uint32_t stage) {
         ring_fetch<KB, WAVES>(sb, b_off0, b_off1, c_of(i), stage + B_AT, wave8);
-        if constexpr (FOLD) fetch_fold(i, stage);
+        if constexpr (FOLD) {
+            // (always one load, so that every stage has the same number; behind X's part of the range it is not used)
+            const int c0 = c_of(i);
+            if (lane < 32) ring_load<0>(fs.base, fs.src_off + (unsigned)(fs.on && c0 < fs.limit ? c0 : 0) * 2u, stage + E_AT + wave8 * 512);
+        }
     };
     PH_PHASE(1);
 #pragma unroll
@@ -1223,106 +1222,129 @@ __device__ __forceinline__ void reduce_in_ring(const MfmaIn &P, int g, int m0, i
 #define PH_FOLD(buf) do { if (FOLD && e_mul) { \
         if (fs.own_hi) fs.acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fe[buf], fr[buf][1], fs.acc, 0, 0, 0); \
         else fs.acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fe[buf], fr[buf][0], fs.acc, 0, 0, 0); } } while (0)
-    // What goes on between two barriers is one piece of code: the last quarter of step t and the other quarters of step t + 1, and behind matrix instructions
-    // of the latter (two stages: of the former, as the next barrier waits for them) the loads of the tile of step t + RING, to the slot that step t leaves.
-    // Regular shapes: one by one.  Other shapes work out an address per load and issue an operand's together, half of them behind the barrier and half in
-    // the next step.  A condition on each load, with one loop in the place of three, took 63.3 us where this takes 59.7 (weight gradients 8192 x
-    // 1024 over 4096 rows).
-    enum { NO_LOADS, BURSTS, ONE_BY_ONE };
-    RingCursor<KA, WA> ca;
-    RingCursor<KB, WAVES> cb;
-    uint32_t cur = lds0, next = lds0;                  // slots of step t and step t + 1
-    int t = 0;
-    bf16x8 fe[2];                                      // the block's operands
-    bool e_mul = false;                                // uniform per wavefront
-    auto loads_behind = [&](auto kind, auto slot) {    // ... matrix instruction `slot` behind the barrier
-        constexpr int KIND = decltype(kind)::value, S = decltype(slot)::value, SLOTS = RING == 2 ? 4 : 4 * QUARTERS;
-        if constexpr (KIND == ONE_BY_ONE) {
-            ring_each<NL>([&](auto load) {
-                constexpr int J = decltype(load)::value, JB = J - CA::NV;
-                if constexpr ((RING == 2 ? J * SLOTS / NL : 4 + J * (SLOTS - 4) / NL) == S) {
-                    if constexpr (JB < 0) ring_load<J * WA * 1024>(ca.base, ca.off[J], cur + a_at + wave_a * 1024);
-                    else if constexpr (JB < CB::NV) ring_load<JB * WAVES * 1024>(cb.base, cb.off[JB], cur + B_AT + wave8 * 1024);
-                    else fetch_fold(t + RING, cur);
+    auto read_all = [&](bf16x8 (&f)[4], uint32_t stage, int q) { ring_each<4>([&](auto nth) { read(f, stage, q, nth); }); };
+    read_all(fr[0], lds0, 0);
+    if constexpr (FOLD || LEVELS != ONE_SUM) {
+        // With a second set of sums, or the compression's, one loop with its conditions: three of them do not fit the registers (179 spilled; us a step, so : in
+        // three: 4 layers of 2000 + 36 trained at batch 2048 384 : 585, 3 of 1024 + 700 at 4000 241 : 250).
+        uint32_t cur = lds0, prev = lds0;
+        for (int t = 0; t < steps; ++t) {                  // uniform; on entry fr[0] holds the operands of the step's first quarter
+            const uint32_t next = cur + STAGE == lds0 + RING * STAGE ? lds0 : cur + STAGE;
+            bf16x8 fe[2];                                  // the block's operands
+            const bool e_mul = FOLD && fs.owner && c_of(t) < fs.limit;              // uniform per wavefront
+            if constexpr (FOLD) {
+                if (e_mul) {
+                    const int at = ring_lane_at<LD_KC>(0, lane);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) fe[q] = ring_operand<LD_KC>(cur + E_AT, at, 0, q0 + q);
                 }
-            });
-        } else if constexpr (KIND == BURSTS) {
-            if (S == 0) fetch_a(t + RING, cur);
-            if (S == (RING == 2 ? 0 : 4)) fetch_b(t + RING, cur);
-        }
-    };
-    auto last_quarter = [&](auto kind) {
-        ring_each<4>([&](auto m) {
-            constexpr int M = decltype(m)::value;
-            PH_PIN; read(fr[0], next, 0, m); PH_PIN;
-            PH_MFMA(1, M / 2, M % 2); PH_PIN;
-            loads_behind(kind, m);
-        });
-        PH_FOLD(1); PH_PIN;
-        if constexpr (LEVELS) {
-            if (t + 1 == steps || (LEVELS == SUMS_OF_8 ? t % 8 == 7 : t + 1 == steps / 2)) {      // uniform
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) { sums[i][j][e] += acc[i][j][e]; acc[i][j][e] = 0.f; }
             }
-        }
-    };
-    // of step `step`, in slot `at`; fr[0] holds the operands of the first
-    auto other_quarters = [&](auto kind, int step, uint32_t at) {
-        if constexpr (FOLD) {
-            e_mul = fs.owner && c_of(step) < fs.limit;
-            if (e_mul) {
-                const int row = ring_lane_at<LD_KC>(0, lane);
 #pragma unroll
-                for (int q = 0; q < 2; ++q) fe[q] = ring_operand<LD_KC>(at + E_AT, row, 0, q0 + q);
+            for (int q = 0; q + 1 < QUARTERS; ++q) {
+                PH_PIN; read_all(fr[(q + 1) & 1], cur, q + 1); PH_PIN;
+                PH_MFMA(q & 1, 0, 0); PH_PIN;
+                if (RING > 2 && q == 0 && t > 0 && t - 1 + RING < steps) fetch_b(t - 1 + RING, prev);
+                PH_PIN; PH_MFMA(q & 1, 0, 1); PH_MFMA(q & 1, 1, 0); PH_MFMA(q & 1, 1, 1); PH_FOLD(0); PH_PIN;
             }
-        }
-        ring_each<QUARTERS - 1>([&](auto quarter) {
-            constexpr int q = decltype(quarter)::value;
-            ring_each<4>([&](auto m) {
-                constexpr int M = decltype(m)::value;
-                PH_PIN; read(fr[(q + 1) & 1], at, q + 1, m); PH_PIN;
-                PH_MFMA(q & 1, M / 2, M % 2); PH_PIN;
-                if constexpr (RING > 2) loads_behind(kind, std::integral_constant<int, 4 + 4 * q + M>{});
-            });
-            PH_FOLD(0); PH_PIN;
-        });
-    };
-    auto between_barriers = [&](auto kind) {
-        next = cur + STAGE == lds0 + RING * STAGE ? lds0 : cur + STAGE;
-        last_quarter(kind);
-        other_quarters(kind, t + 1, next);
-        cur = next;
-        ++t;
-    };
-    ring_each<4>([&](auto m) { read(fr[0], lds0, 0, m); });
-    other_quarters(std::integral_constant<int, NO_LOADS>{}, 0, lds0);
-    // (each barrier: the next stage has landed, and everybody has read this one)
-    if (sa.regular && sb.regular) {                    // uniform
-        while (t + RING < steps) {
-            ring_run<KA, WA>(ca, sa, a_off0, a_off1, c_of(t + RING));
-            ring_run<KB, WAVES>(cb, sb, b_off0, b_off1, c_of(t + RING));
-            for (int run = min(min(ca.left, cb.left) + 1, steps - RING - t); run > 0; --run) {
-                ring_wait<(RING - 2) * NL>();
-                between_barriers(std::integral_constant<int, ONE_BY_ONE>{});
-                ca.base = (const __bf16 *)((uintptr_t)ca.base - ca.step);
-                cb.base = (const __bf16 *)((uintptr_t)cb.base - cb.step);
+            ring_wait_stage<NL, RING - 2>(steps - 2 - t);  // the next stage has landed, and everybody has read this one
+            if (t + 1 < steps) read_all(fr[0], next, 0);
+            PH_PIN; PH_MFMA(1, 0, 0); PH_PIN;
+            if (t + RING < steps) {
+                fetch_a(t + RING, cur);                    // (the other operand's loads follow in the next step: half the burst)
+                if (RING == 2) fetch_b(t + RING, cur);     // (... which waits for them itself with two stages)
             }
+            PH_PIN; PH_MFMA(1, 0, 1); PH_MFMA(1, 1, 0); PH_MFMA(1, 1, 1); PH_FOLD(1); PH_PIN;
+            if constexpr (LEVELS) {
+                if (t + 1 == steps || (LEVELS == SUMS_OF_8 ? t % 8 == 7 : t + 1 == steps / 2)) {      // uniform
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) { sums[i][j][e] += acc[i][j][e]; acc[i][j][e] = 0.f; }
+                }
+            }
+            prev = cur;
+            cur = next;
         }
     } else {
-        while (t + RING < steps) {
-            ring_wait<(RING - 2) * NL>();
-            between_barriers(std::integral_constant<int, BURSTS>{});
+        // What goes on between two barriers is one piece of code: the last quarter of step t and the other quarters of step t + 1, and behind matrix instructions
+        // of the latter (two stages: of the former, as the next barrier waits for them) the loads of the tile of step t + RING, to the slot that step t leaves.
+        // Regular shapes: one by one.  Other shapes work out an address per load and issue an operand's together, half of them behind the barrier and half in
+        // the next step.  A condition on each load, with one loop in the place of three, took 63.3 us where this takes 59.7 (weight gradients 8192 x
+        // 1024 over 4096 rows).
+        enum { NO_LOADS, BURSTS, ONE_BY_ONE };
+        RingCursor<KA, WA> ca;
+        RingCursor<KB, WAVES> cb;
+        uint32_t cur = lds0, next = lds0;                  // slots of step t and step t + 1
+        int t = 0;
+        auto loads_behind = [&](auto kind, auto slot) {    // ... matrix instruction `slot` behind the barrier
+            constexpr int KIND = decltype(kind)::value, S = decltype(slot)::value, SLOTS = RING == 2 ? 4 : 4 * QUARTERS;
+            if constexpr (KIND == ONE_BY_ONE) {
+                ring_each<NL>([&](auto load) {
+                    constexpr int J = decltype(load)::value, JB = J - CA::NV;
+                    if constexpr ((RING == 2 ? J * SLOTS / NL : 4 + J * (SLOTS - 4) / NL) == S) {
+                        if constexpr (JB < 0) ring_load<J * WA * 1024>(ca.base, ca.off[J], cur + a_at + wave_a * 1024);
+                        else ring_load<JB * WAVES * 1024>(cb.base, cb.off[JB], cur + B_AT + wave8 * 1024);
+                    }
+                });
+            } else if constexpr (KIND == BURSTS) {
+                if (S == 0) fetch_a(t + RING, cur);
+                if (S == (RING == 2 ? 0 : 4)) fetch_b(t + RING, cur);
+            }
+        };
+        auto last_quarter = [&](auto kind) {
+            ring_each<4>([&](auto m) {
+                constexpr int M = decltype(m)::value;
+                PH_PIN; read(fr[0], next, 0, m); PH_PIN;
+                PH_MFMA(1, M / 2, M % 2); PH_PIN;
+                loads_behind(kind, m);
+            });
+        };
+        // of step `step`, in slot `at`; fr[0] holds the operands of the first
+        auto other_quarters = [&](auto kind, int step, uint32_t at) {
+            ring_each<QUARTERS - 1>([&](auto quarter) {
+                constexpr int q = decltype(quarter)::value;
+                ring_each<4>([&](auto m) {
+                    constexpr int M = decltype(m)::value;
+                    PH_PIN; read(fr[(q + 1) & 1], at, q + 1, m); PH_PIN;
+                    PH_MFMA(q & 1, M / 2, M % 2); PH_PIN;
+                    if constexpr (RING > 2) loads_behind(kind, std::integral_constant<int, 4 + 4 * q + M>{});
+                });
+            });
+        };
+        auto between_barriers = [&](auto kind) {
+            next = cur + STAGE == lds0 + RING * STAGE ? lds0 : cur + STAGE;
+            last_quarter(kind);
+            other_quarters(kind, t + 1, next);
+            cur = next;
+            ++t;
+        };
+        other_quarters(std::integral_constant<int, NO_LOADS>{}, 0, lds0);
+        // (each barrier: the next stage has landed, and everybody has read this one)
+        if (sa.regular && sb.regular) {                    // uniform
+            while (t + RING < steps) {
+                ring_run<KA, WA>(ca, sa, a_off0, a_off1, c_of(t + RING));
+                ring_run<KB, WAVES>(cb, sb, b_off0, b_off1, c_of(t + RING));
+                for (int run = min(min(ca.left, cb.left) + 1, steps - RING - t); run > 0; --run) {
+                    ring_wait<(RING - 2) * NL>();
+                    between_barriers(std::integral_constant<int, ONE_BY_ONE>{});
+                    ca.base = (const __bf16 *)((uintptr_t)ca.base - ca.step);
+                    cb.base = (const __bf16 *)((uintptr_t)cb.base - cb.step);
+                }
+            }
+        } else {
+            while (t + RING < steps) {
+                ring_wait<(RING - 2) * NL>();
+                between_barriers(std::integral_constant<int, BURSTS>{});
+            }
         }
+        while (t + 1 < steps) {
+            ring_wait_stage<NL, RING - 2>(steps - 2 - t);
+            between_barriers(std::integral_constant<int, NO_LOADS>{});
+        }
+        last_quarter(std::integral_constant<int, NO_LOADS>{});
     }
-    while (t + 1 < steps) {
-        ring_wait_stage<NL, RING - 2>(steps - 2 - t);
-        between_barriers(std::integral_constant<int, NO_LOADS>{});
-    }
-    last_quarter(std::integral_constant<int, NO_LOADS>{});
     if constexpr (LEVELS) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
