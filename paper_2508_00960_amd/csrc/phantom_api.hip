@@ -1271,21 +1271,22 @@ int few_rows_blocks(const Geo &g, const FwdArgs &f)
     return 0;
 }
 
-template <int ROWS>
+template <int ROWS, int TEAMS>
 ph_status launch_few_rows_kernel(const FewBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
 {
-    constexpr int LDS = few_lds_bytes(ROWS);
     static thread_local bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)few_rows_kernel<ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
+        constexpr int MOST = few_lds_bytes(ROWS, TEAMS, (FEW_SHORT + 31) / 32);
+        hipError_t e = hipFuncSetAttribute((const void *)few_rows_kernel<ROWS, TEAMS>, hipFuncAttributeMaxDynamicSharedMemorySize, MOST);
+        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MOST, hipGetErrorString(e));
         configured = true;
     }
-    hipLaunchKernelGGL(few_rows_kernel<ROWS>, dim3(total_wg), dim3(FEW_WAVES * 64), LDS, st, batch);
+    hipLaunchKernelGGL((few_rows_kernel<ROWS, TEAMS>), dim3(total_wg), dim3(FEW_WAVES * 64), few_lds_bytes(ROWS, TEAMS, batch.chunks), st, batch);
     return check_launch(what);
 }
 
-ph_status launch_few_rows(const Geo &g, const FwdProducts &pr, int blocks, hipStream_t st)
+// teams: those of the tiles of gemm_flex.h that these products would have
+ph_status launch_few_rows(const Geo &g, const FwdProducts &pr, int blocks, int teams, hipStream_t st)
 {
     FewBatch batch{};
     int next = 0;
@@ -1303,13 +1304,18 @@ ph_status launch_few_rows(const Geo &g, const FwdProducts &pr, int blocks, hipSt
         }
         P.tiles_n = (P.N + FEW_TILE - 1) / FEW_TILE; P.pitch = (P.tiles_n + 7) & ~7;
         if (batch.count == 1) batch.first_wg = next;
+        batch.chunks = std::max(batch.chunks, (P.K + 31) / 32);
         next += (P.M + blocks * FEW_TILE - 1) / (blocks * FEW_TILE) * P.pitch;
         ++batch.count;
     }
     const char *what = batch.count == 2 ? "layer update + compression" : "layer update";
     ProfScope prof(what, pr.update.M, pr.update.N, pr.update.K, 1, st, pr.compress.M, pr.compress.N, pr.compress.K);
-    return blocks == 1 ? launch_few_rows_kernel<1>(batch, (unsigned)next, st, what) : blocks == 2 ? launch_few_rows_kernel<2>(batch, (unsigned)next, st, what)
-                       : launch_few_rows_kernel<4>(batch, (unsigned)next, st, what);
+    const unsigned total = (unsigned)next;
+    if (teams == 8)
+        return blocks == 1 ? launch_few_rows_kernel<1, 8>(batch, total, st, what) : blocks == 2 ? launch_few_rows_kernel<2, 8>(batch, total, st, what)
+                           : launch_few_rows_kernel<4, 8>(batch, total, st, what);
+    return blocks == 1 ? launch_few_rows_kernel<1, 2>(batch, total, st, what) : blocks == 2 ? launch_few_rows_kernel<2, 2>(batch, total, st, what)
+                       : launch_few_rows_kernel<4, 2>(batch, total, st, what);
 }
 
 // Forward through gemm_flex.h.  mse_tiles: with f.mse, the number of partial sums of the loss it leaves.
@@ -1324,7 +1330,11 @@ ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tile
     }
     const Product both[2] = {pr.update, pr.compress};
     if constexpr (sizeof(T) == 2)
-        if (const int blocks = few_rows_blocks(g, f)) return launch_few_rows(g, pr, blocks, st);
+        if (const int blocks = few_rows_blocks(g, f)) {
+            // (a dense layer has no compression: its product has no rows)
+            const FlexTile tile = flex_tile_for<T>(both, 2, 1, true, true);
+            if (tile == FLEX_32_8 || (tile == FLEX_64_2 && g.Kc < FEW_SHORT)) return launch_few_rows(g, pr, blocks, tile == FLEX_32_8 ? 8 : 2, st);
+        }
     if (f.apart) {
         PH_TRY((launch_flex<T>(&pr.update, 1, true, g, LossTail{}, st, "layer update")));
         return launch_flex<T>(&pr.compress, 1, true, g, LossTail{}, st, "compression");
