@@ -20,6 +20,7 @@
 #include "few_rows.h"
 #include "gemm_flex.h"
 #include "gemm_mfma.h"
+#include "lds_reserve.h"
 #include "thin_product.h"
 #include "views.h"
 
@@ -478,17 +479,19 @@ struct Product {
     bool km;             // gemm_flex kernels: weight-gradient layout (both operands along their free index), float out
 };
 
+ph_status reserve_lds(LdsReserved &reserved, const void *kernel, int bytes, const char *what)
+{
+    const hipError_t e = reserved.reserve(kernel, bytes);
+    return e == hipSuccess ? PH_OK : fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, bytes, hipGetErrorString(e));
+}
+
 template <int KA, int KB, int VEC, typename TOut, bool PAIR, int MODE, int EPI>
 ph_status launch_mfma_kernel(const MfmaBatch &batch, hipStream_t st, const char *what)
 {
     auto kern = gemm_mfma_kernel<KA, KB, VEC, VEC, TOut, PAIR, MODE, EPI>;
     constexpr int LDS = mfma_lds_bytes(MODE);
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, LDS, what));
     hipLaunchKernelGGL(kern, dim3((unsigned)batch.total_wg), dim3(mfma_threads(MODE)), LDS, st, batch);
     return check_launch(what);
 }
@@ -615,13 +618,8 @@ template <int VEC>
 ph_status launch_tail_kernel(const MfmaTailBatch &tb, unsigned total_wg, hipStream_t st, const char *what)
 {
     auto kern = gemm_mfma_tail_kernel<VEC>;
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES,
-                                         hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, MFMA_LDS_BYTES, what));
     hipLaunchKernelGGL(kern, dim3(total_wg), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, tb);
     return check_launch(what);
 }
@@ -716,13 +714,8 @@ ph_status launch_product_table(const ProductTable *table, int grid, hipStream_t 
                                const Product &prof_b, int prof_groups)
 {
     auto kern = gemm_mfma_table_kernel<8, HALVES>;
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES,
-                                         hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, MFMA_LDS_BYTES, what));
     ProfScope prof(what, prof_a.M, prof_a.N, prof_a.K, prof_groups, st, prof_b.M, prof_b.N, prof_b.K);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, table);
     return check_launch(what);
@@ -733,12 +726,8 @@ ph_status launch_uniform_kernel(const UniformGradients &u, const Product &dw, co
 {
     auto kern = gemm_mfma_uniform_kernel<8, SOLO, HALVES>;
     constexpr int MODE = SOLO ? TILE_SOLO : TILE_DUAL, LDS = mfma_lds_bytes(MODE);
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, LDS, what));
     ProfScope prof(what, dw.M, dw.N, dw.K, u.layers, st, dc.M, dc.N, dc.K);
     hipLaunchKernelGGL(kern, dim3((unsigned)(u.layers * (u.dc_wg + u.dw_wg))), dim3(mfma_threads(MODE)), LDS, st, u);
     return check_launch(what);
@@ -793,12 +782,8 @@ template <int VEC, bool DUAL>
 ph_status launch_many_kernel(const MfmaMany &many, hipStream_t st, const char *what)
 {
     auto kern = gemm_mfma_many_kernel<VEC, DUAL>;
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES, hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, MFMA_LDS_BYTES, what));
     hipLaunchKernelGGL(kern, dim3((unsigned)many.first_wg[many.count]), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, many);
     return check_launch(what);
 }
@@ -827,13 +812,8 @@ template <int VEC, bool DUAL, bool FOLD = false>
 ph_status launch_fwd_kernel(const MfmaFwdBatch &fb, unsigned total_wg, hipStream_t st, const char *what)
 {
     auto kern = gemm_mfma_fwd_kernel<VEC, DUAL, FOLD>;
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MFMA_LDS_BYTES);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MFMA_LDS_BYTES,
-                                         hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, MFMA_LDS_BYTES, what));
     hipLaunchKernelGGL(kern, dim3(total_wg), dim3(MFMA_THREADS), MFMA_LDS_BYTES, st, fb);
     return check_launch(what);
 }
@@ -990,12 +970,8 @@ ph_status launch_flex_kernel(const FlexBatch &batch, unsigned total_wg, hipStrea
     auto kern = gemm_flex_kernel<T, TM, TN, TEAMS, FORWARD, FINE>;
     constexpr int LDS = FORWARD ? flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KC, FLEX_KC>()
                                 : flex_max(flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KC, FLEX_KM>(), flex_lds_bytes<T, TM, TN, TEAMS, FLEX_KM, FLEX_KM>());
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, LDS, what));
     hipLaunchKernelGGL(kern, dim3(total_wg), dim3(FlexShape<T, TM, TN, TEAMS, FINE>::THREADS), LDS, st, batch);
     return check_launch(what);
 }
@@ -1012,12 +988,8 @@ ph_status launch_flex_f32(const FlexBatch &batch, unsigned total_wg, hipStream_t
 template <bool FORWARD, int GROUPS>
 ph_status launch_flex_f32_few(const FlexBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
 {
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)(gemm_flex_f32_few_kernel<FORWARD, GROUPS>), hipFuncAttributeMaxDynamicSharedMemorySize, f32_few_lds(GROUPS));
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, f32_few_lds(GROUPS), hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)(gemm_flex_f32_few_kernel<FORWARD, GROUPS>), f32_few_lds(GROUPS), what));
     hipLaunchKernelGGL((gemm_flex_f32_few_kernel<FORWARD, GROUPS>), dim3(total_wg), dim3(512), f32_few_lds(GROUPS), st, batch);
     return check_launch(what);
 }
@@ -1036,12 +1008,8 @@ ph_status launch_flex_ring(const FlexBatch &batch, unsigned total_wg, hipStream_
 {
     auto kern = gemm_flex_ring_kernel<TEAMS, RING, FORWARD>;
     constexpr int LDS = flex_ring_lds<TEAMS, RING>();
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, LDS, hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)kern, LDS, what));
     hipLaunchKernelGGL(kern, dim3(total_wg), dim3(TEAMS * 256), LDS, st, batch);
     return check_launch(what);
 }
@@ -1274,13 +1242,9 @@ int few_rows_blocks(const Geo &g, const FwdArgs &f)
 template <int ROWS, int TEAMS>
 ph_status launch_few_rows_kernel(const FewBatch &batch, unsigned total_wg, hipStream_t st, const char *what)
 {
-    static thread_local bool configured = false;
-    if (!configured) {
-        constexpr int MOST = few_lds_bytes(ROWS, TEAMS, (FEW_SHORT + 31) / 32);
-        hipError_t e = hipFuncSetAttribute((const void *)few_rows_kernel<ROWS, TEAMS>, hipFuncAttributeMaxDynamicSharedMemorySize, MOST);
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "%s: cannot reserve %d bytes of LDS: %s", what, MOST, hipGetErrorString(e));
-        configured = true;
-    }
+    constexpr int MOST = few_lds_bytes(ROWS, TEAMS, (FEW_SHORT + 31) / 32);
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)(few_rows_kernel<ROWS, TEAMS>), MOST, what));
     hipLaunchKernelGGL((few_rows_kernel<ROWS, TEAMS>), dim3(total_wg), dim3(FEW_WAVES * 64), few_lds_bytes(ROWS, TEAMS, batch.chunks), st, batch);
     return check_launch(what);
 }
@@ -1345,12 +1309,8 @@ ph_status flex_fwd(const Geo &g, const FwdArgs &f, hipStream_t st, int *mse_tile
 template <int NF>
 ph_status launch_thin_product(dim3 grid, const FwdArgs &f, int64_t B, int64_t k, int64_t si, const ClearList &clear, hipStream_t st)
 {
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)thin_product_kernel<NF>, hipFuncAttributeMaxDynamicSharedMemorySize, THIN_WAVES * thin_region(NF, NF == 4 ? 3 : THIN_AHEAD));
-        if (e != hipSuccess) return fail(PH_ERR_LAUNCH, "compression: cannot reserve its LDS: %s", hipGetErrorString(e));
-        configured = true;
-    }
+    static LdsReserved reserved;
+    PH_TRY(reserve_lds(reserved, (const void *)(thin_product_kernel<NF>), THIN_WAVES * thin_region(NF, NF == 4 ? 3 : THIN_AHEAD), "compression"));
     // all chunks of 32 that a wavefront may have, up to four (three of 64 phantom neurons: 144 KB of LDS)
     const int most = NF == 4 ? 3 : THIN_AHEAD, ahead = (int)std::max<int64_t>(1, std::min<int64_t>(most, (si / 16 + 2 * THIN_WAVES - 1) / (2 * THIN_WAVES)));
     hipLaunchKernelGGL(thin_product_kernel<NF>, grid, dim3(THIN_WAVES * 64), THIN_WAVES * thin_region(NF, ahead), st, (const __bf16 *)f.X, (const __bf16 *)f.Cw,
