@@ -33,6 +33,7 @@
 #include "common.h"
 #include "elementwise.h"
 #include "epilogue.h"
+#include "launch_rules.h"
 #include "mfma_ring.h"
 
 namespace phantom {
@@ -1189,12 +1190,11 @@ __device__ __forceinline__ void flex_f32_workgroup(const FlexIn &P, int product,
 // instructions that are fetched cold.  So nothing is in a loop, what the epilogue reads is requested with the operands, and a wavefront stages what it
 // alone reads: one barrier, ahead of the epilogue.
 // 2 layers of 4 ranks of 64 + 24 trained at batch 32, ten launches (us a step, flex_workgroup : so): 54.9 : 44.4.
-constexpr int F32_FEW_TERMS = 16, F32_FEW_KC = F32_FEW_TERMS + 4, F32_FEW_KM = 32;      // floats per LDS row
+constexpr int F32_FEW_KC = F32_FEW_TERMS + 4, F32_FEW_KM = 32;                          // floats per LDS row
 constexpr int F32_FEW_STAGE = 2 * 32 * F32_FEW_KC * 4;                                  // bytes of a group's two operands
 // A team's region: the tiles of its groups' sums, its operands over the last one's place
 constexpr int f32_few_region(int groups) { return (groups - 1) * FlexTileShape<32, 32>::C_BYTES + F32_FEW_STAGE; }
 constexpr int f32_few_lds(int groups) { return 8 * f32_few_region(groups) + 512 * 4 + 64; }
-constexpr int F32_FEW_GROUPS = 4;                      // a team's groups, at most
 
 // All ranks on the device, at most 8: dg_own is summed on read by the launch that needs it first, the senders in the order in which reduce_scatter_kernel
 // adds them, and stored by the workgroups of tile column 0 for the launches behind it (the same step, with two launches for the sums : without, 44.4 : 42.4).

@@ -34,7 +34,7 @@ def outputs(n, p, k, B, L, act, dtype, rank=0):
     return got
 
 
-@pytest.mark.parametrize("n,p,k,B,L,act", [
+BF16 = [
     # few rows (csrc/few_rows.h).  In tiles with eight teams: reductions of 960 and more, and of 512
     (8192, 8, 64, 48, 2, "relu"),        # 23 tiles of 64: the last two wavefronts have one less
     (8192, 8, 64, 96, 2, "gelu"),        # 2 blocks of rows
@@ -51,19 +51,23 @@ def outputs(n, p, k, B, L, act, dtype, rank=0):
     (16, 2, 8, 5, 2, "relu"),            # one tile, a quarter full: the second team has none
     (320, 4, 24, 19, 3, "identity"),     # 152: two and a half
     (576, 8, 24, 260, 2, "relu"),        # 240: an odd number of chunks
-])
+]
+F32 = [
+    # without the compression the launch is one of few tiles (gemm_flex_f32_few_kernel), with it it is not
+    (192, 2, 32, 4480, 1, "relu", 0),    # one group of 16 terms to a team: 420 and 560 workgroups, at most 512
+    (384, 2, 64, 2560, 1, "gelu", 1),    # two groups: 480 and 640
+    (896, 2, 64, 544, 1, "relu", 0),     # four groups: 238 and 272, at most 256
+    (640, 2, 64, 360, 1, "identity", -1),    # ... all ranks, in two launches: 240
+]
+
+
+@pytest.mark.parametrize("n,p,k,B,L,act", BF16)
 def test_bf16(n, p, k, B, L, act):
     print(f"case forward bits bf16 n={n} p={p} k={k} B={B} L={L} {act}", flush=True)
     assert torch.equal(*outputs(n, p, k, B, L, act, "bf16"))
 
 
-@pytest.mark.parametrize("n,p,k,B,L,act,rank", [
-    # without the compression the launch is one of few tiles (gemm_flex_f32_few_kernel), with it it is not
-    (192, 2, 32, 4480, 1, "relu", 0),    # one group of 16 terms to a team: 420 and 560 workgroups, at most 512
-    (384, 2, 64, 2560, 1, "gelu", 1),    # two groups: 480 and 640
-    (896, 2, 64, 544, 1, "relu", 0),     # four groups: 238 and 272, at most 256
-    (640, 2, 64, 360, 1, "identity", -1),    # ... all ranks: 240, 288
-])
+@pytest.mark.parametrize("n,p,k,B,L,act,rank", F32)
 def test_f32(n, p, k, B, L, act, rank):
     print(f"case forward bits f32 n={n} p={p} k={k} B={B} L={L} {act} rank={rank}", flush=True)
     assert torch.equal(*outputs(n, p, k, B, L, act, "f32", rank))
