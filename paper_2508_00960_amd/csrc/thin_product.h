@@ -177,7 +177,9 @@ __global__ __launch_bounds__(THIN_WAVES * 64) void thin_product_kernel(const __b
     uint32_t slot = lds0;
     for (int i = 0; i < count; ++i) {                  // uniform
         const int later = min(count - 1 - i, ahead - 1);
-        if (clear.count) ring_own<0>();                // (its stores count among the outstanding operations)
+        // (The rider's stores count among the outstanding operations.  They are out by the second chunk, but counting from there on is slower: 8 ranks of 2048 + 32
+        // at batch 1024 6.6 : 6.6 us a launch, of 4096 + 32 13.4 : 15.3, of 2048 + 64 9.6 : 9.8, 4 of 4096 + 16 at 2048 12.4 : 13.2.)
+        if (clear.count) ring_own<0>();
         else ring_landed<NL, THIN_AHEAD - 1>(later);
         thin_bf16x8 a[MF], b[NF];
 #pragma unroll

@@ -74,6 +74,8 @@ def test_all_gradients_of_large_layers_together(n, p, k, B, L, act, mode):
     (2176, 4, 16, 2001, 1, "relu", -1, "forward"),        # shard 544: chunks that the wavefronts share unevenly; a last block of 17 rows
     (2112, 4, 24, 2000, 2, "relu", -1, "no_update"),      # shard 528, two blocks
     (4160, 4, 64, 1100, 1, "relu", -1, "forward"),        # four blocks
+    (3168, 2, 24, 1200, 2, "relu", -1, "no_update"),      # shard 1584: up to seven chunks a wavefront, four in flight, behind the stores that clear the bias gradients
+    (3168, 2, 64, 1200, 2, "gelu", -1, "train"),          # ... three in flight
     (4128, 2, 40, 2100, 1, "relu", 0, "forward"),         # one rank's step of one layer: behind the update's epilogue, shares of 16 rows
     (4128, 2, 24, 2100, 1, "relu", 1, "forward"),
 ])
