@@ -26,14 +26,29 @@ FLAGS = [
 LLVM = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(HIPCC) or HIPCC))), "llvm", "bin")
 
 
-def device_code(library: str) -> str:
-    """Disassembly of the kernels in a library that was built here."""
+def _on_device_object(library: str, tool: str, *args: str) -> str:
+    """What an LLVM tool prints about the kernels in a library that was built here."""
     with tempfile.TemporaryDirectory() as tmp:
         fat, obj = os.path.join(tmp, "fat"), os.path.join(tmp, "obj")
-        run = lambda tool, *args: subprocess.run([os.path.join(LLVM, tool), *args], check=True, capture_output=True, text=True).stdout
+        run = lambda name, *a: subprocess.run([os.path.join(LLVM, name), *a], check=True, capture_output=True, text=True).stdout
         run("llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", library, os.path.join(tmp, "copy"))
         run("clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={fat}", f"--output={obj}")
-        return run("llvm-objdump", "-d", "--no-show-raw-insn", "--symbolize-operands", obj)
+        return run(tool, *args, obj)
+
+
+def device_code(library: str) -> str:
+    """Disassembly of the kernels."""
+    return _on_device_object(library, "llvm-objdump", "-d", "--no-show-raw-insn", "--symbolize-operands")
+
+
+def scratch_bytes(library: str):
+    """{kernel: bytes of scratch memory per lane} of the kernels that have any: registers spilled, or arrays that did not fit them."""
+    out = {}
+    for kernel in re.split(r"\n\s+- \.agpr_count", _on_device_object(library, "llvm-readelf", "--notes"))[1:]:
+        entry = dict(re.findall(r"\.(\w+):\s+(\S+)", kernel))
+        if int(entry["private_segment_fixed_size"]):
+            out[entry["name"]] = int(entry["private_segment_fixed_size"])
+    return out
 
 
 def _scalar_registers(operand: str):

@@ -1,11 +1,11 @@
-"""What the inline assembly of csrc/ owes the compiler and the hardware, on the host."""
+"""What the inline assembly of csrc/ owes the compiler and the hardware, and what the compiler made of the kernels, on the host."""
 import os
 import re
 import subprocess
 
 import pytest
 
-from paper_2508_00960_amd.build import CSRC, FLAGS, HIPCC, LIB, LLVM, device_code, missing_wait_states
+from paper_2508_00960_amd.build import CSRC, FLAGS, HIPCC, LIB, LLVM, device_code, missing_wait_states, scratch_bytes
 
 # base and LDS address are known per lane only: v_readfirstlane brings them to scalar registers right ahead of the loads
 PROBE = """
@@ -56,6 +56,38 @@ def test_a_kernel_without_them_is_found(tmp_path):
     subprocess.run([HIPCC, *FLAGS, "-w", "-I", CSRC, str(src), "-o", str(lib)], check=True, capture_output=True)
     wrong = missing_wait_states(device_code(str(lib)))
     assert wrong and all("probe" in w and "global_load_lds_dwordx4" in w for w in wrong), wrong
+
+
+# The one kernel that keeps values in scratch memory: eight registers, three of them read again in its loop.
+SCRATCH = {"gemm_flex_f32_kernelILb0ELb1E": 36}
+
+
+@needs_compiler
+def test_no_kernel_spills():
+    """(A loop of the 128 x 128 kernels written for one set of sums once spilled 179 registers with two, at 1.5 times the time, and gave the same results.)"""
+    if not os.path.exists(LIB):
+        pytest.skip("not built")
+    for kernel, size in scratch_bytes(LIB).items():
+        assert size <= max((most for name, most in SCRATCH.items() if name in kernel), default=0), f"{kernel}: {size} bytes of scratch a lane"
+
+
+@needs_compiler
+def test_a_kernel_that_spills_is_found(tmp_path):
+    src, lib = tmp_path / "probe.hip", tmp_path / "probe.so"
+    src.write_text("""
+#include <hip/hip_runtime.h>
+__global__ __launch_bounds__(64) void fits(float *out) { out[threadIdx.x] = 1.f; }
+__global__ __launch_bounds__(64) void spills(float *out, const int *at)
+{
+    float a[1000];
+    for (int i = 0; i < 1000; ++i) a[i] = out[i];
+    for (int i = 0; i < 1000; ++i) a[at[i]] += 1.f;
+    for (int i = 0; i < 1000; ++i) out[i] = a[i];
+}
+""")
+    subprocess.run([HIPCC, *FLAGS, "-w", str(src), "-o", str(lib)], check=True, capture_output=True)
+    found = scratch_bytes(str(lib))
+    assert len(found) == 1 and "spills" in next(iter(found)) and next(iter(found.values())) >= 4000
 
 
 INSTRUCTIONS = """
