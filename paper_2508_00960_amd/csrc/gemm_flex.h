@@ -1205,7 +1205,7 @@ __device__ __forceinline__ u32x4 f32_few_sum(const SumOnRead &rs, int g, int64_t
 #pragma unroll
     for (int a = 0; a < MOST; ++a) {
         const int i = min(a, rs.p - 2), from = i < g ? i : i + 1, slot = g < from ? g : g - 1;      // the i-th sender other than g
-        v[a] = gload<f32x4>((const float *)(const void *)rs.src + ((int64_t)from * (rs.p - 1) + slot) * rs.per_slot + at);
+        v[a] = gload<f32x4>((const float *)rs.src + ((int64_t)from * (rs.p - 1) + slot) * rs.per_slot + at);
     }
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1255,7 +1255,7 @@ __device__ __forceinline__ void f32_few_fetch(u32x4 (&v)[2], const FlexOperand &
     for (int j = 0; j < 2; ++j) {
         if (summed[j]) v[j] = f32_few_sum(*rs, g, own[j]);
         else v[j] = gload<u32x4>(at[j]);
-        if (store[j]) gstore<u32x4>((float *)(void *)rs->out + (int64_t)g * rs->per_slot + own[j], v[j]);
+        if (store[j]) gstore<u32x4>((float *)rs->out + (int64_t)g * rs->per_slot + own[j], v[j]);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j)

@@ -397,7 +397,7 @@ __device__ __forceinline__ void fetch_summed(const SumOnRead &rs, int g, int r0,
             const int i = min(a0 + a, senders - 1);            // the i-th sender other than g
             const int from = i < g ? i : i + 1;
             const int slot = g < from ? g : g - 1;
-            const __bf16 *base = rs.src + ((int64_t)from * (rs.p - 1) + slot) * rs.per_slot;
+            const __bf16 *base = (const __bf16 *)rs.src + ((int64_t)from * (rs.p - 1) + slot) * rs.per_slot;
 #pragma unroll
             for (int j = 0; j < C::NV; ++j) v[a][j] = load_global<u32x4>(base + row_off[j]);
         }
@@ -420,7 +420,7 @@ __device__ __forceinline__ void fetch_summed(const SumOnRead &rs, int g, int r0,
 #pragma unroll
         for (int u = 0; u < VEC; ++u) x.e[u] = (__bf16)acc[j][u];
         *lds_at<u32x4>(tile + (j * WAVES + wave) * 1024 + lane * 16) = x.v;
-        if (write_out) *(u32x4 *)(rs.out + (int64_t)g * rs.per_slot + row_off[j]) = x.v;
+        if (write_out) *(u32x4 *)((__bf16 *)rs.out + (int64_t)g * rs.per_slot + row_off[j]) = x.v;
     }
 }
 

@@ -1600,7 +1600,7 @@ ph_status bwd_impl(const Geo &g, const BwdArgs &b, const BwdWs &w, hipStream_t s
         const bool sum_on_read = g.vec == 8 && q > 0 && b.dX && g.p <= 8 && k <= KT &&
                                  KT % k == 0 && so % KT == 0 && !(rs_force && rs_force[0] == '0');
         if (sum_on_read) {
-            dx.rs.src = (const __bf16 *)b.dG_send; dx.rs.out = (__bf16 *)b.dg_own;
+            dx.rs.src = b.dG_send; dx.rs.out = b.dg_own;
             dx.rs.per_slot = B * k; dx.rs.p = (int)g.p; dx.rs.k = (int)k;
         } else if (q > 0) {
             PH_TRY(launch_reduce_scatter<T>(g, b.dG_send, b.dg_own, take_tail(), st));
@@ -1798,7 +1798,7 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
             PH_TRY(go("error compression | gradients above"));
             PH_TRY(tap_rows<T>(gl, tap_send, b.dG_send, send_rows, st));
             // the launch that needs dg_own first sums it on read where it can: the input gradient, or (first layer) the compressor gradient's
-            const SumOnRead sum{(const __bf16 *)b.dG_send, (__bf16 *)b.dg_own, B * gl.k, (int)g.p, (int)gl.k};
+            const SumOnRead sum{b.dG_send, b.dg_own, B * gl.k, (int)g.p, (int)gl.k};
             const Product last[2] = {pr.dw, pr.dc};
             const bool on_read = sizeof(T) == 4 && g.p <= 8 && (l > 0 ? f32_few_groups(&pr.dx, 1, g) : f32_few_groups(last, 2, g)) > 0;
             if (on_read) (l > 0 ? pr.dx : pr.dc).rs = sum;

@@ -132,14 +132,14 @@ inline View view_colstack(const void *top, int64_t ld0, int split, int64_t gtop,
     return v;
 }
 
-// Reduce-scatter as a sum on read (all ranks on the device; Algorithm 1, backward): the tail block of operand A
-// (the k columns behind a.c.split, dg_own in the input-gradient product) is not read from memory but summed
-// from what the other ranks sent, dg_own[g] = sum_{j != g} src[j][slot of g on j], src = dG_send [p, p-1, per_slot],
-// per_slot = rows * k.  The workgroups of tile column 0 also write the sums to out [p, per_slot] for later kernels.
+// Reduce-scatter as a sum on read (all ranks on the device; Algorithm 1, backward): dg_own, the tail block of operand A in the
+// input-gradient product (the k columns behind a.c.split) and all of A in the compressor gradient, is not read from memory but
+// summed from what the other ranks sent, dg_own[g] = sum_{j != g} src[j][slot of g on j], src = dG_send [p, p-1, per_slot] in the
+// storage type, per_slot = rows * k.  The workgroups of tile column 0 also write the sums to out [p, per_slot] for later kernels.
 // src == nullptr: operand A is read as its View says.
 struct SumOnRead {
-    const __bf16 *src;
-    __bf16 *out;
+    const void *src;
+    void *out;
     int64_t per_slot;
     int p, k;
 };
