@@ -744,7 +744,8 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaIn &P, const MfmaOut
     uint32_t out_at = (uint32_t)(m0 + row0) * out_ld, aux_at = (uint32_t)(m0 + row0) * (uint32_t)ep.aux_ld + (uint32_t)n;
     const int64_t aux_first = g * ep.aux_g;
     const float *ct = ctile + row0 * CT_PITCH + col;
-    const bool mse = EPI == EPI_BIAS_ACT && sizeof(TOut) == 2 && ep.mode == EPI_BIAS_ACT && ep.mse_target;      // uniform
+    // (the last layer, which has the error, keeps no derivative)
+    const bool mse = EPI == EPI_BIAS_ACT && ACT != EPI_GELU_DERIV && sizeof(TOut) == 2 && ep.mode == EPI_BIAS_ACT && ep.mse_target;      // uniform
     const bool sums = EPI != EPI_STORE && ep.colsum;                                                            // uniform
     float csum[VEC];                                   // this thread's share of the column sums (ep.colsum)
 #pragma unroll
@@ -921,7 +922,7 @@ __device__ __forceinline__ void epilogue_from_lds(const MfmaIn &P, const MfmaOut
             gstore<__bf16>((__bf16 *)Q.sgd.bias_w + at, (__bf16)nb);
         }
     }
-    if (EPI == EPI_BIAS_ACT && sizeof(TOut) == 2 && ep.mode == EPI_BIAS_ACT && ep.mse_target) {          // uniform
+    if (mse) {
         // the tile's share of sum (y - t)^2: wavefront sums, then one thread adds those of the tile's wavefronts
         // (wave_sums lies behind the fp32 tiles; nothing else uses it)
 #pragma unroll
