@@ -345,8 +345,9 @@ struct MfmaIn {          // what a product's reduction needs ...
     SumOnRead rs;
     int M, N, K;
     int tiles_m, tiles_n;
-    int ksplit;          // > 1: the reduction range is cut into ksplit pieces; their results are added
+    short ksplit;        // > 1: the reduction range is cut into ksplit pieces; their results are added
                          //   by the piece that finishes last (parts)
+    short bursts;        // an operand's loads of a step together in regular shapes, too (see rows_off_lines in phantom_api.hip)
     int k_per_split;     // multiple of KT
     int total_wg;
     uint32_t magic_tiles, magic_band;        // div_by: tiles_m * tiles_n, RASTER rows of them
@@ -1271,9 +1272,9 @@ __device__ __forceinline__ void reduce_in_ring(const MfmaIn &P, int g, int m0, i
     } else {
         // What goes on between two barriers is one piece of code: the last quarter of step t and the other quarters of step t + 1, and behind matrix instructions
         // of the latter (two stages: of the former, as the next barrier waits for them) the loads of the tile of step t + RING, to the slot that step t leaves.
-        // Regular shapes: one by one.  Other shapes work out an address per load and issue an operand's together, half of them behind the barrier and half in
-        // the next step.  A condition on each load, with one loop in the place of three, took 63.3 us where this takes 59.7 (weight gradients 8192 x
-        // 1024 over 4096 rows).
+        // Regular shapes: one by one, unless P.bursts.  Other shapes work out an address per load and issue an operand's together, half of them behind the barrier
+        // and half in the next step.  A condition on each load, with one loop in the place of three, took 63.3 us where this takes 59.7 (weight gradients
+        // 8192 x 1024 over 4096 rows).
         enum { NO_LOADS, BURSTS, ONE_BY_ONE };
         RingCursor<KA, WA> ca;
         RingCursor<KB, WAVES> cb;
@@ -1323,7 +1324,7 @@ __device__ __forceinline__ void reduce_in_ring(const MfmaIn &P, int g, int m0, i
         };
         other_quarters(std::integral_constant<int, NO_LOADS>{}, 0, lds0);
         // (each barrier: the next stage has landed, and everybody has read this one)
-        if (sa.regular && sb.regular) {                    // uniform
+        if (sa.regular && sb.regular && !P.bursts) {       // uniform
             while (t + RING < steps) {
                 ring_run<KA, WA>(ca, sa, a_off0, a_off1, c_of(t + RING));
                 ring_run<KB, WAVES>(cb, sb, b_off0, b_off1, c_of(t + RING));

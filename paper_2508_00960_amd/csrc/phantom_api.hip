@@ -522,6 +522,21 @@ ph_status launch_mfma_vec(const MfmaBatch &batch, int vec, int mode, hipStream_t
     return launch_mfma_inst<KA, KB, 4, TOut, EPI>(batch, mode, st, what);
 }
 
+// Do rows of an operand's head block start off the cache lines of 128 bytes?  (Those that hold less than one: no.)  A step's 128 bytes of a row then lie in two
+// lines, each of which the next step needs again, and loads that are spread over a step find the second one gone more often than loads in a burst.
+// Us a launch, one by one : in bursts: forward 1000 x 3000 x 3000 35.0 : 33.3, 1500 x 2040 x 2040 26.4 : 24.4, 4000 x 2040 x 2040 42.9 : 42.3, 2000 x 3000 x 3000 53.5 :
+// 54.0; the gradients of two layers of 2040 over 4000 rows, two tiles to a workgroup, 81.9 : 77.6, of 2024 over 8000 146.8 : 139.6.
+// Not the input gradient (2000 x 3000 x 3000 41.8 : 45.1), nor other gradients (one layer of 3000 over 4000 rows 103 : 111, two in one-tile workgroups 197.6 :
+// 200, of 2040 over 1500 40.1 : 39.9).  Rows on lines: 4000 x 4096 x 4096 forward 61 : 64.
+bool rows_off_lines(const Product &pr)
+{
+    auto off = [](const View &v) {
+        const int64_t row = std::max(v.r.mult0, v.c.mult0);        // (one of the two is 1)
+        return row % 64 != 0 && row >= 64;
+    };
+    return off(pr.a) || off(pr.b);
+}
+
 MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
 {
     MfmaParams params{};
@@ -534,7 +549,8 @@ MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
     P.tiles_n = (int)((pr.N + MT - 1) / MT);
     const int ksteps = (int)((pr.K + KT - 1) / KT);
     const int steps_per = (ksteps + ksplit - 1) / ksplit;
-    P.ksplit = (ksteps + steps_per - 1) / steps_per;
+    P.ksplit = (short)((ksteps + steps_per - 1) / steps_per);
+    P.bursts = pr.a.c.mult0 == 1 && pr.b.c.mult0 == 1 && rows_off_lines(pr);           // (forward layout)
     P.k_per_split = steps_per * KT;
     P.total_wg = P.tiles_m * P.tiles_n * groups * P.ksplit;
     P.magic_tiles = div_magic(P.tiles_m * P.tiles_n); P.magic_band = div_magic(mfma_raster(dual) * P.tiles_n);
@@ -756,6 +772,7 @@ ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::ve
     if (solo) pieces = 1;                              // (whole, with sums in levels: gemm_mfma_uniform_kernel)
     u.dw_dual = tiles > 256 && !solo;
     u.dw = mfma_params(dw[0], 1, 1, u.dw_dual);
+    u.dw.in.bursts = u.dw_dual && rows_off_lines(dw[0]);
     u.dw_wg = (u.dw.in.total_wg + 7) & ~7;
     if (two) {
         u.dc = mfma_params(dc[0], 1, pieces, false);

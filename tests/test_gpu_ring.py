@@ -82,8 +82,10 @@ def test_layer_one_rank(n, p, k, B, act):
     (256, 4, 8, 1100, 2, "relu", 2, "train"),
     (128, 1, 0, 2050, 2, "gelu", 0, "train"),
     (256, 4, 16, 769, 2, "relu", -1, "no_update"),
+    (512, 1, 0, 100, 2, "gelu", 0, "no_update"),             # (forward alone, and the first layer here: few rows, csrc/few_rows.h)
     (512, 1, 0, 100, 2, "gelu", 0, "forward"),
     (2048, 4, 8, 72, 2, "relu", -1, "train"),                # (the compressions of all ranks)
+    (1792, 2, 64, 70, 2, "relu", 1, "no_update"),            # (... 960)
     (1792, 2, 64, 70, 2, "relu", 1, "forward"),
     (8192, 8, 64, 225, 2, "gelu", 1, "forward"),             # a forward reduction of 1472 in 256 tiles of 32 x 32
     (8192, 8, 64, 257, 2, "relu", 1, "forward"),             # ... of 64 x 64, two teams
@@ -117,3 +119,29 @@ def test_partial_sums_of_few_tiles(n, B, bound):
     err = float((dLw.double() - want).norm() / want.norm())
     print(f"dLw {err:.2e}", flush=True)
     assert err <= bound, f"{err:.2e} > {bound:.1e}"
+
+
+@pytest.mark.parametrize("s,B,L", [
+    (1000, 2001, 2),      # 128 tiles a layer; the last stage is five eighths full
+    (2040, 3100, 2),      # 512 tiles, two to a workgroup, the gradients of both layers in one round of workgroups
+    (1032, 8200, 3),      # rows of 16 lines and an eighth; the last stage one eighth full
+])
+def test_rows_off_cache_lines(s, B, L):
+    """Dense layers whose rows start off the cache lines load a stage in bursts (rows_off_lines in phantom_api.hip).  Each product against 64 bits, from the step's
+    own operands: a bf16 output within one rounding (2^-8 of the value and of the sum's rms for what cancels), gradients in float within 1e-6 (2-norm)."""
+    print(f"case rows off lines s={s} B={B} L={L}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    rand = lambda *shape, by=1.0: (torch.randn(shape, device="cuda", generator=gen) * by).bfloat16()
+    X, T = rand(B, s), rand(B, s)
+    Lw, bias = [rand(s, s, by=s ** -0.5) for _ in range(L)], [rand(s, by=0.1) for _ in range(L)]
+    dLw, dbias = [torch.full((s, s), float("nan"), device="cuda") for _ in range(L)], [torch.empty(s, device="cuda") for _ in range(L)]
+    Y, delta = [torch.empty_like(X) for _ in range(L)], [torch.empty_like(X) for _ in range(L)]
+    prob = ph.make_problem(s, 1, 0, B, L, "relu", "bf16", 0)
+    ph.ffn_step(prob, X, T, Lw, None, None, bias, dLw=dLw, dbias=dbias, loss=torch.zeros(4, device="cuda"), mode="no_update",
+                workspace=workspace(ph.workspace_bytes(prob)), taps={"Y": Y, "delta": delta})
+    for l in range(L):
+        x = (X if l == 0 else Y[l - 1]).double()
+        want = (x @ Lw[l].double().t().contiguous() + bias[l].double()).clamp(min=0)
+        assert ((Y[l].double() - want).abs() <= 2 ** -8 * (want.abs() + 1e-3)).all()
+        want = delta[l].double().t().contiguous() @ x
+        assert float((dLw[l].double() - want).norm() / want.norm()) <= 1e-6
