@@ -1324,7 +1324,8 @@ __device__ __forceinline__ void reduce_in_ring(const MfmaIn &P, int g, int m0, i
         };
         other_quarters(std::integral_constant<int, NO_LOADS>{}, 0, lds0);
         // (each barrier: the next stage has landed, and everybody has read this one)
-        if (sa.regular && sb.regular && !P.bursts) {       // uniform
+        constexpr bool BURSTS_TOO = KA == KB && (KA == LD_KC || DUAL);         // (what the host sets it for)
+        if (sa.regular && sb.regular && !(BURSTS_TOO && P.bursts)) {           // uniform
             while (t + RING < steps) {
                 ring_run<KA, WA>(ca, sa, a_off0, a_off1, c_of(t + RING));
                 ring_run<KB, WAVES>(cb, sb, b_off0, b_off1, c_of(t + RING));
