@@ -43,7 +43,8 @@ struct SgdInPlace {
     float *master0, *master1;    // bf16 storage: fp32 master copies: master -= lr * gradient.  NULL with fp32 storage.
     void *w0, *w1;               // bf16: compute copies, w = bf16(master).  fp32: w -= lr * gradient
     float lr;
-    int keep_grad;               // also store the gradient (the caller wants to see it)
+    short keep_grad;             // also store the gradient (the caller wants to see it)
+    short past_caches;           // gemm_mfma kernels: read the masters past the caches (step_fits_last_cache)
     float *bias_master;          // weight gradients only: the layer's bias [M], likewise
     void *bias_w;                //   NULL: none
     const float *bias_grad;      // gemm_mfma kernels: its finished gradient (Eq. (bpb): column sums of delta, left by earlier

@@ -630,9 +630,8 @@ struct EpilogueReads {
     static constexpr int PASSES = MT * PER_ROW / THREADS, ROWS_PER_PASS = THREADS / PER_ROW;
     static_assert(THREADS % PER_ROW == 0, "a thread keeps its columns from pass to pass");
     static constexpr bool MSE = EPI == EPI_BIAS_ACT && sizeof(TOut) == 2;
-    // The master weights of an update: streaming reads, as nothing else reads them for the rest of the step.  Kept in L2, they push the operand tiles that
-    // other workgroups still share out of it (us a pass, kept : streaming: dense 4 x 4096 trained at batch 1024 541 : 503, 8 layers of 1024 + 960 at 4096
-    // 587 : 577, 8 ranks of 512 / 1024 337 : 326; a launch of 4096 x 4096 over 2048 rows alone, whose masters stay in the last-level cache, 93 : 97).
+    // The master weights of an update, which nothing else reads for the rest of the step: past the caches unless the whole step fits the last-level one
+    // (step_fits_last_cache).  Kept, they push the operand tiles that other workgroups still share out of L2.
     static constexpr bool MASTERS = EPI == EPI_STORE && sizeof(TOut) == 4;
     // passes that are unrolled together and whose reads are in flight together, a group ahead of their use
     static constexpr int GROUP = EPI == EPI_DACT ? PASSES : MASTERS && MODE == TILE_DUAL ? 8 : MASTERS || MSE ? 4 : 2;
@@ -662,8 +661,16 @@ struct EpilogueReads {
                 const Loc lc = locate(Q.o.c, n, Q.o.skip0 + g * Q.o.skip_g);
                 const float *base = lc.region > 0 ? Q.sgd.master1 + g * Q.o.g1 + lc.off1 : Q.sgd.master0 + g * Q.o.g0 + lc.off0;
                 const uint32_t ld = (uint32_t)(lc.region > 0 ? Q.o.r.mult1 : Q.o.r.mult0);
+                if (Q.sgd.past_caches) {                       // uniform
+                    // (the statements keep the compiler from making one of the two loops, which would be without the hint)
+                    asm volatile("; masters past the caches");
 #pragma unroll
-                for (int h = 0; h < GROUP; ++h) masters[h] = gload_nt<FlV>(base + (uint32_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
+                    for (int h = 0; h < GROUP; ++h) masters[h] = gload_nt<FlV>(base + (uint32_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
+                    asm volatile("; masters requested");
+                } else {
+#pragma unroll
+                    for (int h = 0; h < GROUP; ++h) masters[h] = gload<FlV>(base + (uint32_t)min(row + h * ROWS_PER_PASS, P.M - 1) * ld);
+                }
             }
         }
     }

@@ -1707,11 +1707,12 @@ ph_status check_ws(void *ws, size_t have, size_t want)
 
 // The update of layer l in the epilogues that finish its gradients (Section VI: plain SGD), `weights` (L, D and the bias) or
 // C; keep: the gradients are stored too.
-SgdInPlace sgd_of(const ph_step_args &a, int l, int64_t q, bool weights, const float *bias_grad)
+SgdInPlace sgd_of(const ph_step_args &a, int l, int64_t q, bool weights, const float *bias_grad, bool past_caches = false)
 {
     auto at = [l](auto *const *arr) { return arr ? arr[l] : nullptr; };
     SgdInPlace s{};
     s.lr = a.lr;
+    s.past_caches = past_caches;
     if (weights) {
         s.master0 = at(a.Lw_master); s.w0 = a.Lw[l];
         s.master1 = q ? at(a.Dw_master) : nullptr; s.w1 = q ? a.Dw[l] : nullptr;
@@ -1845,6 +1846,27 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
     return go("weight + compressor gradients");
 }
 
+// Do a bf16 training step's tensors (weights, masters, activations, what the peers send and get) fit the last-level cache of 256 MB?  Repeated steps then
+// find their masters there, and streaming reads would give that up.
+// Trained, us a step, masters past the caches : kept.  Smaller steps: dense 4096 at batch 1024 (128 MB) 103.8 : 95.8, two (240 MB) 228.9 : 220.4, 3 of 3072 (210 MB)
+// 248.0 : 242.5, 6 of 1024 + 448 at 4096 (190 MB) 376.2 : 372.0, 8 ranks of 1024 + 224, two layers at 1024 (220 MB), 203.9 : 197.0; larger: 4 of 3072 at
+// 1024 (276 MB) 337.7 : 351.0, 8 ranks of 512 / 1024 (262 MB) 329.4 : 337.0, 4 of 4096 485 : 530, 8 of 1024 + 960 with GELU at 4096 (430 MB) 594 : 598;
+// 6 of 2048 at 2048 (256 MB) 387.3 : 389.2.
+bool step_fits_last_cache(const std::vector<Geo> &geos)
+{
+    int64_t bytes = 0, send = 0;
+    for (const Geo &g : geos) {
+        const int64_t act = g.B * g.so, peers = g.q * g.B * g.k, e = (int64_t)g.esz;
+        bytes += g.groups * ((g.so * g.Kc + g.k * g.si) * (e + 4) + 2 * act * e + g.B * g.k * e);
+        if (g.act == PH_ACT_GELU && &g != &geos.back()) bytes += g.groups * act * 4;
+        if (!g.all) bytes += (peers + g.B * g.k) * e;
+        send = std::max(send, g.groups * peers * e);
+    }
+    const Geo &first = geos.front(), &last = geos.back();
+    bytes += send + first.groups * first.B * (first.si + last.so) * (int64_t)first.esz;
+    return bytes <= (int64_t)256 << 20;
+}
+
 // One bf16 step on the 128 x 128 kernels of gemm_mfma.h.
 ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const StepWs &w, hipStream_t st)
 {
@@ -1864,7 +1886,7 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
     // Bias gradients (Eq. (bpb)) are column sums of delta: the product that writes a layer's delta (the input gradient
     // of the layer above; for the last layer its own update, see below) adds them up on its way out, so every
     // layer's bias gradient has a buffer of its own that is zeroed once for the whole step.
-    const bool train = a.mode != PH_STEP_FORWARD, update = a.mode == PH_STEP_TRAIN;
+    const bool train = a.mode != PH_STEP_FORWARD, update = a.mode == PH_STEP_TRAIN, past_caches = update && !step_fits_last_cache(geos);
     auto dbias_of = [&](int l) { return a.dbias ? a.dbias[l] : w.dbias + w.dbias_at[(size_t)l]; };
     // What the step adds into is cleared by its first forward launch that can do it on the way, else by one of its own (the
     // words for cut reductions lie right behind the workspace's block and are cleared with it).
@@ -1913,8 +1935,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
             b.dCw = q ? (a.dCw ? a.dCw[l] : w.dCw[0]) : nullptr;
             b.dDw = q ? (a.dDw ? a.dDw[l] : w.dDw[0]) : nullptr;
             if (update) {
-                b.sgd_w = sgd_of(a, l, q, true, dbias_of(l));
-                b.sgd_c = sgd_of(a, l, q, false, nullptr);
+                b.sgd_w = sgd_of(a, l, q, true, dbias_of(l), past_caches);
+                b.sgd_c = sgd_of(a, l, q, false, nullptr, past_caches);
             }
             const BwdProducts all = make_bwd_products(geos[(size_t)l], b, w.delta_of[(size_t)l]);
             all_dw.push_back(all.dw);
@@ -1982,8 +2004,8 @@ ph_status step_impl(const std::vector<Geo> &geos, const ph_step_args &a, const S
         b.dG_send = w.dG_send;
         // SGD on this layer in the epilogues of its gradients: every launch that reads its weights is out by then
         if (update && !deferred) {
-            b.sgd_w = sgd_of(a, l, q, true, b.dbias);
-            b.sgd_c = sgd_of(a, l, q, false, nullptr);
+            b.sgd_w = sgd_of(a, l, q, true, b.dbias, past_caches);
+            b.sgd_c = sgd_of(a, l, q, false, nullptr, past_caches);
         }
         const Geo &gl = geos[(size_t)l];
         if (a.taps) {
