@@ -18,6 +18,7 @@
 #pragma once
 #include "common.h"
 #include "epilogue.h"
+#include "launch_rules.h"
 #include "mfma_ring.h"
 
 namespace phantom {
@@ -25,7 +26,6 @@ namespace phantom {
 constexpr int FEW_WAVES = 8, FEW_TILE = 16;
 constexpr int few_ahead(int rows) { return rows == 1 ? 8 : rows == 2 ? 6 : 3; }        // chunks of a wavefront in flight
 constexpr int few_chunk_bytes(int rows) { return (rows + 1) * 1024; }
-constexpr int FEW_SHORT = 960;                         // TEAMS = 2: reductions below it
 // chunks: of the launch's longest reduction (TEAMS = 2: behind them, the teams' sums)
 constexpr int few_lds_bytes(int rows, int teams, int chunks)
 {

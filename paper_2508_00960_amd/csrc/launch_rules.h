@@ -20,21 +20,33 @@ inline int f32_few_groups_for(int64_t workgroups, int64_t longest)
     return workgroups <= (groups <= 2 ? 512 : 256) ? groups : 0;
 }
 
+constexpr int FEW_SHORT = 960;                         // few_rows.h: reductions below it in two teams, ...
+inline bool few_rows_in_eight_teams(int64_t Kc) { return Kc >= FEW_SHORT || Kc == 512; }      // ... others, and this one, in eight (as the tiles of gemm_flex.h)
+
 // Does a layer's forward pass (one rank, bf16, 8 divides the widths and phantom widths) run on the kernel for few rows (few_rows.h), and how many blocks
 // of 16 rows does a workgroup take?  0: no.  Kc: the update's reduction; k = 0: dense.
 // The fewest with which the launch is one round of workgroups, while a workgroup's operands (16 columns and those rows by the reduction) are
-// not so long that gemm_flex.h, whose larger tiles read less, is the faster one.  Measured, us, 6 layers forward (dense: 4), gemm_flex.h : 1 block : 2 : 4:
-// 1024 + 448 at batch 48 / 96 / 128 46.4 : 36.3 : 39.4 : 43.6, 48.5 : 64.6 : 41.6 : 45.8, 49.3 : 85 : 63.5 : 48.1; 1024 + 1792 at 32 / 96 / 128 67.1 : 54.4 : 61.3 : 64.8,
-// 67.6 : 98.6 : 59.8 : 68.7, 67.9 : 116 : 81.4 : 72.0; 512 + 960 at 96 / 192 47.2 : 36.2 : 39.0 : 43.3, 48.7 : 67 : 42.8 : 47.9; 512 + 3840 at 64 / 128 75.8 : 70.5 : 81.9 : 103,
-// 76.2 : 83.6 : 81.6 : 102; 256 + 48 at 384 / 768 36.3 : 37.9 : 26.6 : 27.4, 36.3 : 63.5 : 41.1 : 31.0; 1280 + 280 at 40 / 96 59.9 : 56.6 : 43.6 : 47.9, 62.3 : 83.5 : 64.1 : 50.4;
-// 2048 + 224 at 32 / 48 59.8 : 80 : 54.5 : 56.7, 59.2 : 87 : 83 : 60.9; 2048 + 1024 at 32 63.1 : 91 : 64.3 : 67.9; dense 512 at 128 21.9 : 16.2 : 17.1 : 19.9, 1024 at 64 / 128
-// 27.5 : 20.7 : 22.3 : 25.2, 27.8 : 35 : 23.6 : 25.8, 2048 at 32 / 64 / 128 34.8 : 31.4 : 33.1 : 34.7, 35.3 : 55 : 35.3 : 39.2, 36.0 : 103 : 62 : 41.8, 2560 at 16 34.0 : 36.5 : 37.1 : 39.3,
-// 4096 at 16 44.2 : 49.0 : 50.9 : 55.9.
+// not so long that gemm_flex.h, whose larger tiles read less, is the faster one.  With eight teams a workgroup has a compute unit for itself, and one round
+// means 32 on every XCD, each of which takes every eighth column of either product: 1280 + 280 at batch 40 / 96 with 33 on some of them 55.8, 64.2 us; 43.2,
+// 48.2 with one step more (gemm_flex.h 60.0, 62.6).
+// Measured, us, 6 layers forward (dense: 4), gemm_flex.h : 1 block : 2 : 4:
+// 1024 + 448 at batch 48 / 96 / 128 46.4 : 36.7 : 39.8 : 43.3, 48.6 : 64.6 : 42.1 : 45.2, 49.2 : 84 : 63.7 : 46.7; 1024 + 1792 at 32 / 96 / 128 66.7 : 52.5 : 58.9 : 61.5,
+// 67.9 : 95.9 : 59.9 : 64.8, 68.0 : 114 : 82.3 : 67.2; 512 + 960 at 96 / 192 48.6 : 36.8 : 39.6 : 43.5, 50.0 : 67.3 : 44.0 : 47.1; 512 + 3840 at 64 / 128 76.1 : 68.8 : 77.5 : 94.1,
+// 76.3 : 79.8 : 78.6 : 93.1; 256 + 56 at 48 / 384 / 768 39.1 : 25.2 : 27.0 : 29.4, 40.7 : 27.9 : 27.4 : 30.2, 40.6 : 33.4 : 30.4 : 31.0; 512 + 336 at 96 51.6 : 31.9 : 33.4 : 36.6;
+// 2048 + 224 at 32 / 48 60.0 : 81.0 : 55.7 : 55.8, 59.4 : 88.9 : 85.0 : 58.9; 2048 + 1024 at 32 63.5 : 94.6 : 69.7 : 71.4; dense 512 at 128 / 512 23.5 : 17.9 : 19.0 : 21.8, 24.0 : 44.9 :
+// 29.3 : 23.3, 1024 at 64 / 128 / 256 26.5 : 22.3 : 23.5 : 26.3, 26.9 : 35.0 : 24.7 : 26.5, 29.0 : 64.2 : 40.7 : 28.1, 2048 at 32 35.0 : 32.7 : 34.0 : 34.8, 2560 at 16 33.7 : 36.8 : 37.2 : 39.3.
+// Dense reductions of three and four times 512 load the eight teams of gemm_flex.h evenly, and with two blocks or more it is the faster one: 1472 / 1536 / 1600 at 64
+// 31.7 : 28.7 (2 blocks), 28.2 : 28.8, 37.6 : 30.7; 1984 / 2048 39.6 : 34.7, 35.1 : 37.8.
 inline int few_rows_blocks_for(int64_t B, int64_t so, int64_t k, int64_t Kc)
 {
-    const int64_t rows = (B + 15) / 16, columns = (so + 15) / 16 + (k + 15) / 16;
-    for (int blocks = 1; blocks <= 4; blocks *= 2)
-        if ((rows + blocks - 1) / blocks * columns <= 256) return (blocks + 1) * Kc <= (k > 0 ? 9000 : 6144) && (k > 0 || Kc <= 2048) ? blocks : 0;
+    const bool alone = few_rows_in_eight_teams(Kc);
+    auto workgroups = [alone](int64_t columns) { const int64_t n = (columns + 15) / 16; return alone ? (n + 7) / 8 * 8 : n; };
+    const int64_t rows = (B + 15) / 16, columns = workgroups(so) + workgroups(k);
+    for (int blocks = 1; blocks <= 4; blocks *= 2) {
+        if ((rows + blocks - 1) / blocks * columns > 256) continue;
+        if (k > 0) return (blocks + 1) * Kc <= 9000 ? blocks : 0;
+        return (blocks + 1) * Kc <= 6144 && Kc <= 2048 && !(blocks > 1 && Kc > 1024 && Kc % 512 == 0) ? blocks : 0;
+    }
     return 0;
 }
 

@@ -63,3 +63,16 @@ def test_forward_bits_f32_lines(rules, n, p, k, B, L, act, rank):
     update, compress = (B, s, s + (p - 1) * k), (B, k, s)
     assert f32_groups(rules, held, update) > 0
     assert rank < 0 or f32_groups(rules, held, update, compress) == 0
+
+
+@pytest.mark.parametrize("B,so,k,Kc,blocks", [
+    (40, 1280, 40, 1560, 2),         # 33 workgroups of one block on some XCDs
+    (96, 1280, 40, 1560, 4),         # ... of two
+    (64, 1472, 0, 1472, 2),
+    (64, 1536, 0, 1536, 0),          # dense: gemm_flex.h's teams are evenly loaded, and it is the faster one
+    (64, 2048, 0, 2048, 0),
+    (32, 2048, 0, 2048, 1),
+    (128, 1024, 0, 1024, 2),
+])
+def test_few_rows_lines(rules, B, so, k, Kc, blocks):
+    assert rules.few_rows(B, so, k, Kc) == blocks
