@@ -530,6 +530,8 @@ ph_status launch_mfma_vec(const MfmaBatch &batch, int vec, int mode, hipStream_t
 // 200, of 2040 over 1500 40.1 : 39.9).  Rows on lines: 4000 x 4096 x 4096 forward 61 : 64.
 bool rows_off_lines(const Product &pr)
 {
+    static const char *force = tuning_env("PHANTOM_BURSTS");           // =0 / 1 (for measurements)
+    if (force) return force[0] == '1';
     auto off = [](const View &v) {
         const int64_t row = std::max(v.r.mult0, v.c.mult0);        // (one of the two is 1)
         return row % 64 != 0 && row >= 64;
@@ -1854,6 +1856,8 @@ ph_status flex_step(const std::vector<Geo> &geos, const ph_step_args &a, const S
 // 6 of 2048 at 2048 (256 MB) 387.3 : 389.2.
 bool step_fits_last_cache(const std::vector<Geo> &geos)
 {
+    static const char *force = tuning_env("PHANTOM_KEEP_MASTERS");     // =0 / 1 (for measurements)
+    if (force) return force[0] == '1';
     int64_t bytes = 0, send = 0;
     for (const Geo &g : geos) {
         const int64_t act = g.B * g.so, peers = g.q * g.B * g.k, e = (int64_t)g.esz;
