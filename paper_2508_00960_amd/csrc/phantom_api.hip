@@ -440,6 +440,11 @@ inline unsigned blocks_for(int64_t count, int per_block = 256, int cap = 8192)
 //   512 / 768 63 : 58, 65.8 : 69.8, 64 of 128 + 8 74.8 : 70, 77 : 87.5.  With more than 32 phantom neurons the compression has two column blocks
 //   there, or no kernel of its own: 8 of 256 + 40 at 640 72.5 : 70, 4 of 1024 + 64 at 768 103 : 88, 8 of 512 + 128 107 : 97, 32 of 128 + 64 at 640
 //   117 : 115, but 64 of 128 + 48 at 640 164 : 179.
+// All of these were measured before the 128 x 128 kernels' loop was rewritten.  With the present one (128 x 128 : these) they are right where tiles are few
+// (trained, 3 layers of 1024 at 64 / 96 tiles 109 : 93, 116 : 112; dense 4096 at 64 376 : 348; a layer's calls of 1024 at 128 53 : 44; 8 ranks of 256 + 32 at 256 / 512 / 768
+// small tiles 142 : 121, 169 : 164, 191 : 186), and lie too far out near the lines: 3 layers of 1024 trained at 128 123 : 130, of 2048 174 : 192, dense 4096 403 : 458; 4 of
+// 1024 forward at 128 53 : 57; 32 ranks of 128 + 16 trained at 768 218 : 233, + 32 at 512 175 : 194, 64 of 128 + 16 at 512 196 : 214; all ranks forward at 768 8 of 256 + 32 58 : 64,
+// of 512 + 32 64 : 70, 4 of 1024 + 64 85 : 92, 32 of 128 + 64 at 640 97 : 118; their layer forward calls 15 : 17.5.
 // 4-element vectors, which take the renumbering kernel, keep the lines that were measured for it: 96 and 128 tiles, 192 for a layer's call.
 bool use_flex(const std::vector<Geo> &geos, bool backward, bool single_call)
 {
@@ -568,6 +573,9 @@ MfmaParams mfma_params(const Product &pr, int groups, int ksplit, bool dual)
 //   589 : 565 : 564 and at 1536 769 : 767 : 755; longer: dense at 2048 863 : 864 : 863, at 4096 1539 : 1568 : 1534;
 //   gradients alone: 64 ranks of 256 at 512 449 : 436 : 437, dense at 1024 528 : 495 : 495.  Not caught by it: 8 ranks of 1024 with GELU, gradients
 //   at 2048, 871 : 850 : 872.
+//   Those are from before the loop was rewritten.  With the present one, no launch in SOLO : every launch that can be : this rule: 32 ranks of 1024 trained at 256
+//   368 : 350 : 347, 64 of 128 at 1024 721 : 655 : 656, 64 of 256 at 512 482 : 486 : 486 and its gradients 436 : 436 : 436, at 2048 with GELU 1542 : 1561 : 1517,
+//   8 ranks of 1024 with GELU 803 : 808 : 803, 8 of unequal widths 333 : 330 : 330.
 // The forward layout lost at 760 already (488 : 498, operands through registers).
 template <typename TOut>
 bool solo_tiles(const GemmPlan &plan, const Product *prods, int count)
@@ -755,10 +763,11 @@ ph_status launch_uniform_kernel(const UniformGradients &u, const Product &dw, co
 // The same launch for layers of one shape, without a table (dw, dc: by layer; without compressors the dc have no rows).
 // More tiles than compute units: one tile to a workgroup, two workgroups to a compute unit (TILE_SOLO), where that takes no more rounds of
 // the chip than two tiles to a workgroup, whose compressor gradients are cut and start the launch: there the epilogues of the first
-// round run beside the second's loops.  Us a step, two tiles : SOLO: 4 layers of 4096 trained at batch 1024 554 : 547, 3 of 3072 with GELU at 1500 402 : 390; 3 of
-// 2048 + 192 at 2048 267 : 262; 8 of 512 + 960 at 4096 357 : 347; 6 of 1024 + 448 at 2100 282 : 272.  A round more: 8 of 1024 + 960 at 4096 (1088 tiles) 673 : 702, at
-// 2560 457 : 474.  Not with whole rounds of two tiles a workgroup and long reductions, where loops are most of the time: 2 of 4096 at 3072 / 3500 / 4096
-// 604 : 601, 651 : 657, 725 : 732, 4 of them at 4096 1601 : 1624, 2 of 2048 196.3 : 198.8 (4 of 2048 and 8 of 1024 alike either way).
+// round run beside the second's loops.  Us a step, two tiles : SOLO: 3 layers of 3072 with GELU trained at batch 1500 367 : 363, 8 of 512 + 960 at 4096 329 : 321 (their
+// gradients 325 : 319), 4 of 1024 + 224 at 4096 233 : 228.  A round more: 8 of 1024 + 960 at 4096 (1088 tiles) 622 : 651, at 2560 426 : 439.  Not with whole rounds of two tiles a
+// workgroup and long reductions, where loops are most of the time: 2 of 4096 at 3500 / 4096 565 : 587, 614 : 646, 4 of them at 4096 1396 : 1451, 2 and 4 of 2048 183 : 190, 389 : 398.
+// The loop with single loads moved the line: up to 3072 rows and with rounds that are not whole, two tiles are now the faster one for dense 4096 (4 layers at 1024 / 2048 482 : 486,
+// 747 : 764, two at 3072 525 : 541) and 3 of 2048 + 192 at 2048 / 4096 (242 : 247, 378 : 387), as fast for 4 of 2048 and 6 of 1024 + 448.
 ph_status launch_uniform_gradients(const std::vector<Product> &dw, const std::vector<Product> &dc, int pieces, float *parts,
                                    unsigned *arrived, const LossTail &tail, bool halves, hipStream_t st, const char *what)
 {
@@ -2086,6 +2095,7 @@ std::vector<Geo> padded_geos(const ph_problem *prob, const std::vector<Geo> &geo
 // counts; training also moves D's masters, by the shard.  Forward, 2 and 4 layers at batch 64: 256 + 1054 21.3 : 21.6, 42.6 : 40.2, 128 + 1550 27.6 : 25.0, 55.3 : 46.8; 3 of 512 +
 // 620 28.2 : 31.1.  Trained: 128 + 1054 46.8 : 43.9, 83.7 : 75.5, 256 + 1550 52.2 : 52.7, 95.1 : 92.6, 256 + 2646 67.2 : 61.4, 129.8 : 104.4, 512 + 1638 (2) 56.2 : 63.4, 512 + 3276 (2)
 // 76.3 : 78.2; 3 of 512 + 620 at 128 64.0 : 71.0 (at 192, past that line, 86.0 : 71.6), 4 of 1024 + 378 at 64 100.9 : 114.7 (at 96 126.0 : 112.9).
+// (The forward ones are older than the kernel for few rows, which copies may run on and the caller's tensors may not: 2 of 256 + 1054 21.2 : 18.1, 3 of 512 + 620 28.2 : 24.8.)
 bool padding_pays(const std::vector<Geo> &padded, bool train)
 {
     if (padded.empty()) return false;
