@@ -23,6 +23,27 @@ def test_parity(n, p, k, B, L, rank):
     check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act="relu", dtype="f32", rank=rank), seed=12, lr=0.02, mode="train")
 
 
+@pytest.mark.parametrize("n,p,k,B,L,act,rank,mode", [
+    (256, 4, 8, 32, 2, "relu", -1, "train"),
+    (288, 4, 12, 127, 3, "gelu", -1, "train"),       # shard 72 + 36: tiles of eight and four columns left over; 127 terms in the weight gradients
+    (384, 4, 8, 128, 2, "relu", 1, "train"),         # one rank, 120 and 128 terms: all teams
+    (20, 5, 4, 2, 3, "gelu", -1, "no_update"),       # shard 4 = k: one team with terms, one vector to a piece
+    (64, 1, 0, 16, 2, "relu", 0, "train"),           # dense
+    (512, 8, 4, 36, 2, "identity", -1, "forward"),
+    (512, 4, 16, 130, 2, "gelu", -1, "train"),       # two groups to a team: 176 and 130 terms
+    (1008, 4, 4, 256, 2, "relu", -1, "train"),       # ... 264: four, the last of them in part; 256: two
+    (1024, 4, 64, 500, 2, "gelu", -1, "train"),      # 448, 320 and 500 terms in 512 and more tiles: past the line
+    (512, 1, 0, 512, 2, "relu", 0, "train"),         # dense, 512 terms: all groups of all teams
+    (768, 3, 120, 90, 3, "identity", 2, "train"),    # one rank
+    (1024, 8, 20, 300, 2, "relu", -1, "no_update"),  # reduce-scatter on read with segments of 20
+    (576, 9, 8, 100, 2, "gelu", -1, "train"),        # nine ranks: a launch for the sums
+])
+def test_few_tiles_and_short_reductions(n, p, k, B, L, act, rank, mode):
+    """32 x 32 tiles, one, two or four groups of 16 terms to each of eight teams."""
+    print(f"case f32 few n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode}", flush=True)
+    check_stages(pin.Problem(n=n, p=p, k=k, batch=B, layers=L, act=act, dtype="f32", rank=rank), seed=12, lr=0.02, mode=mode)
+
+
 # ..., (groups of 16 terms to a team in the update, the input gradient, the first layer's gradients; 0: another kernel; None: it shares its launch)
 FEW = [
     (256, 4, 8, 32, 2, "relu", -1, "train", (1, 1, 1)),
@@ -47,7 +68,7 @@ FEW = [
 
 
 @pytest.mark.parametrize("n,p,k,B,L,act,rank,mode,groups", FEW)
-def test_few_tiles_and_short_reductions(n, p, k, B, L, act, rank, mode, groups):
+def test_groups_of_terms_and_sums_on_read(n, p, k, B, L, act, rank, mode, groups):
     """32 x 32 tiles, one, two or four groups of 16 terms to each of eight teams (that the rule says so: test_launch_rules_host.py)."""
     print(f"case f32 few n={n} p={p} k={k} B={B} L={L} {act} rank={rank} {mode}", flush=True)
     ph.profile_begin()

@@ -14,7 +14,27 @@ from test_gpu_parity import run_layer_one_rank
 pytestmark = pytest.mark.gpu
 
 
-# ..., blocks of 16 rows to a workgroup
+@pytest.mark.parametrize("n,p,k,B,act", [
+    (8, 1, 0, 1, "identity"),        # a quarter of a chunk
+    (16, 2, 8, 1, "gelu"),           # one row, shard 8, half a chunk
+    (80, 2, 24, 15, "relu"),         # shard 40: head block and segment straddle chunks
+    (192, 8, 8, 17, "gelu"),         # shard 24, segments of 8
+    (2048, 8, 16, 16, "relu"),       # 1 block of rows
+    (8192, 8, 64, 48, "gelu"),
+    (8192, 8, 64, 49, "relu"),       # 2 blocks
+    (8192, 8, 64, 113, "gelu"),      # 4 blocks
+    (6080, 8, 24, 81, "relu"),       # shard 760: the last tile of columns is half empty
+    (8192, 16, 256, 33, "identity"), # 17 chunks a wavefront: more than are in flight, 1 block
+    (8192, 16, 160, 130, "relu"),    # ... 2 blocks
+    (5120, 4, 200, 97, "gelu"),      # past the line: gemm_flex.h
+    (1024, 4, 16, 768, "relu"),      # many blocks of rows
+])
+def test_layer(n, p, k, B, act):
+    print(f"case few rows layer n={n} p={p} k={k} B={B} {act}", flush=True)
+    run_layer_one_rank(pin.Problem(n=n, p=p, k=k, batch=B, layers=1, act=act, dtype="bf16", rank=p - 1), seed=3)
+
+
+# The cases of test_layer, and the blocks of 16 rows that a workgroup takes (test_launch_rules_host.py)
 LAYERS = [
     (8, 1, 0, 1, "identity", 1),        # a quarter of a chunk
     (16, 2, 8, 1, "gelu", 1),           # one row, shard 8, half a chunk
@@ -27,19 +47,19 @@ LAYERS = [
     (6080, 8, 24, 81, "relu", 2),       # shard 760: the last tile of columns is half empty
     (8192, 16, 256, 33, "identity", 1), # 16 to 18 chunks a wavefront, 8 of them in flight
     (8192, 16, 160, 130, "relu", 2),    # ... 10 to 12, 6 of them
-    (5120, 4, 168, 97, "gelu", 4),      # ... 6 to 8, 3 of them
     (5120, 4, 200, 97, "gelu", 0),      # past the line: gemm_flex.h
+    (1024, 4, 16, 768, "relu", 4),      # many blocks of rows
+]
+MORE_LAYERS = [
+    (5120, 4, 168, 97, "gelu", 4),      # 6 to 8 chunks a wavefront, 3 of them in flight
     (1600, 2, 144, 60, "relu", 1),      # two teams: 944 indices, the longest; half a chunk left over
     (1280, 2, 312, 200, "gelu", 4),     # ... 952, 4 blocks: all of the LDS
-    (1024, 4, 16, 768, "relu", 4),      # many blocks of rows
 ]
 
 
-@pytest.mark.parametrize("n,p,k,B,act,blocks", LAYERS)
-def test_layer(n, p, k, B, act, blocks):
-    """(That the rule takes so many blocks: test_launch_rules_host.py.)"""
-    print(f"case few rows layer n={n} p={p} k={k} B={B} {act}", flush=True)
-    run_layer_one_rank(pin.Problem(n=n, p=p, k=k, batch=B, layers=1, act=act, dtype="bf16", rank=p - 1), seed=3)
+@pytest.mark.parametrize("n,p,k,B,act,blocks", MORE_LAYERS)
+def test_layer_with_all_blocks(n, p, k, B, act, blocks):
+    test_layer(n, p, k, B, act)
 
 
 @pytest.mark.parametrize("n,p,k,B,L,act,mode", [

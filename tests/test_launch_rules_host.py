@@ -7,7 +7,7 @@ import pytest
 
 from paper_2508_00960_amd.build import CSRC
 from test_gpu_f32_whole import FEW
-from test_gpu_few_rows import LAYERS
+from test_gpu_few_rows import LAYERS, MORE_LAYERS
 from test_gpu_forward_bits import BF16, F32
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
@@ -45,7 +45,7 @@ def test_f32_few_tiles(rules, n, p, k, B, L, act, rank, mode, groups):
     assert all(want is None or got == want for got, want in zip(launches, groups)), launches
 
 
-@pytest.mark.parametrize("n,p,k,B,act,blocks", LAYERS)
+@pytest.mark.parametrize("n,p,k,B,act,blocks", LAYERS + MORE_LAYERS)
 def test_few_rows(rules, n, p, k, B, act, blocks):
     s = n // p
     assert rules.few_rows(B, s, k, s + (p - 1) * k) == blocks
