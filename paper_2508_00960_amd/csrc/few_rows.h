@@ -143,7 +143,6 @@ __global__ __launch_bounds__(FEW_WAVES * 64) void few_rows_kernel(FewBatch batch
             f32x4 acc[2];                              // quarters 0 and 2 of a tile, quarters 1 and 3
 #pragma unroll
             for (int h = 0; h < 2; ++h) acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
             for (int tile = tiles - 1 - team; tile >= 0; tile -= 2) {                  // uniform
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
