@@ -32,6 +32,7 @@ constexpr int few_lds_bytes(int rows, int teams, int chunks)
     return teams == 8 ? FEW_WAVES * few_ahead(rows) * few_chunk_bytes(rows) : (chunks + 1) / 2 * 2 * few_chunk_bytes(rows) + 2 * rows * 1024;
 }
 static_assert(few_lds_bytes(4, 2, (FEW_SHORT - 1) / 32 + 1) <= 160 * 1024 && few_lds_bytes(2, 8, 0) <= 160 * 1024, "a compute unit's LDS");
+static_assert(few_lds_bytes(4, 2, 24) == few_short_lds(4, 768), "as the rule has it");
 
 // out(m, n) = sum_c A(m, c) B(n, c): both operands a head block [rows x split] and peers' segments of seg columns
 struct FewProduct {

@@ -21,6 +21,7 @@ inline int f32_few_groups_for(int64_t workgroups, int64_t longest)
 }
 
 constexpr int FEW_SHORT = 960;                         // few_rows.h: reductions below it in two teams, ...
+constexpr int64_t few_short_lds(int blocks, int64_t Kc) { return (Kc + 63) / 64 * 2 * (blocks + 1) * 1024 + 2 * blocks * 1024; }    // bytes of a workgroup's LDS, in two teams
 inline bool few_rows_in_eight_teams(int64_t Kc) { return Kc >= FEW_SHORT || Kc == 512; }      // ... others, and this one, in eight (as the tiles of gemm_flex.h)
 
 // Does a layer's forward pass (one rank, bf16, 8 divides the widths and phantom widths) run on the kernel for few rows (few_rows.h), and how many blocks
@@ -28,7 +29,11 @@ inline bool few_rows_in_eight_teams(int64_t Kc) { return Kc >= FEW_SHORT || Kc =
 // The fewest with which the launch is one round of workgroups, while a workgroup's operands (16 columns and those rows by the reduction) are
 // not so long that gemm_flex.h, whose larger tiles read less, is the faster one.  With eight teams a workgroup has a compute unit for itself, and one round
 // means 32 on every XCD, each of which takes every eighth column of either product: 1280 + 280 at batch 40 / 96 with 33 on some of them 55.8, 64.2 us; 43.2,
-// 48.2 with one step more (gemm_flex.h 60.0, 62.6).
+// 48.2 with one step more (gemm_flex.h 60.0, 62.6).  So does one with two teams and more than half of the LDS; but there the compression may be in a second
+// round, where its reduction (the shard) is the shorter one.  gemm_flex.h : 4 blocks, us a layer forward, updates + compressions on the fullest XCD: 288 + 480 at batch 728
+// (36 + 12) 7.97 : 9.28 (trained, 7 layers, 125 : 133.5), 392 + 240 at 542 (36 + 9) 8.03 : 9.23, 144 + 672 at 1078 (34 + 17) 8.91 : 11.45, 312 + 600 at 662 (33 + 11) 9.13 : 10.24, 536 + 24 at
+// 408 (35 + 7) 7.67 : 8.13; 200 + 744 at 791 (26 + 13) 9.14 : 7.14, 288 + 392 at 637 (30 + 10) 7.97 : 7.77, 352 + 248 at 524 (27 + 9) 8.01 : 6.31; with a long one 704 + 120 at 257 (30 + 5)
+// 8.16 : 8.31 (trained, 6 layers, 109.4 : 111.7), 496 + 56 at 493 (32 + 8) 7.68 : 7.78, and 400 + 120 at 476 (32 + 8), the line, 7.87 : 7.45.
 // Measured, us, 6 layers forward (dense: 4), gemm_flex.h : 1 block : 2 : 4:
 // 1024 + 448 at batch 48 / 96 / 128 46.4 : 36.7 : 39.8 : 43.3, 48.6 : 64.6 : 42.1 : 45.2, 49.2 : 84 : 63.7 : 46.7; 1024 + 1792 at 32 / 96 / 128 66.7 : 52.5 : 58.9 : 61.5,
 // 67.9 : 95.9 : 59.9 : 64.8, 68.0 : 114 : 82.3 : 67.2; 512 + 960 at 96 / 192 48.6 : 36.8 : 39.6 : 43.5, 50.0 : 67.3 : 44.0 : 47.1; 512 + 3840 at 64 / 128 76.1 : 68.8 : 77.5 : 94.1,
@@ -39,11 +44,14 @@ inline bool few_rows_in_eight_teams(int64_t Kc) { return Kc >= FEW_SHORT || Kc =
 // 31.7 : 28.7 (2 blocks), 28.2 : 28.8, 37.6 : 30.7; 1984 / 2048 39.6 : 34.7, 35.1 : 37.8.
 inline int few_rows_blocks_for(int64_t B, int64_t so, int64_t k, int64_t Kc)
 {
-    const bool alone = few_rows_in_eight_teams(Kc);
-    auto workgroups = [alone](int64_t columns) { const int64_t n = (columns + 15) / 16; return alone ? (n + 7) / 8 * 8 : n; };
+    const bool eight = few_rows_in_eight_teams(Kc);
+    auto on_an_xcd = [](int64_t columns) { return (columns + 127) / 128; };            // workgroups of a row of them, at most
+    auto workgroups = [=](int64_t columns) { return eight ? on_an_xcd(columns) * 8 : (columns + 15) / 16; };
     const int64_t rows = (B + 15) / 16, columns = workgroups(so) + workgroups(k);
     for (int blocks = 1; blocks <= 4; blocks *= 2) {
-        if ((rows + blocks - 1) / blocks * columns > 256) continue;
+        const int64_t tall = (rows + blocks - 1) / blocks;
+        if (tall * columns > 256) continue;
+        if (!eight && few_short_lds(blocks, Kc) > 80 * 1024 && !(tall * (on_an_xcd(so) + on_an_xcd(k)) <= 32 || (tall * on_an_xcd(so) <= 32 && 5 * so <= 4 * Kc))) continue;
         if (k > 0) return (blocks + 1) * Kc <= 9000 ? blocks : 0;
         return (blocks + 1) * Kc <= 6144 && Kc <= 2048 && !(blocks > 1 && Kc > 1024 && Kc % 512 == 0) ? blocks : 0;
     }

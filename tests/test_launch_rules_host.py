@@ -73,6 +73,13 @@ def test_forward_bits_f32_lines(rules, n, p, k, B, L, act, rank):
     (64, 2048, 0, 2048, 0),
     (32, 2048, 0, 2048, 1),
     (128, 1024, 0, 1024, 2),
+    (728, 288, 32, 768, 0),          # two teams, one workgroup to a compute unit: 36 of the update on an XCD
+    (662, 312, 40, 912, 0),          # ... 33
+    (637, 288, 56, 680, 4),          # ... 30, and 10 of the short compression in a second round
+    (257, 704, 8, 824, 0),           # ... a long one
+    (476, 400, 8, 520, 4),           # ... at the line
+    (146, 768, 8, 824, 4),           # ... 30 and 5 of two blocks; one step more fits
+    (609, 144, 8, 200, 2),           # two to a compute unit: 40 of the update
 ])
 def test_few_rows_lines(rules, B, so, k, Kc, blocks):
     assert rules.few_rows(B, so, k, Kc) == blocks
